@@ -514,16 +514,14 @@ static sg_status direct_run(const sg_grid *g, int nf, const double *h, const T *
     const int with_self = !(flags & SG_SELF_CELL_EXCLUDE);
     if (with_self) {
         GLNodes gl;
-        sg_gl_nodes(gl);
+        sg_gl_nodes(gl, lin ? sg_lin_aspect(*g, dphi) : du / dphi);
         if (lin) {
             const int per = percell ? nphi : 1;
             const int64_t items = (int64_t)nf * nf * nr * per;
             hipLaunchKernelGGL(k_ss_self_lin, dim3((unsigned)items), dim3(256), 0, s, (const double *)Hd, nf, nr,
                                per, g->r_min, dr, dphi, 0, 0, self, gl);
         } else if (percell) {
-            const int64_t items = (int64_t)nf * nf * N;
-            hipLaunchKernelGGL(k_self_cell_percell<T>, dim3((unsigned)items), dim3(256), 0, s, H, nf,
-                               nr, nphi, lnrmin, du, dphi, self, gl);
+            sg_self_cells<T>(H, nf, nr, nphi, lnrmin, du, dphi, self, s);
         } else {
             SelfItems it{};
             for (int a = 0; a < nf; ++a)
@@ -643,11 +641,7 @@ static sg_status potential_run(const sg_grid *g, int nf, const double *h, const 
     }
     const int with_self = !(flags & SG_SELF_CELL_EXCLUDE);
     if (with_self) {
-        GLNodes gl;
-        sg_gl_nodes(gl);
-        const int64_t items = (int64_t)nf * nf * (percell ? N : nr);
-        hipLaunchKernelGGL(k_pot_self<T>, dim3((unsigned)items), dim3(256), 0, s, H, (const double *)dh, nf,
-                           nr, nphi, lnrmin, du, dphi, percell ? 0 : 1, self, gl, 0);
+        sg_pot_cells<T>(H, (const double *)dh, nf, nr, nphi, lnrmin, du, dphi, percell ? 0 : 1, self, 0, s);
         SG_HIP(hipGetLastError());
     }
     DirectArgs<T> A;

@@ -75,15 +75,10 @@ __device__ inline void sg_hat_corner(int P, int Q, int sx, int sy, bool sym, dou
                                      double hb, int which, const GLNodes &gl, const double *wq, int k0, int dk,
                                      double &wr, double &wp)
 {
-    constexpr int NX = SG_PANELS * SG_GLX_N;
-    for (int idx = k0; idx < NX * SG_GL_N; idx += dk) {
-        const int ix = idx / SG_GL_N, j = idx % SG_GL_N;
-        const int pnl = ix / SG_GLX_N, i = ix % SG_GLX_N;
-        const double hi = ldexp(1.0, -2 * (SG_PANELS - 1 - pnl));
-        const double lo = pnl == 0 ? 0.0 : 0.25 * hi;
-        const double xi = lo + (hi - lo) * gl.xr[i];
-        const double eta = gl.x[j];
-        const double wgt = (hi - lo) * gl.wr[i] * gl.w[j] * xi;
+    const int nx = sg_own_nx(du, dphi, fmin(ha, hb)), n = nx * gl.ne;
+    for (int idx = k0; idx < n; idx += dk) {
+        double xi, eta, wgt;
+        sg_own_node(gl, nx, idx, xi, eta, wgt);
         for (int tri = 0; tri < 2; ++tri) {
             const double x = tri == 0 ? xi : xi * eta, y = tri == 0 ? xi * eta : xi;
             const double X = sx * x * du, ph = sy * y * dphi;

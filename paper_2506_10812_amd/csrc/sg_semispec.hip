@@ -373,19 +373,15 @@ k_ss_self_lin(const double *H, int nf, int nr, int per, double rmin, double dr, 
     const double Ha = H[fa * cells + c], Hb = H[fb * cells + c];
     const double ha = Ha / r, hb = Hb / r, Hab = sqrt(0.5 * (Ha * Ha + Hb * Hb));
     const double b = 0.5 * dphi;
-    constexpr int NX = SG_PANELS * SG_GLX_N;
     double acc = 0.0;
     for (int sd = 0; sd < 2; ++sd) {
         const double sgn = sd == 0 ? 1.0 : -1.0;
         const double a = sd == 0 ? log1p(0.5 * dr / r) : -log1p(-0.5 * dr / r);
-        for (int idx = threadIdx.x; idx < NX * SG_GL_N; idx += blockDim.x) {
-            const int ix = idx / SG_GL_N, j = idx % SG_GL_N;
-            const int pnl = ix / SG_GLX_N, i = ix % SG_GLX_N;
-            const double hi = ldexp(1.0, -2 * (SG_PANELS - 1 - pnl));
-            const double lo = pnl == 0 ? 0.0 : 0.25 * hi;
-            const double xi = lo + (hi - lo) * gl.xr[i];
-            const double eta = gl.x[j];
-            const double wgt = (hi - lo) * gl.wr[i] * gl.w[j] * xi * a * b;
+        const int nx = sg_own_nx(a, b, fmin(ha, hb)), n = nx * gl.ne;
+        for (int idx = threadIdx.x; idx < n; idx += blockDim.x) {
+            double xi, eta, wgt;
+            sg_own_node(gl, nx, idx, xi, eta, wgt);
+            wgt *= a * b;
             double f = 0.0;
             for (int tri = 0; tri < 2; ++tri) {
                 const double X = sgn * (tri == 0 ? a * xi : a * xi * eta);
@@ -523,21 +519,19 @@ sg_status sg_ss_table_build(const sg_grid *grid, int nf, const double *d_H, uint
     const bool pot = (flags & SG_POTENTIAL) != 0;
     if (!excl && !second) {  // second order: the own cell is a hat weight of the rows
         // one item per (pair, ring): the per-cell quadratures with one cell per ring
-        GLNodes gl;
-        sg_gl_nodes(gl);
         if (lin) {
+            GLNodes gl;
+            sg_gl_nodes(gl, sg_lin_aspect(*grid, dphi));
             hipLaunchKernelGGL(k_ss_self_lin, dim3(nf * nf * nr), dim3(256), 0, s, d_H, nf, nr, 1, grid->r_min, dr,
                                dphi, pot ? 1 : 0, 0, self, gl);
         } else if (pot) {
-            hipLaunchKernelGGL(k_pot_self<double>, dim3(nf * nf * nr), dim3(256), 0, s, d_H, (const double *)nullptr,
-                               nf, nr, 1, log(grid->r_min), du, dphi, 0, self, gl, 0);
+            sg_pot_cells<double>(d_H, nullptr, nf, nr, 1, log(grid->r_min), du, dphi, 0, self, 0, s);
             SG_HIP(hipGetLastError());
             // own-cell integral I of P: the sample -I / (du dphi) scales to I / N
             hipLaunchKernelGGL(k_ss_scale, dim3((nf * nf * nr + 255) / 256), dim3(256), 0, s, self, nf * nf * nr,
                                -1.0 / (du * dphi));
         } else {
-            hipLaunchKernelGGL(k_self_cell_percell<double>, dim3(nf * nf * nr), dim3(256), 0, s, d_H, nf, nr, 1,
-                               log(grid->r_min), du, dphi, self, gl);
+            sg_self_cells<double>(d_H, nf, nr, 1, log(grid->r_min), du, dphi, self, s);
         }
         SG_HIP(hipGetLastError());
     }
@@ -555,7 +549,7 @@ sg_status sg_ss_table_build(const sg_grid *grid, int nf, const double *d_H, uint
     A.rmin = grid->r_min;
     A.dr = dr;
     A.second = second ? 1 : 0;
-    sg_gl_nodes(A.gl);
+    sg_gl_nodes(A.gl, du / dphi);
     const size_t crows = ss_chunk_rows(L);
     for (size_t r0 = 0; r0 < L.rows; r0 += crows) {
         const int n = (int)std::min(crows, L.rows - r0);
@@ -1137,18 +1131,17 @@ sg_status sg_ss_grad_run(const sg_disc &d0, const double *d_H, const float *lam_
     A.rmin = grid->r_min;
     A.dr = (grid->r_max - grid->r_min) / nr;
     A.second = (flags & SG_SECOND_ORDER) ? 1 : 0;
-    sg_gl_nodes(A.gl);
+    sg_gl_nodes(A.gl, A.du / dphi);
     if (!A.excl && !A.second) {  // second order: the own cell is one of the integrated samples
         GLNodes gl;
-        sg_gl_nodes(gl);
+        sg_gl_nodes(gl, lin ? sg_lin_aspect(*grid, dphi) : A.du / dphi);
         for (int which = 1; which <= 2; ++which) {
             double *out = dself + (size_t)(which - 1) * nf * nf * nr;
             if (lin) {
                 hipLaunchKernelGGL(k_ss_self_lin, dim3(nf * nf * nr), dim3(256), 0, s, d_H, nf, nr, 1, grid->r_min,
                                    A.dr, dphi, A.pot, which, out, gl);
             } else if (A.pot) {
-                hipLaunchKernelGGL(k_pot_self<double>, dim3(nf * nf * nr), dim3(256), 0, s, d_H,
-                                   (const double *)nullptr, nf, nr, 1, A.lnrmin, A.du, dphi, 0, out, gl, which);
+                sg_pot_cells<double>(d_H, nullptr, nf, nr, 1, A.lnrmin, A.du, dphi, 0, out, which, s);
                 SG_HIP(hipGetLastError());
                 // as the forward's own-cell sample: -I / (du dphi)
                 hipLaunchKernelGGL(k_ss_scale, dim3((nf * nf * nr + 255) / 256), dim3(256), 0, s, out, nf * nf * nr,

@@ -2,22 +2,73 @@
 #pragma once
 #include "sg_internal.h"
 
-#define SG_GL_N 48          // Gauss-Legendre order across the self cell (eta)
+#define SG_GL_N 48          // largest Gauss-Legendre order across the self cell (eta)
 #define SG_GLX_N 16         // Gauss-Legendre order per radial panel (xi)
 #define SG_PANELS 7         // geometric xi panels [0,4^-6], [4^-(j+1), 4^-j]
+#define SG_GLT_N 24         // Gauss-Legendre order of the graded xi rule (xi = t^4)
+#define SG_OWN_RMAX 8.0     // largest (half cell side) / H of the graded rule
 #define SG_SELF_MAX 64      // items per self-cell launch
 
+// Nodes of the own-cell rules.  eta: order ne, chosen from the cell's aspect
+// ratio.  xi: the graded rule (tx, tw), or the panel rule (xr, wr per panel).
 struct GLNodes {
+    int ne;
     double x[SG_GL_N], w[SG_GL_N];
     double xr[SG_GLX_N], wr[SG_GLX_N];
+    double tx[SG_GLT_N], tw[SG_GLT_N];
 };
+
+// Node idx of the rule with nx xi nodes: (xi, eta) and its weight, the
+// Jacobian's xi included.
+//
+// Both xi rules integrate over [0, 1] with a logarithm at 0.  xi = t^4 takes
+// the logarithm down to t^7 log t and 24 nodes then reach 1e-13, the level
+// of the panel rule's 112 (measured against 9 panels x 24 nodes on cells of
+// aspect 1/2 to 2 and H_a/H_b of 1/10 to 10: field <= 3e-13, its h
+// derivatives <= 2e-13 beside 2e-13 of the panels, potential <= 1e-15 beside
+// 1e-12).  It holds while the cell is not much larger than H: at half side /
+// H = 16 the derivatives are at 1e-11, so beyond SG_OWN_RMAX the panels
+// resolve the transition of F at distances ~ H.  In eta the integrand's
+// nearest singularities sit at +-i (short side / long side): 20 nodes give
+// 4e-15 up to an aspect of 2, 32 give 5e-15 up to 8, 48 beyond.
+__device__ inline void sg_own_node(const GLNodes &gl, int nx, int idx, double &xi, double &eta, double &wgt)
+{
+    const int ix = idx / gl.ne, j = idx % gl.ne;
+    eta = gl.x[j];
+    if (nx == SG_GLT_N) {
+        xi = gl.tx[ix];
+        wgt = gl.tw[ix] * gl.w[j] * xi;
+        return;
+    }
+    const int pnl = ix / SG_GLX_N, i = ix % SG_GLX_N;
+    const double hi = ldexp(1.0, -2 * (SG_PANELS - 1 - pnl));
+    const double lo = pnl == 0 ? 0.0 : 0.25 * hi;
+    xi = lo + (hi - lo) * gl.xr[i];
+    wgt = (hi - lo) * gl.wr[i] * gl.w[j] * xi;
+}
+
+// xi nodes for an own cell of half sides a, b (in ln r and phi) and aspect
+// ratio h (the smallest of the heights involved, over r).
+__device__ inline int sg_own_nx(double a, double b, double h)
+{
+    return fmax(a, b) <= SG_OWN_RMAX * h ? SG_GLT_N : SG_PANELS * SG_GLX_N;
+}
 
 struct SelfItems {
     double ha[SG_SELF_MAX], hb[SG_SELF_MAX];
     int which[SG_SELF_MAX];
 };
 
-void sg_gl_nodes(GLNodes &gl);
+void sg_gl_nodes(GLNodes &gl, double aspect);  // aspect: cell sides' ratio (either way round)
+// Worst aspect ratio of the cells of a uniform radial grid: ln(1 + dr/(2r)) and
+// -ln(1 - dr/(2r)) against dphi / 2, at the innermost and outermost rings.
+inline double sg_lin_aspect(const sg_grid &g, double dphi)
+{
+    const double dr = (g.r_max - g.r_min) / g.n_r;
+    const double hi = -log1p(-0.5 * dr / (g.r_min + 0.5 * dr)), lo = log1p(0.5 * dr / (g.r_max - 0.5 * dr));
+    const double p = 2.0 * hi / dphi, q = 0.5 * dphi / lo;
+    return p > q ? p : q;
+}
 size_t sg_table_ws_bytes(int nr, int nphi);
 sg_status sg_table_build(const sg_grid *grid, const sg_fluids *fl, uint32_t flags, void *d_table,
                          void *d_ws, hipStream_t s);
@@ -34,10 +85,12 @@ __global__ void k_ss_self_lin(const double *H, int nf, int nr, int per, double r
                               int pot, int which, double *out, GLNodes gl);
 __global__ void k_self_cell_ring(const double *H, int nf, int nr, double lnrmin, double du, double dphi, int which,
                                  double *out, GLNodes gl);
+// Own-cell integrals on the log grid for every pair and cell (nphi = 1: one
+// value per ring), H [F][n_r * nphi]: out[pair][cell].
 template <typename T>
-__global__ void k_self_cell_percell(const T *H, int nf, int nr, int nphi, double lnrmin, double du,
-                                    double dphi, double *out, GLNodes gl);
+void sg_self_cells(const T *H, int nf, int nr, int nphi, double lnrmin, double du, double dphi, double *out,
+                   hipStream_t s);
 template <typename T>
-__global__ void k_pot_self(const T *H, const double *h, int nf, int nr, int nphi, double lnrmin,
-                           double du, double dphi, int per_row, double *out, GLNodes gl, int which);
+void sg_pot_cells(const T *H, const double *h, int nf, int nr, int nphi, double lnrmin, double du, double dphi,
+                  int per_row, double *out, int which, hipStream_t s);
 __global__ void k_fill_f64(double *p, int64_t n, double v);

@@ -46,26 +46,58 @@ __global__ void k_twiddles(float2 *tw_u, int nu, float2 *tw_phi, int nphi)
 // mapped to the unit square with the singular corner collapsed
 // (X = a xi, phi = b xi eta and X = a xi eta, phi = b xi; Jacobian a b xi),
 // which turns the direction-dependent limit at the corner into a smooth
-// integrand.  eta: one Gauss-Legendre rule; xi: Gauss-Legendre on geometric
-// panels [0, 4^-6], [4^-(j+1), 4^-j] so that the transition of F at distances
-// ~H inside cells much larger than H is resolved.  Nodes come from the host.
-__device__ inline double self_cell_partial(double ha, double hb, int which, double a, double b,
-                                           const GLNodes &gl, const double *wq)
+// integrand.  The rules in xi and eta are those of sg_own_node.
+//
+// An OwnPt holds what one node contributes independently of the scale
+// heights: with h^2(X) = h0 cosh X + g sinh X, h0 = (h_a^2 + h_b^2)/2,
+// g = (h_b^2 - h_a^2)/2, and x = c / (4 h^2(X)),
+//   S w = gp F(x) h^-3 |_X + gm F(x) h^-3 |_-X   (1/(8 sqrt(pi)) left out),
+// gp, gm = (w/2) e^{-+3X/2} (e^{+-X} - cos phi); gs = gp + gm without their
+// cancellation, for h_a = h_b, where both sides share one F.  The pair
+// (b, a) swaps the two F of (a, b), so each unordered pair costs two F.
+struct OwnPt {
+    double c, ch, sh, gp, gm, gs;
+};
+
+__device__ inline OwnPt own_pt(double X, double phi, double w)
 {
-    constexpr int NX = SG_PANELS * SG_GLX_N;
-    double acc = 0.0;
-    for (int idx = threadIdx.x; idx < NX * SG_GL_N; idx += blockDim.x) {
-        const int ix = idx / SG_GL_N, j = idx % SG_GL_N;
-        const int pnl = ix / SG_GLX_N, i = ix % SG_GLX_N;
-        const double hi = ldexp(1.0, -2 * (SG_PANELS - 1 - pnl));
-        const double lo = pnl == 0 ? 0.0 : 0.25 * hi;
-        const double xi = lo + (hi - lo) * gl.xr[i];
-        const double eta = gl.x[j];
-        const double wgt = (hi - lo) * gl.wr[i] * gl.w[j] * xi;
-        acc += wgt * (sg_sym_kr64(a * xi, b * xi * eta, ha, hb, which, wq) +
-                      sg_sym_kr64(a * xi * eta, b * xi, ha, hb, which, wq));
-    }
-    return acc;
+    const double s = sinh(0.5 * X), co = sqrt(1.0 + s * s), sp = sin(0.5 * phi);
+    const double ep = co + s, em = co - s;  // e^{X/2}, e^{-X/2}
+    const double p2 = 2.0 * sp * sp;        // 1 - cos phi
+    OwnPt q;
+    q.c = 2.0 * s * s + p2;
+    q.ch = 1.0 + 2.0 * s * s;
+    q.sh = 2.0 * s * co;
+    q.gp = 0.5 * w * (2.0 * s * em * em + p2 * em * em * em);
+    q.gm = 0.5 * w * (-2.0 * s * ep * ep + p2 * ep * ep * ep);
+    q.gs = 0.5 * w * (-4.0 * s * q.sh + p2 * (ep * ep * ep + em * em * em));
+    return q;
+}
+
+// F(x) h^-3, x = c / (4 h^2)
+__device__ inline double own_val(double c, double h2, const double *wq)
+{
+    const double rs = rsqrt(h2), r2 = rs * rs;
+    return sg_F64<true>(0.25 * c * r2, wq) * (r2 * rs);
+}
+
+// (-x F' - 3/2 F) h^-5
+__device__ inline double own_dval(double c, double h2, const double *wq)
+{
+    const double rs = rsqrt(h2), r2 = rs * rs, x = 0.25 * c * r2;
+    double F, dF;
+    sg_F64_dF<true>(x, wq, F, dF);
+    return (-x * dF - 1.5 * F) * (r2 * r2 * rs);
+}
+
+// One node of the h derivative (which = 1: h_a, 2: h_b) of one pair:
+// dK/dh = dK/d(h^2) d(h^2)/dh, d(h^2(X))/dh_a = h_a e^{-X}, /dh_b = h_b e^X.
+__device__ inline double own_dnode(const OwnPt &q, double ha, double hb, int which, const double *wq)
+{
+    const double h0 = 0.5 * (ha * ha + hb * hb), g = 0.5 * (hb * hb - ha * ha);
+    const double eX = q.ch + q.sh, emX = q.ch - q.sh;
+    const double vp = own_dval(q.c, h0 * q.ch + g * q.sh, wq), vm = own_dval(q.c, h0 * q.ch - g * q.sh, wq);
+    return which == 1 ? ha * (q.gp * vp * emX + q.gm * vm * eX) : hb * (q.gp * vp * eX + q.gm * vm * emX);
 }
 
 __device__ inline double block_sum256(double v, double *red)
@@ -77,6 +109,32 @@ __device__ inline double block_sum256(double v, double *red)
         __syncthreads();
     }
     return red[0];
+}
+
+#define SG_OWN_SCALE (1.0 / (8.0 * SG_SQRT_PI))
+
+// This thread's part of one item (pair h_a, h_b; which as above).
+__device__ inline double self_cell_partial(double ha, double hb, int which, double a, double b,
+                                           const GLNodes &gl, const double *wq)
+{
+    const int nx = sg_own_nx(a, b, fmin(ha, hb)), n = nx * gl.ne;
+    const double h0 = 0.5 * (ha * ha + hb * hb), g = 0.5 * (hb * hb - ha * ha);
+    double acc = 0.0;
+    for (int idx = threadIdx.x; idx < n; idx += blockDim.x) {
+        double xi, eta, w;
+        sg_own_node(gl, nx, idx, xi, eta, w);
+#pragma unroll 1
+        for (int tri = 0; tri < 2; ++tri) {
+            const OwnPt q = tri == 0 ? own_pt(a * xi, b * xi * eta, w) : own_pt(a * xi * eta, b * xi, w);
+            if (which)
+                acc += own_dnode(q, ha, hb, which, wq);
+            else if (g == 0.0)
+                acc += q.gs * own_val(q.c, h0 * q.ch, wq);
+            else
+                acc += q.gp * own_val(q.c, h0 * q.ch + g * q.sh, wq) + q.gm * own_val(q.c, h0 * q.ch - g * q.sh, wq);
+        }
+    }
+    return acc * SG_OWN_SCALE;
 }
 
 __global__ void k_self_cell(SelfItems items, double *out, double du, double dphi, GLNodes gl)
@@ -92,32 +150,121 @@ __global__ void k_self_cell(SelfItems items, double *out, double du, double dphi
     if (threadIdx.x == 0) out[it] = tot;
 }
 
-// Per-cell variant for the direct path with general H: item = (pair, cell);
-// h_a = H_a[i]/r_i, h_b = H_b[i]/r_i computed from the caller's arrays.
-template <typename T>
-__global__ void k_self_cell_percell(const T *H, int nf, int nr, int nphi, double lnrmin, double du,
-                                    double dphi, double *out, GLNodes gl)
+// Sum of each of the n per-thread values over the block, value k to out(k);
+// red: one double per wave and value.
+template <int n, typename Out> __device__ inline void own_block_sums(double (&v)[n], double *red, Out out)
+{
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+#pragma unroll
+    for (int k = 0; k < n; ++k) {
+        double x = v[k];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+        if (lane == 0) red[k * 4 + wv] = x;
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < n) {
+        const double *r = red + 4 * threadIdx.x;
+        out((int)threadIdx.x, (r[0] + r[1]) + (r[2] + r[3]));
+    }
+    __syncthreads();
+}
+
+// Per-cell variant (the direct path with general H, and per ring with nphi =
+// 1): h_f = H_f[i]/r_i from the caller's arrays, all pairs of CPB cells per
+// block.  FP64 VALU bound: a node's geometry (a sinh, a sine, two square
+// roots) depends on the grid only and is formed once for the CPB cells, whose
+// heights are wave-uniform; the two-fluid case takes 4 F per node and
+// triangle for its four pairs.  Two fluids, 101 x 250 cells: 1.43 ms, against
+// 30.9 ms with 112 x 48 nodes, one (cell, pair) per block and the kernel
+// evaluated whole at +-X.
+template <typename T, int NF, int CPB>
+__global__ void __launch_bounds__(256)
+k_self_cells(const T *H, int64_t N, int nphi, double lnrmin, double du, double dphi, double *out, GLNodes gl)
 {
     __shared__ double wq[FQuad<double>::TABLE];
-    __shared__ double red[256];
+    __shared__ double red[4 * NF * NF * CPB];
     sg_fill_weights<double>(wq);
     __syncthreads();
-    const int64_t N = (int64_t)nr * nphi;
-    const int64_t item = blockIdx.x;  // pair * N + cell
-    if (item >= (int64_t)nf * nf * N) return;
-    const int pair = (int)(item / N);
-    const int64_t cell = item % N;
-    const int fa = pair / nf, fb = pair % nf;
-    const int ir = (int)(cell / nphi);
-    const double r = exp(lnrmin + (ir + 0.5) * du);
-    const double ha = (double)H[fa * N + cell] / r, hb = (double)H[fb * N + cell] / r;
-    const double acc = self_cell_partial(ha, hb, 0, 0.5 * du, 0.5 * dphi, gl, wq);
-    const double tot = block_sum256(acc, red);
-    if (threadIdx.x == 0) out[item] = tot;
+    const int64_t c0 = (int64_t)blockIdx.x * CPB;
+    double h2[CPB][NF], hm = INFINITY;  // h_f^2 of each cell (past the last: the last cell's)
+#pragma unroll
+    for (int c = 0; c < CPB; ++c) {
+        const int64_t cell = c0 + c < N ? c0 + c : N - 1;
+        const double r = exp(lnrmin + ((int)(cell / nphi) + 0.5) * du);
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            const double h = (double)H[f * N + cell] / r;
+            h2[c][f] = h * h;
+            hm = fmin(hm, h);
+        }
+    }
+    const double a = 0.5 * du, b = 0.5 * dphi;
+    const int nx = sg_own_nx(a, b, hm), n = nx * gl.ne;
+    double acc[CPB * NF * NF];
+#pragma unroll
+    for (int k = 0; k < CPB * NF * NF; ++k) acc[k] = 0.0;
+    for (int idx = threadIdx.x; idx < n; idx += 256) {
+        double xi, eta, w;
+        sg_own_node(gl, nx, idx, xi, eta, w);
+#pragma unroll 1
+        for (int tri = 0; tri < 2; ++tri) {
+            const OwnPt q = tri == 0 ? own_pt(a * xi, b * xi * eta, w) : own_pt(a * xi * eta, b * xi, w);
+#pragma unroll
+            for (int c = 0; c < CPB; ++c)
+#pragma unroll
+                for (int fa = 0; fa < NF; ++fa) {
+                    acc[(c * NF + fa) * NF + fa] += q.gs * own_val(q.c, h2[c][fa] * q.ch, wq);
+#pragma unroll
+                    for (int fb = fa + 1; fb < NF; ++fb) {
+                        const double h0 = 0.5 * (h2[c][fa] + h2[c][fb]), g = 0.5 * (h2[c][fb] - h2[c][fa]);
+                        const double vp = own_val(q.c, h0 * q.ch + g * q.sh, wq);
+                        const double vm = own_val(q.c, h0 * q.ch - g * q.sh, wq);
+                        acc[(c * NF + fa) * NF + fb] += q.gp * vp + q.gm * vm;
+                        acc[(c * NF + fb) * NF + fa] += q.gp * vm + q.gm * vp;
+                    }
+                }
+        }
+    }
+    own_block_sums(acc, red, [&](int k, double v) {
+        const int c = k / (NF * NF), pair = k % (NF * NF);
+        if (c0 + c < N) out[(int64_t)pair * N + c0 + c] = v * SG_OWN_SCALE;
+    });
 }
+
+// Cells per block: as many as keep the accumulators (one per cell and pair)
+// in registers, but fewer where that would leave the GPU idle.
+template <typename T>
+void sg_self_cells(const T *H, int nf, int nr, int nphi, double lnrmin, double du, double dphi, double *out,
+                   hipStream_t s)
+{
+    const int64_t N = (int64_t)nr * nphi;
+    GLNodes gl;
+    sg_gl_nodes(gl, du / dphi);
+#define SG_OWN(NF, CPB)                                                                                     \
+    hipLaunchKernelGGL((k_self_cells<T, NF, CPB>), dim3((unsigned)((N + CPB - 1) / CPB)), dim3(256), 0, s, H, N, \
+                       nphi, lnrmin, du, dphi, out, gl)
+    const bool many = N >= 4096;
+    switch (nf) {
+    case 1:
+        if (many) SG_OWN(1, 8);
+        else SG_OWN(1, 1);
+        break;
+    case 2:
+        if (many) SG_OWN(2, 4);
+        else SG_OWN(2, 1);
+        break;
+    case 3: SG_OWN(3, 1); break;
+    default: SG_OWN(4, 1); break;
+    }
+#undef SG_OWN
+}
+template void sg_self_cells<float>(const float *, int, int, int, double, double, double, double *, hipStream_t);
+template void sg_self_cells<double>(const double *, int, int, int, double, double, double, double *, hipStream_t);
+
 // Per-ring variant with a derivative selector for the semi-spectral
-// gradient: item = (pair, ring), h = H[f][ring] / r; which = 0: Kbar,
-// 1: dKbar/dh_a, 2: dKbar/dh_b.
+// gradient: item = (pair, ring), h = H[f][ring] / r; which = 1: dKbar/dh_a,
+// 2: dKbar/dh_b.
 __global__ void k_self_cell_ring(const double *H, int nf, int nr, double lnrmin, double du, double dphi, int which,
                                  double *out, GLNodes gl)
 {
@@ -135,11 +282,6 @@ __global__ void k_self_cell_ring(const double *H, int nf, int nr, double lnrmin,
     if (threadIdx.x == 0) out[item] = tot;
 }
 
-template __global__ void k_self_cell_percell<float>(const float *, int, int, int, double, double,
-                                                    double, double *, GLNodes);
-template __global__ void k_self_cell_percell<double>(const double *, int, int, int, double, double,
-                                                     double, double *, GLNodes);
-
 // Own-cell integral of the potential kernel (reading: the paper does not
 // treat k = i): int P_ab(|x_i - x'|) dA' over the cell, x' = r e^X (cos phi,
 // sin phi) relative to the centre direction, |x_i - x'|^2 = r^2 e^X
@@ -149,75 +291,104 @@ template __global__ void k_self_cell_percell<double>(const double *, int, int, i
 // which = 0: P; which = 1: dP/dH_ab (H_ab the r.m.s. height: with
 // G0 = e^y K0(y), dG0/dy = -F(y), so dP/dH = -(2 y F(y) - G0(y)) /
 // (2 sqrt(pi) H^2); like P, logarithmic at s -> 0).
-__device__ inline double pot_integrand(double X, double phi, double r, double Hab, const double *wq, int which = 0)
-{
-    const double sx = sinh(0.5 * X), sp = sin(0.5 * phi);
-    const double s2 = r * r * exp(X) * 4.0 * (sx * sx + sp * sp);
-    const double y = s2 / (8.0 * Hab * Hab);
-    if (which) return -(2.0 * y * sg_F64(y, wq) - sg_G0_64(y, wq)) / (2.0 * SG_SQRT_PI * Hab * Hab) * r * r * exp(2.0 * X);
-    return -sg_G0_64(y, wq) / (2.0 * SG_SQRT_PI * Hab) * r * r * exp(2.0 * X);
-}
-
-__device__ inline double pot_self_partial(double r, double Hab, double a, double b, const GLNodes &gl,
-                                          const double *wq, int which = 0)
-{
-    constexpr int NX = SG_PANELS * SG_GLX_N;
-    double acc = 0.0;
-    for (int idx = threadIdx.x; idx < NX * SG_GL_N; idx += blockDim.x) {
-        const int ix = idx / SG_GL_N, j = idx % SG_GL_N;
-        const int pnl = ix / SG_GLX_N, i = ix % SG_GLX_N;
-        const double hi = ldexp(1.0, -2 * (SG_PANELS - 1 - pnl));
-        const double lo = pnl == 0 ? 0.0 : 0.25 * hi;
-        const double xi = lo + (hi - lo) * gl.xr[i];
-        const double eta = gl.x[j];
-        const double wgt = (hi - lo) * gl.wr[i] * gl.w[j] * xi * a * b;
-        double f = 0.0;
-        for (int sg = -1; sg <= 1; sg += 2)
-            f += pot_integrand(sg * a * xi, b * xi * eta, r, Hab, wq, which) +
-                 pot_integrand(sg * a * xi * eta, b * xi, r, Hab, wq, which);
-        acc += 2.0 * wgt * f;
-    }
-    return acc;
-}
-
-// Item = (pair, row) when per_row (H_f = h_f r: depends on the row only),
-// else (pair, cell) with the caller's H at that cell.  which = 1, 2: the
-// integral's derivative with respect to h_a = H_a / r, h_b = H_b / r
-// (dH_ab/dh_a = H_a r / (2 H_ab), likewise for b) instead.
-template <typename T>
-__global__ void k_pot_self(const T *H, const double *h, int nf, int nr, int nphi, double lnrmin,
-                           double du, double dphi, int per_row, double *out, GLNodes gl, int which)
+//
+// One block per CPB cells and unordered pair (P_ab = P_ba), or rows when
+// per_row (H_f = h_f r: depends on the row only); a node's geometry is shared
+// by the CPB cells (96 x 200 cells in double: 0.30 ms, against 5.0 ms with
+// 112 x 48 nodes and one cell per block).  which = 1, 2 of the item: the integral's derivative with
+// respect to h_a = H_a / r, h_b = H_b / r (dH_ab/dh_a = H_a r / (2 H_ab),
+// likewise for b) instead.
+template <typename T, int CPB, bool DER>
+__global__ void __launch_bounds__(256)
+k_pot_cells(const T *H, const double *h, int nf, int64_t per, int nphi, double lnrmin, double du, double dphi,
+            int per_row, double *out, GLNodes gl, int which)
 {
     __shared__ double wq[FQuad<double>::TABLE];
-    __shared__ double red[256];
+    __shared__ double red[4 * CPB];
     sg_fill_weights<double>(wq);
     __syncthreads();
-    const int64_t N = (int64_t)nr * nphi, per = per_row ? nr : N;
-    const int64_t item = blockIdx.x;
-    if (item >= (int64_t)nf * nf * per) return;
-    const int pair = (int)(item / per);
-    const int64_t c = item % per;
-    const int fa = pair / nf, fb = pair % nf;
-    const int ir = per_row ? (int)c : (int)(c / nphi);
-    const double r = exp(lnrmin + (ir + 0.5) * du);
-    double Ha, Hb;
-    if (per_row) {
-        Ha = h[fa] * r;
-        Hb = h[fb] * r;
-    } else {
-        Ha = (double)H[fa * N + c];
-        Hb = (double)H[fb * N + c];
+    int fa = 0, fb = blockIdx.y;  // unordered pair blockIdx.y of (0,0), (0,1), ..., (1,1), ...
+    while (fb >= nf - fa) {
+        fb -= nf - fa;
+        ++fa;
     }
-    const double Hab = sqrt(0.5 * (Ha * Ha + Hb * Hb));
-    const double chain = which == 0 ? 1.0 : (which == 1 ? Ha : Hb) * r / (2.0 * Hab);
-    const double acc = pot_self_partial(r, Hab, 0.5 * du, 0.5 * dphi, gl, wq, which != 0);
-    const double tot = block_sum256(acc, red);
-    if (threadIdx.x == 0) out[item] = chain * tot;
+    fb += fa;
+    const int64_t c0 = (int64_t)blockIdx.x * CPB;
+    double r2H[CPB], hm = INFINITY;  // r^2 / (4 H_ab^2) of each cell
+    auto heights = [&](int64_t c, double &r, double &Ha, double &Hb) {
+        r = exp(lnrmin + ((per_row ? (int)c : (int)(c / nphi)) + 0.5) * du);
+        Ha = per_row ? h[fa] * r : (double)H[fa * per + c];
+        Hb = per_row ? h[fb] * r : (double)H[fb * per + c];
+    };
+#pragma unroll
+    for (int c = 0; c < CPB; ++c) {
+        double r, Ha, Hb;
+        heights(c0 + c < per ? c0 + c : per - 1, r, Ha, Hb);
+        const double Hab2 = 0.5 * (Ha * Ha + Hb * Hb);
+        r2H[c] = r * r / (4.0 * Hab2);
+        hm = fmin(hm, sqrt(Hab2) / r);
+    }
+    const double a = 0.5 * du, b = 0.5 * dphi;
+    const int nx = sg_own_nx(a, b, hm), n = nx * gl.ne;
+    double acc[CPB];
+#pragma unroll
+    for (int c = 0; c < CPB; ++c) acc[c] = 0.0;
+    for (int idx = threadIdx.x; idx < n; idx += 256) {
+        double xi, eta, w;
+        sg_own_node(gl, nx, idx, xi, eta, w);
+#pragma unroll 1
+        for (int k = 0; k < 4; ++k) {
+            const double X = (k & 1 ? -a : a) * (k & 2 ? xi * eta : xi), phi = k & 2 ? b * xi : b * xi * eta;
+            const double s = sinh(0.5 * X), sp = sin(0.5 * phi), e1 = sqrt(1.0 + s * s) + s;
+            const double eX = e1 * e1, cy = eX * (2.0 * s * s + 2.0 * sp * sp), we = w * eX * eX;
+#pragma unroll
+            for (int c = 0; c < CPB; ++c) {
+                const double y = cy * r2H[c], G = sg_G0_64<true>(y, wq);
+                acc[c] += we * (DER ? 2.0 * y * sg_F64<true>(y, wq) - G : G);
+            }
+        }
+    }
+    own_block_sums(acc, red, [&](int c, double v) {
+        if (c0 + c >= per) return;
+        double r, Ha, Hb;
+        heights(c0 + c, r, Ha, Hb);
+        const double Hab = sqrt(0.5 * (Ha * Ha + Hb * Hb));
+        v *= -2.0 * a * b * r * r / (2.0 * SG_SQRT_PI * Hab);
+        const int64_t ab = (int64_t)(fa * nf + fb) * per + c0 + c, ba = (int64_t)(fb * nf + fa) * per + c0 + c;
+        if constexpr (DER) {
+            v *= r / (2.0 * Hab * Hab);
+            out[ab] = v * (which == 1 ? Ha : Hb);
+            out[ba] = v * (which == 1 ? Hb : Ha);
+        } else {
+            out[ab] = v;
+            out[ba] = v;
+        }
+    });
 }
-template __global__ void k_pot_self<float>(const float *, const double *, int, int, int, double, double,
-                                           double, int, double *, GLNodes, int);
-template __global__ void k_pot_self<double>(const double *, const double *, int, int, int, double, double,
-                                            double, int, double *, GLNodes, int);
+
+template <typename T>
+void sg_pot_cells(const T *H, const double *h, int nf, int nr, int nphi, double lnrmin, double du, double dphi,
+                  int per_row, double *out, int which, hipStream_t s)
+{
+    const int64_t per = per_row ? nr : (int64_t)nr * nphi;
+    GLNodes gl;
+    sg_gl_nodes(gl, du / dphi);
+    const unsigned pairs = (unsigned)(nf * (nf + 1) / 2);
+#define SG_POT(CPB, DER)                                                                                         \
+    hipLaunchKernelGGL((k_pot_cells<T, CPB, DER>), dim3((unsigned)((per + CPB - 1) / CPB), pairs), dim3(256), 0, s, \
+                       H, h, nf, per, nphi, lnrmin, du, dphi, per_row, out, gl, which)
+    if (which)
+        SG_POT(1, true);
+    else if (per >= 4096)
+        SG_POT(8, false);
+    else
+        SG_POT(1, false);
+#undef SG_POT
+}
+template void sg_pot_cells<float>(const float *, const double *, int, int, int, double, double, double, int, double *,
+                                  int, hipStream_t);
+template void sg_pot_cells<double>(const double *, const double *, int, int, int, double, double, double, int,
+                                   double *, int, hipStream_t);
 
 __global__ void k_fill_f64(double *p, int64_t n, double v)
 {
@@ -504,16 +675,33 @@ static void gl_rule(int n, double *x, double *w)
     }
 }
 
-void sg_gl_nodes(GLNodes &gl)
-{
-    static GLNodes cache;
-    static bool ready = false;
-    if (!ready) {
-        gl_rule(SG_GL_N, cache.x, cache.w);
-        gl_rule(SG_GLX_N, cache.xr, cache.wr);
-        ready = true;
+namespace {
+struct GLCache {  // eta orders 20, 32 and 48 (sg_own_node), the same xi rules in each
+    GLNodes g[3];
+    GLCache()
+    {
+        const int order[3] = {20, 32, SG_GL_N};
+        for (int k = 0; k < 3; ++k) {
+            g[k] = GLNodes{};
+            g[k].ne = order[k];
+            gl_rule(order[k], g[k].x, g[k].w);
+            gl_rule(SG_GLX_N, g[k].xr, g[k].wr);
+            gl_rule(SG_GLT_N, g[k].tx, g[k].tw);
+            for (int i = 0; i < SG_GLT_N; ++i) {
+                const double t = g[k].tx[i];
+                g[k].tx[i] = t * t * t * t;
+                g[k].tw[i] *= 4.0 * t * t * t;
+            }
+        }
     }
-    gl = cache;
+};
+}  // namespace
+
+void sg_gl_nodes(GLNodes &gl, double aspect)
+{
+    static const GLCache cache;  // built once, by the first caller
+    const double q = aspect < 1.0 ? 1.0 / aspect : aspect;
+    gl = cache.g[q <= 2.0 ? 0 : q <= 8.0 ? 1 : 2];
 }
 
 template <int NPHI>
@@ -626,7 +814,7 @@ sg_status sg_table_build(const sg_grid *grid, const sg_fluids *fl, uint32_t flag
         SG_HIP(hipGetLastError());
     } else if (!second) {  // second order: W_r(0, 0) is copied in per pair below
         GLNodes gl;
-        sg_gl_nodes(gl);
+        sg_gl_nodes(gl, du / dphi);
         hipLaunchKernelGGL(k_self_cell, dim3(nit), dim3(256), 0, s, items, selfbuf, du, dphi, gl);
         SG_HIP(hipGetLastError());
     }
@@ -644,7 +832,7 @@ sg_status sg_table_build(const sg_grid *grid, const sg_fluids *fl, uint32_t flag
                 const double *sv = w == 0 ? selfbuf + pair : selfbuf + L.npair + 2 * pair + (w - 1);
                 if (second) {
                     GLNodes gl;
-                    sg_gl_nodes(gl);
+                    sg_gl_nodes(gl, du / dphi);
                     hipLaunchKernelGGL(k_sample_hat_far, dim3((nphi + 255) / 256, 2 * nr), dim3(256), 0, s, A, nr,
                                        nphi, du, fl->h[a], fl->h[b], w);
                     hipLaunchKernelGGL(k_sample_hat_near, dim3(9), dim3(256), 0, s, A, nr, nphi, du, fl->h[a],
@@ -706,10 +894,10 @@ sg_status sg_self_cell_launch(const sg_grid *grid, const double *ha, const doubl
         items.hb[i] = hb[i];
         items.which[i] = which;
     }
-    GLNodes gl;
-    sg_gl_nodes(gl);
     const double du = log(grid->r_max / grid->r_min) / grid->n_r;
     const double dphi = 2.0 * SG_PI / grid->n_phi;
+    GLNodes gl;
+    sg_gl_nodes(gl, du / dphi);
     hipLaunchKernelGGL(k_self_cell, dim3(n), dim3(256), 0, s, items, d_out, du, dphi, gl);
     SG_HIP(hipGetLastError());
     return SG_OK;
