@@ -17,6 +17,11 @@
 // the radial factors 4 sinh^2(X/2) = (r_i - r_k)^2 / (r_i r_k) and
 // expm1(X) = (r_i - r_k) / r_k are formed per source row instead.
 //
+// H = h r (d_H == NULL) makes the kernel between two rings a function of the
+// azimuth offset alone: k_ring_sum evaluates it once per offset and sums it
+// against the source row as a Toeplitz product.  The rest of this comment is
+// about the general sum with a scale height per cell.
+//
 // Layout: one thread per target cell (256 per workgroup), all target fluids
 // in registers; the source loop runs over whole radial rows so every
 // per-source quantity is wave-uniform (scalar loads); the source rows are
@@ -35,6 +40,8 @@
 // terms and the compensated outer sum is exact to first order, so the result
 // sits at the rounding floor of the individual terms.  Each split hands
 // (sum, carried error) to the reduction, which adds them in double.
+#include <algorithm>
+
 #include "sg_direct.h"
 #include "sg_kfn.h"
 #include "sg_table.h"
@@ -104,6 +111,9 @@ __global__ void k_direct_prep(int nr, int nphi, int nf, double lnrmin, double du
 template <typename T> __device__ inline T sg_F_any(T x, const T *w);
 template <> __device__ inline double sg_F_any<double>(double x, const double *w) { return sg_F64<true>(x, w); }
 template <> __device__ inline float sg_F_any<float>(float x, const float *w) { return sg_F32(x, w); }
+template <typename T> __device__ inline T sg_G0_any(T x, const T *w);
+template <> __device__ inline double sg_G0_any<double>(double x, const double *w) { return sg_G0_64<true>(x, w); }
+template <> __device__ inline float sg_G0_any<float>(float x, const float *w) { return sg_G0_32(x, w); }
 
 template <typename T, int NF>
 __global__ void __launch_bounds__(256) k_direct(DirectArgs<T> A)
@@ -190,6 +200,223 @@ __global__ void __launch_bounds__(256) k_direct(DirectArgs<T> A)
         o[A.N] = errr[b];
         o[2 * A.N] = accp[b];
         o[3 * A.N] = errp[b];
+    }
+}
+
+// ------------------------------------------------- ring sums (H = h r)
+// One block: target ring blockIdx.x / ntile (a tile of TJ = 8 JT of its
+// azimuths), target fluid blockIdx.z, source rings of split blockIdx.y.  Per
+// source ring and fluid the kernel is a vector over the azimuth offset q (K_r
+// even, K_phi odd: nphi/2 + 1 evaluations), staged in LDS in the order of
+// l - j so that the sum over the source azimuths l is a Toeplitz product:
+// thread (jt, g) holds the 8 targets j0 = 8 jt .. j0 + 7 of its tile, loads 8
+// offsets and 8 masses at a time and does 64 FMAs per component on them and
+// the previous 8 offsets.  The 256 / JT groups g share the work as KS source
+// rings at a time times LG interleaved 64-azimuth chunks; their sums are
+// combined in a fixed order at the end.
+//
+// FP32 / FP64 VALU bound, two FMAs per pair of cells and fluid pair (one for
+// the potential) in place of a kernel evaluation.  The whole call: 256 x 512 in
+// float 1.08 ms (32e12 FMA/s of 39e12), against 21.4 ms with a kernel
+// evaluation per pair; 64 x 128 in double 55 us against 580 us.  8 x 8 per step keeps LDS below the VALU
+// (per wave 6 16-byte reads for 128 FMAs in float, 12 in double); rows are
+// padded by 16 bytes per 8 elements, which puts the 8 lanes of a 16-byte
+// access phase (one element group apart) on different banks.
+#define SG_RING_LDS (48 << 10)  // staged rows per block: three blocks per CU
+struct RingShape {
+    int JT, KS, LG;   // threads along j, source rings staged at a time, chunk groups
+    int ntile, TL;    // azimuth tiles of a target ring; staged source azimuths (multiple of 8)
+    int rps;          // source rings per split (multiple of KS)
+    size_t lds;
+};
+
+template <typename T> struct RingPad {
+    static constexpr int G = 8 + 16 / (int)sizeof(T);  // elements per padded group of 8
+};
+
+template <typename T, int NC>
+static RingShape ring_shape(int nr, int nphi, int nf, int smax)
+{
+    const int jtmax = sizeof(T) == 4 ? 256 : 128, tlmax = sizeof(T) == 4 ? 1024 : 512;
+    RingShape P;
+    const int g8 = (nphi + 7) / 8;
+    P.ntile = (g8 + jtmax - 1) / jtmax;
+    P.JT = (g8 + P.ntile - 1) / P.ntile;
+    P.TL = std::min(8 * g8, tlmax);
+    const int S = 256 / P.JT, nch = (P.TL + 63) / 64;
+    P.LG = std::min(nch, S);
+    const size_t row = (size_t)(P.JT + P.TL / 8) * RingPad<T>::G, per = sizeof(T) * (NC * row + P.TL);
+    P.KS = std::max(1, std::min({S / P.LG, nr, (int)(SG_RING_LDS / per)}));
+    // splits: about 2048 blocks, within the partial-sum buffer
+    const int64_t blocks = (int64_t)nr * P.ntile * nf;
+    const int64_t want = std::max<int64_t>(1, std::min<int64_t>((2048 + blocks - 1) / blocks, smax));
+    int rps = (int)((nr + want - 1) / want);
+    P.rps = (rps + P.KS - 1) / P.KS * P.KS;
+    P.lds = std::max(P.KS * per, sizeof(T) * (size_t)P.JT * P.KS * P.LG * 16);
+    return P;
+}
+
+// Kernel per unit mass between ring ir (fluid b) and source ring kr (fluid a)
+// at azimuth offset q: (g_r, g_phi), or the potential.
+template <typename T, int NC>
+__device__ inline void ring_kernel(const DirectArgs<T> &A, int ir, int kr, int a, int b, int q, const T *wq, T (&K)[NC])
+{
+    const T ri = A.rrow[ir], rk = A.rrow[kr];
+    T SX, EX;
+    if (A.lin) {
+        const T d = ri - rk;
+        SX = d * d / (ri * rk);
+        EX = d / rk;
+    } else {
+        const int p = ir - kr + A.nr - 1;
+        SX = A.sx[p];
+        EX = A.ex[p];
+    }
+    const T sp = A.sph[q], s2_8 = ri * rk * T(0.125) * (SX + sp);
+    const T H2ab = T(0.5) * (A.H2[a * A.N + (int64_t)kr * A.nphi] + A.H2[b * A.N + (int64_t)ir * A.nphi]);
+    const T rH = sg_rsqrt(H2ab), rH2 = rH * rH;
+    const bool self = kr == ir && q == 0;
+    const T x = self ? T(1) : s2_8 * rH2;
+    if constexpr (NC == 2) {
+        const T c = self ? T(0) : T(-1.0 / (8.0 * SG_SQRT_PI)) * rk * sg_F_any<T>(x, wq) * (rH2 * rH);
+        K[0] = c * (EX + T(0.5) * sp);
+        K[1] = c * A.snp[q];
+    } else {
+        K[0] = self ? T(0) : T(-0.5 / SG_SQRT_PI) * sg_G0_any<T>(x, wq) * rH;
+    }
+}
+
+template <typename T, int NC>
+__global__ void __launch_bounds__(256) k_ring_sum(DirectArgs<T> A, RingShape P, int nf)
+{
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    __shared__ T wq[FQuad<T>::TABLE];
+    constexpr int PG = RingPad<T>::G;
+    sg_fill_weights<T>(wq);
+    const int ir = blockIdx.x / P.ntile, jb = (blockIdx.x % P.ntile) * 8 * P.JT, b = blockIdx.z;
+    const int nphi = A.nphi, rowg = P.JT + P.TL / 8;
+    T *D = (T *)smem, *M = D + (size_t)P.KS * NC * rowg * PG;
+    const int jt = threadIdx.x % P.JT, g = threadIdx.x / P.JT;
+    const int ks = g % P.KS, lg = g / P.KS;
+    const bool act = lg < P.LG;
+    T acc[NC][8], err[NC][8];
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int r = 0; r < 8; ++r) acc[c][r] = err[c][r] = T(0);
+    const int r0 = blockIdx.y * P.rps, r1 = min(A.nr, r0 + P.rps);
+    const bool whole = nphi <= P.TL;  // every offset of the row is staged at once
+    for (int k0 = r0; k0 < r1; k0 += P.KS)
+        for (int l0 = 0; l0 < nphi; l0 += P.TL)
+            for (int a = 0; a < nf; ++a) {
+                __syncthreads();  // the weights; the previous stage's readers
+                const int tl = min(P.TL, nphi - l0), lpad = (tl + 7) & ~7;
+                // element y of a row: offset x = l - j = y + l0 - jb - TJ, q = -x mod nphi
+                const int x0 = l0 - jb - 8 * P.JT, wn = 8 * P.JT + lpad;
+                const int per = whole ? nphi / 2 + 1 : wn;
+                for (int e = threadIdx.x; e < P.KS * per; e += 256) {
+                    const int s = e / per, v = e - s * per, kr = k0 + s;
+                    int q = v;
+                    if (!whole) {
+                        q = (int)(-(int64_t)(x0 + v) % nphi);
+                        q += q < 0 ? nphi : 0;
+                    }
+                    T K[NC];
+#pragma unroll
+                    for (int c = 0; c < NC; ++c) K[c] = T(0);
+                    if (kr < r1) ring_kernel<T, NC>(A, ir, kr, a, b, q, wq, K);
+                    T *row = D + (size_t)s * NC * rowg * PG;
+                    auto put = [&](int y, T sgn) {
+                        T *d = row + (y >> 3) * PG + (y & 7);
+                        d[0] = K[0];
+                        if constexpr (NC == 2) d[(size_t)rowg * PG] = sgn * K[1];
+                    };
+                    if (!whole) {
+                        put(v, T(1));
+                        continue;
+                    }
+                    // x = -q and x = +q (where K_phi changes sign), every period
+                    // (jb < nphi and TJ < nphi + 8, so x0 > -2 nphi - 8)
+                    for (int x = -q; x >= x0; x -= nphi)
+                        if (x < x0 + wn) put(x - x0, T(1));
+                    for (int x = -q + nphi; x < x0 + wn; x += nphi)
+                        if (x >= x0) put(x - x0, T(1));
+                    for (int x = q; x >= x0; x -= nphi)
+                        if (x < x0 + wn) put(x - x0, T(-1));
+                    for (int x = q + nphi; x < x0 + wn; x += nphi)
+                        if (x >= x0) put(x - x0, T(-1));
+                }
+                for (int e = threadIdx.x; e < P.KS * lpad; e += 256) {
+                    const int s = e / lpad, l = e - s * lpad;
+                    M[s * P.TL + l] =
+                        (k0 + s < r1 && l < tl) ? A.mass[a * A.N + (int64_t)(k0 + s) * nphi + l0 + l] : T(0);
+                }
+                __syncthreads();
+                if (!act) continue;
+                const T *dr = D + (size_t)ks * NC * rowg * PG + (P.JT - jt) * PG, *mr = M + ks * P.TL;
+                const int ng = lpad / 8;
+                for (int c0 = 8 * lg; c0 < ng; c0 += 8 * P.LG) {
+                    T part[NC][8], prev[NC][8];
+#pragma unroll
+                    for (int c = 0; c < NC; ++c)
+#pragma unroll
+                        for (int r = 0; r < 8; ++r) {
+                            part[c][r] = T(0);
+                            prev[c][r] = dr[(size_t)c * rowg * PG + (c0 - 1) * PG + r];
+                        }
+                    const int c1 = min(ng, c0 + 8);
+                    for (int cg = c0; cg < c1; ++cg) {
+                        T m[8];
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) m[i] = mr[8 * cg + i];
+#pragma unroll
+                        for (int c = 0; c < NC; ++c) {
+                            T cur[8];
+#pragma unroll
+                            for (int i = 0; i < 8; ++i) cur[i] = dr[(size_t)c * rowg * PG + cg * PG + i];
+#pragma unroll
+                            for (int i = 0; i < 8; ++i)
+#pragma unroll
+                                for (int r = 0; r < 8; ++r)
+                                    part[c][r] += m[i] * (i >= r ? cur[i - r] : prev[c][8 + i - r]);
+#pragma unroll
+                            for (int i = 0; i < 8; ++i) prev[c][i] = cur[i];
+                        }
+                    }
+#pragma unroll
+                    for (int c = 0; c < NC; ++c)
+#pragma unroll
+                        for (int r = 0; r < 8; ++r) sg_two_sum_acc(acc[c][r], err[c][r], part[c][r]);
+                }
+            }
+    // the groups' sums, added in group order, one component after the other:
+    // red[group][jt][sum, error][8]
+    T *red = (T *)smem;
+    const int ngr = P.KS * P.LG;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        __syncthreads();
+        if (act) {
+            T *o = red + (size_t)(g * P.JT + jt) * 16;
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                o[r] = acc[c][r];
+                o[8 + r] = err[c][r];
+            }
+        }
+        __syncthreads();
+        for (int j = threadIdx.x; j < 8 * P.JT; j += 256) {
+            if (jb + j >= nphi) continue;
+            T sum = T(0), er = T(0);
+            for (int q = 0; q < ngr; ++q) {
+                const T *o = red + (size_t)(q * P.JT + (j >> 3)) * 16 + (j & 7);
+                sg_two_sum_acc(sum, er, o[0]);
+                er += o[8];
+            }
+            T *o = A.partial + ((int64_t)(blockIdx.y * nf + b) * 2 * NC + 2 * c) * A.N + (int64_t)ir * nphi + jb + j;
+            o[0] = sum;
+            o[A.N] = er;
+        }
     }
 }
 
@@ -315,10 +542,6 @@ __global__ void k_direct_reduce(const T *partial, int S, int64_t N, const double
 // H_ab from the source cell's H_a and the target cell's H_b; the own cell
 // adds Sigma_a[i] times the cell integral of P_ab (k_pot_self).  Same
 // layout and splitting as the field sum; one accumulator per target fluid.
-template <typename T> __device__ inline T sg_G0_any(T x, const T *w);
-template <> __device__ inline double sg_G0_any<double>(double x, const double *w) { return sg_G0_64<true>(x, w); }
-template <> __device__ inline float sg_G0_any<float>(float x, const float *w) { return sg_G0_32(x, w); }
-
 template <typename T, int NF>
 __global__ void __launch_bounds__(256) k_potential(DirectArgs<T> A)
 {
@@ -461,6 +684,16 @@ size_t sg_direct_ws_bytes(int nr, int nphi, int nf, sg_dtype dt, int percell)
     return o;
 }
 
+// H = h r: the ring sums into at most smax splits; returns the splits used.
+template <typename T, int NC> static int ring_sum(const DirectArgs<T> &A, int nf, int smax, hipStream_t s)
+{
+    const RingShape P = ring_shape<T, NC>(A.nr, A.nphi, nf, smax);
+    const int S = (A.nr + P.rps - 1) / P.rps;
+    hipLaunchKernelGGL((k_ring_sum<T, NC>), dim3((unsigned)(A.nr * P.ntile), (unsigned)S, (unsigned)nf), dim3(256),
+                       (unsigned)P.lds, s, A, P, nf);
+    return S;
+}
+
 template <typename T>
 static sg_status direct_run(const sg_grid *g, int nf, const double *h, const T *sigma, const T *H,
                             T *gr, T *gp, uint32_t flags, void *ws, hipStream_t s)
@@ -472,7 +705,7 @@ static sg_status direct_run(const sg_grid *g, int nf, const double *h, const T *
     const double lnrmin = log(g->r_min);
     const int lin = (flags & SG_LINEAR_R) ? 1 : 0;
     const double dr = (g->r_max - g->r_min) / nr;
-    const int S = direct_splits(nr, N);
+    int S = direct_splits(nr, N);
     const int rps = (nr + S - 1) / S;
     char *o = (char *)ws;
     auto take = [&](size_t bytes) {
@@ -557,12 +790,16 @@ static sg_status direct_run(const sg_grid *g, int nf, const double *h, const T *
     A.mass = mass;
     A.H2 = H2;
     A.partial = partial;
-    dim3 grid((unsigned)((N + 255) / 256), (unsigned)S);
-    switch (nf) {
-    case 1: hipLaunchKernelGGL((k_direct<T, 1>), grid, dim3(256), 0, s, A); break;
-    case 2: hipLaunchKernelGGL((k_direct<T, 2>), grid, dim3(256), 0, s, A); break;
-    case 3: hipLaunchKernelGGL((k_direct<T, 3>), grid, dim3(256), 0, s, A); break;
-    default: hipLaunchKernelGGL((k_direct<T, 4>), grid, dim3(256), 0, s, A); break;
+    if (percell) {
+        dim3 grid((unsigned)((N + 255) / 256), (unsigned)S);
+        switch (nf) {
+        case 1: hipLaunchKernelGGL((k_direct<T, 1>), grid, dim3(256), 0, s, A); break;
+        case 2: hipLaunchKernelGGL((k_direct<T, 2>), grid, dim3(256), 0, s, A); break;
+        case 3: hipLaunchKernelGGL((k_direct<T, 3>), grid, dim3(256), 0, s, A); break;
+        default: hipLaunchKernelGGL((k_direct<T, 4>), grid, dim3(256), 0, s, A); break;
+        }
+    } else {
+        S = ring_sum<T, 2>(A, nf, S, s);
     }
     SG_HIP(hipGetLastError());
     const unsigned nb = (unsigned)((N + 255) / 256);
@@ -607,7 +844,7 @@ static sg_status potential_run(const sg_grid *g, int nf, const double *h, const 
     const double du = log(g->r_max / g->r_min) / nr;
     const double dphi = 2.0 * SG_PI / nphi;
     const double lnrmin = log(g->r_min);
-    const int S = direct_splits(nr, N);
+    int S = direct_splits(nr, N);
     const int rps = (nr + S - 1) / S;
     char *o = (char *)ws;
     auto take = [&](size_t bytes) {
@@ -658,12 +895,16 @@ static sg_status potential_run(const sg_grid *g, int nf, const double *h, const 
     A.mass = mass;
     A.H2 = H2;
     A.partial = partial;
-    dim3 grid((unsigned)((N + 255) / 256), (unsigned)S);
-    switch (nf) {
-    case 1: hipLaunchKernelGGL((k_potential<T, 1>), grid, dim3(256), 0, s, A); break;
-    case 2: hipLaunchKernelGGL((k_potential<T, 2>), grid, dim3(256), 0, s, A); break;
-    case 3: hipLaunchKernelGGL((k_potential<T, 3>), grid, dim3(256), 0, s, A); break;
-    default: hipLaunchKernelGGL((k_potential<T, 4>), grid, dim3(256), 0, s, A); break;
+    if (percell) {
+        dim3 grid((unsigned)((N + 255) / 256), (unsigned)S);
+        switch (nf) {
+        case 1: hipLaunchKernelGGL((k_potential<T, 1>), grid, dim3(256), 0, s, A); break;
+        case 2: hipLaunchKernelGGL((k_potential<T, 2>), grid, dim3(256), 0, s, A); break;
+        case 3: hipLaunchKernelGGL((k_potential<T, 3>), grid, dim3(256), 0, s, A); break;
+        default: hipLaunchKernelGGL((k_potential<T, 4>), grid, dim3(256), 0, s, A); break;
+        }
+    } else {
+        S = ring_sum<T, 1>(A, nf, S, s);
     }
     SG_HIP(hipGetLastError());
     const unsigned nb = (unsigned)((N + 255) / 256);

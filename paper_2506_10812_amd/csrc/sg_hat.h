@@ -76,10 +76,13 @@ __device__ inline void sg_hat_corner(int P, int Q, int sx, int sy, bool sym, dou
                                      double &wr, double &wp)
 {
     const int nx = sg_own_nx(du, dphi, fmin(ha, hb)), n = nx * gl.ne;
+    const OwnEta e0(du, dphi), e1(dphi, du);
     for (int idx = k0; idx < n; idx += dk) {
-        double xi, eta, wgt;
-        sg_own_node(gl, nx, idx, xi, eta, wgt);
+        double xi, s, wn;
+        sg_own_node(gl, nx, idx, xi, s, wn);
         for (int tri = 0; tri < 2; ++tri) {
+            double wgt = wn;
+            const double eta = (tri == 0 ? e0 : e1).at(s, wgt);
             const double x = tri == 0 ? xi : xi * eta, y = tri == 0 ? xi * eta : xi;
             const double X = sx * x * du, ph = sy * y * dphi;
             // hats from the corner: 1 - x at a corner s = 0, x at s = +-1

@@ -378,12 +378,14 @@ k_ss_self_lin(const double *H, int nf, int nr, int per, double rmin, double dr, 
         const double sgn = sd == 0 ? 1.0 : -1.0;
         const double a = sd == 0 ? log1p(0.5 * dr / r) : -log1p(-0.5 * dr / r);
         const int nx = sg_own_nx(a, b, fmin(ha, hb)), n = nx * gl.ne;
+        const OwnEta e0(a, b), e1(b, a);
         for (int idx = threadIdx.x; idx < n; idx += blockDim.x) {
-            double xi, eta, wgt;
-            sg_own_node(gl, nx, idx, xi, eta, wgt);
-            wgt *= a * b;
-            double f = 0.0;
+            double xi, s, wn;
+            sg_own_node(gl, nx, idx, xi, s, wn);
+            wn *= a * b;
             for (int tri = 0; tri < 2; ++tri) {
+                double wgt = wn, f;
+                const double eta = (tri == 0 ? e0 : e1).at(s, wgt);
                 const double X = sgn * (tri == 0 ? a * xi : a * xi * eta);
                 const double phi = tri == 0 ? b * xi * eta : b * xi;
                 if (pot) {
@@ -391,20 +393,20 @@ k_ss_self_lin(const double *H, int nf, int nr, int per, double rmin, double dr, 
                     const double s2 = r * r * exp(X) * 4.0 * (sx * sx + sp * sp);
                     const double y = s2 / (8.0 * Hab * Hab);
                     if (which == 0) {
-                        f += -sg_G0_64(y, wq) / (2.0 * SG_SQRT_PI * Hab) * r * r * exp(2.0 * X);
+                        f = -sg_G0_64(y, wq) / (2.0 * SG_SQRT_PI * Hab) * r * r * exp(2.0 * X);
                     } else {
                         // dP/dH_ab = -(2 y F(y) - G0(y)) / (2 sqrt(pi) H_ab^2), times dH_ab/dh
                         const double ch = (which == 1 ? Ha : Hb) * r / (2.0 * Hab);
-                        f += -(2.0 * y * sg_F64(y, wq) - sg_G0_64(y, wq)) / (2.0 * SG_SQRT_PI * Hab * Hab) * ch *
+                        f = -(2.0 * y * sg_F64(y, wq) - sg_G0_64(y, wq)) / (2.0 * SG_SQRT_PI * Hab * Hab) * ch *
                              r * r * exp(2.0 * X);
                     }
                 } else {
                     double kr, kp;
                     sg_conv_kernel64(X, sin(0.5 * phi), sin(phi), ha, hb, which, wq, kr, kp);
-                    f += kr;
+                    f = kr;
                 }
+                acc += wgt * f;
             }
-            acc += wgt * f;
         }
     }
     red[threadIdx.x] = acc;

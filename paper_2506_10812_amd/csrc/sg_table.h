@@ -2,7 +2,7 @@
 #pragma once
 #include "sg_internal.h"
 
-#define SG_GL_N 48          // largest Gauss-Legendre order across the self cell (eta)
+#define SG_GL_N 24          // largest Gauss-Legendre order across the self cell (eta)
 #define SG_GLX_N 16         // Gauss-Legendre order per radial panel (xi)
 #define SG_PANELS 7         // geometric xi panels [0,4^-6], [4^-(j+1), 4^-j]
 #define SG_GLT_N 24         // Gauss-Legendre order of the graded xi rule (xi = t^4)
@@ -18,23 +18,22 @@ struct GLNodes {
     double tx[SG_GLT_N], tw[SG_GLT_N];
 };
 
-// Node idx of the rule with nx xi nodes: (xi, eta) and its weight, the
-// Jacobian's xi included.
+// Node idx of the rule with nx xi nodes: xi, the eta node's s in [0, 1] (see
+// OwnEta) and the weight, the Jacobian's xi included.
 //
 // Both xi rules integrate over [0, 1] with a logarithm at 0.  xi = t^4 takes
 // the logarithm down to t^7 log t and 24 nodes then reach 1e-13, the level
 // of the panel rule's 112 (measured against 9 panels x 24 nodes on cells of
 // aspect 1/2 to 2 and H_a/H_b of 1/10 to 10: field <= 3e-13, its h
-// derivatives <= 2e-13 beside 2e-13 of the panels, potential <= 1e-15 beside
-// 1e-12).  It holds while the cell is not much larger than H: at half side /
-// H = 16 the derivatives are at 1e-11, so beyond SG_OWN_RMAX the panels
-// resolve the transition of F at distances ~ H.  In eta the integrand's
-// nearest singularities sit at +-i (short side / long side): 20 nodes give
-// 4e-15 up to an aspect of 2, 32 give 5e-15 up to 8, 48 beyond.
-__device__ inline void sg_own_node(const GLNodes &gl, int nx, int idx, double &xi, double &eta, double &wgt)
+// derivatives <= 2e-13, potential <= 1e-15).  It holds while the cell is not
+// much larger than H: at half side / H = 16 the derivatives are at 1e-11, so
+// beyond SG_OWN_RMAX the panels resolve the transition of F at distances
+// ~ H, the innermost one graded likewise (its logarithm left 1e-12 to 1e-10
+// in the potential of cells 10 to 1000 H across; 4e-16 with the grading).
+__device__ inline void sg_own_node(const GLNodes &gl, int nx, int idx, double &xi, double &s, double &wgt)
 {
     const int ix = idx / gl.ne, j = idx % gl.ne;
-    eta = gl.x[j];
+    s = gl.x[j];
     if (nx == SG_GLT_N) {
         xi = gl.tx[ix];
         wgt = gl.tw[ix] * gl.w[j] * xi;
@@ -42,10 +41,26 @@ __device__ inline void sg_own_node(const GLNodes &gl, int nx, int idx, double &x
     }
     const int pnl = ix / SG_GLX_N, i = ix % SG_GLX_N;
     const double hi = ldexp(1.0, -2 * (SG_PANELS - 1 - pnl));
-    const double lo = pnl == 0 ? 0.0 : 0.25 * hi;
-    xi = lo + (hi - lo) * gl.xr[i];
-    wgt = (hi - lo) * gl.wr[i] * gl.w[j] * xi;
+    const double t = gl.xr[i];
+    xi = pnl == 0 ? hi * (t * t) * (t * t) : 0.25 * hi + 0.75 * hi * t;
+    wgt = hi * (pnl == 0 ? 4.0 * t * t * t : 0.75) * gl.wr[i] * gl.w[j] * xi;
 }
+
+// The triangle X = a xi, phi = b xi eta has its nearest singularities at eta
+// = +-i a/b (the other triangle at +-i b/a).  eta = q sinh(s asinh(1/q)), q
+// that ratio, moves them to a distance that shrinks only with log(1/q): 16
+// nodes reach 4e-14 up to an aspect of 8 and 24 nodes 2e-13 up to 500 (plain
+// Gauss-Legendre: 48 nodes 1e-13 at 20, 4e-7 at 100).
+struct OwnEta {
+    double q, L;
+    __device__ inline OwnEta(double num, double den) : q(num / den), L(asinh(den / num)) {}
+    __device__ inline double at(double s, double &w) const
+    {
+        const double e = sinh(s * L);
+        w *= q * L * sqrt(1.0 + e * e);
+        return q * e;
+    }
+};
 
 // xi nodes for an own cell of half sides a, b (in ln r and phi) and aspect
 // ratio h (the smallest of the heights involved, over r).

@@ -74,6 +74,13 @@ __device__ inline OwnPt own_pt(double X, double phi, double w)
     return q;
 }
 
+// Node of triangle tri (0: X = a xi, phi = b xi eta; 1: X = a xi eta, phi = b xi).
+__device__ inline OwnPt own_tri_pt(double a, double b, const OwnEta &e, int tri, double xi, double s, double w)
+{
+    const double eta = e.at(s, w);
+    return tri == 0 ? own_pt(a * xi, b * xi * eta, w) : own_pt(a * xi * eta, b * xi, w);
+}
+
 // F(x) h^-3, x = c / (4 h^2)
 __device__ inline double own_val(double c, double h2, const double *wq)
 {
@@ -119,13 +126,14 @@ __device__ inline double self_cell_partial(double ha, double hb, int which, doub
 {
     const int nx = sg_own_nx(a, b, fmin(ha, hb)), n = nx * gl.ne;
     const double h0 = 0.5 * (ha * ha + hb * hb), g = 0.5 * (hb * hb - ha * ha);
+    const OwnEta e0(a, b), e1(b, a);
     double acc = 0.0;
     for (int idx = threadIdx.x; idx < n; idx += blockDim.x) {
-        double xi, eta, w;
-        sg_own_node(gl, nx, idx, xi, eta, w);
+        double xi, s, w;
+        sg_own_node(gl, nx, idx, xi, s, w);
 #pragma unroll 1
         for (int tri = 0; tri < 2; ++tri) {
-            const OwnPt q = tri == 0 ? own_pt(a * xi, b * xi * eta, w) : own_pt(a * xi * eta, b * xi, w);
+            const OwnPt q = own_tri_pt(a, b, tri == 0 ? e0 : e1, tri, xi, s, w);
             if (which)
                 acc += own_dnode(q, ha, hb, which, wq);
             else if (g == 0.0)
@@ -204,12 +212,13 @@ k_self_cells(const T *H, int64_t N, int nphi, double lnrmin, double du, double d
     double acc[CPB * NF * NF];
 #pragma unroll
     for (int k = 0; k < CPB * NF * NF; ++k) acc[k] = 0.0;
+    const OwnEta e0(a, b), e1(b, a);
     for (int idx = threadIdx.x; idx < n; idx += 256) {
-        double xi, eta, w;
-        sg_own_node(gl, nx, idx, xi, eta, w);
+        double xi, s, w;
+        sg_own_node(gl, nx, idx, xi, s, w);
 #pragma unroll 1
         for (int tri = 0; tri < 2; ++tri) {
-            const OwnPt q = tri == 0 ? own_pt(a * xi, b * xi * eta, w) : own_pt(a * xi * eta, b * xi, w);
+            const OwnPt q = own_tri_pt(a, b, tri == 0 ? e0 : e1, tri, xi, s, w);
 #pragma unroll
             for (int c = 0; c < CPB; ++c)
 #pragma unroll
@@ -333,14 +342,17 @@ k_pot_cells(const T *H, const double *h, int nf, int64_t per, int nphi, double l
     double acc[CPB];
 #pragma unroll
     for (int c = 0; c < CPB; ++c) acc[c] = 0.0;
+    const OwnEta e0(a, b), e1(b, a);
     for (int idx = threadIdx.x; idx < n; idx += 256) {
-        double xi, eta, w;
-        sg_own_node(gl, nx, idx, xi, eta, w);
+        double xi, sn, w;
+        sg_own_node(gl, nx, idx, xi, sn, w);
 #pragma unroll 1
         for (int k = 0; k < 4; ++k) {
+            double wk = w;
+            const double eta = (k & 2 ? e1 : e0).at(sn, wk);
             const double X = (k & 1 ? -a : a) * (k & 2 ? xi * eta : xi), phi = k & 2 ? b * xi : b * xi * eta;
-            const double s = sinh(0.5 * X), sp = sin(0.5 * phi), e1 = sqrt(1.0 + s * s) + s;
-            const double eX = e1 * e1, cy = eX * (2.0 * s * s + 2.0 * sp * sp), we = w * eX * eX;
+            const double s = sinh(0.5 * X), sp = sin(0.5 * phi), ex = sqrt(1.0 + s * s) + s;
+            const double eX = ex * ex, cy = eX * (2.0 * s * s + 2.0 * sp * sp), we = wk * eX * eX;
 #pragma unroll
             for (int c = 0; c < CPB; ++c) {
                 const double y = cy * r2H[c], G = sg_G0_64<true>(y, wq);
@@ -676,12 +688,12 @@ static void gl_rule(int n, double *x, double *w)
 }
 
 namespace {
-struct GLCache {  // eta orders 20, 32 and 48 (sg_own_node), the same xi rules in each
-    GLNodes g[3];
+struct GLCache {  // eta orders 16 and 24 (OwnEta), the same xi rules in each
+    GLNodes g[2];
     GLCache()
     {
-        const int order[3] = {20, 32, SG_GL_N};
-        for (int k = 0; k < 3; ++k) {
+        const int order[2] = {16, SG_GL_N};
+        for (int k = 0; k < 2; ++k) {
             g[k] = GLNodes{};
             g[k].ne = order[k];
             gl_rule(order[k], g[k].x, g[k].w);
@@ -700,8 +712,7 @@ struct GLCache {  // eta orders 20, 32 and 48 (sg_own_node), the same xi rules i
 void sg_gl_nodes(GLNodes &gl, double aspect)
 {
     static const GLCache cache;  // built once, by the first caller
-    const double q = aspect < 1.0 ? 1.0 / aspect : aspect;
-    gl = cache.g[q <= 2.0 ? 0 : q <= 8.0 ? 1 : 2];
+    gl = cache.g[aspect <= 8.0 && aspect >= 0.125 ? 0 : 1];
 }
 
 template <int NPHI>
