@@ -24,7 +24,8 @@
 //      (shared by two rows, whose transforms are real),
 //      T_r(m) = (Z[m] + Z[-m])/2, t_phi(m) = (Z[-m] - Z[m])/2,
 //      scaled by -du dphi / n_phi (the inverse transform of the last pass is
-//      unnormalised); rows are written [row][m] to a chunk buffer;
+//      unnormalised); rows are written [row][m] to a chunk buffer.  Ring
+//      pairs far apart take fewer samples (SsClass below);
 //   3. a tiled transpose moves each chunk into the table: full modes keep
 //      every (i', i) entry, banded modes the diagonals |i' - i| <= w (the
 //      band rule is in sg_internal.h; dropped couplings are below about
@@ -44,6 +45,9 @@
 //
 // Solve (sg_field_fft with discs flagged SG_SEMI_SPECTRAL): pass 1 and pass 3
 // of the FFT path (phi transforms), and k_ss_pass in place of pass 2.
+#include <algorithm>
+#include <vector>
+
 #include "sg_kfn.h"
 #include "sg_semispec.h"
 #include "sg_adjoint.h"
@@ -73,43 +77,147 @@ struct SsRowArgs {
 // parts in thread order), so that no single lane carries a polar rule.
 #define SG_SS_HAT_NEAR 32.0
 
+// Band-limited rows.  The kernels between rings |X| apart are analytic in phi
+// within |Im phi| < |X|, so their Fourier coefficients fall off as e^{-m|X|}
+// and M samples give every mode m <= M/2 to e^{-(M-m)|X|} of the axisymmetric
+// coupling.  A row takes the smallest power of two M >= SG_SS_MIN_M with
+// M |X| >= SG_SS_ALIAS instead of n_phi samples: aliases and the modes above
+// M/2, which stay zero, are below e^{-40} = 4e-18, under the rounding of a
+// double transform.  Most ring pairs are far apart: on the 1200 x 2048 grid
+// the rows take 0.17 of the samples.  SG_SS_FULL keeps n_phi throughout.
+//
+// The rows of one M form a class: the tiles of SG_SS_TI consecutive target
+// rings (of one b, a, i') whose nearest ring lies x1 <= |X| < x2 away.  They
+// are numbered unit = (pair n_r + i') U + v, v counting the class's tiles of
+// source ring i' (right of it first, then left), U an upper bound.
+#define SG_SS_ALIAS 80.0
+#define SG_SS_ALIAS_GRAD 96.0  // h derivatives have double poles at phi = +-i X
+#define SG_SS_MIN_M 128
+#define SG_SS_TI 16
+
+struct SsClass {
+    int on;          // 0: every row, in the plain (b, a, i', i) order
+    int U, nt;       // units per source ring; tiles of a ring's targets
+    int first;       // contains |X| = 0
+    double x1, x2;   // the class's range of |X| (x2 infinite in the last)
+};
+
+// First target row right of ring ip with X >= x, and last one left of it with
+// X <= -x (clamped to one past the grid).
+__device__ __host__ inline void ss_reach(bool lin, double du, double rmin, double dr, int nr, int ip, double x,
+                                         int &right, int &left)
+{
+    double hi, lo;
+    if (lin) {
+        const double r = rmin + (ip + 0.5) * dr;
+        hi = ceil((r * exp(fmin(x, 700.0)) - rmin) / dr - 0.5);
+        lo = floor((r * exp(-fmin(x, 700.0)) - rmin) / dr - 0.5);
+    } else {
+        const double k = ceil(fmin(x / du, 1e9));
+        hi = ip + k;
+        lo = ip - k;
+    }
+    right = hi > nr + SG_SS_TI ? nr + SG_SS_TI : (int)hi;
+    left = lo < -SG_SS_TI - 1.0 ? -SG_SS_TI - 1 : (int)lo;
+}
+
+__device__ __host__ inline int ss_tiles_up(int x) { return (x + SG_SS_TI - 1) / SG_SS_TI; }      // ceil, x >= 0
+__device__ __host__ inline int ss_tiles_down(int x) { return x < 0 ? -1 - (-1 - x) / SG_SS_TI : x / SG_SS_TI; }  // floor
+
 template <int N> struct SsRowShape {
     static constexpr int P = FftShape<N>::P, T = FftShape<N>::T;
     static constexpr int WGS = T > 256 ? T : 256;
     static constexpr int G = WGS / T;
 };
 
-// A group of T threads takes RPG consecutive rows R = r0 + row of the
-// (b, a, i', i) order (i fastest), out: [nrows][ncol] float2 (T_r, t_phi),
+// Row idx of a class (or of the plain order): its ring pair; false where the
+// class has none (i may then be past the grid, never a padding row's tile).
+__device__ inline bool ss_row(const SsRowArgs &A, const SsClass &C, size_t idx, int &b, int &a, int &ip, int &i)
+{
+    size_t rest;
+    bool ok = true;
+    if (!C.on) {
+        i = (int)(idx % A.nrt);
+        rest = idx / A.nrt;
+        ip = (int)(rest % A.nr);
+    } else {
+        const size_t unit = idx / SG_SS_TI;
+        int v = (int)(unit % C.U);
+        rest = unit / C.U;
+        ip = (int)(rest % A.nr);
+        int r1, l1, r2, l2;  // x1 and x2 to the right and to the left
+        ss_reach(A.lin != 0, A.du, A.rmin, A.dr, A.nr, ip, C.x1, r1, l1);
+        ss_reach(A.lin != 0, A.du, A.rmin, A.dr, A.nr, ip, C.x2, r2, l2);
+        // tiles right: first row in [r1, r2); left: last row in (l2, l1]
+        int ra = ss_tiles_up(max(r1, 0)), rb = min(ss_tiles_up(max(r2, 0)), C.nt);
+        int la = max(ss_tiles_down(l2 - (SG_SS_TI - 1)) + 1, 0), lb = min(ss_tiles_down(l1 - (SG_SS_TI - 1)) + 1, C.nt);
+        if (C.first) {  // both sides and the tile around i' in one run
+            ra = la;
+            lb = la;
+        }
+        const int nright = max(rb - ra, 0);
+        int t = ra + v;
+        if (v >= nright) {
+            v -= nright;
+            t = la + v;
+            ok = v < lb - la;
+        }
+        i = t * SG_SS_TI + (int)(idx % SG_SS_TI);
+        ok = ok && i < A.nrt;
+    }
+    rest /= A.nr;
+    a = (int)(rest % A.nf);
+    b = (int)(rest / A.nf);
+    return ok && b < A.nf;
+}
+
+// Second-order sample away from the singular point: the point value plus the
+// second moments of the hats, W = K + (D_X^2 K + D_phi^2 K)/12.
+__device__ inline void ss_far_weight(const ConvRow64 &c0, const ConvRow64 &c1, const ConvRow64 &c2, double phi_pi,
+                                     double step_pi, const double *wq, double &kr, double &kp)
+{
+    double r[5], p[5];
+#pragma unroll 1
+    for (int k = 0; k < 5; ++k) {
+        double sh, ch;  // half angle
+        sincospi(0.5 * (phi_pi + (k == 3 ? step_pi : k == 4 ? -step_pi : 0.0)), &sh, &ch);
+        sg_conv_kernel64_row(k == 1 ? c1 : k == 2 ? c2 : c0, sh, 2.0 * sh * ch, wq, r[k], p[k]);
+    }
+    kr = r[0] + (r[1] + r[2] + r[3] + r[4] - 4.0 * r[0]) / 12.0;
+    kp = p[0] + (p[1] + p[2] + p[3] + p[4] - 4.0 * p[0]) / 12.0;
+}
+
+// A group of T threads takes RPG consecutive rows r0 + row of a class (or of
+// the plain (b, a, i', i) order, i fastest), out: [nrows][ncol] float2 (T_r, t_phi),
 // m = 0 .. N/2.  Point-sampled rows go two to a group (RPG = 2): a row's
 // samples z = K_r + i K_phi are Hermitian in phi, so its transform Z is real,
 // and the group transforms z_A + i z_B once, reading Z_A from the real part
 // and Z_B from the imaginary part.  The row count is even (n_rt is) and so
 // is every chunk, so the two rows are always i and i + 1 of one (b, a, i').
-// Second-order rows (SO) keep one row per group.
-template <int N, bool SO>
+// N: the samples of the rows, n_phi or a class's M.  SO: 0 point samples; 1
+// second-order rows with samples to integrate (one row per group); 2
+// second-order rows beyond SG_SS_HAT_NEAR, whose samples are the weights of
+// ss_far_weight.
+template <int N, int SO>
 __global__ void __launch_bounds__(SsRowShape<N>::WGS)
-k_ss_rows(const double *H, const double *self, SsRowArgs A, size_t r0, int nrows, float2 *out)
+k_ss_rows(const double *H, const double *self, SsRowArgs A, SsClass C, size_t r0, int nrows, float2 *out)
 {
     using S = SsRowShape<N>;
     constexpr int P = S::P, T = S::T, G = S::G, W = LdsPlane<double>::elems(N);
     constexpr int NC = N / 2 + 1;
-    constexpr int RPG = SO ? 1 : 2;
+    constexpr int RPG = SO == 1 ? 1 : 2;
     __shared__ __attribute__((aligned(16))) double2 lds[W * G];
     __shared__ double wq[FQuad<double>::TABLE];
-    __shared__ double2 qres[SO ? NC * G : 1];  // SO: the group's integrated samples
-    __shared__ int qmax_wg;                    // SO: last integrated sample of any group
-    sg_fill_weights<double>(wq);
+    __shared__ double2 qres[SO == 1 ? NC * G : 1];  // SO: the group's integrated samples
+    __shared__ int qmax_wg;                         // SO: last integrated sample of any group
     const int g = threadIdx.x / T, t = threadIdx.x % T;
     const LdsPlane<double> pl{lds + W * g};
     const int row = (blockIdx.x * G + g) * RPG;  // the group's first row
-    const bool valid = row < nrows;
-    const size_t R = r0 + (size_t)(valid ? row : 0);
-    const int i0 = (int)(R % A.nrt);
-    size_t rest = R / A.nrt;
-    const int ip = (int)(rest % A.nr);
-    rest /= A.nr;
-    const int a = (int)(rest % A.nf), b = (int)(rest / A.nf);
+    int i0, ip, a, b;
+    const bool valid = ss_row(A, C, r0 + (size_t)(row < nrows ? row : 0), b, a, ip, i0) && row < nrows;
+    if (!__syncthreads_or(valid ? 1 : 0)) return;
+    if (!valid) b = a = ip = i0 = 0;
+    sg_fill_weights<double>(wq);
     const double rp = A.lin ? A.rmin + (ip + 0.5) * A.dr : exp(A.lnrmin + (ip + 0.5) * A.du);
     const double ha = H[a * A.nr + ip] / rp;
     // per row of the group: target ring (padding rows take the last ring and
@@ -130,7 +238,7 @@ k_ss_rows(const double *H, const double *self, SsRowArgs A, size_t r0, int nrows
     const int ic = ic_[0];
     const double ri = ri_[0], hb = hb_[0], X = X_[0];
     __syncthreads();
-    if constexpr (SO) {
+    if constexpr (SO == 1) {
         // 1'. hat-weighted samples (see SG_SS_HAT_NEAR): point values of K go
         // to the plane for the neighbours' second differences, the weights
         // stay in registers until every neighbour has been read
@@ -212,11 +320,15 @@ k_ss_rows(const double *H, const double *self, SsRowArgs A, size_t r0, int nrows
     // 1. samples q in [0, N/2] of both rows, packed as z_A + i z_B and
     // mirrored into the upper half (z(-q) = conj z(q) for each row); the
     // factors that depend on a row alone are formed once
-    ConvRow64 cr[RPG];
+    ConvRow64 cr[RPG], cp1[SO == 2 ? RPG : 1], cp2[SO == 2 ? RPG : 1];
     double sx[RPG], Hab2[RPG], pot_pref[RPG];
 #pragma unroll
     for (int u = 0; u < RPG; ++u) {
         cr[u] = sg_conv_row64(X_[u], ha, hb_[u]);
+        if constexpr (SO == 2) {
+            cp1[u] = sg_conv_row64(X_[u] + A.du, ha, hb_[u]);
+            cp2[u] = sg_conv_row64(X_[u] - A.du, ha, hb_[u]);
+        }
         sx[u] = sinh(0.5 * X_[u]);
         Hab2[u] = 0.5 * (ha * rp * ha * rp + hb_[u] * ri_[u] * hb_[u] * ri_[u]);
         pot_pref[u] = rp * rp / (2.0 * SG_SQRT_PI * sqrt(Hab2[u]));
@@ -230,6 +342,10 @@ k_ss_rows(const double *H, const double *self, SsRowArgs A, size_t r0, int nrows
         for (int u = 0; u < RPG; ++u) {
             kr[u] = 0.0;
             kp[u] = 0.0;
+            if constexpr (SO == 2) {
+                ss_far_weight(cr[u], cp1[u], cp2[u], 2.0 * q / N, A.dphi / SG_PI, wq, kr[u], kp[u]);
+                continue;
+            }
             if (ic_[u] == ip && q == 0) {
                 kr[u] = A.excl ? 0.0 : self[(size_t)(a * A.nf + b) * A.nr + ic_[u]];
             } else if (A.pot) {
@@ -288,28 +404,27 @@ k_ss_rows(const double *H, const double *self, SsRowArgs A, size_t r0, int nrows
 }
 
 // ------------------------------------------------------- table: transpose
-// src [nrows][ncol] (rows r0 + row of the (b, a, i', i) order) into the
-// modes' layouts, 32 x 32 tiles: for a fixed mode consecutive rows are
-// consecutive target columns in both layouts.
+// src [nrows][ncol] (rows r0 + row of a class or of the plain order, its modes
+// m < ncol) into the modes' layouts, 32 x 32 tiles: for a fixed mode
+// consecutive rows are consecutive target columns in both layouts.
 __global__ void __launch_bounds__(256)
-k_ss_scatter(const float2 *src, int nrows, int ncol, float2 *coef, const SsMode *modes, size_t r0, int nr,
-             int nrt)
+k_ss_scatter(const float2 *src, int nrows, int ncol, float2 *coef, const SsMode *modes, SsRowArgs A, SsClass C,
+             size_t r0)
 {
     __shared__ float2 tile[32][33];
     const int rb = blockIdx.x * 32, mb = blockIdx.y * 32;
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+    const int r = rb + tx;
+    int i, ip, a, b;
+    const bool ok = ss_row(A, C, r0 + (r < nrows ? r : 0), b, a, ip, i) && r < nrows;
+    if (!__syncthreads_or(ok ? 1 : 0)) return;
     for (int k = ty; k < 32; k += 8) {
-        const int r = rb + k, m = mb + tx;
-        if (r < nrows && m < ncol) tile[k][tx] = gload2(src, (size_t)r * ncol + m);
+        const int rr = rb + k, m = mb + tx;
+        if (rr < nrows && m < ncol) tile[k][tx] = gload2(src, (size_t)rr * ncol + m);
     }
     __syncthreads();
-    const int r = rb + tx;
-    if (r >= nrows) return;
-    const size_t R = r0 + r;
-    const int i = (int)(R % nrt);
-    const size_t rest = R / nrt;
-    const int ip = (int)(rest % nr);
-    const size_t pair = rest / nr;  // b * F + a
+    if (!ok) return;
+    const size_t pair = (size_t)b * A.nf + a;
     for (int k = ty; k < 32; k += 8) {
         const int m = mb + k;
         if (m >= ncol) break;
@@ -318,29 +433,46 @@ k_ss_scatter(const float2 *src, int nrows, int ncol, float2 *coef, const SsMode 
         if (md.banded) {
             const int d = ip - i + md.w;
             if (d < 0 || d > 2 * md.w) continue;
-            dst = md.off + (pair * (2 * md.w + 1) + d) * nrt + i;
+            dst = md.off + (pair * (2 * md.w + 1) + d) * A.nrt + i;
         } else {
-            dst = md.off + (pair * nr + ip) * nrt + i;
+            dst = md.off + (pair * A.nr + ip) * A.nrt + i;
         }
         gstore2(coef, dst, tile[tx][k]);
     }
 }
 
-// Mode descriptors (one thread; the same band rule as the host layout, with
-// the host's du).
-__global__ void k_ss_modes(SsMode *modes, int ncol, int nr, int nrt, int nf, double du, int full)
+// Mode descriptors (one block; the same band rule as the host layout, with
+// the host's du): thread t takes ncol/256 consecutive modes, the offsets come
+// from a prefix sum over the threads (a single thread took 66 to 125 us for
+// 513 to 1025 modes).
+__global__ void __launch_bounds__(256) k_ss_modes(SsMode *modes, int ncol, int nr, int nrt, int nf, double du, int full)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    uint64_t off = 0;
-    for (int m = 0; m < ncol; ++m) {
-        const int w = sg_ss_band(m, nr, du, full != 0);
-        const bool b = sg_ss_is_banded(w, nr);
+    __shared__ uint64_t sum[256];
+    const int per = (ncol + 255) / 256, m0 = threadIdx.x * per, m1 = min(ncol, m0 + per);
+    auto rows = [&](int m, int &w) {
+        w = sg_ss_band(m, nr, du, full != 0);
+        return sg_ss_is_banded(w, nr) ? 2 * w + 1 : nr;
+    };
+    uint64_t mine = 0;
+    int w;
+    for (int m = m0; m < m1; ++m) mine += (uint64_t)rows(m, w);
+    sum[threadIdx.x] = mine;
+    __syncthreads();
+    for (int o = 1; o < 256; o <<= 1) {
+        const uint64_t v = (int)threadIdx.x >= o ? sum[threadIdx.x - o] : 0;
+        __syncthreads();
+        sum[threadIdx.x] += v;
+        __syncthreads();
+    }
+    uint64_t off = sum[threadIdx.x] - mine;
+    for (int m = m0; m < m1; ++m) {
+        const int n = rows(m, w);
         SsMode md;
-        md.off = off;
+        md.off = off * ((uint64_t)nf * nf * nrt);
         md.w = w;
-        md.banded = b ? 1 : 0;
+        md.banded = sg_ss_is_banded(w, nr) ? 1 : 0;
         modes[m] = md;
-        off += (uint64_t)nf * nf * (b ? 2 * w + 1 : nr) * nrt;
+        off += (uint64_t)n;
     }
 }
 
@@ -460,35 +592,77 @@ size_t sg_ss_ws_bytes(int nr, int nphi, int nf)
            sg_align256(sizeof(float2) * L.ncol * ss_chunk_rows(L));
 }
 
-template <int N>
-static void launch_ss_rows(const double *H, const double *self, const SsRowArgs &A, size_t r0, int nrows,
-                           float2 *out, hipStream_t s)
+// The row classes of a build: one launch set each (kind: SO of k_ss_rows).
+struct SsPart {
+    int M, kind;
+    SsClass C;
+};
+
+// full: no band limit.  alias: SG_SS_ALIAS or SG_SS_ALIAS_GRAD.
+static std::vector<SsPart> ss_parts(const SsRowArgs &A, int nphi, bool full, double alias)
 {
-    using S = SsRowShape<N>;
-    if (A.second)  // its own instance: the quadrature's registers stay out of the point-sampled rows
-        hipLaunchKernelGGL((k_ss_rows<N, true>), dim3((nrows + S::G - 1) / S::G), dim3(S::WGS), 0, s, H, self,
-                           A, r0, nrows, out);
-    else  // two rows per group (nrows is even: see k_ss_rows)
-        hipLaunchKernelGGL((k_ss_rows<N, false>), dim3((nrows + 2 * S::G - 1) / (2 * S::G)), dim3(S::WGS), 0, s,
-                           H, self, A, r0, nrows, out);
+    std::vector<SsPart> out;
+    SsClass C{};
+    const bool split = A.nr >= 2 * SG_SS_TI && (A.second || (!full && nphi > SG_SS_MIN_M));
+    if (!split) {
+        out.push_back({nphi, A.second ? 1 : 0, C});
+        return out;
+    }
+    const double rlast = A.rmin + (A.nr - 0.5) * A.dr, rfirst = A.rmin + 0.5 * A.dr;
+    const double xmax = A.lin ? log(rlast / rfirst) : (A.nr - 1) * A.du;
+    const double inf = INFINITY, rn = A.second ? SG_SS_HAT_NEAR * fmax(A.du, A.dphi) : 0.0;
+    C.on = 1;
+    C.nt = (A.nrt + SG_SS_TI - 1) / SG_SS_TI;
+    auto add = [&](int M, int kind, double x1, double x2) {
+        if (x1 >= x2 || x1 > xmax) return;
+        C.first = x1 == 0.0 ? 1 : 0;
+        C.x1 = x1;
+        C.x2 = x2;
+        C.U = C.nt;
+        if (!A.lin) {  // a bound on the tiles per source ring
+            const double k1 = ceil(x1 / A.du), k2 = ceil(fmin(x2 / A.du, 1e9));
+            const double n = C.first ? (2.0 * k2 + SG_SS_TI) / SG_SS_TI + 2.0 : 2.0 * ((k2 - k1) / SG_SS_TI + 1.0);
+            if (n < C.U) C.U = (int)n;
+        }
+        out.push_back({M, kind, C});
+    };
+    if (A.second) add(nphi, 1, 0.0, rn);
+    for (int M = nphi;; M /= 2) {
+        const bool last = full || M / 2 < SG_SS_MIN_M;
+        const double x1 = M == nphi ? 0.0 : alias / M, x2 = last ? inf : alias / (M / 2);
+        add(M, A.second ? 2 : 0, fmax(x1, rn), fmax(x2, rn));
+        if (last) break;
+    }
+    return out;
 }
 
-static bool dispatch_ss_rows(int nphi, const double *H, const double *self, const SsRowArgs &A, size_t r0,
+template <int N>
+static void launch_ss_rows(const double *H, const double *self, const SsRowArgs &A, const SsPart &P, size_t r0,
+                           int nrows, float2 *out, hipStream_t s)
+{
+    using S = SsRowShape<N>;
+    // the quadrature's registers stay out of the other rows; two rows per
+    // group unless integrated (nrows is even: see k_ss_rows)
+    const dim3 one((nrows + S::G - 1) / S::G), two((nrows + 2 * S::G - 1) / (2 * S::G));
+    if (P.kind == 1)
+        hipLaunchKernelGGL((k_ss_rows<N, 1>), one, dim3(S::WGS), 0, s, H, self, A, P.C, r0, nrows, out);
+    else if (P.kind == 2)
+        hipLaunchKernelGGL((k_ss_rows<N, 2>), two, dim3(S::WGS), 0, s, H, self, A, P.C, r0, nrows, out);
+    else
+        hipLaunchKernelGGL((k_ss_rows<N, 0>), two, dim3(S::WGS), 0, s, H, self, A, P.C, r0, nrows, out);
+}
+
+static bool dispatch_ss_rows(const double *H, const double *self, const SsRowArgs &A, const SsPart &P, size_t r0,
                              int nrows, float2 *out, hipStream_t s)
 {
-    switch (nphi) {
-    case 4: launch_ss_rows<4>(H, self, A, r0, nrows, out, s); return true;
-    case 8: launch_ss_rows<8>(H, self, A, r0, nrows, out, s); return true;
-    case 16: launch_ss_rows<16>(H, self, A, r0, nrows, out, s); return true;
-    case 32: launch_ss_rows<32>(H, self, A, r0, nrows, out, s); return true;
-    case 64: launch_ss_rows<64>(H, self, A, r0, nrows, out, s); return true;
-    case 128: launch_ss_rows<128>(H, self, A, r0, nrows, out, s); return true;
-    case 256: launch_ss_rows<256>(H, self, A, r0, nrows, out, s); return true;
-    case 512: launch_ss_rows<512>(H, self, A, r0, nrows, out, s); return true;
-    case 1024: launch_ss_rows<1024>(H, self, A, r0, nrows, out, s); return true;
-    case 2048: launch_ss_rows<2048>(H, self, A, r0, nrows, out, s); return true;
-    default: return false;
+#define SG_ROWS(N) \
+    case N: launch_ss_rows<N>(H, self, A, P, r0, nrows, out, s); return true;
+    switch (P.M) {
+        SG_ROWS(4) SG_ROWS(8) SG_ROWS(16) SG_ROWS(32) SG_ROWS(64) SG_ROWS(128) SG_ROWS(256) SG_ROWS(512)
+        SG_ROWS(1024) SG_ROWS(2048)
     }
+#undef SG_ROWS
+    return false;
 }
 
 sg_status sg_ss_table_build(const sg_grid *grid, int nf, const double *d_H, uint32_t flags, void *d_table,
@@ -511,14 +685,30 @@ sg_status sg_ss_table_build(const sg_grid *grid, int nf, const double *d_H, uint
                        (float2 *)(tb + L.off_tw_phi), nphi);
     SG_HIP(hipGetLastError());
     SsMode *modes = (SsMode *)(tb + L.off_modes);
-    hipLaunchKernelGGL(k_ss_modes, dim3(1), dim3(64), 0, s, modes, L.ncol, nr, L.nrt, nf, du, full ? 1 : 0);
+    hipLaunchKernelGGL(k_ss_modes, dim3(1), dim3(256), 0, s, modes, L.ncol, nr, L.nrt, nf, du, full ? 1 : 0);
     SG_HIP(hipGetLastError());
     float2 *coef = (float2 *)(tb + L.off_coef);
-    if (L.max_w >= 0) {  // banded modes: entries the scatter does not reach stay zero
+    const bool pot = (flags & SG_POTENTIAL) != 0;
+    SsRowArgs A;
+    A.nr = nr;
+    A.nrt = L.nrt;
+    A.nf = nf;
+    A.excl = excl ? 1 : 0;
+    A.ind = (flags & SG_INDIRECT) ? 1 : 0;
+    A.pot = pot ? 1 : 0;
+    A.lnrmin = log(grid->r_min);
+    A.du = du;
+    A.dphi = dphi;
+    A.lin = lin ? 1 : 0;
+    A.rmin = grid->r_min;
+    A.dr = dr;
+    A.second = second ? 1 : 0;
+    sg_gl_nodes(A.gl, du / dphi);
+    const std::vector<SsPart> parts = ss_parts(A, nphi, full, SG_SS_ALIAS);
+    if (L.max_w >= 0 || parts.size() > 1) {  // entries the scatter does not reach stay zero
         hipLaunchKernelGGL(k_ss_zero, dim3(2048), dim3(256), 0, s, coef, L.coef_elems);
         SG_HIP(hipGetLastError());
     }
-    const bool pot = (flags & SG_POTENTIAL) != 0;
     if (!excl && !second) {  // second order: the own cell is a hat weight of the rows
         // one item per (pair, ring): the per-cell quadratures with one cell per ring
         if (lin) {
@@ -537,29 +727,21 @@ sg_status sg_ss_table_build(const sg_grid *grid, int nf, const double *d_H, uint
         }
         SG_HIP(hipGetLastError());
     }
-    SsRowArgs A;
-    A.nr = nr;
-    A.nrt = L.nrt;
-    A.nf = nf;
-    A.excl = excl ? 1 : 0;
-    A.ind = (flags & SG_INDIRECT) ? 1 : 0;
-    A.pot = pot ? 1 : 0;
-    A.lnrmin = log(grid->r_min);
-    A.du = du;
-    A.dphi = dphi;
-    A.lin = lin ? 1 : 0;
-    A.rmin = grid->r_min;
-    A.dr = dr;
-    A.second = second ? 1 : 0;
-    sg_gl_nodes(A.gl, du / dphi);
-    const size_t crows = ss_chunk_rows(L);
-    for (size_t r0 = 0; r0 < L.rows; r0 += crows) {
-        const int n = (int)std::min(crows, L.rows - r0);
-        if (!dispatch_ss_rows(nphi, d_H, self, A, r0, n, chunk, s)) return SG_ERR_UNSUPPORTED;
-        SG_HIP(hipGetLastError());
-        hipLaunchKernelGGL(k_ss_scatter, dim3((n + 31) / 32, (L.ncol + 31) / 32), dim3(256), 0, s, chunk, n,
-                           L.ncol, coef, (const SsMode *)modes, r0, nr, L.nrt);
-        SG_HIP(hipGetLastError());
+    // the chunk buffer holds whole units of each class's rows
+    const size_t cbytes = sizeof(float2) * (size_t)L.ncol * ss_chunk_rows(L);
+    for (const SsPart &P : parts) {
+        const int mc = P.M / 2 + 1;
+        const size_t rows = P.C.on ? (size_t)nf * nf * nr * P.C.U * SG_SS_TI : L.rows;
+        size_t crows = P.C.on ? cbytes / (sizeof(float2) * mc) / SG_SS_TI * SG_SS_TI : ss_chunk_rows(L);
+        if (crows > (size_t)1 << 30) crows = (size_t)1 << 30;
+        for (size_t r0 = 0; r0 < rows; r0 += crows) {
+            const int n = (int)std::min(crows, rows - r0);
+            if (!dispatch_ss_rows(d_H, self, A, P, r0, n, chunk, s)) return SG_ERR_UNSUPPORTED;
+            SG_HIP(hipGetLastError());
+            hipLaunchKernelGGL(k_ss_scatter, dim3((n + 31) / 32, (mc + 31) / 32), dim3(256), 0, s, chunk, n, mc,
+                               coef, (const SsMode *)modes, A, P.C, r0);
+            SG_HIP(hipGetLastError());
+        }
     }
     sg_ss_header proto{};
     proto.magic = SG_SS_MAGIC;
@@ -818,10 +1000,13 @@ k_ssg_phi(const float *lam_r, const float *lam_p, const float *sigma, const floa
 // derivatives of the hat weights (k_ss_rows<N, true>: integrated near the
 // singular point, point value plus second moments beyond; both are linear
 // in the kernel, so they apply to its derivatives sample by sample).
-template <int N, bool SO>
+// N: samples of the rows, as in k_ss_rows; the contraction runs over the modes
+// they resolve (m <= N/2; the others' derivatives are below e^{-48} of the
+// axisymmetric one).  nphi: the grid's.  SO as in k_ss_rows.
+template <int N, int SO>
 __global__ void __launch_bounds__(SsRowShape<N>::WGS)
-k_ssg_rows(const double *H, const double *dself, SsRowArgs A, const float2 *lt, const float2 *st, size_t r0,
-           int nrows, double *rowpart)
+k_ssg_rows(const double *H, const double *dself, SsRowArgs A, SsClass C, int nphi, const float2 *lt,
+           const float2 *st, size_t r0, int nrows, double *rowpart)
 {
     using S = SsRowShape<N>;
     constexpr int P = S::P, T = S::T, G = S::G, W = LdsPlane<double>::elems(N);
@@ -829,19 +1014,16 @@ k_ssg_rows(const double *H, const double *dself, SsRowArgs A, const float2 *lt, 
     __shared__ __attribute__((aligned(16))) double2 lds[W * G];
     __shared__ double wq[FQuad<double>::TABLE];
     __shared__ double red[S::WGS];
-    __shared__ double2 qres[SO ? 2 * NC * G : 1];  // SO: the group's integrated samples, both derivatives
+    __shared__ double2 qres[SO == 1 ? 2 * NC * G : 1];  // SO: the group's integrated samples, both derivatives
     __shared__ int qmax_wg;
-    sg_fill_weights<double>(wq);
     const int g = threadIdx.x / T, t = threadIdx.x % T;
     const LdsPlane<double> pl{lds + W * g};
     const int row = blockIdx.x * G + g;
-    const bool valid = row < nrows;
-    const size_t R = r0 + (size_t)(valid ? row : 0);
-    const int i = (int)(R % A.nrt);
-    size_t rest = R / A.nrt;
-    const int ip = (int)(rest % A.nr);
-    rest /= A.nr;
-    const int a = (int)(rest % A.nf), b = (int)(rest / A.nf);
+    int i, ip, a, b;
+    const bool valid = ss_row(A, C, r0 + (size_t)(row < nrows ? row : 0), b, a, ip, i) && row < nrows;
+    if (!__syncthreads_or(valid ? 1 : 0)) return;
+    if (!valid) b = a = ip = i = 0;
+    sg_fill_weights<double>(wq);
     const bool live = valid && i < A.nr;
     const int ic = i < A.nr ? i : A.nr - 1;
     const double ri = A.lin ? A.rmin + (ic + 0.5) * A.dr : exp(A.lnrmin + (ic + 0.5) * A.du);
@@ -849,7 +1031,7 @@ k_ssg_rows(const double *H, const double *dself, SsRowArgs A, const float2 *lt, 
     const double ha = H[a * A.nr + ip] / rp, hb = H[b * A.nr + ic] / ri;
     const double X = A.lin ? log(ri / rp) : (double)(ic - ip) * A.du;
     const double scale = -(A.lin ? A.dr / rp : A.du) * A.dphi / N;
-    const uint32_t fs = (uint32_t)sg_blk_field_elems(N, A.nr);
+    const uint32_t fs = (uint32_t)sg_blk_field_elems(nphi, A.nr);
     __syncthreads();
     // Both derivatives are sampled in one sweep (one F, F' evaluation per
     // azimuth) and transformed together.  Row d is z_d = K_r,d + i K_phi,d
@@ -857,7 +1039,7 @@ k_ssg_rows(const double *H, const double *dself, SsRowArgs A, const float2 *lt, 
     // plane holds z = z_1 + i z_2, whose transform carries Z_1 (d/dh_a) in
     // its real part and Z_2 (d/dh_b) in its imaginary part.
     constexpr int Q = P / 2 + 1;
-    if constexpr (SO) {
+    if constexpr (SO == 1) {
         // integrated samples, cooperatively (as in k_ss_rows<N, true>)
         const int Pr = ic - ip;
         const double rn = SG_SS_HAT_NEAR * fmax(A.du, A.dphi), xq = Pr * A.du;
@@ -949,7 +1131,22 @@ k_ssg_rows(const double *H, const double *dself, SsRowArgs A, const float2 *lt, 
         const int q = t + T * u;
         if (q > N / 2) break;
         double kr1 = 0.0, kp1 = 0.0, kr2 = 0.0, kp2 = 0.0;
-        if (ic == ip && q == 0) {
+        if constexpr (SO == 2) {
+            // K + (D_X^2 K + D_phi^2 K)/12 of both derivatives
+#pragma unroll 1
+            for (int k = 0; k < 5; ++k) {
+                const double ph = 2.0 * q / N + (k == 3 ? A.dphi : k == 4 ? -A.dphi : 0.0) / SG_PI;
+                double sh, ch, a1, b1, a2, b2;
+                sincospi(0.5 * ph, &sh, &ch);
+                sg_conv_kernel64_dh(X + (k == 1 ? A.du : k == 2 ? -A.du : 0.0), sh, 2.0 * sh * ch, ha, hb, wq, a1, b1,
+                                    a2, b2);
+                const double w = k == 0 ? 2.0 / 3.0 : 1.0 / 12.0;
+                kr1 += w * a1;
+                kp1 += w * b1;
+                kr2 += w * a2;
+                kp2 += w * b2;
+            }
+        } else if (ic == ip && q == 0) {
             if (!A.excl) {
                 const size_t o = (size_t)(a * A.nf + b) * A.nr + ic, wst = (size_t)A.nf * A.nf * A.nr;
                 kr1 = dself[o];
@@ -1002,7 +1199,7 @@ k_ssg_rows(const double *H, const double *dself, SsRowArgs A, const float2 *lt, 
             // Re[conj(lr) T_r s] + Re[conj(lp) i t_phi s]
             const double cr = (double)lr.x * sv.x + (double)lr.y * sv.y;
             const double cp = -(double)lp.x * sv.y + (double)lp.y * sv.x;
-            const double wm = ((m == 0 || m == N / 2) ? 1.0 : 2.0) * scale;
+            const double wm = ((m == 0 || m == nphi / 2) ? 1.0 : 2.0) * scale;
             double tr = 0.5 * (zm.x + zn.x), tp = A.pot ? 0.0 : 0.5 * (zn.x - zm.x);
             if (m == 1) {
                 tr += dind;
@@ -1022,7 +1219,7 @@ k_ssg_rows(const double *H, const double *dself, SsRowArgs A, const float2 *lt, 
             if (t < o) red[threadIdx.x] += red[threadIdx.x + o];
             __syncthreads();
         }
-        if (t == 0 && live) rowpart[2 * R + d] = red[threadIdx.x];
+        if (t == 0 && live) rowpart[2 * ((((size_t)b * A.nf + a) * A.nr + ip) * A.nrt + i) + d] = red[threadIdx.x];
         __syncthreads();
     }
 }
@@ -1074,24 +1271,34 @@ static SsGradWs ssg_ws(int nr, int nphi, int nf)
 size_t sg_ss_grad_ws_bytes(int nr, int nphi, int nf) { return ssg_ws(nr, nphi, nf).total; }
 
 template <int N>
-static void launch_ssg(const double *H, const double *dself, const SsRowArgs &A, const float *lam_r,
-                       const float *lam_p, const float *sigma, const float2 *tw, float2 *lt, float2 *st,
-                       double *rowpart, hipStream_t s)
+static void launch_ssg_phi(const SsRowArgs &A, const float *lam_r, const float *lam_p, const float *sigma,
+                           const float2 *tw, float2 *lt, float2 *st, hipStream_t s)
 {
     using S = SsRowShape<N>;
-    const int nphi_jobs = A.nf * A.nr + A.nf * ((A.nr + 1) / 2);
-    hipLaunchKernelGGL(k_ssg_phi<N>, dim3((nphi_jobs + S::G - 1) / S::G), dim3(S::WGS), 0, s, lam_r, lam_p,
-                       sigma, tw, lt, st, A.nr, A.nf);
-    const size_t rows = (size_t)A.nf * A.nf * A.nr * A.nrt;
+    const int jobs = A.nf * A.nr + A.nf * ((A.nr + 1) / 2);
+    hipLaunchKernelGGL(k_ssg_phi<N>, dim3((jobs + S::G - 1) / S::G), dim3(S::WGS), 0, s, lam_r, lam_p, sigma, tw, lt,
+                       st, A.nr, A.nf);
+}
+
+template <int N>
+static void launch_ssg_rows(const double *H, const double *dself, const SsRowArgs &A, const SsPart &P, int nphi,
+                            const float2 *lt, const float2 *st, double *rowpart, hipStream_t s)
+{
+    using S = SsRowShape<N>;
+    const size_t rows = P.C.on ? (size_t)A.nf * A.nf * A.nr * P.C.U * SG_SS_TI : (size_t)A.nf * A.nf * A.nr * A.nrt;
     const size_t chunk = (size_t)1 << 22;
     for (size_t r0 = 0; r0 < rows; r0 += chunk) {
         const int n = (int)std::min(chunk, rows - r0);
-        if (A.second)
-            hipLaunchKernelGGL((k_ssg_rows<N, true>), dim3((n + S::G - 1) / S::G), dim3(S::WGS), 0, s, H, dself,
-                               A, lt, st, r0, n, rowpart);
+        const dim3 grid((n + S::G - 1) / S::G);
+        if (P.kind == 1)
+            hipLaunchKernelGGL((k_ssg_rows<N, 1>), grid, dim3(S::WGS), 0, s, H, dself, A, P.C, nphi, lt, st, r0, n,
+                               rowpart);
+        else if (P.kind == 2)
+            hipLaunchKernelGGL((k_ssg_rows<N, 2>), grid, dim3(S::WGS), 0, s, H, dself, A, P.C, nphi, lt, st, r0, n,
+                               rowpart);
         else
-            hipLaunchKernelGGL((k_ssg_rows<N, false>), dim3((n + S::G - 1) / S::G), dim3(S::WGS), 0, s, H, dself,
-                               A, lt, st, r0, n, rowpart);
+            hipLaunchKernelGGL((k_ssg_rows<N, 0>), grid, dim3(S::WGS), 0, s, H, dself, A, P.C, nphi, lt, st, r0, n,
+                               rowpart);
     }
 }
 
@@ -1155,19 +1362,23 @@ sg_status sg_ss_grad_run(const sg_disc &d0, const double *d_H, const float *lam_
             SG_HIP(hipGetLastError());
         }
     }
+#define SG_SIZES(F) F(4) F(8) F(16) F(32) F(64) F(128) F(256) F(512) F(1024) F(2048)
     switch (nphi) {
-    case 4: launch_ssg<4>(d_H, dself, A, lam_r, lam_p, d.sigma, tw, lt, st, rowpart, s); break;
-    case 8: launch_ssg<8>(d_H, dself, A, lam_r, lam_p, d.sigma, tw, lt, st, rowpart, s); break;
-    case 16: launch_ssg<16>(d_H, dself, A, lam_r, lam_p, d.sigma, tw, lt, st, rowpart, s); break;
-    case 32: launch_ssg<32>(d_H, dself, A, lam_r, lam_p, d.sigma, tw, lt, st, rowpart, s); break;
-    case 64: launch_ssg<64>(d_H, dself, A, lam_r, lam_p, d.sigma, tw, lt, st, rowpart, s); break;
-    case 128: launch_ssg<128>(d_H, dself, A, lam_r, lam_p, d.sigma, tw, lt, st, rowpart, s); break;
-    case 256: launch_ssg<256>(d_H, dself, A, lam_r, lam_p, d.sigma, tw, lt, st, rowpart, s); break;
-    case 512: launch_ssg<512>(d_H, dself, A, lam_r, lam_p, d.sigma, tw, lt, st, rowpart, s); break;
-    case 1024: launch_ssg<1024>(d_H, dself, A, lam_r, lam_p, d.sigma, tw, lt, st, rowpart, s); break;
-    case 2048: launch_ssg<2048>(d_H, dself, A, lam_r, lam_p, d.sigma, tw, lt, st, rowpart, s); break;
+#define SG_PHI(N) \
+    case N: launch_ssg_phi<N>(A, lam_r, lam_p, d.sigma, tw, lt, st, s); break;
+        SG_SIZES(SG_PHI)
+#undef SG_PHI
     default: return SG_ERR_UNSUPPORTED;
     }
+    for (const SsPart &P : ss_parts(A, nphi, (flags & SG_SS_FULL) != 0, SG_SS_ALIAS_GRAD)) {
+        switch (P.M) {
+#define SG_ROWS(N) \
+    case N: launch_ssg_rows<N>(d_H, dself, A, P, nphi, lt, st, rowpart, s); break;
+            SG_SIZES(SG_ROWS)
+#undef SG_ROWS
+        }
+    }
+#undef SG_SIZES
     SG_HIP(hipGetLastError());
     hipLaunchKernelGGL(k_ssg_finish, dim3(nf * nr), dim3(256), 0, s, rowpart, A, dH);
     SG_HIP(hipGetLastError());
