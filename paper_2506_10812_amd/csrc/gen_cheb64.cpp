@@ -22,6 +22,19 @@
 // x = 0, lies one interval length below every interval, so all intervals
 // converge alike); the program checks that the last kept coefficients are
 // that small and fails otherwise.
+//
+// The kernels that evaluate many points take shorter local polynomials
+// instead: PSUB intervals per octave from 2^POCT0 to 2^POCT1, PNC monomial
+// coefficients each in the local variable t in [-1, 1) (fitted the same way,
+// the last ones below 1e-15 of the value, the dropped ones below 3e-17), of F, G0 and
+//     D(x) = -x F'(x) - 3/2 F(x)
+//          = -1/2 int_0^inf e^{-x (cosh t - 1)} tanh^3(t/2) sinh t dt,
+// the combination the derivatives with respect to the scale heights need (the
+// two terms cancel to O(1/x) of themselves, the integral does not), and of
+//     E(x) = 2 x F(x) - G0(x) = int_0^inf e^{-x (cosh t - 1)} (2 x (cosh t - 1) - 1) dt
+// likewise for the potential.  Also written: the double twiddles of the table
+// builds' transforms.  The library evaluates these; the Chebyshev
+// series above are the fits' reference, kept for the generator's own test.
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -29,6 +42,60 @@
 static const int NI = 6;   // intervals [1/2,1), [1,2), [2,4), ..., [16,32)
 static const int M = 27;   // terms kept
 static const int NN = 48;  // Chebyshev points per interval
+
+static const int PSUB = 8, POCT0 = -4, POCT1 = 8, PNC = 12, PNN = 24;
+
+// F, D, G0 and E by the same trapezoid rule.
+static void fdg(long double x, long double (&v)[4])
+{
+    const long double h = 1.0L / 64.0L;
+    v[0] = v[1] = v[2] = v[3] = 0.0L;
+    for (int k = 0;; ++k) {
+        const long double t = k * h, sh = sinhl(0.5L * t), th = tanhl(0.5L * t);
+        const long double c = 2.0L * sh * sh, e = expl(-x * c) * (k == 0 ? 0.5L : 1.0L) * h;
+        v[0] += e * c;
+        v[1] -= 0.5L * e * th * th * th * sinhl(t);
+        v[2] += e;
+        v[3] += e * (2.0L * x * c - 1.0L);
+        if (x * c > 60.0L) break;
+    }
+}
+
+// Monomial coefficients of the fits on the interval [a, a + w).
+static bool poly_fit(long double a, long double w, double (&out)[4][PNC])
+{
+    const long double pi = 3.141592653589793238462643383279502884L;
+    long double val[4][PNN], top[4] = {0.0L, 0.0L, 0.0L, 0.0L};
+    for (int j = 0; j < PNN; ++j) {
+        long double v[4];
+        fdg(a + 0.5L * w * (1.0L + cosl(pi * (j + 0.5L) / PNN)), v);
+        for (int f = 0; f < 4; ++f) {
+            val[f][j] = v[f];
+            top[f] = fmaxl(top[f], fabsl(v[f]));
+        }
+    }
+    for (int f = 0; f < 4; ++f) {
+        long double mono[PNC] = {}, t0[PNC] = {}, t1[PNC] = {}, last = 0.0L;
+        t0[0] = 1.0L;
+        t1[1] = 1.0L;
+        for (int m = 0; m < PNC; ++m) {
+            long double c = 0.0L;
+            for (int j = 0; j < PNN; ++j) c += val[f][j] * cosl(pi * m * (j + 0.5L) / PNN);
+            c *= (m == 0 ? 1.0L : 2.0L) / PNN;
+            last = c;
+            for (int i = 0; i < PNC; ++i) mono[i] += c * t0[i];
+            long double t2[PNC];  // T_{m+2} = 2 t T_{m+1} - T_m
+            for (int i = 0; i < PNC; ++i) t2[i] = (i ? 2.0L * t1[i - 1] : 0.0L) - t0[i];
+            for (int i = 0; i < PNC; ++i) {
+                t0[i] = t1[i];
+                t1[i] = t2[i];
+            }
+        }
+        if (fabsl(last) > 1e-15L * top[f]) return false;  // the next one is 34 times smaller
+        for (int i = 0; i < PNC; ++i) out[f][i] = (double)mono[i];
+    }
+    return true;
+}
 
 static void fdf(long double x, long double &F, long double &dF, long double &G)
 {
@@ -96,5 +163,40 @@ int main()
             for (int m = 0; m < M; ++m) printf("    %.17e,\n", tabs[q][k][m]);
         printf("};\n");
     }
+    const int pni = (POCT1 - POCT0) * PSUB;
+    printf("#define SG_POLY_SUB %d\n#define SG_POLY_OCT0 %d\n#define SG_POLY_NI %d\n#define SG_POLY_NC %d\n", PSUB, POCT0,
+           pni, PNC);
+    static double poly[4][(POCT1 - POCT0) * PSUB][PNC];
+    for (int i = 0; i < pni; ++i) {
+        const long double oct = ldexpl(1.0L, POCT0 + i / PSUB), w = oct / PSUB;
+        double c[4][PNC];
+        if (!poly_fit(oct + w * (i % PSUB), w, c)) {
+            fprintf(stderr, "gen_cheb64: local polynomial %d: truncation too large\n", i);
+            return 1;
+        }
+        for (int f = 0; f < 4; ++f)
+            for (int m = 0; m < PNC; ++m) poly[f][i][m] = c[f][m];
+    }
+    // one array [F, D, G0, E][interval][coefficient]
+    printf("static __device__ const double sg_poly64[4 * SG_POLY_NI * SG_POLY_NC] = {\n");
+    for (int f = 0; f < 4; ++f)
+        for (int i = 0; i < pni; ++i)
+            for (int m = 0; m < PNC; ++m) printf("    %.17e,\n", poly[f][i][m]);
+    printf("};\n");
+    // cos and sin of 2 pi k / 4096 (the first octant's values, mirrored)
+    printf("#define SG_TW64_N 4096\nstatic __device__ const double sg_tw64[2 * SG_TW64_N] = {\n");
+    for (int k = 0; k < 4096; ++k) {
+        const long double a = 2.0L * pi / 4096.0L;
+        const int q = k % 1024, m = q <= 512 ? q : 1024 - q;
+        long double c = cosl(a * m), sn = sinl(a * m);
+        if (q > 512) {
+            const long double t = c;
+            c = sn;
+            sn = t;
+        }
+        const long double x[4] = {c, -sn, -c, sn}, y[4] = {sn, c, -sn, -c};
+        printf("    %.17e, %.17e,\n", (double)x[k / 1024], (double)y[k / 1024]);
+    }
+    printf("};\n");
     return 0;
 }

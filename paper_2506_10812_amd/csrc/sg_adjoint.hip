@@ -576,8 +576,8 @@ __global__ void __launch_bounds__(256) k_adj_ind_sig(const sg_table_header *hd, 
 __global__ void k_adj_ind_dh(const sg_table_header *hd, const double *spart, int nb, int nf, double *dh)
 {
     // the wave fills the coefficient table; lane 0 sums
-    __shared__ double w[FQuad<double>::TABLE];
-    sg_fill_weights<double>(w);
+    __shared__ __attribute__((aligned(16))) double w[FQuad<double>::TABLE];
+    sg_fill64(w, SG_FN_D);
     __syncthreads();
     if (threadIdx.x != 0) return;
     const double du = log(hd->r_max / hd->r_min) / hd->n_r, dphi = 2.0 * SG_PI / hd->n_phi;
@@ -585,9 +585,7 @@ __global__ void k_adj_ind_dh(const sg_table_header *hd, const double *spart, int
         double S = 0.0;
         for (int b = 0; b < nb; ++b) S += spart[4 * b + a];
         const double h = hd->h[a], x = 0.25 / (h * h);
-        double F, dF;
-        sg_F64_dF(x, w, F, dF);
-        const double cp = SG_SQRT2 / SG_SQRT_PI * du * dphi * (-3.0 * F - 2.0 * x * dF) / (4.0 * h * h * h * h);
+        const double cp = SG_SQRT2 / SG_SQRT_PI * du * dphi * sg_D64(x, w) / (2.0 * h * h * h * h);
         dh[a] += cp * S;
     }
 }

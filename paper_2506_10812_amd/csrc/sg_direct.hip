@@ -109,16 +109,16 @@ __global__ void k_direct_prep(int nr, int nphi, int nf, double lnrmin, double du
 }
 
 template <typename T> __device__ inline T sg_F_any(T x, const T *w);
-template <> __device__ inline double sg_F_any<double>(double x, const double *w) { return sg_F64<true>(x, w); }
+template <> __device__ inline double sg_F_any<double>(double x, const double *w) { return sg_F64(x, w); }
 template <> __device__ inline float sg_F_any<float>(float x, const float *w) { return sg_F32(x, w); }
 template <typename T> __device__ inline T sg_G0_any(T x, const T *w);
-template <> __device__ inline double sg_G0_any<double>(double x, const double *w) { return sg_G0_64<true>(x, w); }
+template <> __device__ inline double sg_G0_any<double>(double x, const double *w) { return sg_G0_64(x, w); }
 template <> __device__ inline float sg_G0_any<float>(float x, const float *w) { return sg_G0_32(x, w); }
 
 template <typename T, int NF>
 __global__ void __launch_bounds__(256) k_direct(DirectArgs<T> A)
 {
-    __shared__ T wq[FQuad<T>::TABLE];
+    __shared__ __attribute__((aligned(16))) T wq[FQuad<T>::TABLE];
     sg_fill_weights<T>(wq);
     __syncthreads();
     const int64_t t = blockIdx.x * (int64_t)256 + threadIdx.x;
@@ -290,9 +290,9 @@ template <typename T, int NC>
 __global__ void __launch_bounds__(256) k_ring_sum(DirectArgs<T> A, RingShape P, int nf)
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    __shared__ T wq[FQuad<T>::TABLE];
+    __shared__ __attribute__((aligned(16))) T wq[FQuad<T>::TABLE];
     constexpr int PG = RingPad<T>::G;
-    sg_fill_weights<T>(wq);
+    sg_fill_weights<T>(wq, NC == 2 ? SG_FN_F : SG_FN_G0);
     const int ir = blockIdx.x / P.ntile, jb = (blockIdx.x % P.ntile) * 8 * P.JT, b = blockIdx.z;
     const int nphi = A.nphi, rowg = P.JT + P.TL / 8;
     T *D = (T *)smem, *M = D + (size_t)P.KS * NC * rowg * PG;
@@ -433,7 +433,7 @@ __global__ void __launch_bounds__(256) k_indirect_part(int nr, int nphi, int nf,
                                                        const T *H, double2 *part, int lin, double rmin,
                                                        double dr)
 {
-    __shared__ double wq[FQuad<double>::TABLE];
+    __shared__ __attribute__((aligned(16))) double wq[FQuad<double>::TABLE];
     __shared__ double ra[256], rb[256];
     sg_fill_weights<double>(wq);
     __syncthreads();
@@ -545,8 +545,8 @@ __global__ void k_direct_reduce(const T *partial, int S, int64_t N, const double
 template <typename T, int NF>
 __global__ void __launch_bounds__(256) k_potential(DirectArgs<T> A)
 {
-    __shared__ T wq[FQuad<T>::TABLE];
-    sg_fill_weights<T>(wq);
+    __shared__ __attribute__((aligned(16))) T wq[FQuad<T>::TABLE];
+    sg_fill_weights<T>(wq, SG_FN_G0);
     __syncthreads();
     const int64_t t = blockIdx.x * (int64_t)256 + threadIdx.x;
     if (t >= A.N) return;

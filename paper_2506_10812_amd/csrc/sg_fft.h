@@ -19,6 +19,7 @@
 // (stages contain __syncthreads()).
 #pragma once
 #include "sg_internal.h"
+#include "sg_cheb64.h"
 
 // ------------------------------------------------------------ small DFTs
 template <bool INV, typename V> __device__ inline void dft2(V &a, V &b)
@@ -203,11 +204,12 @@ template <int N, bool SF = false> struct TwRegC {
 };
 
 // Stage plan of a twiddle provider: its own Plan type, else the default.
-// Double twiddles for the FP64 row transforms of the table builds: one exact
-// base e^{-2 pi i k/(L R)} per butterfly (sincospi), legs j = 2..R-1 as its
+// Double twiddles for the FP64 row transforms of the table builds: one base
+// e^{-2 pi i k/(L R)} per butterfly from the constant table sg_tw64 (64 KB,
+// read through the caches; computing it took a sincospi per butterfly, more
+// instructions than the radix-8 butterfly itself), legs j = 2..R-1 as its
 // powers by complex products (a few ulps in double; every caller rounds the
-// result to float or accumulates a derivative checked at 1e-6), so a
-// length-2048 transform evaluates 3 sincospi per thread instead of 17.
+// result to float or accumulates a derivative checked at 1e-6).
 template <int N> struct TwPow64 {
     using Plan = FftPlan<N>;
     static constexpr bool POWERS = true;
@@ -215,10 +217,10 @@ template <int N> struct TwPow64 {
     template <int S> __device__ inline double2 base(int beta) const
     {
         constexpr int L = Plan::L(S), LR = Plan::L(S) * Plan::RAD(S);
+        static_assert(SG_TW64_N % LR == 0, "twiddle table");
         const int k = (t + Plan::T * beta) & (L - 1);
-        double s, c;
-        sincospi(-2.0 * (double)k / (double)LR, &s, &c);
-        return make_double2(c, s);
+        const double2 v = ((const double2 *)sg_tw64)[k * (SG_TW64_N / LR)];
+        return make_double2(v.x, -v.y);
     }
 };
 

@@ -6,12 +6,26 @@
 //     K_ab(s) = pi^{-1/2} H_ab^{-2} (d/8) F(d^2/8),  d = s/H_ab.
 // Evaluation never forms e^x K1(x) and e^x K0(x) separately at large x (their
 // difference cancels and e^x overflows, the NaN problem noted in Sect. 5.3):
-//   x < 1/2 (float: x < 1)  power series of I0, I1, K0, K1 (Abramowitz &
-//           Stegun 9.6.10, 9.6.11), F = e^x (K1 - K0), where the two
-//           cancellations inside K0 and K1 - K0 cost at most a few ulps (in
-//           double they grow to 3e-14 just below x = 2, hence the Chebyshev
-//           branch above 1/2);
-//   1 <= x < 32 (float)  F = sqrt(2) x^{-3/2} J(x),  J(x) = int_0^inf v^2 e^{-v^2}
+//   double
+//     x < 1/16          power series of I0, I1, K0, K1 (Abramowitz & Stegun
+//           9.6.10, 9.6.11), F = e^x (K1 - K0);
+//     1/16 <= x < 256   local polynomials of 12 terms on 8 intervals per
+//           octave (gen_cheb64.cpp -> sg_cheb64.h, fitted at build time in
+//           long double), within 4e-16 of F, with no square root or division;
+//     x >= 256          the asymptotic series F = (sqrt(2 pi)/4) x^{-3/2}
+//           sum_n c_n x^-n, c_0 = 1, c_n = -c_{n-1} (4 n^2 - 1)/(8 n) (its
+//           first three terms are the expansion printed in Sect. 5.3) through
+//           c_7: the remainder is below the first omitted term, 6e-18.
+//     The same three branches give D(x) = -x F' - 3/2 F (what the derivatives
+//     with respect to the scale heights need; the difference of its two terms
+//     would lose log10(x) digits), G0(x) = e^x K0(x) (the potential's kernel)
+//     and E(x) = 2 x F - G0 (its derivative).  A block copies the one table
+//     it needs (9 KB) into LDS.  Per wave an evaluation is 12 LDS reads and 11
+//     FMAs in a dependent chain; the Chebyshev series of 27 terms used before
+//     took 27 reads and 53 operations, and below 32 only.
+//   float
+//     x < 1             the same power series;
+//     1 <= x < 32       F = sqrt(2) x^{-3/2} J(x),  J(x) = int_0^inf v^2 e^{-v^2}
 //           (1 + v^2/(2x))^{-1/2} dv, obtained from the integral
 //           representation K_nu(x) = int_0^inf e^{-x cosh t} cosh(nu t) dt by
 //           the substitution sinh(t/2) = v / sqrt(2x).  The integrand is even
@@ -19,41 +33,21 @@
 //           fixed grid converges geometrically, its error ~ exp(-2 pi
 //           sqrt(2x) / step): step 1/2 and 9 nodes (2e-8 at x = 1, below a
 //           float ulp; the tail beyond v = 4.5 is e^{-20});
-//   1/2 <= x < 32 (double) Chebyshev series of F and F' on the dyadic
-//           intervals [1/2, 1), [1, 2), ..., [16, 32), 27 terms each, their
-//           coefficients computed at build time in long double from the same
-//           integral representation (gen_cheb64.cpp; sg_cheb64.h): within
-//           7e-16 of F and F' over the range, with no square roots (a
-//           26-node trapezoid in double, used before, took a double
-//           reciprocal square root per node and ten times the instructions);
-//   x >= 32 the asymptotic series J = (sqrt(pi)/4)
-//           sum_n c_n x^-n, c_0 = 1, c_n = -c_{n-1} (4 n^2 - 1)/(8 n)
-//           (term-by-term integration of the binomial series; its first three
-//           terms are the expansion printed in Sect. 5.3), truncated after c_5
-//           (float) or c_16 (double).  (1 + t)^{-1/2} is completely monotone, so
-//           the binomial remainder alternates and is bounded by the first
-//           omitted term, and so is J's: |c_17| 32^-17 = 1.3e-18 for F, and for F'
-//           (series differentiated term by term, two such pieces of one sign)
-//           |c_17| (17 + 3/2) / (3/2) 32^-17 = 1.7e-17 of its leading term.
-// The float trapezoidal weights e^{-v_k^2}, and for double the asymptotic
-// coefficients (for the rolled series) and the Chebyshev coefficients, are
-// copied once per workgroup into LDS by sg_fill_weights().
+//     x >= 32           the asymptotic series through c_5.
+// The float trapezoidal weights e^{-v_k^2} and the double tables are copied
+// once per workgroup into LDS (sg_fill_weights, sg_fill64).
 #pragma once
 #include "sg_internal.h"
 #include "sg_cheb64.h"
 
 #define SG_EULER_GAMMA 0.57721566490153286061
 
-// Table of TABLE entries.  Float: w[k-1] = exp(-(k STEP)^2), k = 1..NODES.
-// Double: c_n (n = 0..ASYM), -(n + 3/2) c_n, the G0 coefficients a_n, and the
-// Chebyshev coefficients of F, F' and G0 (SG_CHEB_NI intervals of SG_CHEB_M).
+// LDS table of TABLE entries.  Float: w[k-1] = exp(-(k STEP)^2), k = 1..NODES.
+// Double: the local polynomials of one function.
+enum { SG_FN_F = 0, SG_FN_D = 1, SG_FN_G0 = 2, SG_FN_E = 3 };
 template <typename R> struct FQuad;
 template <> struct FQuad<double> {
-    static constexpr int ASYM = 16;
-    static constexpr int C = 0, D = C + ASYM + 1, A = D + ASYM + 1;
-    static constexpr int CH = A + ASYM + 1, CHD = CH + SG_CHEB_NI * SG_CHEB_M;
-    static constexpr int CHG = CHD + SG_CHEB_NI * SG_CHEB_M;
-    static constexpr int TABLE = CHG + SG_CHEB_NI * SG_CHEB_M;
+    static constexpr int TABLE = SG_POLY_NI * SG_POLY_NC;
 };
 template <> struct FQuad<float> {
     static constexpr int NODES = 9;
@@ -70,49 +64,25 @@ __device__ inline double sg_rcp(double x) { return 1.0 / x; }
 __device__ inline float sg_rsqrt(float x) { return __builtin_amdgcn_rsqf(x); }
 __device__ inline double sg_rsqrt(double x) { return rsqrt(x); }
 
-// Double asymptotic coefficients, generated at compile time from their
-// recurrences: c_n (F), d_n = -(n + 3/2) c_n (F'), a_n (G0); see the branch
-// comments below.
-struct AsymCoef64 {
-    static constexpr int N = FQuad<double>::ASYM;
-    double c[N + 1], d[N + 1], a[N + 1];
-    constexpr AsymCoef64() : c{}, d{}, a{}
-    {
-        double v = 1.0, g = 1.0;
-        for (int n = 0; n <= N; ++n) {
-            if (n) {
-                v = -v * (4.0 * n * n - 1.0) / (8.0 * n);
-                g = -g * (2.0 * n - 1.0) * (2.0 * n - 1.0) / (8.0 * n);
-            }
-            c[n] = v;
-            d[n] = -v * (n + 1.5);
-            a[n] = g;
+// Call from every thread, then sync.  fn: the function of a double table
+// (uniform over the block).
+__device__ inline void sg_fill64(double *w, int fn)
+{
+    for (int k = threadIdx.x; k < FQuad<double>::TABLE; k += blockDim.x) w[k] = sg_poly64[fn * FQuad<double>::TABLE + k];
+}
+template <typename R> __device__ inline void sg_fill_weights(R *w, int fn = SG_FN_F)
+{
+    if constexpr (sizeof(R) == 8) {
+        sg_fill64(w, fn);
+    } else {
+        for (int k = threadIdx.x; k < FQuad<R>::TABLE; k += blockDim.x) {
+            const double v = (k + 1) * (double)FQuad<float>::STEP;
+            w[k] = (R)exp(-v * v);
         }
     }
-};
-
-template <typename R> __device__ inline R sg_weight_entry(int k)
-{
-    if constexpr (sizeof(R) == 4) {
-        const double v = (k + 1) * (double)FQuad<float>::STEP;
-        return (R)exp(-v * v);
-    } else {
-        using Q = FQuad<double>;
-        if (k >= Q::CHG) return sg_cheb_g0[k - Q::CHG];
-        if (k >= Q::CHD) return sg_cheb_df[k - Q::CHD];
-        if (k >= Q::CH) return sg_cheb_f[k - Q::CH];
-        constexpr AsymCoef64 C;
-        return k >= Q::A ? C.a[k - Q::A] : k >= Q::D ? C.d[k - Q::D] : C.c[k - Q::C];
-    }
 }
 
-// Call from every thread, then sync.
-template <typename R> __device__ inline void sg_fill_weights(R *w)
-{
-    for (int k = threadIdx.x; k < FQuad<R>::TABLE; k += blockDim.x) w[k] = sg_weight_entry<R>(k);
-}
-
-// Series branch, x < 2.  NT terms.
+// Series branch, small x.  NT terms.
 template <typename R, int NT>
 __device__ inline void sg_F_series(R x, R &F, R *dF)
 {
@@ -179,41 +149,6 @@ struct AsymCoef {
     }
 };
 
-// Asymptotic branch (double), x >= 32: F and F' = (sqrt(2 pi)/4) sum_n c_n
-// (-n - 3/2) x^{-n-5/2}.  ROLLED: a rolled Horner loop over the LDS copy of
-// the coefficients.  Unrolled with literal coefficients, the compiler keeps
-// them in registers across the caller's loop, which drops the direct sums
-// from 3 to 1 waves per SIMD; the table and gradient kernels, whose occupancy
-// is set by other state, run fastest that way.
-template <bool ROLLED>
-__device__ inline void sg_F_asym64(double x, const double *w, double &F, double *dF)
-{
-    using Q = FQuad<double>;
-    const double u = 1.0 / x;
-    double s, sd = 0.0;
-    if constexpr (ROLLED) {
-        s = w[Q::C + Q::ASYM];
-        sd = w[Q::D + Q::ASYM];
-#pragma unroll 1
-        for (int n = Q::ASYM - 1; n >= 0; --n) {
-            s = s * u + w[Q::C + n];
-            if (dF) sd = sd * u + w[Q::D + n];
-        }
-    } else {
-        constexpr AsymCoef64 C;
-        s = C.c[Q::ASYM];
-        sd = C.d[Q::ASYM];
-#pragma unroll
-        for (int n = Q::ASYM - 1; n >= 0; --n) {
-            s = s * u + C.c[n];
-            if (dF) sd = sd * u + C.d[n];
-        }
-    }
-    const double pre = (SG_SQRT2 * SG_SQRT_PI * 0.25) * rsqrt(x) * u;
-    F = pre * s;
-    if (dF) *dF = pre * u * sd;
-}
-
 __device__ inline float sg_F_asym(float x)
 {
     constexpr AsymCoef C;
@@ -226,94 +161,77 @@ __device__ inline float sg_F_asym(float x)
     return float(SG_SQRT2) * rx * u * J;
 }
 
-// Mid-range branch (double), 1/2 <= x < 32: x = m 2^e with m in [1/2, 1) lies
-// in interval k = e at t = 4 m - 3 in [-1, 1); the series of F (and F')
-// are summed by Clenshaw's recurrence from the LDS copy of the coefficients.
-// Lanes outside the range (whose result is discarded) are clamped to an
-// interval so that every address stays in the table.
-__device__ inline void sg_F_cheb64(double x, const double *w, double &F, double *dF)
-{
-    using Q = FQuad<double>;
-    int e;
-    const double m = frexp(x, &e);
-    const int k = min(max(e, 0), SG_CHEB_NI - 1);
-    const double t = 4.0 * m - 3.0, t2 = 2.0 * t;
-    const double *cf = w + Q::CH + k * SG_CHEB_M;
-    const double *cd = w + Q::CHD + k * SG_CHEB_M;
-    double b1 = 0.0, b2 = 0.0, d1 = 0.0, d2 = 0.0;
-#pragma unroll 3
-    for (int j = SG_CHEB_M - 1; j > 0; --j) {
-        const double b0 = fma(t2, b1, cf[j] - b2);
-        b2 = b1;
-        b1 = b0;
-        if (dF) {
-            const double d0 = fma(t2, d1, cd[j] - d2);
-            d2 = d1;
-            d1 = d0;
-        }
-    }
-    F = fma(t, b1, cf[0] - b2);
-    if (dF) *dF = fma(t, d1, cd[0] - d2);
-}
-
-// Full-range evaluators.  The double asymptotic branch alone runs when every
-// active lane of the wave has x >= 32.  Otherwise the series (x < 1/2), the
-// double Chebyshev branch (1/2 <= x < 32) or the float trapezoid (x >= 1), and
-// the double asymptotic branch (x >= 32) each run only when some lane of the
-// wave needs them, every lane keeping its own branch's value.
-// SG_NO_SPECULATE, an empty asm statement that emits no instruction, keeps
-// the compiler from if-converting such wave-uniform branches into
-// straight-line code that evaluates every branch for every lane.
+// Wave-uniform branches: the series and the asymptotic form each run only
+// when some lane of the wave needs them, every lane keeping its own branch's
+// value.  SG_NO_SPECULATE, an empty asm statement that emits no instruction,
+// keeps the compiler from if-converting such branches into straight-line code
+// that evaluates every branch for every lane.
 #define SG_NO_SPECULATE() asm volatile("")
 
-template <bool ROLLED>
-__device__ inline void sg_F64_any(double x, const double *w, double &F, double *dF)
+// Series branch of the double functions (x < 1/16: y = x^2/4 < 1e-3, so 5
+// terms leave y^5/(5!)^2 < 1e-19).
+template <int FN> __device__ inline double sg_series64(double x);
+template <typename R, int NT> __device__ inline R sg_G0_series(R x);
+
+// Asymptotic coefficients n = 0..7 of F / ((sqrt(2 pi)/4) x^{-3/2}), of D over
+// the same (n c_n), of G0 / sqrt(pi/(2x)) (a_n = -a_{n-1} (2n - 1)^2/(8n)) and
+// of E over the same (c_n - a_n).
+template <int FN> struct Asym64 {
+    double c[8];
+    constexpr Asym64() : c{}
+    {
+        double v = 1.0, g = 1.0;
+        for (int n = 0; n < 8; ++n) {
+            if (n) {
+                v = -v * (4.0 * n * n - 1.0) / (8.0 * n);
+                g = -g * (2.0 * n - 1.0) * (2.0 * n - 1.0) / (8.0 * n);
+            }
+            c[n] = FN == SG_FN_F ? v : FN == SG_FN_D ? n * v : FN == SG_FN_G0 ? g : v - g;
+        }
+    }
+};
+
+// The function FN at x > 0; w: its table.  Lanes outside the polynomials'
+// range (whose value is discarded) are clamped to an interval.
+template <int FN> __device__ inline double sg_fn64(double x, const double *w)
 {
-    if (__all(x >= 32.0)) {
-        sg_F_asym64<ROLLED>(x, w, F, dF);
-        return;
+    static_assert(SG_POLY_SUB == 8 && SG_POLY_NC == 12, "index arithmetic below");
+    const int hi = __double2hiint(x);
+    const int k = min(max((hi >> 17) - ((1023 + SG_POLY_OCT0) << 3), 0), SG_POLY_NI - 1);
+    // the 3 leading mantissa bits are in k; the rest as v in [1, 1 + 1/8), t = 16 v - 17
+    const double t = fma(16.0, __hiloint2double((hi & 0x1ffff) | 0x3ff00000, __double2loint(x)), -17.0);
+    const double2 *c = (const double2 *)(w + k * SG_POLY_NC);
+    double2 q[6];
+#pragma unroll
+    for (int j = 0; j < 6; ++j) q[j] = c[j];
+    double f = q[5].y;
+#pragma unroll
+    for (int j = 5; j >= 0; --j) {
+        if (j < 5) f = fma(f, t, q[j].y);
+        f = fma(f, t, q[j].x);
     }
-    const bool ser = x < 0.5, asy = x >= 32.0, mid = !ser && !asy;
-    double t, td = 0.0;
-    F = 0.0;
-    if (dF) *dF = 0.0;
-    if (__any(ser)) {
+    if (__any(!(x < 256.0))) {  // NaN included
         SG_NO_SPECULATE();
-        sg_F_series<double, 10>(x, t, dF ? &td : nullptr);  // y = x^2/4 < 1/16: y^10/(10!)^2 < 1e-25
-        if (ser) {
-            F = t;
-            if (dF) *dF = td;
-        }
+        constexpr Asym64<FN> A;
+        const double r = rsqrt(x), u = r * r;
+        double s = A.c[7];
+#pragma unroll
+        for (int n = 6; n >= 0; --n) s = fma(s, u, A.c[n]);
+        s *= FN == SG_FN_F || FN == SG_FN_D ? (SG_SQRT2 * SG_SQRT_PI * 0.25) * (u * r) : (SG_SQRT_PI / SG_SQRT2) * r;
+        f = x < 256.0 ? f : s;
     }
-    if (__any(mid)) {
+    if (__any(x < 0.0625)) {
         SG_NO_SPECULATE();
-        sg_F_cheb64(x, w, t, dF ? &td : nullptr);
-        if (mid) {
-            F = t;
-            if (dF) *dF = td;
-        }
+        const double s = sg_series64<FN>(x);
+        f = x < 0.0625 ? s : f;
     }
-    if (__any(asy)) {
-        SG_NO_SPECULATE();
-        sg_F_asym64<ROLLED>(x, w, t, dF ? &td : nullptr);
-        if (asy) {
-            F = t;
-            if (dF) *dF = td;
-        }
-    }
+    return f;
 }
 
-template <bool ROLLED = false> __device__ inline double sg_F64(double x, const double *w)
-{
-    double F;
-    sg_F64_any<ROLLED>(x, w, F, nullptr);
-    return F;
-}
-
-template <bool ROLLED = false> __device__ inline void sg_F64_dF(double x, const double *w, double &F, double &dF)
-{
-    sg_F64_any<ROLLED>(x, w, F, &dF);
-}
+__device__ inline double sg_F64(double x, const double *w) { return sg_fn64<SG_FN_F>(x, w); }
+__device__ inline double sg_D64(double x, const double *w) { return sg_fn64<SG_FN_D>(x, w); }
+__device__ inline double sg_G0_64(double x, const double *w) { return sg_fn64<SG_FN_G0>(x, w); }
+__device__ inline double sg_E64(double x, const double *w) { return sg_fn64<SG_FN_E>(x, w); }
 
 // Float: each branch runs only when some lane of the wave needs it, and each
 // lane keeps its own branch's value (a wave whose lanes all fall in one range
@@ -343,15 +261,13 @@ __device__ inline float sg_F32(float x, const float *w)
 // ------------------------------------------------------------------------
 // G0(x) = e^x K0(x), the kernel of the conservative potential (Sect. 5.5,
 // appendix "Conservative force"): P_ab(s) = -G0(d^2/8) / (2 sqrt(pi) H_ab).
-//   x < 1/2 (float: x < 1)  A&S series of I0 and K0, G0 = e^x K0;
-//   1 <= x < 32 (float)  G0 = sqrt(2/x) int_0^inf e^{-v^2}
+// Double: sg_fn64 above.  Float:
+//   x < 1   A&S series of I0 and K0, G0 = e^x K0;
+//   1 <= x < 32  G0 = sqrt(2/x) int_0^inf e^{-v^2}
 //        (1 + v^2/(2x))^{-1/2} dv (the same substitution as for F; the
 //        trapezoid's v = 0 node has value 1 and weight STEP/2);
-//   1/2 <= x < 32 (double)  Chebyshev series on the same dyadic intervals as
-//        F (gen_cheb64.cpp, from G0 = int_0^inf e^{-x (cosh t - 1)} dt);
 //   x >= 32  sqrt(pi/(2x)) sum_n a_n x^-n, a_0 = 1,
-//        a_n = -a_{n-1} (2n - 1)^2 / (8 n), through a_5 (float) or a_16
-//        (double: remainder 1.2e-16 at x = 32).
+//        a_n = -a_{n-1} (2n - 1)^2 / (8 n), through a_5.
 // ------------------------------------------------------------------------
 template <typename R, int NT> __device__ inline R sg_G0_series(R x)
 {
@@ -393,70 +309,17 @@ struct AsymCoefG0 {
     }
 };
 
-// double, x >= 32: through a_16 (LDS table); K0's asymptotic remainder for
-// real x is bounded by the first omitted term.
-template <bool ROLLED> __device__ inline double sg_G0_asym64(double x, const double *w)
+template <int FN> __device__ inline double sg_series64(double x)
 {
-    using Q = FQuad<double>;
-    const double u = 1.0 / x;
-    double s;
-    if constexpr (ROLLED) {
-        s = w[Q::A + Q::ASYM];
-#pragma unroll 1
-        for (int n = Q::ASYM - 1; n >= 0; --n) s = s * u + w[Q::A + n];
+    if constexpr (FN == SG_FN_G0) {
+        return sg_G0_series<double, 5>(x);
     } else {
-        constexpr AsymCoef64 C;
-        s = C.a[Q::ASYM];
-#pragma unroll
-        for (int n = Q::ASYM - 1; n >= 0; --n) s = s * u + C.a[n];
+        double F, dF;
+        sg_F_series<double, 5>(x, F, FN == SG_FN_D ? &dF : nullptr);
+        if constexpr (FN == SG_FN_F) return F;
+        else if constexpr (FN == SG_FN_D) return -x * dF - 1.5 * F;
+        else return 2.0 * x * F - sg_G0_series<double, 5>(x);
     }
-    return sqrt(SG_PI * 0.5 * u) * s;
-}
-
-// double, 1/2 <= x < 32: Clenshaw's recurrence over the G0 coefficients, with
-// the interval mapping of sg_F_cheb64.
-__device__ inline double sg_G0_cheb64(double x, const double *w)
-{
-    using Q = FQuad<double>;
-    int e;
-    const double m = frexp(x, &e);
-    const int k = min(max(e, 0), SG_CHEB_NI - 1);
-    const double t = 4.0 * m - 3.0, t2 = 2.0 * t;
-    const double *cg = w + Q::CHG + k * SG_CHEB_M;
-    double b1 = 0.0, b2 = 0.0;
-#pragma unroll 3
-    for (int j = SG_CHEB_M - 1; j > 0; --j) {
-        const double b0 = fma(t2, b1, cg[j] - b2);
-        b2 = b1;
-        b1 = b0;
-    }
-    return fma(t, b1, cg[0] - b2);
-}
-
-// Branches as in sg_F64_any: the asymptotic series alone when the whole wave
-// has x >= 32, else each of series, Chebyshev and asymptotic series runs when
-// some lane needs it.
-template <bool ROLLED = false> __device__ inline double sg_G0_64(double x, const double *w)
-{
-    if (__all(x >= 32.0)) return sg_G0_asym64<ROLLED>(x, w);
-    const bool ser = x < 0.5, asy = x >= 32.0, mid = !ser && !asy;
-    double G = 0.0;
-    if (__any(ser)) {
-        SG_NO_SPECULATE();
-        const double t = sg_G0_series<double, 10>(x);  // y = x^2/4 < 1/16
-        G = ser ? t : G;
-    }
-    if (__any(mid)) {
-        SG_NO_SPECULATE();
-        const double t = sg_G0_cheb64(x, w);
-        G = mid ? t : G;
-    }
-    if (__any(asy)) {
-        SG_NO_SPECULATE();
-        const double t = sg_G0_asym64<ROLLED>(x, w);
-        G = asy ? t : G;
-    }
-    return G;
 }
 
 // Branches as in sg_F32: run only when some lane of the wave needs them.
@@ -496,9 +359,10 @@ __device__ inline float sg_G0_32(float x, const float *w)
 // cosh X - cos phi = 2 sinh^2(X/2) + 2 sin^2(phi/2) and e^X - cos phi =
 // expm1(X) + 2 sin^2(phi/2) avoid cancellation near the origin.
 // which = 1, 2: derivatives with respect to h_a, h_b:
-//   dK/d(h^2) = K-prefactor (h^2)^{-5/2} [-x F'(x) - 3/2 F(x)],
+//   dK/d(h^2) = K-prefactor (h^2)^{-5/2} D(x), D = -x F'(x) - 3/2 F(x),
 //   d(h^2)/dh_a = h_a e^{-X},  d(h^2)/dh_b = h_b e^{X}.
 // sin(phi/2), sin(phi) are passed in so callers can use exact arguments.
+// w: the table of F (which = 0) or D (which = 1, 2).
 // ------------------------------------------------------------------------
 // The factors of sg_conv_kernel64 (which = 0) that depend on the row alone
 // (X, h_a, h_b): a semi-spectral operator row samples the kernel at N/2 + 1
@@ -510,16 +374,26 @@ struct ConvRow64 {
     double pref;      // e^{-3X/2} / (8 sqrt(pi) h_ab^3)
 };
 
+// e^{X/2} and e^{-X/2} from one sinh (the larger as cosh + |sinh|, without
+// cancellation, the other as its reciprocal).
+__device__ inline void sg_exp_half(double X, double &s, double &ep, double &em)
+{
+    s = sinh(0.5 * X);
+    const double big = sqrt(1.0 + s * s) + fabs(s), inv = 1.0 / big;
+    ep = X >= 0.0 ? big : inv;
+    em = X >= 0.0 ? inv : big;
+}
+
 __device__ inline ConvRow64 sg_conv_row64(double X, double ha, double hb)
 {
-    const double eX = exp(X);
-    const double h2 = 0.5 * (ha * ha / eX + hb * hb * eX);
-    const double sxh = sinh(0.5 * X);
+    double s, ep, em;
+    sg_exp_half(X, s, ep, em);
+    const double rs = rsqrt(0.5 * (ha * ha * (em * em) + hb * hb * (ep * ep))), r2 = rs * rs;
     ConvRow64 c;
-    c.two_sxh2 = 2.0 * sxh * sxh;
-    c.em1 = expm1(X);
-    c.inv4h2 = 1.0 / (4.0 * h2);
-    c.pref = exp(-1.5 * X) * (1.0 / (8.0 * SG_SQRT_PI)) / (h2 * sqrt(h2));
+    c.two_sxh2 = 2.0 * s * s;
+    c.em1 = 2.0 * s * ep;
+    c.inv4h2 = 0.25 * r2;
+    c.pref = em * em * em * (1.0 / (8.0 * SG_SQRT_PI)) * (r2 * rs);
     return c;
 }
 
@@ -537,46 +411,50 @@ __device__ inline void sg_conv_kernel64(double X, double sphi_half, double sphi,
                                         double hb, int which, const double *w, double &Kr,
                                         double &Kp)
 {
-    const double eX = exp(X);
-    const double h2 = 0.5 * (ha * ha / eX + hb * hb * eX);
-    const double sxh = sinh(0.5 * X);
+    double s, ep, em;
+    sg_exp_half(X, s, ep, em);
+    const double rs = rsqrt(0.5 * (ha * ha * (em * em) + hb * hb * (ep * ep))), r2 = rs * rs;
     const double two_s2 = 2.0 * sphi_half * sphi_half;
-    const double cmc = 2.0 * sxh * sxh + two_s2;   // cosh X - cos phi
-    const double emc = expm1(X) + two_s2;          // e^X - cos phi
-    const double x = cmc / (4.0 * h2);
-    const double G = exp(-1.5 * X) * (1.0 / (8.0 * SG_SQRT_PI));
-    if (which == 0) {
-        const double F = sg_F64(x, w);
-        const double pref = F * G / (h2 * sqrt(h2));
-        Kr = pref * emc;
-        Kp = pref * sphi;
-        return;
-    }
-    double F, dF;
-    sg_F64_dF(x, w, F, dF);
-    const double dK = G / (h2 * h2 * sqrt(h2)) * (-x * dF - 1.5 * F);
-    const double dh2 = which == 1 ? ha / eX : hb * eX;
-    Kr = dK * dh2 * emc;
-    Kp = dK * dh2 * sphi;
+    const double x = 0.25 * (2.0 * s * s + two_s2) * r2;  // (cosh X - cos phi) / (4 h^2)
+    const double emc = 2.0 * s * ep + two_s2;             // e^X - cos phi
+    double p = em * em * em * (1.0 / (8.0 * SG_SQRT_PI)) * (r2 * rs);
+    if (which == 0)
+        p *= sg_F64(x, w);
+    else
+        p *= sg_D64(x, w) * r2 * (which == 1 ? ha * (em * em) : hb * (ep * ep));
+    Kr = p * emc;
+    Kp = p * sphi;
 }
 
-// Both h derivatives at once (one F, F' evaluation): (Kr1, Kp1) = d/dh_a,
-// (Kr2, Kp2) = d/dh_b, as sg_conv_kernel64 with which = 1 and 2.
-__device__ inline void sg_conv_kernel64_dh(double X, double sphi_half, double sphi, double ha, double hb,
-                                           const double *w, double &Kr1, double &Kp1, double &Kr2, double &Kp2)
+// Both h derivatives at once (one D evaluation per azimuth): the row's
+// factors and one sample, (Kr1, Kp1) = d/dh_a, (Kr2, Kp2) = d/dh_b, as
+// sg_conv_kernel64 with which = 1 and 2.
+struct ConvRowDh64 {
+    double two_sxh2, em1, inv4h2;  // as in ConvRow64
+    double p1, p2;                 // e^{-3X/2} / (8 sqrt(pi) h^5) times d(h^2)/dh_a, d(h^2)/dh_b
+};
+
+__device__ inline ConvRowDh64 sg_conv_row64_dh(double X, double ha, double hb)
 {
-    const double eX = exp(X);
-    const double h2 = 0.5 * (ha * ha / eX + hb * hb * eX);
-    const double sxh = sinh(0.5 * X);
-    const double two_s2 = 2.0 * sphi_half * sphi_half;
-    const double cmc = 2.0 * sxh * sxh + two_s2;
-    const double emc = expm1(X) + two_s2;
-    const double x = cmc / (4.0 * h2);
-    const double G = exp(-1.5 * X) * (1.0 / (8.0 * SG_SQRT_PI));
-    double F, dF;
-    sg_F64_dF(x, w, F, dF);
-    const double dK = G / (h2 * h2 * sqrt(h2)) * (-x * dF - 1.5 * F);
-    const double d1 = dK * (ha / eX), d2 = dK * (hb * eX);
+    double s, ep, em;
+    sg_exp_half(X, s, ep, em);
+    const double rs = rsqrt(0.5 * (ha * ha * (em * em) + hb * hb * (ep * ep))), r2 = rs * rs;
+    const double g = em * em * em * (1.0 / (8.0 * SG_SQRT_PI)) * (r2 * r2 * rs);
+    ConvRowDh64 c;
+    c.two_sxh2 = 2.0 * s * s;
+    c.em1 = 2.0 * s * ep;
+    c.inv4h2 = 0.25 * r2;
+    c.p1 = g * ha * (em * em);
+    c.p2 = g * hb * (ep * ep);
+    return c;
+}
+
+__device__ inline void sg_conv_kernel64_dh(const ConvRowDh64 &c, double sphi_half, double sphi, const double *w,
+                                           double &Kr1, double &Kp1, double &Kr2, double &Kp2)
+{
+    const double two_s2 = 2.0 * sphi_half * sphi_half, emc = c.em1 + two_s2;
+    const double D = sg_D64((c.two_sxh2 + two_s2) * c.inv4h2, w);
+    const double d1 = D * c.p1, d2 = D * c.p2;
     Kr1 = d1 * emc;
     Kp1 = d1 * sphi;
     Kr2 = d2 * emc;

@@ -86,10 +86,14 @@ struct SsRowArgs {
 // double transform.  Most ring pairs are far apart: on the 1200 x 2048 grid
 // the rows take 0.17 of the samples.  SG_SS_FULL keeps n_phi throughout.
 //
-// The rows of one M form a class: the tiles of SG_SS_TI consecutive target
-// rings (of one b, a, i') whose nearest ring lies x1 <= |X| < x2 away.  They
-// are numbered unit = (pair n_r + i') U + v, v counting the class's tiles of
-// source ring i' (right of it first, then left), U an upper bound.
+// The rows of one M form a class: by units of SG_SS_TI consecutive target
+// rings i (tile t) at one offset k = i' - i, whose last ring lies
+// x1 <= |X| < x2 from its source ring (on the log grid |X| = |k| du for the
+// whole unit; on a uniform grid |X| falls with i, so the last is the
+// nearest).  Row index = ((pair n_t + t) n_k + offset) SG_SS_TI + i % SG_SS_TI:
+// rows of a unit are consecutive entries of a diagonal in the banded modes'
+// layout, and the units of one tile lie together for the full modes' (the
+// scatter goes through them in that order).
 #define SG_SS_ALIAS 80.0
 #define SG_SS_ALIAS_GRAD 96.0  // h derivatives have double poles at phi = +-i X
 #define SG_SS_MIN_M 128
@@ -97,32 +101,26 @@ struct SsRowArgs {
 
 struct SsClass {
     int on;          // 0: every row, in the plain (b, a, i', i) order
-    int U, nt;       // units per source ring; tiles of a ring's targets
-    int first;       // contains |X| = 0
+    int nt;          // tiles of target rings
+    int K1, K2;      // |k| of the class in [K1, K2) (K1 = 0: all of -K2 < k < K2)
+    int nk;          // offsets: 2 K2 - 1 or 2 (K2 - K1)
     double x1, x2;   // the class's range of |X| (x2 infinite in the last)
 };
 
-// First target row right of ring ip with X >= x, and last one left of it with
-// X <= -x (clamped to one past the grid).
-__device__ __host__ inline void ss_reach(bool lin, double du, double rmin, double dr, int nr, int ip, double x,
-                                         int &right, int &left)
+__device__ inline int ss_class_offset(const SsClass &C, int q)
 {
-    double hi, lo;
-    if (lin) {
-        const double r = rmin + (ip + 0.5) * dr;
-        hi = ceil((r * exp(fmin(x, 700.0)) - rmin) / dr - 0.5);
-        lo = floor((r * exp(-fmin(x, 700.0)) - rmin) / dr - 0.5);
-    } else {
-        const double k = ceil(fmin(x / du, 1e9));
-        hi = ip + k;
-        lo = ip - k;
-    }
-    right = hi > nr + SG_SS_TI ? nr + SG_SS_TI : (int)hi;
-    left = lo < -SG_SS_TI - 1.0 ? -SG_SS_TI - 1 : (int)lo;
+    if (C.K1 == 0) return q - (C.K2 - 1);
+    const int half = C.K2 - C.K1;
+    return q < half ? C.K1 + q : -(C.K1 + q - half);
 }
 
-__device__ __host__ inline int ss_tiles_up(int x) { return (x + SG_SS_TI - 1) / SG_SS_TI; }      // ceil, x >= 0
-__device__ __host__ inline int ss_tiles_down(int x) { return x < 0 ? -1 - (-1 - x) / SG_SS_TI : x / SG_SS_TI; }  // floor
+// |X| of the last ring of tile t at offset k on a uniform grid (infinite where
+// the source ring would lie inside the centre).
+__device__ __host__ inline double ss_tile_dist(double rmin, double dr, int t, int k)
+{
+    const double r = rmin + (t * SG_SS_TI + (SG_SS_TI - 0.5)) * dr, rp = r + k * dr;
+    return rp > 0.0 ? fabs(log(rp / r)) : INFINITY;
+}
 
 template <int N> struct SsRowShape {
     static constexpr int P = FftShape<N>::P, T = FftShape<N>::T;
@@ -130,42 +128,47 @@ template <int N> struct SsRowShape {
     static constexpr int G = WGS / T;
 };
 
-// Row idx of a class (or of the plain order): its ring pair; false where the
-// class has none (i may then be past the grid, never a padding row's tile).
-__device__ inline bool ss_row(const SsRowArgs &A, const SsClass &C, size_t idx, int &b, int &a, int &ip, int &i)
+// sin and cos of half the azimuth 2 pi q / N, q <= N/2.
+template <int N> __device__ inline void ss_half_angle(int q, double &s, double &c)
 {
-    size_t rest;
+    static_assert(SG_TW64_N % (2 * N) == 0, "sine table");
+    const double2 v = ((const double2 *)sg_tw64)[q * (SG_TW64_N / (2 * N))];
+    c = v.x;
+    s = v.y;
+}
+
+// Whether tile t at offset k belongs to the class.
+__device__ inline bool ss_in_class(const SsRowArgs &A, const SsClass &C, int t, int k)
+{
+    const int ak = abs(k);
+    if (ak < C.K1 || ak >= C.K2) return false;
+    if (!A.lin) return true;
+    const double x = ss_tile_dist(A.rmin, A.dr, t, k);
+    return x >= C.x1 && x < C.x2;
+}
+
+// Row idx of a class (or of the plain order): its ring pair.  False where
+// there is none (the caller drops the row; in the plain order i may be the
+// padding column of an odd n_r).
+__device__ inline bool ss_row(const SsRowArgs &A, const SsClass &C, uint32_t idx, int &b, int &a, int &ip, int &i)
+{
+    uint32_t rest;  // (at most 16 pairs x 2048 rings x 4095 offsets)
     bool ok = true;
     if (!C.on) {
         i = (int)(idx % A.nrt);
         rest = idx / A.nrt;
         ip = (int)(rest % A.nr);
+        rest /= A.nr;
     } else {
-        const size_t unit = idx / SG_SS_TI;
-        int v = (int)(unit % C.U);
-        rest = unit / C.U;
-        ip = (int)(rest % A.nr);
-        int r1, l1, r2, l2;  // x1 and x2 to the right and to the left
-        ss_reach(A.lin != 0, A.du, A.rmin, A.dr, A.nr, ip, C.x1, r1, l1);
-        ss_reach(A.lin != 0, A.du, A.rmin, A.dr, A.nr, ip, C.x2, r2, l2);
-        // tiles right: first row in [r1, r2); left: last row in (l2, l1]
-        int ra = ss_tiles_up(max(r1, 0)), rb = min(ss_tiles_up(max(r2, 0)), C.nt);
-        int la = max(ss_tiles_down(l2 - (SG_SS_TI - 1)) + 1, 0), lb = min(ss_tiles_down(l1 - (SG_SS_TI - 1)) + 1, C.nt);
-        if (C.first) {  // both sides and the tile around i' in one run
-            ra = la;
-            lb = la;
-        }
-        const int nright = max(rb - ra, 0);
-        int t = ra + v;
-        if (v >= nright) {
-            v -= nright;
-            t = la + v;
-            ok = v < lb - la;
-        }
+        const uint32_t unit = idx / SG_SS_TI;
+        const int k = ss_class_offset(C, (int)(unit % C.nk));
+        rest = unit / C.nk;
+        const int t = (int)(rest % C.nt);
+        rest /= C.nt;
         i = t * SG_SS_TI + (int)(idx % SG_SS_TI);
-        ok = ok && i < A.nrt;
+        ip = i + k;
+        ok = i < A.nr && ip >= 0 && ip < A.nr && ss_in_class(A, C, t, k);
     }
-    rest /= A.nr;
     a = (int)(rest % A.nf);
     b = (int)(rest / A.nf);
     return ok && b < A.nf;
@@ -188,8 +191,7 @@ __device__ inline void ss_far_weight(const ConvRow64 &c0, const ConvRow64 &c1, c
 }
 
 // A group of T threads takes RPG consecutive rows r0 + row of a class (or of
-// the plain (b, a, i', i) order, i fastest), out: [nrows][ncol] float2 (T_r, t_phi),
-// m = 0 .. N/2.  Point-sampled rows go two to a group (RPG = 2): a row's
+// the plain (b, a, i', i) order, i fastest).  Point-sampled rows go two to a group (RPG = 2): a row's
 // samples z = K_r + i K_phi are Hermitian in phi, so its transform Z is real,
 // and the group transforms z_A + i z_B once, reading Z_A from the real part
 // and Z_B from the imaginary part.  The row count is even (n_rt is) and so
@@ -197,46 +199,55 @@ __device__ inline void ss_far_weight(const ConvRow64 &c0, const ConvRow64 &c1, c
 // N: the samples of the rows, n_phi or a class's M.  SO: 0 point samples; 1
 // second-order rows with samples to integrate (one row per group); 2
 // second-order rows beyond SG_SS_HAT_NEAR, whose samples are the weights of
-// ss_far_weight.
+// ss_far_weight.  out: [nrows][mc] float2 (T_r, t_phi), m < mc <= N/2 + 1.
 template <int N, int SO>
 __global__ void __launch_bounds__(SsRowShape<N>::WGS)
-k_ss_rows(const double *H, const double *self, SsRowArgs A, SsClass C, size_t r0, int nrows, float2 *out)
+k_ss_rows(const double *H, const double *self, SsRowArgs A, SsClass C, size_t r0, int nrows, int mc, float2 *out)
 {
     using S = SsRowShape<N>;
     constexpr int P = S::P, T = S::T, G = S::G, W = LdsPlane<double>::elems(N);
     constexpr int NC = N / 2 + 1;
     constexpr int RPG = SO == 1 ? 1 : 2;
     __shared__ __attribute__((aligned(16))) double2 lds[W * G];
-    __shared__ double wq[FQuad<double>::TABLE];
+    __shared__ __attribute__((aligned(16))) double wq[FQuad<double>::TABLE];
     __shared__ double2 qres[SO == 1 ? NC * G : 1];  // SO: the group's integrated samples
     __shared__ int qmax_wg;                         // SO: last integrated sample of any group
     const int g = threadIdx.x / T, t = threadIdx.x % T;
     const LdsPlane<double> pl{lds + W * g};
     const int row = (blockIdx.x * G + g) * RPG;  // the group's first row
-    int i0, ip, a, b;
-    const bool valid = ss_row(A, C, r0 + (size_t)(row < nrows ? row : 0), b, a, ip, i0) && row < nrows;
-    if (!__syncthreads_or(valid ? 1 : 0)) return;
-    if (!valid) b = a = ip = i0 = 0;
-    sg_fill_weights<double>(wq);
-    const double rp = A.lin ? A.rmin + (ip + 0.5) * A.dr : exp(A.lnrmin + (ip + 0.5) * A.du);
-    const double ha = H[a * A.nr + ip] / rp;
-    // per row of the group: target ring (padding rows take the last ring and
-    // stay zero), its radius, h_b and X
+    // per row of the group: ring pair (padding and missing rows take the first
+    // ring and stay zero), radii, aspect ratios and X
     bool live_[RPG];
-    int ic_[RPG];
-    double ri_[RPG], hb_[RPG], X_[RPG];
+    int ic_[RPG], ip_[RPG], a = 0, b = 0;
+    bool any = false;
 #pragma unroll
     for (int u = 0; u < RPG; ++u) {
-        const int iu = i0 + u;
-        live_[u] = valid && iu < A.nr;
-        ic_[u] = iu < A.nr ? iu : A.nr - 1;
+        int ur = row + u, ua, ub;
+        const bool in = ur < nrows;
+        live_[u] = ss_row(A, C, (uint32_t)r0 + (in ? ur : 0), ub, ua, ip_[u], ic_[u]) && in && ic_[u] < A.nr;
+        if (live_[u]) {
+            a = ua;  // one pair per group: units and plain rows pair up within it
+            b = ub;
+        } else {
+            ic_[u] = ip_[u] = 0;
+        }
+        any = any || live_[u];
+    }
+    const bool valid = row < nrows;
+    if (!__syncthreads_or(any || (valid && !C.on) ? 1 : 0)) return;
+    sg_fill64(wq, A.pot ? SG_FN_G0 : SG_FN_F);
+    double ri_[RPG], rp_[RPG], ha_[RPG], hb_[RPG], X_[RPG];
+#pragma unroll
+    for (int u = 0; u < RPG; ++u) {
         ri_[u] = A.lin ? A.rmin + (ic_[u] + 0.5) * A.dr : exp(A.lnrmin + (ic_[u] + 0.5) * A.du);
+        rp_[u] = A.lin ? A.rmin + (ip_[u] + 0.5) * A.dr : exp(A.lnrmin + (ip_[u] + 0.5) * A.du);
+        ha_[u] = H[a * A.nr + ip_[u]] / rp_[u];
         hb_[u] = H[b * A.nr + ic_[u]] / ri_[u];
-        X_[u] = A.lin ? log(ri_[u] / rp) : (double)(ic_[u] - ip) * A.du;
+        X_[u] = A.lin ? log(ri_[u] / rp_[u]) : (double)(ic_[u] - ip_[u]) * A.du;
     }
     const bool live = live_[0];
-    const int ic = ic_[0];
-    const double ri = ri_[0], hb = hb_[0], X = X_[0];
+    const int ic = ic_[0], ip = ip_[0];
+    const double ha = ha_[0], hb = hb_[0], X = X_[0];
     __syncthreads();
     if constexpr (SO == 1) {
         // 1'. hat-weighted samples (see SG_SS_HAT_NEAR): point values of K go
@@ -282,7 +293,7 @@ k_ss_rows(const double *H, const double *self, SsRowArgs A, SsClass C, size_t r0
             val[j] = make_double2(0.0, 0.0);
             if (q > N / 2) continue;
             double sh, ch;
-            sincospi((double)q / N, &sh, &ch);
+            ss_half_angle<N>(q, sh, ch);
             const double s2 = 2.0 * sh * ch;
             double kr = 0.0, kp = 0.0;
             if (q <= qn) {
@@ -324,33 +335,35 @@ k_ss_rows(const double *H, const double *self, SsRowArgs A, SsClass C, size_t r0
     double sx[RPG], Hab2[RPG], pot_pref[RPG];
 #pragma unroll
     for (int u = 0; u < RPG; ++u) {
-        cr[u] = sg_conv_row64(X_[u], ha, hb_[u]);
+        cr[u] = sg_conv_row64(X_[u], ha_[u], hb_[u]);
         if constexpr (SO == 2) {
-            cp1[u] = sg_conv_row64(X_[u] + A.du, ha, hb_[u]);
-            cp2[u] = sg_conv_row64(X_[u] - A.du, ha, hb_[u]);
+            cp1[u] = sg_conv_row64(X_[u] + A.du, ha_[u], hb_[u]);
+            cp2[u] = sg_conv_row64(X_[u] - A.du, ha_[u], hb_[u]);
         }
+        const double Ha = ha_[u] * rp_[u], Hb = hb_[u] * ri_[u];
         sx[u] = sinh(0.5 * X_[u]);
-        Hab2[u] = 0.5 * (ha * rp * ha * rp + hb_[u] * ri_[u] * hb_[u] * ri_[u]);
-        pot_pref[u] = rp * rp / (2.0 * SG_SQRT_PI * sqrt(Hab2[u]));
+        Hab2[u] = 0.5 * (Ha * Ha + Hb * Hb);
+        pot_pref[u] = rp_[u] * rp_[u] / (2.0 * SG_SQRT_PI * sqrt(Hab2[u]));
     }
 #pragma unroll 1
     for (int q = t; q <= N / 2; q += T) {
         double sp, cp;
-        sincospi((double)q / N, &sp, &cp);
+        ss_half_angle<N>(q, sp, cp);
         double kr[RPG], kp[RPG];
 #pragma unroll
         for (int u = 0; u < RPG; ++u) {
             kr[u] = 0.0;
             kp[u] = 0.0;
+            if (!live_[u]) continue;  // shares its transform with the other row
             if constexpr (SO == 2) {
                 ss_far_weight(cr[u], cp1[u], cp2[u], 2.0 * q / N, A.dphi / SG_PI, wq, kr[u], kp[u]);
                 continue;
             }
-            if (ic_[u] == ip && q == 0) {
+            if (ic_[u] == ip_[u] && q == 0) {
                 kr[u] = A.excl ? 0.0 : self[(size_t)(a * A.nf + b) * A.nr + ic_[u]];
             } else if (A.pot) {
                 // -r'^2 P_ab(s), so that the common scale -du dphi / N gives A_i' P / N
-                const double s2 = 4.0 * ri_[u] * rp * (sx[u] * sx[u] + sp * sp);
+                const double s2 = 4.0 * ri_[u] * rp_[u] * (sx[u] * sx[u] + sp * sp);
                 kr[u] = pot_pref[u] * sg_G0_64(s2 / (8.0 * Hab2[u]), wq);
             } else {
                 sg_conv_kernel64_row(cr[u], sp, 2.0 * sp * cp, wq, kr[u], kp[u]);
@@ -372,21 +385,21 @@ k_ss_rows(const double *H, const double *self, SsRowArgs A, SsClass C, size_t r0
     for (int p = 0; p < P; ++p) pl.st(t + T * p, z[p]);
     __syncthreads();
     if (!valid) return;
-    // the samples carry r'^2 (the log-grid measure per du dphi); the source
-    // cell's measure is r'^2 wgt dphi with wgt = du, or dr / r' on a uniform grid
-    const double scale = -(A.lin ? A.dr / rp : A.du) * A.dphi / N;
-    double ind = 0.0;
-    if (A.ind) {
-        // r'^2 sqrt(2) K_a(d) n_phi / 2 (the convolution-form samples carry the
-        // cell measure r'^2), K_a(d) = pi^{-1/2} H^{-2} (d/4) F(d^2/4)
-        const double Ha = H[a * A.nr + ip], d = rp / Ha;
-        ind = rp * rp * SG_SQRT2 * (1.0 / SG_SQRT_PI) / (Ha * Ha) * (0.25 * d) * sg_F64(0.25 * d * d, wq) *
-              (0.5 * N);
-    }
 #pragma unroll
     for (int u = 0; u < RPG; ++u) {
-        float2 *o = out + (size_t)(row + u) * NC;
-        for (int m = t; m < NC; m += T) {
+        // the samples carry r'^2 (the log-grid measure per du dphi); the source
+        // cell's measure is r'^2 wgt dphi with wgt = du, or dr / r' on a uniform grid
+        const double rp = rp_[u], scale = -(A.lin ? A.dr / rp : A.du) * A.dphi / N;
+        double ind = 0.0;
+        if (A.ind) {
+            // r'^2 sqrt(2) K_a(d) N / 2 (the convolution-form samples carry the
+            // cell measure r'^2), K_a(d) = pi^{-1/2} H^{-2} (d/4) F(d^2/4)
+            const double Ha = ha_[u] * rp, d = rp / Ha;
+            ind = rp * rp * SG_SQRT2 * (1.0 / SG_SQRT_PI) / (Ha * Ha) * (0.25 * d) * sg_F64(0.25 * d * d, wq) *
+                  (0.5 * N);
+        }
+        float2 *o = out + (size_t)(row + u) * mc;
+        for (int m = t; m < mc; m += T) {
             float2 v = make_float2(0.f, 0.f);
             if (live_[u]) {
                 const double2 wm = pl.ld(m), wn = pl.ld((N - m) & (N - 1));
@@ -404,40 +417,76 @@ k_ss_rows(const double *H, const double *self, SsRowArgs A, SsClass C, size_t r0
 }
 
 // ------------------------------------------------------- table: transpose
-// src [nrows][ncol] (rows r0 + row of a class or of the plain order, its modes
-// m < ncol) into the modes' layouts, 32 x 32 tiles: for a fixed mode
-// consecutive rows are consecutive target columns in both layouts.
+// src [nrows][ld] (rows r0 + row of a class or of the plain order) into the layouts of modes m0 <= m < ncol, in 32 x 32 tiles of
+// rows and modes.  The 32 rows of a block are written as runs of consecutive
+// target rings, so they are taken in the order of the modes' layout: in row
+// order (a class's diagonals for the banded modes; the plain order, whose i'
+// rows are the full modes'), or, for the full modes of a class (FULL), as two
+// source rings i' times the 16 target rings of a tile, gathered from the rows
+// of their offsets (each row is read as 256 contiguous bytes either way).
+// Diagonals written across the order, 8 bytes at a time, took 1.9 of the 5.2
+// ms of the 1200 x 2048 build.  A row's place costs several integer divisions,
+// so a block goes through all its modes (blockIdx.y: every gridDim.y-th tile).
+template <bool FULL>
 __global__ void __launch_bounds__(256)
-k_ss_scatter(const float2 *src, int nrows, int ncol, float2 *coef, const SsMode *modes, SsRowArgs A, SsClass C,
-             size_t r0)
+k_ss_scatter(const float2 *src, int ld, int nrows, int ncol, int m0, float2 *coef, const SsMode *modes,
+             SsRowArgs A, SsClass C, size_t r0, int tile0)
 {
     __shared__ float2 tile[32][33];
-    const int rb = blockIdx.x * 32, mb = blockIdx.y * 32;
+    __shared__ int srow[32];
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    const int r = rb + tx;
-    int i, ip, a, b;
-    const bool ok = ss_row(A, C, r0 + (r < nrows ? r : 0), b, a, ip, i) && r < nrows;
-    if (!__syncthreads_or(ok ? 1 : 0)) return;
-    for (int k = ty; k < 32; k += 8) {
-        const int rr = rb + k, m = mb + tx;
-        if (rr < nrows && m < ncol) tile[k][tx] = gload2(src, (size_t)rr * ncol + m);
+    int i, ip, a, b, row;
+    bool ok;
+    if constexpr (FULL) {
+        // unit (pair, t, v): source ring number v of those that tile t meets in the class
+        const int side = C.K1 == 0 ? 2 * C.K2 - 1 + (SG_SS_TI - 1) : C.K2 - C.K1 + (SG_SS_TI - 1);
+        const int per = C.K1 == 0 ? side : 2 * side;
+        const int half = (per + 1) / 2;  // blocks per tile
+        const int pt = tile0 + (int)(blockIdx.x / half), v = 2 * (int)(blockIdx.x % half) + (tx >> 4);
+        const int t = pt % C.nt, pair = pt / C.nt;
+        a = pair % A.nf;
+        b = pair / A.nf;
+        i = t * SG_SS_TI + (tx & 15);
+        if (C.K1 == 0) ip = t * SG_SS_TI - (C.K2 - 1) + v;
+        else ip = v < side ? t * SG_SS_TI + C.K1 + v : t * SG_SS_TI + (SG_SS_TI - 1) - C.K1 - (v - side);
+        const int k = ip - i;
+        ok = b < A.nf && v < per && i < A.nr && ip >= 0 && ip < A.nr && ss_in_class(A, C, t, k);
+        // a ring may come up on both sides; only its own side's offsets count
+        if (C.K1 != 0) ok = ok && (v < side ? k > 0 : k < 0);
+        const int q = C.K1 == 0 ? k + C.K2 - 1 : k > 0 ? k - C.K1 : (C.K2 - C.K1) - k - C.K1;
+        const int64_t rr = (((int64_t)pt * C.nk + q) * SG_SS_TI + (tx & 15)) - (int64_t)r0;
+        ok = ok && rr >= 0 && rr < nrows;
+        row = ok ? (int)rr : 0;
+    } else {
+        row = blockIdx.x * 32 + tx;
+        ok = ss_row(A, C, (uint32_t)r0 + (row < nrows ? row : 0), b, a, ip, i) && row < nrows;
+        row = ok ? row : 0;
     }
-    __syncthreads();
-    if (!ok) return;
-    const size_t pair = (size_t)b * A.nf + a;
-    for (int k = ty; k < 32; k += 8) {
-        const int m = mb + k;
-        if (m >= ncol) break;
-        const SsMode md = modes[m];
-        size_t dst;
-        if (md.banded) {
-            const int d = ip - i + md.w;
-            if (d < 0 || d > 2 * md.w) continue;
-            dst = md.off + (pair * (2 * md.w + 1) + d) * A.nrt + i;
-        } else {
-            dst = md.off + (pair * A.nr + ip) * A.nrt + i;
+    if (!__syncthreads_or(ok ? 1 : 0)) return;
+    if (ty == 0) srow[tx] = row;
+    const uint32_t pair = b * A.nf + a;
+    for (int mb = m0 + blockIdx.y * 32; mb < ncol; mb += gridDim.y * 32) {
+        __syncthreads();  // srow; the previous tile has been read
+        const int m = mb + tx;
+        float2 v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = gload2(src, (size_t)srow[ty + 8 * k] * ld + (m < ncol ? m : 0));
+#pragma unroll
+        for (int k = 0; k < 4; ++k) tile[ty + 8 * k][tx] = v[k];
+        __syncthreads();
+        if (!ok) continue;
+        for (int k = ty; k < 32 && mb + k < ncol; k += 8) {
+            const SsMode md = modes[mb + k];
+            size_t dst;
+            if (md.banded) {
+                const int d = ip - i + md.w;
+                if (d < 0 || d > 2 * md.w) continue;
+                dst = md.off + (size_t)(pair * (2 * md.w + 1) + d) * A.nrt + i;
+            } else {
+                dst = md.off + (size_t)(pair * A.nr + ip) * A.nrt + i;
+            }
+            gstore2(coef, dst, tile[tx][k]);
         }
-        gstore2(coef, dst, tile[tx][k]);
     }
 }
 
@@ -491,9 +540,9 @@ __global__ void __launch_bounds__(256)
 k_ss_self_lin(const double *H, int nf, int nr, int per, double rmin, double dr, double dphi, int pot, int which,
               double *out, GLNodes gl)
 {
-    __shared__ double wq[FQuad<double>::TABLE];
+    __shared__ __attribute__((aligned(16))) double wq[FQuad<double>::TABLE];
     __shared__ double red[256];
-    sg_fill_weights<double>(wq);
+    sg_fill64(wq, pot ? (which ? SG_FN_E : SG_FN_G0) : (which ? SG_FN_D : SG_FN_F));
     __syncthreads();
     const int64_t cells = (int64_t)nr * per;
     const int64_t item = blockIdx.x;
@@ -529,8 +578,7 @@ k_ss_self_lin(const double *H, int nf, int nr, int per, double rmin, double dr, 
                     } else {
                         // dP/dH_ab = -(2 y F(y) - G0(y)) / (2 sqrt(pi) H_ab^2), times dH_ab/dh
                         const double ch = (which == 1 ? Ha : Hb) * r / (2.0 * Hab);
-                        f = -(2.0 * y * sg_F64(y, wq) - sg_G0_64(y, wq)) / (2.0 * SG_SQRT_PI * Hab * Hab) * ch *
-                             r * r * exp(2.0 * X);
+                        f = -sg_E64(y, wq) / (2.0 * SG_SQRT_PI * Hab * Hab) * ch * r * r * exp(2.0 * X);
                     }
                 } else {
                     double kr, kp;
@@ -608,22 +656,34 @@ static std::vector<SsPart> ss_parts(const SsRowArgs &A, int nphi, bool full, dou
         out.push_back({nphi, A.second ? 1 : 0, C});
         return out;
     }
-    const double rlast = A.rmin + (A.nr - 0.5) * A.dr, rfirst = A.rmin + 0.5 * A.dr;
-    const double xmax = A.lin ? log(rlast / rfirst) : (A.nr - 1) * A.du;
     const double inf = INFINITY, rn = A.second ? SG_SS_HAT_NEAR * fmax(A.du, A.dphi) : 0.0;
     C.on = 1;
-    C.nt = (A.nrt + SG_SS_TI - 1) / SG_SS_TI;
+    C.nt = (A.nr + SG_SS_TI - 1) / SG_SS_TI;
     auto add = [&](int M, int kind, double x1, double x2) {
-        if (x1 >= x2 || x1 > xmax) return;
-        C.first = x1 == 0.0 ? 1 : 0;
+        if (x1 >= x2) return;
         C.x1 = x1;
         C.x2 = x2;
-        C.U = C.nt;
-        if (!A.lin) {  // a bound on the tiles per source ring
-            const double k1 = ceil(x1 / A.du), k2 = ceil(fmin(x2 / A.du, 1e9));
-            const double n = C.first ? (2.0 * k2 + SG_SS_TI) / SG_SS_TI + 2.0 : 2.0 * ((k2 - k1) / SG_SS_TI + 1.0);
-            if (n < C.U) C.U = (int)n;
+        C.K1 = x1 == 0.0 ? 0 : A.nr;
+        C.K2 = 0;
+        if (!A.lin) {
+            if (x1 > 0.0) C.K1 = (int)fmin(ceil(x1 / A.du), (double)A.nr);
+            C.K2 = (int)fmin(ceil(fmin(x2 / A.du, 1e9)), (double)A.nr);
+        } else {
+            // offsets of which some tile falls into the class: the distance falls
+            // with the tile, from the first to the last that has a ring pair
+            C.K2 = x1 == 0.0 ? 1 : 0;
+            for (int k = 1; k < A.nr; ++k) {
+                const int last = (A.nr - 1 - k) / SG_SS_TI;
+                const double hi = fmax(ss_tile_dist(A.rmin, A.dr, 0, k), ss_tile_dist(A.rmin, A.dr, k / SG_SS_TI, -k));
+                const double lo = fmin(ss_tile_dist(A.rmin, A.dr, last, k),
+                                       ss_tile_dist(A.rmin, A.dr, (A.nr - 1) / SG_SS_TI, -k));
+                if (hi < x1 || lo >= x2) continue;
+                if (k < C.K1 && x1 > 0.0) C.K1 = k;
+                C.K2 = k + 1;
+            }
         }
+        if (C.K1 >= C.K2) return;
+        C.nk = C.K1 == 0 ? 2 * C.K2 - 1 : 2 * (C.K2 - C.K1);
         out.push_back({M, kind, C});
     };
     if (A.second) add(nphi, 1, 0.0, rn);
@@ -636,27 +696,32 @@ static std::vector<SsPart> ss_parts(const SsRowArgs &A, int nphi, bool full, dou
     return out;
 }
 
+static size_t ss_class_rows(const SsRowArgs &A, const SsClass &C)
+{
+    return (size_t)A.nf * A.nf * C.nt * C.nk * SG_SS_TI;
+}
+
 template <int N>
 static void launch_ss_rows(const double *H, const double *self, const SsRowArgs &A, const SsPart &P, size_t r0,
-                           int nrows, float2 *out, hipStream_t s)
+                           int nrows, int mc, float2 *out, hipStream_t s)
 {
     using S = SsRowShape<N>;
     // the quadrature's registers stay out of the other rows; two rows per
     // group unless integrated (nrows is even: see k_ss_rows)
     const dim3 one((nrows + S::G - 1) / S::G), two((nrows + 2 * S::G - 1) / (2 * S::G));
     if (P.kind == 1)
-        hipLaunchKernelGGL((k_ss_rows<N, 1>), one, dim3(S::WGS), 0, s, H, self, A, P.C, r0, nrows, out);
+        hipLaunchKernelGGL((k_ss_rows<N, 1>), one, dim3(S::WGS), 0, s, H, self, A, P.C, r0, nrows, mc, out);
     else if (P.kind == 2)
-        hipLaunchKernelGGL((k_ss_rows<N, 2>), two, dim3(S::WGS), 0, s, H, self, A, P.C, r0, nrows, out);
+        hipLaunchKernelGGL((k_ss_rows<N, 2>), two, dim3(S::WGS), 0, s, H, self, A, P.C, r0, nrows, mc, out);
     else
-        hipLaunchKernelGGL((k_ss_rows<N, 0>), two, dim3(S::WGS), 0, s, H, self, A, P.C, r0, nrows, out);
+        hipLaunchKernelGGL((k_ss_rows<N, 0>), two, dim3(S::WGS), 0, s, H, self, A, P.C, r0, nrows, mc, out);
 }
 
 static bool dispatch_ss_rows(const double *H, const double *self, const SsRowArgs &A, const SsPart &P, size_t r0,
-                             int nrows, float2 *out, hipStream_t s)
+                             int nrows, int mc, float2 *out, hipStream_t s)
 {
 #define SG_ROWS(N) \
-    case N: launch_ss_rows<N>(H, self, A, P, r0, nrows, out, s); return true;
+    case N: launch_ss_rows<N>(H, self, A, P, r0, nrows, mc, out, s); return true;
     switch (P.M) {
         SG_ROWS(4) SG_ROWS(8) SG_ROWS(16) SG_ROWS(32) SG_ROWS(64) SG_ROWS(128) SG_ROWS(256) SG_ROWS(512)
         SG_ROWS(1024) SG_ROWS(2048)
@@ -705,7 +770,7 @@ sg_status sg_ss_table_build(const sg_grid *grid, int nf, const double *d_H, uint
     A.second = second ? 1 : 0;
     sg_gl_nodes(A.gl, du / dphi);
     const std::vector<SsPart> parts = ss_parts(A, nphi, full, SG_SS_ALIAS);
-    if (L.max_w >= 0 || parts.size() > 1) {  // entries the scatter does not reach stay zero
+    if (L.max_w >= 0 || parts[0].C.on) {  // entries the scatter does not reach stay zero
         hipLaunchKernelGGL(k_ss_zero, dim3(2048), dim3(256), 0, s, coef, L.coef_elems);
         SG_HIP(hipGetLastError());
     }
@@ -730,16 +795,39 @@ sg_status sg_ss_table_build(const sg_grid *grid, int nf, const double *d_H, uint
     // the chunk buffer holds whole units of each class's rows
     const size_t cbytes = sizeof(float2) * (size_t)L.ncol * ss_chunk_rows(L);
     for (const SsPart &P : parts) {
-        const int mc = P.M / 2 + 1;
-        const size_t rows = P.C.on ? (size_t)nf * nf * nr * P.C.U * SG_SS_TI : L.rows;
+        // modes that the class's nearest ring pairs keep (on a uniform grid the
+        // band is counted in rings, so by M alone): full ones, and banded ones
+        // whose band reaches them
+        int mc = P.M / 2 + 1;
+        if (P.C.on && !lin) {
+            const int k1 = P.C.K1;
+            while (mc > 1) {
+                const int w = sg_ss_band(mc - 1, nr, du, full);
+                if (!sg_ss_is_banded(w, nr) || w >= k1) break;
+                --mc;
+            }
+        }
+        int mfull = 0;  // the leading full modes
+        while (mfull < mc && !sg_ss_is_banded(sg_ss_band(mfull, nr, du, full), nr)) ++mfull;
+        const size_t rows = P.C.on ? ss_class_rows(A, P.C) : L.rows;
         size_t crows = P.C.on ? cbytes / (sizeof(float2) * mc) / SG_SS_TI * SG_SS_TI : ss_chunk_rows(L);
         if (crows > (size_t)1 << 30) crows = (size_t)1 << 30;
         for (size_t r0 = 0; r0 < rows; r0 += crows) {
             const int n = (int)std::min(crows, rows - r0);
-            if (!dispatch_ss_rows(d_H, self, A, P, r0, n, chunk, s)) return SG_ERR_UNSUPPORTED;
+            if (!dispatch_ss_rows(d_H, self, A, P, r0, n, mc, chunk, s)) return SG_ERR_UNSUPPORTED;
             SG_HIP(hipGetLastError());
-            hipLaunchKernelGGL(k_ss_scatter, dim3((n + 31) / 32, (mc + 31) / 32), dim3(256), 0, s, chunk, n, mc,
-                               coef, (const SsMode *)modes, A, P.C, r0);
+            const int ms = P.C.on ? mfull : 0;
+            if (ms < mc)
+                hipLaunchKernelGGL(k_ss_scatter<false>, dim3((n + 31) / 32, (mc - ms + 255) / 256), dim3(256), 0, s,
+                                   chunk, mc, n, mc, ms, coef, (const SsMode *)modes, A, P.C, r0, 0);
+            if (ms > 0) {
+                const size_t per_tile = (size_t)P.C.nk * SG_SS_TI;
+                const int t0 = (int)(r0 / per_tile), t1 = (int)((r0 + n - 1) / per_tile) + 1;
+                const int side = P.C.K1 == 0 ? 2 * P.C.K2 - 1 + (SG_SS_TI - 1) : P.C.K2 - P.C.K1 + (SG_SS_TI - 1);
+                const int half = ((P.C.K1 == 0 ? side : 2 * side) + 1) / 2;
+                hipLaunchKernelGGL(k_ss_scatter<true>, dim3((unsigned)(half * (t1 - t0)), (ms + 255) / 256), dim3(256),
+                                   0, s, chunk, mc, n, ms, 0, coef, (const SsMode *)modes, A, P.C, r0, t0);
+            }
             SG_HIP(hipGetLastError());
         }
     }
@@ -1012,7 +1100,7 @@ k_ssg_rows(const double *H, const double *dself, SsRowArgs A, SsClass C, int nph
     constexpr int P = S::P, T = S::T, G = S::G, W = LdsPlane<double>::elems(N);
     constexpr int NC = N / 2 + 1;
     __shared__ __attribute__((aligned(16))) double2 lds[W * G];
-    __shared__ double wq[FQuad<double>::TABLE];
+    __shared__ __attribute__((aligned(16))) double wq[FQuad<double>::TABLE];
     __shared__ double red[S::WGS];
     __shared__ double2 qres[SO == 1 ? 2 * NC * G : 1];  // SO: the group's integrated samples, both derivatives
     __shared__ int qmax_wg;
@@ -1020,10 +1108,10 @@ k_ssg_rows(const double *H, const double *dself, SsRowArgs A, SsClass C, int nph
     const LdsPlane<double> pl{lds + W * g};
     const int row = blockIdx.x * G + g;
     int i, ip, a, b;
-    const bool valid = ss_row(A, C, r0 + (size_t)(row < nrows ? row : 0), b, a, ip, i) && row < nrows;
+    const bool valid = ss_row(A, C, (uint32_t)r0 + (row < nrows ? row : 0), b, a, ip, i) && row < nrows;
     if (!__syncthreads_or(valid ? 1 : 0)) return;
     if (!valid) b = a = ip = i = 0;
-    sg_fill_weights<double>(wq);
+    sg_fill64(wq, A.pot ? SG_FN_E : SG_FN_D);
     const bool live = valid && i < A.nr;
     const int ic = i < A.nr ? i : A.nr - 1;
     const double ri = A.lin ? A.rmin + (ic + 0.5) * A.dr : exp(A.lnrmin + (ic + 0.5) * A.du);
@@ -1039,6 +1127,12 @@ k_ssg_rows(const double *H, const double *dself, SsRowArgs A, SsClass C, int nph
     // plane holds z = z_1 + i z_2, whose transform carries Z_1 (d/dh_a) in
     // its real part and Z_2 (d/dh_b) in its imaginary part.
     constexpr int Q = P / 2 + 1;
+    const ConvRowDh64 d0 = sg_conv_row64_dh(X, ha, hb);
+    ConvRowDh64 dp = d0, dm = d0;  // the D_X neighbours of second-order rows
+    if constexpr (SO != 0) {
+        dp = sg_conv_row64_dh(X + A.du, ha, hb);
+        dm = sg_conv_row64_dh(X - A.du, ha, hb);
+    }
     if constexpr (SO == 1) {
         // integrated samples, cooperatively (as in k_ss_rows<N, true>)
         const int Pr = ic - ip;
@@ -1079,9 +1173,11 @@ k_ssg_rows(const double *H, const double *dself, SsRowArgs A, SsClass C, int nph
             vq[u] = make_double2(0.0, 0.0);
             vm[u] = make_double2(0.0, 0.0);
             if (q > N / 2) continue;
-            const double sh = sinpi((double)q / N), s2 = sinpi(2.0 * q / N);
+            double sh, ch;
+            ss_half_angle<N>(q, sh, ch);
+            const double s2 = 2.0 * sh * ch;
             double kr1 = 0.0, kp1 = 0.0, kr2 = 0.0, kp2 = 0.0;
-            if (Pr != 0 || q != 0) sg_conv_kernel64_dh(X, sh, s2, ha, hb, wq, kr1, kp1, kr2, kp2);
+            if (Pr != 0 || q != 0) sg_conv_kernel64_dh(d0, sh, s2, wq, kr1, kp1, kr2, kp2);
             if (q <= qn) {
                 const double2 w1 = qres[(g * 2 + 0) * NC + q], w2 = qres[(g * 2 + 1) * NC + q];
                 vq[u] = make_double2(w1.x - w2.y, w1.y + w2.x);
@@ -1089,8 +1185,8 @@ k_ssg_rows(const double *H, const double *dself, SsRowArgs A, SsClass C, int nph
             } else {
                 // D_X^2 of the packed rows: samples at X +- du
                 double a1, b1, c1, e1, a2, b2, c2, e2;
-                sg_conv_kernel64_dh(X + A.du, sh, s2, ha, hb, wq, a1, b1, c1, e1);
-                sg_conv_kernel64_dh(X - A.du, sh, s2, ha, hb, wq, a2, b2, c2, e2);
+                sg_conv_kernel64_dh(dp, sh, s2, wq, a1, b1, c1, e1);
+                sg_conv_kernel64_dh(dm, sh, s2, wq, a2, b2, c2, e2);
                 const double dr1 = a1 - 2.0 * kr1 + a2, dp1 = b1 - 2.0 * kp1 + b2;
                 const double dr2 = c1 - 2.0 * kr2 + c2, dp2 = e1 - 2.0 * kp2 + e2;
                 vq[u] = make_double2(kr1 - kp2 + (dr1 - dp2) / 12.0, kp1 + kr2 + (dp1 + dr2) / 12.0);
@@ -1138,8 +1234,7 @@ k_ssg_rows(const double *H, const double *dself, SsRowArgs A, SsClass C, int nph
                 const double ph = 2.0 * q / N + (k == 3 ? A.dphi : k == 4 ? -A.dphi : 0.0) / SG_PI;
                 double sh, ch, a1, b1, a2, b2;
                 sincospi(0.5 * ph, &sh, &ch);
-                sg_conv_kernel64_dh(X + (k == 1 ? A.du : k == 2 ? -A.du : 0.0), sh, 2.0 * sh * ch, ha, hb, wq, a1, b1,
-                                    a2, b2);
+                sg_conv_kernel64_dh(k == 1 ? dp : k == 2 ? dm : d0, sh, 2.0 * sh * ch, wq, a1, b1, a2, b2);
                 const double w = k == 0 ? 2.0 / 3.0 : 1.0 / 12.0;
                 kr1 += w * a1;
                 kp1 += w * b1;
@@ -1156,15 +1251,19 @@ k_ssg_rows(const double *H, const double *dself, SsRowArgs A, SsClass C, int nph
             // d/dh of r'^2 G0(y) / (2 sqrt(pi) H_ab) (the forward's sample):
             // d(G0/H)/dH = (2 y F(y) - G0(y)) / H^2, dH_ab/dh_a = H_a r' / (2 H_ab),
             // dH_ab/dh_b = H_b r_i / (2 H_ab); even in phi (no K_phi part)
-            const double sx = sinh(0.5 * X), sp = sinpi((double)q / N);
+            double sp, cp;
+            ss_half_angle<N>(q, sp, cp);
+            const double sx = sinh(0.5 * X);
             const double s2 = 4.0 * ri * rp * (sx * sx + sp * sp);
             const double Ha = ha * rp, Hb = hb * ri, Hab2 = 0.5 * (Ha * Ha + Hb * Hb), Hab = sqrt(Hab2);
             const double y = s2 / (8.0 * Hab2);
-            const double dq = rp * rp * (2.0 * y * sg_F64(y, wq) - sg_G0_64(y, wq)) / (2.0 * SG_SQRT_PI * Hab2);
+            const double dq = rp * rp * sg_E64(y, wq) / (2.0 * SG_SQRT_PI * Hab2);
             kr1 = dq * Ha * rp / (2.0 * Hab);
             kr2 = dq * Hb * ri / (2.0 * Hab);
         } else {
-            sg_conv_kernel64_dh(X, sinpi((double)q / N), sinpi(2.0 * q / N), ha, hb, wq, kr1, kp1, kr2, kp2);
+            double sh, ch;
+            ss_half_angle<N>(q, sh, ch);
+            sg_conv_kernel64_dh(d0, sh, 2.0 * sh * ch, wq, kr1, kp1, kr2, kp2);
         }
         pl.st(q, make_double2(kr1 - kp2, kp1 + kr2));
         if (q != 0 && q != N / 2) pl.st(N - q, make_double2(kr1 + kp2, kr2 - kp1));
@@ -1184,9 +1283,7 @@ k_ssg_rows(const double *H, const double *dself, SsRowArgs A, SsClass C, int nph
         // d/dh_a of r'^2 sqrt(2) K_a(r'/H_a) n_phi / 2, H_a = h_a r':
         // dK_a/dH = pi^{-1/2} r' / (4 H^4) (-3 F(x) - 2 x F'(x)), x = r'^2 / (4 H^2)
         const double Ha = ha * rp, x = rp * rp / (4.0 * Ha * Ha);
-        double F, dF;
-        sg_F64_dF(x, wq, F, dF);
-        const double dK = (1.0 / SG_SQRT_PI) * rp / (4.0 * Ha * Ha * Ha * Ha) * (-3.0 * F - 2.0 * x * dF);
+        const double dK = (1.0 / SG_SQRT_PI) * rp / (2.0 * Ha * Ha * Ha * Ha) * sg_D64(x, wq);
         dind = rp * rp * SG_SQRT2 * dK * rp * (0.5 * N);
     }
     double part[2] = {0.0, 0.0};
@@ -1285,7 +1382,7 @@ static void launch_ssg_rows(const double *H, const double *dself, const SsRowArg
                             const float2 *lt, const float2 *st, double *rowpart, hipStream_t s)
 {
     using S = SsRowShape<N>;
-    const size_t rows = P.C.on ? (size_t)A.nf * A.nf * A.nr * P.C.U * SG_SS_TI : (size_t)A.nf * A.nf * A.nr * A.nrt;
+    const size_t rows = P.C.on ? ss_class_rows(A, P.C) : (size_t)A.nf * A.nf * A.nr * A.nrt;
     const size_t chunk = (size_t)1 << 22;
     for (size_t r0 = 0; r0 < rows; r0 += chunk) {
         const int n = (int)std::min(chunk, rows - r0);

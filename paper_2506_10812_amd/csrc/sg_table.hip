@@ -85,16 +85,14 @@ __device__ inline OwnPt own_tri_pt(double a, double b, const OwnEta &e, int tri,
 __device__ inline double own_val(double c, double h2, const double *wq)
 {
     const double rs = rsqrt(h2), r2 = rs * rs;
-    return sg_F64<true>(0.25 * c * r2, wq) * (r2 * rs);
+    return sg_F64(0.25 * c * r2, wq) * (r2 * rs);
 }
 
-// (-x F' - 3/2 F) h^-5
+// D(x) h^-5
 __device__ inline double own_dval(double c, double h2, const double *wq)
 {
-    const double rs = rsqrt(h2), r2 = rs * rs, x = 0.25 * c * r2;
-    double F, dF;
-    sg_F64_dF<true>(x, wq, F, dF);
-    return (-x * dF - 1.5 * F) * (r2 * r2 * rs);
+    const double rs = rsqrt(h2), r2 = rs * rs;
+    return sg_D64(0.25 * c * r2, wq) * (r2 * r2 * rs);
 }
 
 // One node of the h derivative (which = 1: h_a, 2: h_b) of one pair:
@@ -145,13 +143,13 @@ __device__ inline double self_cell_partial(double ha, double hb, int which, doub
     return acc * SG_OWN_SCALE;
 }
 
-__global__ void k_self_cell(SelfItems items, double *out, double du, double dphi, GLNodes gl)
+__global__ void __launch_bounds__(256) k_self_cell(SelfItems items, double *out, double du, double dphi, GLNodes gl)
 {
-    __shared__ double wq[FQuad<double>::TABLE];
+    __shared__ __attribute__((aligned(16))) double wq[FQuad<double>::TABLE];
     __shared__ double red[256];
-    sg_fill_weights<double>(wq);
-    __syncthreads();
     const int it = blockIdx.x;
+    sg_fill64(wq, items.which[it] ? SG_FN_D : SG_FN_F);
+    __syncthreads();
     const double acc = self_cell_partial(items.ha[it], items.hb[it], items.which[it], 0.5 * du,
                                          0.5 * dphi, gl, wq);
     const double tot = block_sum256(acc, red);
@@ -190,7 +188,7 @@ template <typename T, int NF, int CPB>
 __global__ void __launch_bounds__(256)
 k_self_cells(const T *H, int64_t N, int nphi, double lnrmin, double du, double dphi, double *out, GLNodes gl)
 {
-    __shared__ double wq[FQuad<double>::TABLE];
+    __shared__ __attribute__((aligned(16))) double wq[FQuad<double>::TABLE];
     __shared__ double red[4 * NF * NF * CPB];
     sg_fill_weights<double>(wq);
     __syncthreads();
@@ -260,7 +258,7 @@ void sg_self_cells(const T *H, int nf, int nr, int nphi, double lnrmin, double d
         else SG_OWN(1, 1);
         break;
     case 2:
-        if (many) SG_OWN(2, 4);
+        if (many) SG_OWN(2, 2);
         else SG_OWN(2, 1);
         break;
     case 3: SG_OWN(3, 1); break;
@@ -274,12 +272,13 @@ template void sg_self_cells<double>(const double *, int, int, int, double, doubl
 // Per-ring variant with a derivative selector for the semi-spectral
 // gradient: item = (pair, ring), h = H[f][ring] / r; which = 1: dKbar/dh_a,
 // 2: dKbar/dh_b.
-__global__ void k_self_cell_ring(const double *H, int nf, int nr, double lnrmin, double du, double dphi, int which,
+__global__ void __launch_bounds__(256)
+k_self_cell_ring(const double *H, int nf, int nr, double lnrmin, double du, double dphi, int which,
                                  double *out, GLNodes gl)
 {
-    __shared__ double wq[FQuad<double>::TABLE];
+    __shared__ __attribute__((aligned(16))) double wq[FQuad<double>::TABLE];
     __shared__ double red[256];
-    sg_fill_weights<double>(wq);
+    sg_fill64(wq, which ? SG_FN_D : SG_FN_F);
     __syncthreads();
     const int item = blockIdx.x;
     if (item >= nf * nf * nr) return;
@@ -298,8 +297,8 @@ __global__ void k_self_cell_ring(const double *H, int nf, int nr, double lnrmin,
 // so 2 x (X >= 0 and X <= 0 halves) over [0,a]x[0,b] with the same Duffy
 // rule as the force self term (the singularity is logarithmic).
 // which = 0: P; which = 1: dP/dH_ab (H_ab the r.m.s. height: with
-// G0 = e^y K0(y), dG0/dy = -F(y), so dP/dH = -(2 y F(y) - G0(y)) /
-// (2 sqrt(pi) H^2); like P, logarithmic at s -> 0).
+// G0 = e^y K0(y), dG0/dy = -F(y), so dP/dH = -E(y) / (2 sqrt(pi) H^2), E(y) =
+// 2 y F(y) - G0(y); like P, logarithmic at s -> 0).
 //
 // One block per CPB cells and unordered pair (P_ab = P_ba), or rows when
 // per_row (H_f = h_f r: depends on the row only); a node's geometry is shared
@@ -312,9 +311,9 @@ __global__ void __launch_bounds__(256)
 k_pot_cells(const T *H, const double *h, int nf, int64_t per, int nphi, double lnrmin, double du, double dphi,
             int per_row, double *out, GLNodes gl, int which)
 {
-    __shared__ double wq[FQuad<double>::TABLE];
+    __shared__ __attribute__((aligned(16))) double wq[FQuad<double>::TABLE];
     __shared__ double red[4 * CPB];
-    sg_fill_weights<double>(wq);
+    sg_fill64(wq, DER ? SG_FN_E : SG_FN_G0);
     __syncthreads();
     int fa = 0, fb = blockIdx.y;  // unordered pair blockIdx.y of (0,0), (0,1), ..., (1,1), ...
     while (fb >= nf - fa) {
@@ -355,8 +354,8 @@ k_pot_cells(const T *H, const double *h, int nf, int64_t per, int nphi, double l
             const double eX = ex * ex, cy = eX * (2.0 * s * s + 2.0 * sp * sp), we = wk * eX * eX;
 #pragma unroll
             for (int c = 0; c < CPB; ++c) {
-                const double y = cy * r2H[c], G = sg_G0_64<true>(y, wq);
-                acc[c] += we * (DER ? 2.0 * y * sg_F64<true>(y, wq) - G : G);
+                const double y = cy * r2H[c];
+                acc[c] += we * (DER ? sg_E64(y, wq) : sg_G0_64(y, wq));
             }
         }
     }
@@ -415,10 +414,10 @@ __global__ void k_fill_f64(double *p, int64_t n, double v)
 // |P| >= 2 or |Q| >= 2 (no singular square); row n_r (offset +-n_r) is zero.
 // which: 0 the weights, 1 and 2 their derivatives in h_a and h_b (the
 // kernel's derivatives integrated with the same rules).
-__global__ void k_sample_hat_far(double2 *A, int nr, int nphi, double du, double ha, double hb, int which)
+__global__ void __launch_bounds__(256) k_sample_hat_far(double2 *A, int nr, int nphi, double du, double ha, double hb, int which)
 {
-    __shared__ double wq[FQuad<double>::TABLE];
-    sg_fill_weights<double>(wq);
+    __shared__ __attribute__((aligned(16))) double wq[FQuad<double>::TABLE];
+    sg_fill64(wq, which ? SG_FN_D : SG_FN_F);
     __syncthreads();
     const int p = blockIdx.y;
     const int q = blockIdx.x * blockDim.x + threadIdx.x;
@@ -444,9 +443,9 @@ __global__ void k_sample_hat_far(double2 *A, int nr, int nphi, double du, double
 __global__ void __launch_bounds__(256) k_sample_hat_near(double2 *A, int nr, int nphi, double du, double ha,
                                                           double hb, int which, GLNodes gl)
 {
-    __shared__ double wq[FQuad<double>::TABLE];
+    __shared__ __attribute__((aligned(16))) double wq[FQuad<double>::TABLE];
     __shared__ double red[256];
-    sg_fill_weights<double>(wq);
+    sg_fill64(wq, which ? SG_FN_D : SG_FN_F);
     __syncthreads();
     const int P = (int)(blockIdx.x % 3) - 1, Q = (int)(blockIdx.x / 3) - 1;
     const double dphi = 2.0 * SG_PI / nphi;
@@ -488,8 +487,8 @@ __global__ void k_copy_w00(const double2 *A, double *out) { *out = A[0].x; }
 __global__ void k_sample(double2 *A, int nr, int nphi, double du, double ha, double hb, int which,
                          const double *self_val)
 {
-    __shared__ double wq[FQuad<double>::TABLE];
-    sg_fill_weights<double>(wq);
+    __shared__ __attribute__((aligned(16))) double wq[FQuad<double>::TABLE];
+    sg_fill64(wq, which ? SG_FN_D : SG_FN_F);
     __syncthreads();
     const int p = blockIdx.y;
     const int q = blockIdx.x * blockDim.x + threadIdx.x;
@@ -598,7 +597,7 @@ __global__ void k_header(sg_table_header *hd, sg_table_header proto, const doubl
                          int npair, int with_dh)
 {
     // one wave fills the coefficient table; lane 0 writes the header
-    __shared__ double w[FQuad<double>::TABLE];
+    __shared__ __attribute__((aligned(16))) double w[FQuad<double>::TABLE];
     sg_fill_weights<double>(w);
     __syncthreads();
     if (threadIdx.x != 0) return;
@@ -626,16 +625,17 @@ __global__ void k_header(sg_table_header *hd, sg_table_header proto, const doubl
 template <typename T>
 __global__ void k_eval_F(const T *x, T *F, T *dF, int64_t n)
 {
-    __shared__ T wq[FQuad<T>::TABLE];
+    __shared__ __attribute__((aligned(16))) T wq[FQuad<T>::TABLE];
+    __shared__ __attribute__((aligned(16))) T wd[sizeof(T) == 8 ? FQuad<T>::TABLE : 2];
     sg_fill_weights<T>(wq);
+    if constexpr (sizeof(T) == 8) sg_fill64(wd, SG_FN_D);
     __syncthreads();
     int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i >= n) return;
     if constexpr (sizeof(T) == 8) {
-        double f, d;
-        sg_F64_dF(x[i], wq, f, d);
+        const double f = sg_F64(x[i], wq);
         F[i] = f;
-        if (dF) dF[i] = d;
+        if (dF) dF[i] = -(sg_D64(x[i], wd) + 1.5 * f) / x[i];
     } else {
         F[i] = sg_F32(x[i], wq);
         if (dF) dF[i] = 0.0f;
@@ -645,8 +645,8 @@ __global__ void k_eval_F(const T *x, T *F, T *dF, int64_t n)
 template <typename T>
 __global__ void k_eval_G0(const T *x, T *G, int64_t n)
 {
-    __shared__ T wq[FQuad<T>::TABLE];
-    sg_fill_weights<T>(wq);
+    __shared__ __attribute__((aligned(16))) T wq[FQuad<T>::TABLE];
+    sg_fill_weights<T>(wq, SG_FN_G0);
     __syncthreads();
     int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i >= n) return;
