@@ -32,7 +32,10 @@
 // the combination the derivatives with respect to the scale heights need (the
 // two terms cancel to O(1/x) of themselves, the integral does not), and of
 //     E(x) = 2 x F(x) - G0(x) = int_0^inf e^{-x (cosh t - 1)} (2 x (cosh t - 1) - 1) dt
-// likewise for the potential.  Also written: the double twiddles of the table
+// likewise for the potential; and, for the direct sums, of
+//     V(u) = u^{-3/2} F(1/u),   Vg(u) = u^{-1/2} G0(1/u)
+// on the octaves of u = 1/x (2^UOCT0 to 2^UOCT1), in double and, on 4
+// intervals per octave with 7 terms, in float.  Also written: the double twiddles of the table
 // builds' transforms.  The library evaluates these; the Chebyshev
 // series above are the fits' reference, kept for the generator's own test.
 #include <cmath>
@@ -61,38 +64,43 @@ static void fdg(long double x, long double (&v)[4])
     }
 }
 
-// Monomial coefficients of the fits on the interval [a, a + w).
-static bool poly_fit(long double a, long double w, double (&out)[4][PNC])
+static const int UOCT0 = -8, UOCT1 = 4;               // double: PSUB intervals, PNC terms
+static const int FSUB = 4, FOCT0 = -6, FOCT1 = 4, FNC = 7;  // float, rows of FNC + 1
+
+// Monomial coefficients of the NF functions' fits on the interval [a, a + w);
+// tol: largest last coefficient over the function's value.
+template <int NF, int NC, typename Fn>
+static bool poly_fit(Fn fn, long double a, long double w, long double tol, double (&out)[NF][NC])
 {
     const long double pi = 3.141592653589793238462643383279502884L;
-    long double val[4][PNN], top[4] = {0.0L, 0.0L, 0.0L, 0.0L};
+    long double val[NF][PNN], top[NF] = {};
     for (int j = 0; j < PNN; ++j) {
-        long double v[4];
-        fdg(a + 0.5L * w * (1.0L + cosl(pi * (j + 0.5L) / PNN)), v);
-        for (int f = 0; f < 4; ++f) {
+        long double v[NF];
+        fn(a + 0.5L * w * (1.0L + cosl(pi * (j + 0.5L) / PNN)), v);
+        for (int f = 0; f < NF; ++f) {
             val[f][j] = v[f];
             top[f] = fmaxl(top[f], fabsl(v[f]));
         }
     }
-    for (int f = 0; f < 4; ++f) {
-        long double mono[PNC] = {}, t0[PNC] = {}, t1[PNC] = {}, last = 0.0L;
+    for (int f = 0; f < NF; ++f) {
+        long double mono[NC] = {}, t0[NC] = {}, t1[NC] = {}, last = 0.0L;
         t0[0] = 1.0L;
         t1[1] = 1.0L;
-        for (int m = 0; m < PNC; ++m) {
+        for (int m = 0; m < NC; ++m) {
             long double c = 0.0L;
             for (int j = 0; j < PNN; ++j) c += val[f][j] * cosl(pi * m * (j + 0.5L) / PNN);
             c *= (m == 0 ? 1.0L : 2.0L) / PNN;
             last = c;
-            for (int i = 0; i < PNC; ++i) mono[i] += c * t0[i];
-            long double t2[PNC];  // T_{m+2} = 2 t T_{m+1} - T_m
-            for (int i = 0; i < PNC; ++i) t2[i] = (i ? 2.0L * t1[i - 1] : 0.0L) - t0[i];
-            for (int i = 0; i < PNC; ++i) {
+            for (int i = 0; i < NC; ++i) mono[i] += c * t0[i];
+            long double t2[NC];  // T_{m+2} = 2 t T_{m+1} - T_m
+            for (int i = 0; i < NC; ++i) t2[i] = (i ? 2.0L * t1[i - 1] : 0.0L) - t0[i];
+            for (int i = 0; i < NC; ++i) {
                 t0[i] = t1[i];
                 t1[i] = t2[i];
             }
         }
-        if (fabsl(last) > 1e-15L * top[f]) return false;  // the next one is 34 times smaller
-        for (int i = 0; i < PNC; ++i) out[f][i] = (double)mono[i];
+        if (fabsl(last) > tol * top[f]) return false;  // the next one is 34 (float: 18) times smaller
+        for (int i = 0; i < NC; ++i) out[f][i] = (double)mono[i];
     }
     return true;
 }
@@ -170,7 +178,8 @@ int main()
     for (int i = 0; i < pni; ++i) {
         const long double oct = ldexpl(1.0L, POCT0 + i / PSUB), w = oct / PSUB;
         double c[4][PNC];
-        if (!poly_fit(oct + w * (i % PSUB), w, c)) {
+        if (!poly_fit<4, PNC>([](long double x, long double(&v)[4]) { fdg(x, v); }, oct + w * (i % PSUB), w, 1e-15L,
+                              c)) {
             fprintf(stderr, "gen_cheb64: local polynomial %d: truncation too large\n", i);
             return 1;
         }
@@ -182,6 +191,49 @@ int main()
     for (int f = 0; f < 4; ++f)
         for (int i = 0; i < pni; ++i)
             for (int m = 0; m < PNC; ++m) printf("    %.17e,\n", poly[f][i][m]);
+    printf("};\n");
+    auto vvg = [](long double u, long double(&v)[2]) {
+        long double f[4];
+        fdg(1.0L / u, f);
+        v[0] = f[0] / (u * sqrtl(u));
+        v[1] = f[2] / sqrtl(u);
+    };
+    const int uni = (UOCT1 - UOCT0) * PSUB, fni = (FOCT1 - FOCT0) * FSUB;
+    static double pu[2][(UOCT1 - UOCT0) * PSUB][PNC];
+    static double pf[2][(FOCT1 - FOCT0) * FSUB][FNC];
+    for (int i = 0; i < uni; ++i) {
+        const long double oct = ldexpl(1.0L, UOCT0 + i / PSUB), w = oct / PSUB;
+        double c[2][PNC];
+        if (!poly_fit<2, PNC>(vvg, oct + w * (i % PSUB), w, 1e-15L, c)) {
+            fprintf(stderr, "gen_cheb64: V polynomial %d: truncation too large\n", i);
+            return 1;
+        }
+        for (int f = 0; f < 2; ++f)
+            for (int m = 0; m < PNC; ++m) pu[f][i][m] = c[f][m];
+    }
+    for (int i = 0; i < fni; ++i) {
+        const long double oct = ldexpl(1.0L, FOCT0 + i / FSUB), w = oct / FSUB;
+        double c[2][FNC];
+        if (!poly_fit<2, FNC>(vvg, oct + w * (i % FSUB), w, 1e-7L, c)) {
+            fprintf(stderr, "gen_cheb64: float V polynomial %d: truncation too large\n", i);
+            return 1;
+        }
+        for (int f = 0; f < 2; ++f)
+            for (int m = 0; m < FNC; ++m) pf[f][i][m] = c[f][m];
+    }
+    printf("#define SG_POLYU_OCT0 %d\n#define SG_POLYF_SUB %d\n#define SG_POLYF_OCT0 %d\n#define SG_POLYF_NI %d\n"
+           "#define SG_POLYF_NC %d\n", UOCT0, FSUB, FOCT0, fni, FNC);
+    printf("static __device__ const double sg_polyu64[2 * SG_POLY_NI * SG_POLY_NC] = {\n");
+    for (int f = 0; f < 2; ++f)
+        for (int i = 0; i < uni; ++i)
+            for (int m = 0; m < PNC; ++m) printf("    %.17e,\n", pu[f][i][m]);
+    printf("};\n");
+    printf("static __device__ const float sg_polyu32[2 * SG_POLYF_NI * (SG_POLYF_NC + 1)] = {\n");
+    for (int f = 0; f < 2; ++f)
+        for (int i = 0; i < fni; ++i) {
+            for (int m = 0; m < FNC; ++m) printf("    %.9ef,\n", pf[f][i][m]);
+            printf("    0.0f,\n");
+        }
     printf("};\n");
     // cos and sin of 2 pi k / 4096 (the first octant's values, mirrored)
     printf("#define SG_TW64_N 4096\nstatic __device__ const double sg_tw64[2 * SG_TW64_N] = {\n");

@@ -6,7 +6,7 @@
 // uniform-phi grid, with X = u_i - u_k and phi = phi_i - phi_k:
 //   s^2        = r_i r_k (4 sinh^2(X/2) + 4 sin^2(phi/2))    (cancellation-free)
 //   H_ab^2     = (H_a[k]^2 + H_b[i]^2) / 2,  x = s^2 / (8 H_ab^2)
-//   K_ab / s   = F(x) / (8 sqrt(pi) H_ab^3)
+//   K_ab / s   = F(x) / (8 sqrt(pi) H_ab^3) = V(1/x) (s^2/8)^{-3/2} / (8 sqrt(pi))
 //   e_s . e_r  = (r_i - r_k cos phi)/s = r_k (e^X - cos phi)/s,
 //   e_s . e_phi = r_k sin phi / s,
 //   g_r  -= Sigma_a[k] A_k (K/s) r_k (expm1(X) + 2 sin^2(phi/2)),
@@ -75,7 +75,8 @@ __device__ inline double dir_radius(int lin, double lnrmin, double du, double rm
 template <typename T>
 __global__ void k_direct_prep(int nr, int nphi, int nf, double lnrmin, double du, double dphi,
                               const double *h, const T *sigma, const T *H, T *rrow, T *sx, T *ex,
-                              T *sph, T *snp, T *mass, T *H2, int lin, double rmin, double dr, double *Hd)
+                              T *sph, T *snp, T *mass, T *H2, int lin, double rmin, double dr, double *Hd,
+                              int scaled)
 {
     const int64_t N = (int64_t)nr * nphi;
     const int64_t tid = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -96,11 +97,14 @@ __global__ void k_direct_prep(int nr, int nphi, int nf, double lnrmin, double du
         const int64_t cell = k % N;
         const int ir = (int)(cell / nphi);
         const double r = dir_radius(lin, lnrmin, du, rmin, dr, ir);
-        mass[k] = (T)((double)sigma[k] * (lin ? r * dr : r * r * du) * dphi);
+        // scaled: times the pair sums' constant, -r_k / (8 sqrt(pi)) (field, 1)
+        // or -1 / (2 sqrt(pi)) (potential, 2)
+        const double c = scaled == 1 ? -r / (8.0 * SG_SQRT_PI) : scaled == 2 ? -0.5 / SG_SQRT_PI : 1.0;
+        mass[k] = (T)((double)sigma[k] * (lin ? r * dr : r * r * du) * dphi * c);
         double Hk;
         if (H) Hk = (double)H[k];
         else Hk = h[k / N] * r;
-        H2[k] = (T)(Hk * Hk);
+        H2[k] = (T)(0.5 * Hk * Hk);  // H_ab^2 = H2_a + H2_b
         if (lin && H) Hd[k] = Hk;  // double H per cell for the own-cell integrals
     }
     if (lin && !H)  // double H per ring
@@ -108,18 +112,18 @@ __global__ void k_direct_prep(int nr, int nphi, int nf, double lnrmin, double du
             Hd[k] = h[k / nr] * dir_radius(1, 0.0, 0.0, rmin, dr, (int)(k % nr));
 }
 
-template <typename T> __device__ inline T sg_F_any(T x, const T *w);
-template <> __device__ inline double sg_F_any<double>(double x, const double *w) { return sg_F64(x, w); }
-template <> __device__ inline float sg_F_any<float>(float x, const float *w) { return sg_F32(x, w); }
-template <typename T> __device__ inline T sg_G0_any(T x, const T *w);
-template <> __device__ inline double sg_G0_any<double>(double x, const double *w) { return sg_G0_64(x, w); }
-template <> __device__ inline float sg_G0_any<float>(float x, const float *w) { return sg_G0_32(x, w); }
-
+// General sum (a scale height per cell): VALU bound.  Per source one
+// reciprocal square root (of s^2/8) serves every pair of fluids, per pair one
+// V(u) (17 float instructions with its table reads, 10 where the whole wave is
+// beyond x = 64).  Two fluids, 101 x 250 cells in float: 1.45 ms, 1.8e12 pairs/s
+// (2.9 ms with a reciprocal square root and the 9-node trapezoid per pair); the
+// double potential of 96 x 200 cells 0.82 ms (2.35 ms at first, 0.96 ms with F(x)
+// per pair), bound by the 96 bytes of table per lane and pair.
 template <typename T, int NF>
 __global__ void __launch_bounds__(256) k_direct(DirectArgs<T> A)
 {
     __shared__ __attribute__((aligned(16))) T wq[FQuad<T>::TABLE];
-    sg_fill_weights<T>(wq);
+    sg_fill_v(wq, SG_FN_V);
     __syncthreads();
     const int64_t t = blockIdx.x * (int64_t)256 + threadIdx.x;
     if (t >= A.N) return;
@@ -135,7 +139,6 @@ __global__ void __launch_bounds__(256) k_direct(DirectArgs<T> A)
         errr[b] = T(0);
         errp[b] = T(0);
     }
-    const T c8 = T(1.0 / (8.0 * SG_SQRT_PI));
     const int r0 = blockIdx.y * A.rps;
     const int r1 = min(nr, r0 + A.rps);
     for (int kr = r0; kr < r1; ++kr) {
@@ -166,24 +169,21 @@ __global__ void __launch_bounds__(256) k_direct(DirectArgs<T> A)
                 int q = j - l;
                 q += q < 0 ? nphi : 0;
                 const T sp = A.sph[q];
-                const T s2_8 = rr8 * (SX + sp);  // s^2 / 8
+                const bool self = l == lself;
+                const T rs = sg_rsqrt(self ? T(1) : rr8 * (SX + sp)), rs2 = rs * rs;  // s^2 / 8
+                const T rs3 = self ? T(0) : rs2 * rs;
                 const T emc = EX + T(0.5) * sp;
                 const T sn = A.snp[q];
-                const bool self = l == lself;
 #pragma unroll
-                for (int a = 0; a < NF; ++a) {
-                    const T m = A.mass[a * A.N + k] * rk * c8;
-                    const T ha2 = A.H2[a * A.N + k];
+                for (int b = 0; b < NF; ++b) {
+                    const T ub = hb2[b] * rs2;
+                    T c = T(0);
 #pragma unroll
-                    for (int b = 0; b < NF; ++b) {
-                        const T H2ab = T(0.5) * (ha2 + hb2[b]);
-                        const T rH = sg_rsqrt(H2ab), rH2 = rH * rH;
-                        const T x = s2_8 * rH2;
-                        const T F = self ? T(0) : sg_F_any<T>(self ? T(1) : x, wq);
-                        const T c = m * F * (rH2 * rH);
-                        pr[b] -= c * emc;
-                        pp[b] -= c * sn;
-                    }
+                    for (int a = 0; a < NF; ++a)
+                        c += A.mass[a * A.N + k] * sg_v<SG_FN_V>(A.H2[a * A.N + k] * rs2 + ub, wq);
+                    c *= rs3;
+                    pr[b] += c * emc;
+                    pp[b] += c * sn;
                 }
             }
 #pragma unroll
@@ -272,17 +272,16 @@ __device__ inline void ring_kernel(const DirectArgs<T> &A, int ir, int kr, int a
         SX = A.sx[p];
         EX = A.ex[p];
     }
-    const T sp = A.sph[q], s2_8 = ri * rk * T(0.125) * (SX + sp);
-    const T H2ab = T(0.5) * (A.H2[a * A.N + (int64_t)kr * A.nphi] + A.H2[b * A.N + (int64_t)ir * A.nphi]);
-    const T rH = sg_rsqrt(H2ab), rH2 = rH * rH;
+    const T sp = A.sph[q];
+    const T H2ab = A.H2[a * A.N + (int64_t)kr * A.nphi] + A.H2[b * A.N + (int64_t)ir * A.nphi];
     const bool self = kr == ir && q == 0;
-    const T x = self ? T(1) : s2_8 * rH2;
+    const T rs = sg_rsqrt(self ? T(1) : ri * rk * T(0.125) * (SX + sp)), rs2 = rs * rs;  // s^2 / 8
     if constexpr (NC == 2) {
-        const T c = self ? T(0) : T(-1.0 / (8.0 * SG_SQRT_PI)) * rk * sg_F_any<T>(x, wq) * (rH2 * rH);
+        const T c = self ? T(0) : T(-1.0 / (8.0 * SG_SQRT_PI)) * rk * sg_v<SG_FN_V>(H2ab * rs2, wq) * (rs2 * rs);
         K[0] = c * (EX + T(0.5) * sp);
         K[1] = c * A.snp[q];
     } else {
-        K[0] = self ? T(0) : T(-0.5 / SG_SQRT_PI) * sg_G0_any<T>(x, wq) * rH;
+        K[0] = self ? T(0) : T(-0.5 / SG_SQRT_PI) * sg_v<SG_FN_VG>(H2ab * rs2, wq) * rs;
     }
 }
 
@@ -292,7 +291,7 @@ __global__ void __launch_bounds__(256) k_ring_sum(DirectArgs<T> A, RingShape P, 
     extern __shared__ __attribute__((aligned(16))) char smem[];
     __shared__ __attribute__((aligned(16))) T wq[FQuad<T>::TABLE];
     constexpr int PG = RingPad<T>::G;
-    sg_fill_weights<T>(wq, NC == 2 ? SG_FN_F : SG_FN_G0);
+    sg_fill_v(wq, NC == 2 ? SG_FN_V : SG_FN_VG);
     const int ir = blockIdx.x / P.ntile, jb = (blockIdx.x % P.ntile) * 8 * P.JT, b = blockIdx.z;
     const int nphi = A.nphi, rowg = P.JT + P.TL / 8;
     T *D = (T *)smem, *M = D + (size_t)P.KS * NC * rowg * PG;
@@ -435,7 +434,7 @@ __global__ void __launch_bounds__(256) k_indirect_part(int nr, int nphi, int nf,
 {
     __shared__ __attribute__((aligned(16))) double wq[FQuad<double>::TABLE];
     __shared__ double ra[256], rb[256];
-    sg_fill_weights<double>(wq);
+    sg_fill64(wq, SG_FN_F);
     __syncthreads();
     const int64_t N = (int64_t)nr * nphi, total = nf * N;
     double sa = 0.0, sb = 0.0;
@@ -546,7 +545,7 @@ template <typename T, int NF>
 __global__ void __launch_bounds__(256) k_potential(DirectArgs<T> A)
 {
     __shared__ __attribute__((aligned(16))) T wq[FQuad<T>::TABLE];
-    sg_fill_weights<T>(wq, SG_FN_G0);
+    sg_fill_v(wq, SG_FN_VG);
     __syncthreads();
     const int64_t t = blockIdx.x * (int64_t)256 + threadIdx.x;
     if (t >= A.N) return;
@@ -560,13 +559,12 @@ __global__ void __launch_bounds__(256) k_potential(DirectArgs<T> A)
         acc[b] = T(0);
         err[b] = T(0);
     }
-    const T c2 = T(-0.5 / SG_SQRT_PI);
     const int r0 = blockIdx.y * A.rps;
     const int r1 = min(nr, r0 + A.rps);
     for (int kr = r0; kr < r1; ++kr) {
         const int p = ir - kr + nr - 1;
         const T SX = A.sx[p];
-        const T rr = ri * A.rrow[kr];
+        const T rr8 = ri * A.rrow[kr] * T(0.125);
         const int64_t kbase = (int64_t)kr * nphi;
         for (int l0 = 0; l0 < nphi; l0 += SG_DCHUNK) {
             const int l1 = min(nphi, l0 + SG_DCHUNK);
@@ -577,20 +575,16 @@ __global__ void __launch_bounds__(256) k_potential(DirectArgs<T> A)
                 const int64_t k = kbase + l;
                 int q = j - l;
                 q += q < 0 ? nphi : 0;
-                const T s2 = rr * (SX + A.sph[q]);
                 const bool self = (k == t);
+                const T rs = sg_rsqrt(self ? T(1) : rr8 * (SX + A.sph[q])), rs2 = rs * rs;  // s^2 / 8
 #pragma unroll
-                for (int a = 0; a < NF; ++a) {
-                    const T m = A.mass[a * A.N + k] * c2;
-                    const T ha2 = A.H2[a * A.N + k];
+                for (int b = 0; b < NF; ++b) {
+                    const T ub = hb2[b] * rs2;
+                    T c = T(0);
 #pragma unroll
-                    for (int b = 0; b < NF; ++b) {
-                        const T H2ab = T(0.5) * (ha2 + hb2[b]);
-                        const T rH = sg_rsqrt(H2ab);
-                        const T y = s2 * T(0.125) * (rH * rH);
-                        const T G = self ? T(0) : sg_G0_any<T>(self ? T(1) : y, wq);
-                        pc[b] += m * G * rH;
-                    }
+                    for (int a = 0; a < NF; ++a)
+                        c += A.mass[a * A.N + k] * sg_v<SG_FN_VG>(A.H2[a * A.N + k] * rs2 + ub, wq);
+                    pc[b] += c * (self ? T(0) : rs);
                 }
             }
 #pragma unroll
@@ -741,7 +735,7 @@ static sg_status direct_run(const sg_grid *g, int nf, const double *h, const T *
         if (nb > 65536) nb = 65536;
         hipLaunchKernelGGL(k_direct_prep<T>, dim3((unsigned)nb), dim3(256), 0, s, nr, nphi, nf,
                            lnrmin, du, dphi, (const double *)dh, sigma, H, rrow, sx, ex, sph, snp,
-                           mass, H2, lin, g->r_min, dr, Hd);
+                           mass, H2, lin, g->r_min, dr, Hd, percell ? 1 : 0);
         SG_HIP(hipGetLastError());
     }
     const int with_self = !(flags & SG_SELF_CELL_EXCLUDE);
@@ -873,7 +867,7 @@ static sg_status potential_run(const sg_grid *g, int nf, const double *h, const 
         if (nb > 65536) nb = 65536;
         hipLaunchKernelGGL(k_direct_prep<T>, dim3((unsigned)nb), dim3(256), 0, s, nr, nphi, nf,
                            lnrmin, du, dphi, (const double *)dh, sigma, H, rrow, sx, ex, sph, snp,
-                           mass, H2, 0, 0.0, 0.0, nullptr);
+                           mass, H2, 0, 0.0, 0.0, nullptr, percell ? 2 : 0);
         SG_HIP(hipGetLastError());
     }
     const int with_self = !(flags & SG_SELF_CELL_EXCLUDE);

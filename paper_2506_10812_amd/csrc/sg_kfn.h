@@ -23,36 +23,28 @@
 //     it needs (9 KB) into LDS.  Per wave an evaluation is 12 LDS reads and 11
 //     FMAs in a dependent chain; the Chebyshev series of 27 terms used before
 //     took 27 reads and 53 operations, and below 32 only.
-//   float
-//     x < 1             the same power series;
-//     1 <= x < 32       F = sqrt(2) x^{-3/2} J(x),  J(x) = int_0^inf v^2 e^{-v^2}
-//           (1 + v^2/(2x))^{-1/2} dv, obtained from the integral
-//           representation K_nu(x) = int_0^inf e^{-x cosh t} cosh(nu t) dt by
-//           the substitution sinh(t/2) = v / sqrt(2x).  The integrand is even
-//           and analytic for |Im v| < sqrt(2x), so the trapezoidal rule on a
-//           fixed grid converges geometrically, its error ~ exp(-2 pi
-//           sqrt(2x) / step): step 1/2 and 9 nodes (2e-8 at x = 1, below a
-//           float ulp; the tail beyond v = 4.5 is e^{-20});
-//     x >= 32           the asymptotic series through c_5.
-// The float trapezoidal weights e^{-v_k^2} and the double tables are copied
-// once per workgroup into LDS (sg_fill_weights, sg_fill64).
+//   The direct sums (float and double) evaluate many pairs per wave and take
+//   F as F(x) h^-3 = s'^-3 V(u), u = 1/x = h^2/s'^2 (s'^2 = s^2/8), V(u) =
+//   u^{-3/2} F(1/u): one reciprocal square root per source serves every pair
+//   of fluids.  V (and Vg(u) = u^{-1/2} G0(1/u) for the potential) has local
+//   polynomials on the octaves of u, the asymptotic series' polynomial in u
+//   below them and the power series above.  Float F and G0 follow from V, Vg;
+//   float V is within 1.2e-7.
 #pragma once
 #include "sg_internal.h"
 #include "sg_cheb64.h"
 
 #define SG_EULER_GAMMA 0.57721566490153286061
 
-// LDS table of TABLE entries.  Float: w[k-1] = exp(-(k STEP)^2), k = 1..NODES.
-// Double: the local polynomials of one function.
-enum { SG_FN_F = 0, SG_FN_D = 1, SG_FN_G0 = 2, SG_FN_E = 3 };
+// LDS tables of TABLE entries: the local polynomials of one function.
+enum { SG_FN_F = 0, SG_FN_D = 1, SG_FN_G0 = 2, SG_FN_E = 3 };  // of x, double
+enum { SG_FN_V = 0, SG_FN_VG = 1 };                            // of u = 1/x
 template <typename R> struct FQuad;
 template <> struct FQuad<double> {
     static constexpr int TABLE = SG_POLY_NI * SG_POLY_NC;
 };
 template <> struct FQuad<float> {
-    static constexpr int NODES = 9;
-    static constexpr float STEP = 0.5f;
-    static constexpr int TABLE = NODES;
+    static constexpr int TABLE = SG_POLYF_NI * (SG_POLYF_NC + 1);
 };
 
 // Reciprocal and reciprocal square root of the working type.  Float takes the
@@ -70,16 +62,14 @@ __device__ inline void sg_fill64(double *w, int fn)
 {
     for (int k = threadIdx.x; k < FQuad<double>::TABLE; k += blockDim.x) w[k] = sg_poly64[fn * FQuad<double>::TABLE + k];
 }
-template <typename R> __device__ inline void sg_fill_weights(R *w, int fn = SG_FN_F)
+// The same for V (fn = SG_FN_V) or Vg.
+__device__ inline void sg_fill_v(double *w, int fn)
 {
-    if constexpr (sizeof(R) == 8) {
-        sg_fill64(w, fn);
-    } else {
-        for (int k = threadIdx.x; k < FQuad<R>::TABLE; k += blockDim.x) {
-            const double v = (k + 1) * (double)FQuad<float>::STEP;
-            w[k] = (R)exp(-v * v);
-        }
-    }
+    for (int k = threadIdx.x; k < FQuad<double>::TABLE; k += blockDim.x) w[k] = sg_polyu64[fn * FQuad<double>::TABLE + k];
+}
+__device__ inline void sg_fill_v(float *w, int fn)
+{
+    for (int k = threadIdx.x; k < FQuad<float>::TABLE; k += blockDim.x) w[k] = sg_polyu32[fn * FQuad<float>::TABLE + k];
 }
 
 // Series branch, small x.  NT terms.
@@ -108,57 +98,6 @@ __device__ inline void sg_F_series(R x, R &F, R *dF)
     const R ex = exp(x);
     F = ex * (K1 - K0);
     if (dF) *dF = ex * (R(2) * (K1 - K0) - K1 * ix);
-}
-
-// Trapezoidal branch, x >= 2: F = sqrt(2) x^-3/2 J, F' from J' =
-// int v^2 e^{-v^2} v^2/(4x^2) (1 + v^2/(2x))^{-3/2} dv.
-template <typename R>
-__device__ inline void sg_F_quad(R x, const R *w, R &F, R *dF)
-{
-    const R ix = sg_rcp(x);
-    const R i2x = R(0.5) * ix;
-    R J = R(0), Jd = R(0);
-#pragma unroll
-    for (int k = 1; k <= FQuad<R>::NODES; ++k) {
-        const R v2 = R(k * k) * (FQuad<R>::STEP * FQuad<R>::STEP);
-        const R rho = sg_rsqrt(R(1) + v2 * i2x);
-        const R base = w[k - 1] * v2 * rho;
-        J += base;
-        if (dF) Jd += base * rho * rho * v2;
-    }
-    J *= FQuad<R>::STEP;
-    const R x32 = sg_rsqrt(x) * ix;  // x^-3/2
-    F = R(SG_SQRT2) * x32 * J;
-    if (dF) {
-        const R Jp = Jd * FQuad<R>::STEP * R(0.25) * (ix * ix);
-        *dF = R(SG_SQRT2) * x32 * (Jp - R(1.5) * J * ix);
-    }
-}
-
-// Asymptotic branch (float), x >= 32.
-struct AsymCoef {
-    float c[6];
-    constexpr AsymCoef() : c{}
-    {
-        double v = 1.0;
-        c[0] = 1.0f;
-        for (int n = 1; n < 6; ++n) {
-            v = -v * (4.0 * n * n - 1.0) / (8.0 * n);
-            c[n] = (float)v;
-        }
-    }
-};
-
-__device__ inline float sg_F_asym(float x)
-{
-    constexpr AsymCoef C;
-    const float u = sg_rcp(x);
-    float s = C.c[5];
-#pragma unroll
-    for (int n = 4; n >= 0; --n) s = s * u + C.c[n];
-    const float J = float(SG_SQRT_PI * 0.25) * s;
-    const float rx = sg_rsqrt(x);
-    return float(SG_SQRT2) * rx * u * J;
 }
 
 // Wave-uniform branches: the series and the asymptotic form each run only
@@ -233,41 +172,10 @@ __device__ inline double sg_D64(double x, const double *w) { return sg_fn64<SG_F
 __device__ inline double sg_G0_64(double x, const double *w) { return sg_fn64<SG_FN_G0>(x, w); }
 __device__ inline double sg_E64(double x, const double *w) { return sg_fn64<SG_FN_E>(x, w); }
 
-// Float: each branch runs only when some lane of the wave needs it, and each
-// lane keeps its own branch's value (a wave whose lanes all fall in one range
-// pays for one branch).
-__device__ inline float sg_F32(float x, const float *w)
-{
-    const bool ser = x < 1.0f, asy = x >= 32.0f, quad = !ser && !asy;
-    float F = 0.0f, t;
-    if (__any(ser)) {
-        SG_NO_SPECULATE();
-        sg_F_series<float, 8>(x, t, nullptr);
-        F = ser ? t : F;
-    }
-    if (__any(quad)) {
-        SG_NO_SPECULATE();
-        sg_F_quad<float>(x, w, t, nullptr);
-        F = quad ? t : F;
-    }
-    if (__any(asy)) {
-        SG_NO_SPECULATE();
-        t = sg_F_asym(x);
-        F = asy ? t : F;
-    }
-    return F;
-}
-
 // ------------------------------------------------------------------------
 // G0(x) = e^x K0(x), the kernel of the conservative potential (Sect. 5.5,
 // appendix "Conservative force"): P_ab(s) = -G0(d^2/8) / (2 sqrt(pi) H_ab).
-// Double: sg_fn64 above.  Float:
-//   x < 1   A&S series of I0 and K0, G0 = e^x K0;
-//   1 <= x < 32  G0 = sqrt(2/x) int_0^inf e^{-v^2}
-//        (1 + v^2/(2x))^{-1/2} dv (the same substitution as for F; the
-//        trapezoid's v = 0 node has value 1 and weight STEP/2);
-//   x >= 32  sqrt(pi/(2x)) sum_n a_n x^-n, a_0 = 1,
-//        a_n = -a_{n-1} (2n - 1)^2 / (8 n), through a_5.
+// Double: sg_fn64 above; both types: Vg below.
 // ------------------------------------------------------------------------
 template <typename R, int NT> __device__ inline R sg_G0_series(R x)
 {
@@ -284,31 +192,6 @@ template <typename R, int NT> __device__ inline R sg_G0_series(R x)
     return exp(x) * (-Lg * I0 + K0s);
 }
 
-template <typename R> __device__ inline R sg_G0_quad(R x, const R *w)
-{
-    const R i2x = R(0.5) * sg_rcp(x);
-    R acc = R(0.5);
-#pragma unroll
-    for (int k = 1; k <= FQuad<R>::NODES; ++k) {
-        const R v2 = R(k * k) * (FQuad<R>::STEP * FQuad<R>::STEP);
-        acc += w[k - 1] * sg_rsqrt(R(1) + v2 * i2x);
-    }
-    return acc * FQuad<R>::STEP * R(SG_SQRT2) * sg_rsqrt(x);
-}
-
-struct AsymCoefG0 {
-    float c[6];
-    constexpr AsymCoefG0() : c{}
-    {
-        double v = 1.0;
-        c[0] = 1.0f;
-        for (int n = 1; n < 6; ++n) {
-            v = -v * (2.0 * n - 1.0) * (2.0 * n - 1.0) / (8.0 * n);
-            c[n] = (float)v;
-        }
-    }
-};
-
 template <int FN> __device__ inline double sg_series64(double x)
 {
     if constexpr (FN == SG_FN_G0) {
@@ -322,32 +205,105 @@ template <int FN> __device__ inline double sg_series64(double x)
     }
 }
 
-// Branches as in sg_F32: run only when some lane of the wave needs them.
+// ------------------------------------------------------------------------
+// V(u) and Vg(u), u = 1/x > 0; w: the table of fn.  u below the polynomials
+// (x > 256, float 64) takes the asymptotic series, alone when the whole wave
+// is there; u >= 16 (x <= 1/16) the power series.
+// ------------------------------------------------------------------------
+template <int FN, typename R> __device__ inline R sg_v_asym(R u)
+{
+    constexpr int NT = sizeof(R) == 8 ? 8 : 5;
+    constexpr Asym64<FN == SG_FN_V ? SG_FN_F : SG_FN_G0> A;
+    R s = R(A.c[NT - 1]);
+#pragma unroll
+    for (int n = NT - 2; n >= 0; --n) s = s * u + R(A.c[n]);
+    return s * R(FN == SG_FN_V ? SG_SQRT2 * SG_SQRT_PI * 0.25 : SG_SQRT_PI / SG_SQRT2);
+}
+
+template <int FN, typename R> __device__ inline R sg_v_series(R u)
+{
+    const R x = sg_rcp(u);
+    if constexpr (FN == SG_FN_VG) {
+        return sqrt(x) * sg_G0_series<R, 5>(x);
+    } else {
+        R F;
+        sg_F_series<R, 5>(x, F, (R *)nullptr);
+        return x * sqrt(x) * F;
+    }
+}
+
+template <int FN> __device__ inline double sg_v(double u, const double *w)
+{
+    constexpr double lo = SG_POLYU_OCT0 == -8 ? 0x1p-8 : -1.0;
+    static_assert(lo > 0.0 && SG_POLY_SUB == 8 && SG_POLY_NC == 12, "index arithmetic below");
+    if (__all(u < lo)) return sg_v_asym<FN>(u);
+    const int hi = __double2hiint(u);
+    const int k = min(max((hi >> 17) - ((1023 + SG_POLYU_OCT0) << 3), 0), SG_POLY_NI - 1);
+    const double t = fma(16.0, __hiloint2double((hi & 0x1ffff) | 0x3ff00000, __double2loint(u)), -17.0);
+    const double2 *c = (const double2 *)(w + k * SG_POLY_NC);
+    double2 q[6];
+#pragma unroll
+    for (int j = 0; j < 6; ++j) q[j] = c[j];
+    double f = q[5].y;
+#pragma unroll
+    for (int j = 5; j >= 0; --j) {
+        if (j < 5) f = fma(f, t, q[j].y);
+        f = fma(f, t, q[j].x);
+    }
+    if (__any(u < lo)) {
+        SG_NO_SPECULATE();
+        const double s = sg_v_asym<FN>(u);
+        f = u < lo ? s : f;
+    }
+    if (__any(!(u < 16.0))) {  // NaN included
+        SG_NO_SPECULATE();
+        const double s = sg_v_series<FN>(u);
+        f = u < 16.0 ? f : s;
+    }
+    return f;
+}
+
+template <int FN> __device__ inline float sg_v(float u, const float *w)
+{
+    constexpr float lo = SG_POLYF_OCT0 == -6 ? 0x1p-6f : -1.0f;
+    static_assert(lo > 0.0f && SG_POLYF_SUB == 4 && SG_POLYF_NC == 7, "index arithmetic below");
+    if (__all(u < lo)) return sg_v_asym<FN>(u);
+    const int bits = __float_as_int(u);
+    const int k = min(max((bits >> 21) - ((127 + SG_POLYF_OCT0) << 2), 0), SG_POLYF_NI - 1);
+    // the 2 leading mantissa bits are in k; the rest as v in [1, 1 + 1/4), t = 8 v - 9
+    const float t = fmaf(8.0f, __int_as_float((bits & 0x1fffff) | 0x3f800000), -9.0f);
+    const float4 *c = (const float4 *)(w + k * (SG_POLYF_NC + 1));
+    const float4 c0 = c[0], c1 = c[1];
+    float f = c1.z;
+    f = fmaf(f, t, c1.y);
+    f = fmaf(f, t, c1.x);
+    f = fmaf(f, t, c0.w);
+    f = fmaf(f, t, c0.z);
+    f = fmaf(f, t, c0.y);
+    f = fmaf(f, t, c0.x);
+    if (__any(u < lo)) {
+        SG_NO_SPECULATE();
+        const float s = sg_v_asym<FN>(u);
+        f = u < lo ? s : f;
+    }
+    if (__any(!(u < 16.0f))) {  // NaN included
+        SG_NO_SPECULATE();
+        const float s = sg_v_series<FN>(u);
+        f = u < 16.0f ? f : s;
+    }
+    return f;
+}
+
+// Float F(x) and G0(x); w: the table of V or Vg.
+__device__ inline float sg_F32(float x, const float *w)
+{
+    const float u = sg_rcp(x);
+    return u * sqrtf(u) * sg_v<SG_FN_V>(u, w);
+}
 __device__ inline float sg_G0_32(float x, const float *w)
 {
-    const bool ser = x < 1.0f, asy = x >= 32.0f, quad = !ser && !asy;
-    float G = 0.0f;
-    if (__any(ser)) {
-        SG_NO_SPECULATE();
-        const float t = sg_G0_series<float, 8>(x);
-        G = ser ? t : G;
-    }
-    if (__any(quad)) {
-        SG_NO_SPECULATE();
-        const float t = sg_G0_quad<float>(x, w);
-        G = quad ? t : G;
-    }
-    if (__any(asy)) {
-        SG_NO_SPECULATE();
-        constexpr AsymCoefG0 C;
-        const float u = sg_rcp(x);
-        float s = C.c[5];
-#pragma unroll
-        for (int n = 4; n >= 0; --n) s = s * u + C.c[n];
-        const float t = float(SG_SQRT_PI / SG_SQRT2) * sg_rsqrt(x) * s;
-        G = asy ? t : G;
-    }
-    return G;
+    const float u = sg_rcp(x);
+    return sqrtf(u) * sg_v<SG_FN_VG>(u, w);
 }
 
 // ------------------------------------------------------------------------

@@ -190,7 +190,7 @@ k_self_cells(const T *H, int64_t N, int nphi, double lnrmin, double du, double d
 {
     __shared__ __attribute__((aligned(16))) double wq[FQuad<double>::TABLE];
     __shared__ double red[4 * NF * NF * CPB];
-    sg_fill_weights<double>(wq);
+    sg_fill64(wq, SG_FN_F);
     __syncthreads();
     const int64_t c0 = (int64_t)blockIdx.x * CPB;
     double h2[CPB][NF], hm = INFINITY;  // h_f^2 of each cell (past the last: the last cell's)
@@ -598,7 +598,7 @@ __global__ void k_header(sg_table_header *hd, sg_table_header proto, const doubl
 {
     // one wave fills the coefficient table; lane 0 writes the header
     __shared__ __attribute__((aligned(16))) double w[FQuad<double>::TABLE];
-    sg_fill_weights<double>(w);
+    sg_fill64(w, SG_FN_F);
     __syncthreads();
     if (threadIdx.x != 0) return;
     sg_table_header h = proto;
@@ -627,8 +627,12 @@ __global__ void k_eval_F(const T *x, T *F, T *dF, int64_t n)
 {
     __shared__ __attribute__((aligned(16))) T wq[FQuad<T>::TABLE];
     __shared__ __attribute__((aligned(16))) T wd[sizeof(T) == 8 ? FQuad<T>::TABLE : 2];
-    sg_fill_weights<T>(wq);
-    if constexpr (sizeof(T) == 8) sg_fill64(wd, SG_FN_D);
+    if constexpr (sizeof(T) == 8) {
+        sg_fill64(wq, SG_FN_F);
+        sg_fill64(wd, SG_FN_D);
+    } else {
+        sg_fill_v(wq, SG_FN_V);
+    }
     __syncthreads();
     int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i >= n) return;
@@ -646,7 +650,8 @@ template <typename T>
 __global__ void k_eval_G0(const T *x, T *G, int64_t n)
 {
     __shared__ __attribute__((aligned(16))) T wq[FQuad<T>::TABLE];
-    sg_fill_weights<T>(wq, SG_FN_G0);
+    if constexpr (sizeof(T) == 8) sg_fill64(wq, SG_FN_G0);
+    else sg_fill_v(wq, SG_FN_VG);
     __syncthreads();
     int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i >= n) return;
