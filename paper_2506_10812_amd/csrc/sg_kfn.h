@@ -405,6 +405,20 @@ __device__ inline ConvRowDh64 sg_conv_row64_dh(double X, double ha, double hb)
     return c;
 }
 
+// The row of one of K, dK/dh_a, dK/dh_b (which = 0, 1, 2): K_r = fn(x) pref
+// (e^X - cos phi) with fn = F or D.
+__device__ inline ConvRow64 sg_conv_row64(double X, double ha, double hb, int which)
+{
+    if (which == 0) return sg_conv_row64(X, ha, hb);
+    const ConvRowDh64 d = sg_conv_row64_dh(X, ha, hb);
+    ConvRow64 c;
+    c.two_sxh2 = d.two_sxh2;
+    c.em1 = d.em1;
+    c.inv4h2 = d.inv4h2;
+    c.pref = which == 1 ? d.p1 : d.p2;
+    return c;
+}
+
 __device__ inline void sg_conv_kernel64_dh(const ConvRowDh64 &c, double sphi_half, double sphi, const double *w,
                                            double &Kr1, double &Kp1, double &Kr2, double &Kp2)
 {

@@ -2,6 +2,11 @@
 #pragma once
 #include "sg_passes.h"
 
+// Fewest samples that give a kernel row's modes: M azimuths with M |X| >=
+// SG_SS_ALIAS, a power of two of at least SG_SS_MIN_M (see k_ss_rows).
+#define SG_SS_ALIAS 80.0
+#define SG_SS_MIN_M 128
+
 // Middle pass of a semi-spectral disc (replaces pass 2 of the FFT path):
 // fn has the pass-kernel signature; a workgroup of wgs threads takes one job
 // (column m, target fluid b, block of tb target rows) and needs

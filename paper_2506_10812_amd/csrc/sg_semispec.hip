@@ -94,9 +94,7 @@ struct SsRowArgs {
 // rows of a unit are consecutive entries of a diagonal in the banded modes'
 // layout, and the units of one tile lie together for the full modes' (the
 // scatter goes through them in that order).
-#define SG_SS_ALIAS 80.0
 #define SG_SS_ALIAS_GRAD 96.0  // h derivatives have double poles at phi = +-i X
-#define SG_SS_MIN_M 128
 #define SG_SS_TI 16
 
 struct SsClass {

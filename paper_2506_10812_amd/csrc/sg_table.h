@@ -8,6 +8,7 @@
 #define SG_GLT_N 24         // Gauss-Legendre order of the graded xi rule (xi = t^4)
 #define SG_OWN_RMAX 8.0     // largest (half cell side) / H of the graded rule
 #define SG_SELF_MAX 64      // items per self-cell launch
+#define SG_SELF_PARTS 4     // blocks per own-cell item of a table build
 
 // Nodes of the own-cell rules.  eta: order ne, chosen from the cell's aspect
 // ratio.  xi: the graded rule (tx, tw), or the panel rule (xr, wr per panel).

@@ -7,18 +7,28 @@
 // Sect. 5.2: zero padding of the radial axis to 2 n_r makes the periodic
 // convolution equal the aperiodic one, and the kernel is computed once.
 // Steps (all double precision):
-//   1. sample K_r + i K_phi on the wrapped offset grid X = p du
-//      (p in (-n_r, n_r), stored at p mod 2 n_r; row n_r is zero), phi = q dphi;
-//      offset (0,0) holds the self-cell average (SG_SECOND_ORDER: every entry,
-//      (0,0) included, is the hat-weighted integral of the kernel instead);
-//   2. phi transform of each row, split into the spectra of K_r and K_phi
-//      (two real rows in one complex transform);
-//   3. u transform (length 2 n_r) of each column m <= n_phi/2, keep
-//      k_u <= n_r (K_r is Hermitian and K_phi anti-Hermitian in k_u because
-//      K_r is even and K_phi odd in phi), scale by -du dphi/(2 n_r n_phi),
-//      round to float.
+//   1. rows X = p du (p in (-n_r, n_r), stored at p mod 2 n_r; row n_r is
+//      zero): samples K_r + i K_phi at phi = q dphi, q <= n_phi/2, mirrored
+//      (K_r even, K_phi odd), and their phi transform, which is real: T_r(m)
+//      and t_phi(m), K_phi's being i t_phi.  Two rows share one transform, and
+//      a row takes only as many azimuths as it resolves (its modes fall off
+//      as e^{-m|X|}; see SG_SS_ALIAS in sg_semispec.h).  SG_SECOND_ORDER:
+//      every sample is the hat-weighted integral of the kernel instead;
+//   2. u transform (length 2 n_r) of each column m of T_r + i t_phi (both
+//      real), split into K_r and K_phi; the own-cell average (offset (0,0), a
+//      flat spectrum in phi) joins T_r at p = 0 here; keep k_u <= n_r (K_r is
+//      Hermitian and K_phi anti-Hermitian in k_u because K_r is even and K_phi
+//      odd in phi), scale by -du dphi/(2 n_r n_phi), round to float.
+// Four launches for up to SG_TAB_ITEMS pairs: own-cell integrals and twiddles
+// (9 us), rows (17 us), columns (36 us), header (4 us) on the two-fluid 1024 x
+// 2048 disc, bound by the columns' FP64 transforms; one sampling, one phi and
+// two u launches per pair on the full grid took 700 us.
+#include <algorithm>
+#include <vector>
+
 #include "sg_fft.h"
 #include "sg_kfn.h"
+#include "sg_semispec.h"
 #include "sg_table.h"
 #include "sg_hat.h"
 
@@ -118,19 +128,20 @@ __device__ inline double block_sum256(double v, double *red)
 
 #define SG_OWN_SCALE (1.0 / (8.0 * SG_SQRT_PI))
 
-// This thread's part of one item (pair h_a, h_b; which as above).
+// Nodes k0, k0 + dk, ... of one item (pair h_a, h_b; which as above).
 __device__ inline double self_cell_partial(double ha, double hb, int which, double a, double b,
-                                           const GLNodes &gl, const double *wq)
+                                           const GLNodes &gl, const double *wq, int k0, int dk)
 {
     const int nx = sg_own_nx(a, b, fmin(ha, hb)), n = nx * gl.ne;
     const double h0 = 0.5 * (ha * ha + hb * hb), g = 0.5 * (hb * hb - ha * ha);
     const OwnEta e0(a, b), e1(b, a);
     double acc = 0.0;
-    for (int idx = threadIdx.x; idx < n; idx += blockDim.x) {
-        double xi, s, w;
-        sg_own_node(gl, nx, idx, xi, s, w);
 #pragma unroll 1
-        for (int tri = 0; tri < 2; ++tri) {
+    for (int idx = k0; idx < 2 * n; idx += dk) {
+        double xi, s, w;
+        const int tri = idx >= n ? 1 : 0;
+        sg_own_node(gl, nx, idx - tri * n, xi, s, w);
+        {
             const OwnPt q = own_tri_pt(a, b, tri == 0 ? e0 : e1, tri, xi, s, w);
             if (which)
                 acc += own_dnode(q, ha, hb, which, wq);
@@ -151,7 +162,7 @@ __global__ void __launch_bounds__(256) k_self_cell(SelfItems items, double *out,
     sg_fill64(wq, items.which[it] ? SG_FN_D : SG_FN_F);
     __syncthreads();
     const double acc = self_cell_partial(items.ha[it], items.hb[it], items.which[it], 0.5 * du,
-                                         0.5 * dphi, gl, wq);
+                                         0.5 * dphi, gl, wq, threadIdx.x, 256);
     const double tot = block_sum256(acc, red);
     if (threadIdx.x == 0) out[it] = tot;
 }
@@ -285,7 +296,8 @@ k_self_cell_ring(const double *H, int nf, int nr, double lnrmin, double du, doub
     const int pair = item / nr, ir = item % nr;
     const int fa = pair / nf, fb = pair % nf;
     const double r = exp(lnrmin + (ir + 0.5) * du);
-    const double acc = self_cell_partial(H[fa * nr + ir] / r, H[fb * nr + ir] / r, which, 0.5 * du, 0.5 * dphi, gl, wq);
+    const double acc = self_cell_partial(H[fa * nr + ir] / r, H[fb * nr + ir] / r, which, 0.5 * du, 0.5 * dphi, gl, wq,
+                                         threadIdx.x, 256);
     const double tot = block_sum256(acc, red);
     if (threadIdx.x == 0) out[item] = tot;
 }
@@ -481,144 +493,278 @@ __global__ void __launch_bounds__(256) k_sample_hat_near(double2 *A, int nr, int
     }
 }
 
-__global__ void k_copy_w00(const double2 *A, double *out) { *out = A[0].x; }
-
-// ------------------------------------------------------------------ sample
-__global__ void k_sample(double2 *A, int nr, int nphi, double du, double ha, double hb, int which,
-                         const double *self_val)
+// The own-cell value of a second-order table is W_r(0, 0).
+__global__ void k_copy_w00(const double2 *A, double *out)
 {
-    __shared__ __attribute__((aligned(16))) double wq[FQuad<double>::TABLE];
-    sg_fill64(wq, which ? SG_FN_D : SG_FN_F);
-    __syncthreads();
-    const int p = blockIdx.y;
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= nphi) return;
-    double kr = 0.0, kp = 0.0;
-    if (p == 0 && q == 0) {
-        kr = *self_val;
-    } else if (p != nr) {
-        const double X = (double)(p < nr ? p : p - 2 * nr) * du;
-        const double sh = sinpi((double)q / nphi);        // sin(phi/2)
-        const double s = sinpi(2.0 * (double)q / nphi);   // sin(phi)
-        sg_conv_kernel64(X, sh, s, ha, hb, which, wq, kr, kp);
-    }
-    A[(size_t)p * nphi + q] = make_double2(kr, kp);
+    out[0] = A[0].x;
+    for (int k = 1; k < SG_SELF_PARTS; ++k) out[k] = 0.0;
 }
 
-// ------------------------------------------------------- phi transform rows
-// One group of T threads per row of A (length N = n_phi, complex K_r + i K_phi).
-// Output B[c][m][p] (c = 0: K_r, 1: K_phi) for m in [0, N/2].
-template <int N>
-__global__ void k_tab_phi(const double2 *A, double2 *B, int rows)
+// ------------------------------------------------------------ build kernels
+// One table item: the kernel of a pair (which = 0) or its derivative in h_a or
+// h_b (which = 1, 2), where its spectra go and their strides.
+struct TabItem {
+    double ha, hb;
+    float2 *dst;         // [m][...] first column, component r
+    uint32_t cs, comp;   // float2 per column; from component r to phi
+    int which;
+};
+#define SG_TAB_ITEMS 8   // items per launch
+struct TabArgs {
+    int nr, nphi, nit;
+    double du, dphi, scale;
+    int ncls, M[5], K1[5], K2[5], blk0[6];  // row classes (as SsClass on the log grid)
+    const double *self;  // [item][SG_SELF_PARTS], null: no own-cell term to add
+    double2 *B;          // [item][n_phi/2 columns in tiles of 4][2 n_r]
+    const double2 *A;    // second order: samples [2 n_r][n_phi] of the one item
+    TabItem it[SG_TAB_ITEMS];
+};
+
+// B: column m < n_phi/2, offset row p.  Column 0 holds (T_r(0), T_r(n_phi/2)):
+// t_phi is zero in both.  Tiles of 4 columns make 64 contiguous bytes per row.
+__device__ __host__ inline size_t tab_index(int m, int p, int nu) { return ((size_t)(m >> 2) * nu + p) * 4 + (m & 3); }
+static size_t tab_item_elems(int nr, int nphi) { return (size_t)((nphi / 2 + 3) / 4 * 4) * 2 * nr; }
+
+// SG_SELF_PARTS blocks per own-cell item (the nodes are few: one or two per
+// thread) and, beyond them, the float twiddle tables.
+__global__ void __launch_bounds__(256)
+k_tab_pre(SelfItems items, int nself, double *out, double du, double dphi, GLNodes gl, float2 *tw_u, int nu,
+          float2 *tw_phi, int nphi)
 {
-    using Sh = FftShape<N>;
-    constexpr int P = Sh::P, T = Sh::T;
-    constexpr int WGS = T > 256 ? T : 256;
-    constexpr int G = WGS / T;
-    constexpr int W = LdsPlane<double>::elems(N);
+    __shared__ __attribute__((aligned(16))) double wq[FQuad<double>::TABLE];
+    __shared__ double red[256];
+    const int nb = nself * SG_SELF_PARTS;
+    if ((int)blockIdx.x < nb) {
+        const int it = blockIdx.x / SG_SELF_PARTS, part = blockIdx.x % SG_SELF_PARTS;
+        sg_fill64(wq, items.which[it] ? SG_FN_D : SG_FN_F);
+        __syncthreads();
+        const double acc = self_cell_partial(items.ha[it], items.hb[it], items.which[it], 0.5 * du, 0.5 * dphi, gl, wq,
+                                             part * 256 + threadIdx.x, SG_SELF_PARTS * 256);
+        const double tot = block_sum256(acc, red);
+        if (threadIdx.x == 0) out[blockIdx.x] = tot;
+        return;
+    }
+    const int i = (blockIdx.x - nb) * 256 + threadIdx.x;
+    const double2 *tw = (const double2 *)sg_tw64;
+    if (i < nu) {
+        const double2 v = tw[i * (SG_TW64_N / nu)];
+        tw_u[i] = make_float2((float)v.x, (float)-v.y);
+    }
+    if (i < nphi) {
+        const double2 v = tw[i * (SG_TW64_N / nphi)];
+        tw_phi[i] = make_float2((float)v.x, (float)-v.y);
+    }
+}
+
+// Rows of one class (M samples), block blk of the class: G groups of T threads,
+// two rows per group (z_A + i z_B, as in k_ss_rows).
+template <int M, int N>
+__device__ inline void tab_rows_body(const TabArgs &A, int cls, int blk, double2 *lds, const double *wq)
+{
+    using Sh = FftShape<M>;
+    constexpr int P = Sh::P, T = Sh::T, G = 256 / T, W = LdsPlane<double>::elems(M);
+    const int g = threadIdx.x / T, t = threadIdx.x % T;
+    const LdsPlane<double> pl{lds + W * g};
+    const TabItem &it = A.it[blockIdx.y];
+    const int nr = A.nr, K1 = A.K1[cls], K2 = A.K2[cls];
+    const int nk = K1 == 0 ? 2 * K2 - 1 : 2 * (K2 - K1);
+    int off[2];
+    bool live[2];
+    ConvRow64 cr[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int q = 2 * (blk * G + g) + u;
+        live[u] = q < nk;
+        off[u] = !live[u] ? 0 : K1 == 0 ? q - (K2 - 1) : q < K2 - K1 ? K1 + q : -(K1 + q - (K2 - K1));
+        cr[u] = sg_conv_row64(off[u] * A.du, it.ha, it.hb, it.which);
+    }
+#pragma unroll 1
+    for (int q = t; q <= M / 2; q += T) {
+        double kr[2], kp[2];
+        if (A.A) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const double2 v = A.A[(size_t)(off[u] < 0 ? off[u] + 2 * nr : off[u]) * N + q];
+                kr[u] = live[u] ? v.x : 0.0;
+                kp[u] = live[u] ? v.y : 0.0;
+            }
+        } else {
+            const double2 v = ((const double2 *)sg_tw64)[q * (SG_TW64_N / (2 * M))];  // half the azimuth
+            const double two_s2 = 2.0 * v.y * v.y, sphi = 2.0 * v.y * v.x;
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const bool none = !live[u] || (off[u] == 0 && q == 0);  // the own cell is added later
+                const double x = none ? 1.0 : (cr[u].two_sxh2 + two_s2) * cr[u].inv4h2;
+                const double p = none ? 0.0 : (it.which ? sg_D64(x, wq) : sg_F64(x, wq)) * cr[u].pref;
+                kr[u] = p * (cr[u].em1 + two_s2);
+                kp[u] = p * sphi;
+            }
+        }
+        pl.st(q, make_double2(kr[0] - kp[1], kp[0] + kr[1]));
+        if (q != 0 && q != M / 2) pl.st(M - q, make_double2(kr[0] + kp[1], kr[1] - kp[0]));
+    }
+    __syncthreads();
+    double2 z[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) z[p] = pl.ld(t + T * p);
+    __syncthreads();
+    fft<M, false>(z, t, pl, TwPow64<M>{t});
+#pragma unroll
+    for (int p = 0; p < P; ++p) pl.st(t + T * p, z[p]);
+    __syncthreads();
+    constexpr double f = 0.5 * (N / M);
+    double2 *B = A.B + blockIdx.y * (size_t)((N / 2 + 3) / 4 * 4) * 2 * nr;
+    for (int m = t; m < (M == N ? N / 2 : M / 2 + 1); m += T) {
+        const double2 zm = pl.ld(m), zn = pl.ld((M - m) & (M - 1));
+        double2 v[2] = {make_double2(f * (zm.x + zn.x), f * (zn.x - zm.x)),
+                        make_double2(f * (zm.y + zn.y), f * (zn.y - zm.y))};
+        if (m == 0) {
+            v[0].y = v[1].y = 0.0;
+            if (M == N) {
+                const double2 zh = pl.ld(M / 2);
+                v[0].y = zh.x;
+                v[1].y = zh.y;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            if (live[u]) B[tab_index(m, off[u] < 0 ? off[u] + 2 * nr : off[u], 2 * nr)] = v[u];
+    }
+}
+
+template <int M, int N>
+__device__ inline void tab_rows_dispatch(const TabArgs &A, int cls, int blk, double2 *lds, const double *wq)
+{
+    if (A.M[cls] == M) {
+        tab_rows_body<M, N>(A, cls, blk, lds, wq);
+        return;
+    }
+    if constexpr (M > SG_SS_MIN_M && M > 4) tab_rows_dispatch<M / 2, N>(A, cls, blk, lds, wq);
+}
+
+// Step 1, all items of a launch (blockIdx.y) and all row classes (blockIdx.x).
+template <int N>
+__global__ void __launch_bounds__(256) k_tab_rows(TabArgs A)
+{
+    // the largest plane set over the classes: 256/T planes of M points
+    constexpr int E = LdsPlane<double>::elems(N) * (256 / FftShape<N>::T);
+    constexpr int E2 = N > SG_SS_MIN_M ? LdsPlane<double>::elems(SG_SS_MIN_M) * (256 / FftShape<SG_SS_MIN_M>::T) : 0;
+    __shared__ __attribute__((aligned(16))) double2 lds[E > E2 ? E : E2];
+    __shared__ __attribute__((aligned(16))) double wq[FQuad<double>::TABLE];
+    if (!A.A) sg_fill64(wq, A.it[blockIdx.y].which ? SG_FN_D : SG_FN_F);
+    __syncthreads();
+    int cls = 0;
+    while (cls + 1 < A.ncls && (int)blockIdx.x >= A.blk0[cls + 1]) ++cls;
+    tab_rows_dispatch<N, N>(A, cls, blockIdx.x - A.blk0[cls], lds, wq);
+}
+
+// Step 2: column m of item blockIdx.y (column 0: the two real columns 0 and
+// n_phi/2 together).  Rows beyond those that resolve mode m are zero and not
+// read.  out: spectra at k <= n_r, scaled and rounded; for the kernel itself
+// (which = 0) also the pair column of the FFT pass that transforms the two real
+// columns as one, (K0 + KN)/2 in the K_r place and (K0 - KN)/2 in the K_phi place.
+template <int NU>
+__global__ void __launch_bounds__((FftShape<NU>::T > 256 ? FftShape<NU>::T : 256)) k_tab_u(TabArgs A)
+{
+    using Sh = FftShape<NU>;
+    constexpr int P = Sh::P, T = Sh::T, H = NU / 2;
+    constexpr int WGS = T > 256 ? T : 256, G = WGS / T, W = LdsPlane<double>::elems(NU);
     __shared__ __attribute__((aligned(16))) double2 lds[W * G];
     const int g = threadIdx.x / T, t = threadIdx.x % T;
-    LdsPlane<double> pl{lds + W * g};
-    const int row = blockIdx.x * G + g;
-    const bool valid = row < rows;
+    const LdsPlane<double> pl{lds + W * g};
+    const int nc = A.nphi / 2, job = sg_xcd_remap(blockIdx.x, 4 / G > 0 ? 4 / G : 1) * G + g;
+    const bool valid = job < nc;
+    const int m = valid ? job : 0;
+    const TabItem &it = A.it[blockIdx.y];
+    const double2 *B = A.B + blockIdx.y * (size_t)((nc + 3) / 4 * 4) * NU;
+    int kmax = 0;  // rows |k| < kmax resolve mode m (column 0 holds mode n_phi/2 too: its rows are zeros there)
+    for (int c = 0; c < A.ncls; ++c)
+        if (A.M[c] / 2 >= m) kmax = max(kmax, A.K2[c]);
     double2 v[P];
 #pragma unroll
-    for (int p = 0; p < P; ++p) v[p] = valid ? A[(size_t)row * N + t + T * p] : make_double2(0, 0);
-    fft<N, false>(v, t, pl, TwPow64<N>{t});
+    for (int p = 0; p < P; ++p) {
+        const int r = t + T * p, k = r < H ? r : r - NU;
+        v[p] = make_double2(0.0, 0.0);
+        if (abs(k) < kmax) v[p] = B[tab_index(m, r, NU)];
+    }
+    if (t == 0 && A.self) {
+        double s = 0.0;
+        for (int q = 0; q < SG_SELF_PARTS; ++q) s += A.self[blockIdx.y * SG_SELF_PARTS + q];
+        v[0].x += s;
+        if (m == 0) v[0].y += s;
+    }
+    fft<NU, false>(v, t, pl, TwPow64<NU>{t});
 #pragma unroll
     for (int p = 0; p < P; ++p) pl.st(t + T * p, v[p]);
     __syncthreads();
     if (!valid) return;
-    const int ncol = N / 2 + 1;
-    for (int m = t; m <= N / 2; m += T) {
-        const double2 Zm = pl.ld(m), Zn = pl.ld((N - m) & (N - 1));
-        const double zr = Zm.x, zi = Zm.y;
-        const double cr = Zn.x, ci = -Zn.y;  // conj Z[-m]
-        // K_r~ = (Z + conj Z[-m]) / 2,  K_phi~ = (Z - conj Z[-m]) / (2i)
-        B[(size_t)m * rows + row] = make_double2(0.5 * (zr + cr), 0.5 * (zi + ci));
-        B[((size_t)ncol + m) * rows + row] = make_double2(0.5 * (zi - ci), -0.5 * (zr - cr));
+    const double sc = 0.5 * A.scale;
+    float2 *o = it.dst + (size_t)m * it.cs;
+    float2 *on = it.dst + (size_t)nc * it.cs, *oq = on + it.cs;  // columns n_phi/2 and the pair column
+    for (int k = t; k <= H; k += T) {
+        const double2 a = pl.ld(k), b = pl.ld((NU - k) & (NU - 1));
+        // (W + conj W')/2 and (W - conj W')/2
+        const float2 e = make_float2((float)(sc * (a.x + b.x)), (float)(sc * (a.y - b.y)));
+        const float2 d = make_float2((float)(sc * (a.x - b.x)), (float)(sc * (a.y + b.y)));
+        o[k] = e;
+        if (m > 0) {
+            o[it.comp + k] = d;  // i times the transform of t_phi
+            continue;
+        }
+        const float2 n = make_float2(d.y, -d.x), zero = make_float2(0.f, 0.f);  // d / i
+        o[it.comp + k] = zero;
+        on[k] = n;
+        on[it.comp + k] = zero;
+        if (it.which == 0) {
+            oq[k] = make_float2(0.5f * (e.x + n.x), 0.5f * (e.y + n.y));
+            oq[it.comp + k] = make_float2(0.5f * (e.x - n.x), 0.5f * (e.y - n.y));
+        }
     }
-}
-
-// ---------------------------------------------------------- u transform cols
-// One group per column (c, m) of B (length NU = 2 n_r).  Writes k in [0, n_r]
-// scaled and rounded into dst[m * col_stride + comp_off[c] + k].
-template <int NU>
-__global__ void k_tab_u(const double2 *B, float2 *dst, int ncol, size_t col_stride,
-                        size_t comp_off0, size_t comp_off1, double scale)
-{
-    using Sh = FftShape<NU>;
-    constexpr int P = Sh::P, T = Sh::T;
-    constexpr int WGS = T > 256 ? T : 256;
-    constexpr int G = WGS / T;
-    constexpr int W = LdsPlane<double>::elems(NU);
-    __shared__ __attribute__((aligned(16))) double2 lds[W * G];
-    const int g = threadIdx.x / T, t = threadIdx.x % T;
-    LdsPlane<double> pl{lds + W * g};
-    const int col = blockIdx.x * G + g;  // c * ncol + m
-    const bool valid = col < 2 * ncol;
-    double2 v[P];
-#pragma unroll
-    for (int p = 0; p < P; ++p) v[p] = valid ? B[(size_t)col * NU + t + T * p] : make_double2(0, 0);
-    fft<NU, false>(v, t, pl, TwPow64<NU>{t});
-    if (!valid) return;
-    const int c = col / ncol, m = col % ncol;
-    float2 *out = dst + (size_t)m * col_stride + (c ? comp_off1 : comp_off0);
-    constexpr int H = NU / 2;
-#pragma unroll
-    for (int p = 0; p < P; ++p) {
-        const int k = t + T * p;
-        if (k <= H) out[k] = make_float2((float)(v[p].x * scale), (float)(v[p].y * scale));
-    }
-}
-
-// The pair column after the last one: for the FFT pass that transforms the
-// two real columns m = 0 and n_phi/2 as one complex column, A = (K0 + KN)/2
-// in the K_r place and B = (K0 - KN)/2 in the K_phi place, from K_r of
-// column 0 (K0) and of column n_phi/2 (KN), for every pair and k.
-__global__ void k_pair_col(float2 *spec, int ncol, int npair, int kk)
-{
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= npair * kk) return;
-    const int pair = e / kk, k = e % kk;
-    const size_t cs = (size_t)npair * 2 * kk;
-    const float2 k0 = spec[(size_t)pair * 2 * kk + k];
-    const float2 kn = spec[(size_t)(ncol - 1) * cs + (size_t)pair * 2 * kk + k];
-    float2 *o = spec + (size_t)ncol * cs + (size_t)pair * 2 * kk;
-    o[k] = make_float2(0.5f * (k0.x + kn.x), 0.5f * (k0.y + kn.y));
-    o[kk + k] = make_float2(0.5f * (k0.x - kn.x), 0.5f * (k0.y - kn.y));
 }
 
 // Header, including the indirect-term coefficient of each source fluid: with
 // H_a = h_a r the star's kernel has d = 1/h_a at every cell, so
 //   sqrt(2) K_a A_k = sqrt(2) pi^{-1/2} h_a^{-3} / 4 F(1 / (4 h_a^2)) du dphi
 // (times Sigma_a[k] e^{i phi_k} in the sum), the same for all cells.
-__global__ void k_header(sg_table_header *hd, sg_table_header proto, const double *selfbuf,
-                         int npair, int with_dh)
+__global__ void __launch_bounds__(256)
+k_header(sg_table_header *hd, sg_table_header proto, const double *selfbuf, int npair, int with_dh)
 {
-    // one wave fills the coefficient table; lane 0 writes the header
+    // the block fills the coefficient table; one wave adds up the header's values
     __shared__ __attribute__((aligned(16))) double w[FQuad<double>::TABLE];
     sg_fill64(w, SG_FN_F);
     __syncthreads();
-    if (threadIdx.x != 0) return;
-    sg_table_header h = proto;
+    const int k = threadIdx.x;
+    if (k >= 64) return;
     const double du = log(proto.r_max / proto.r_min) / proto.n_r;
     const double dphi = 2.0 * SG_PI / proto.n_phi;
-    for (int a = 0; a < 4; ++a) {
-        h.ind_coef[a] = 0.0;
-        if (a < proto.n_fluids) {
-            const double ha = proto.h[a];
-            h.ind_coef[a] = SG_SQRT2 / SG_SQRT_PI / (4.0 * ha * ha * ha) * sg_F64(0.25 / (ha * ha), w) * du * dphi;
-        }
+    auto self = [&](int it) {
+        double s = 0.0;
+        for (int q = 0; q < SG_SELF_PARTS; ++q) s += selfbuf[it * SG_SELF_PARTS + q];
+        return s;
+    };
+    if (k == 0) {  // all but the values that follow
+        hd->magic = proto.magic;
+        hd->version = proto.version;
+        hd->n_r = proto.n_r;
+        hd->n_phi = proto.n_phi;
+        hd->n_fluids = proto.n_fluids;
+        hd->flags = proto.flags;
+        hd->r_min = proto.r_min;
+        hd->r_max = proto.r_max;
+        hd->total_bytes = proto.total_bytes;
     }
-    for (int p = 0; p < npair; ++p) {
-        h.self_r[p] = selfbuf[p];
-        if (with_dh) {
-            h.dself_r[p][0] = selfbuf[npair + 2 * p];
-            h.dself_r[p][1] = selfbuf[npair + 2 * p + 1];
-        }
+    if (k < 4) {
+        hd->h[k] = proto.h[k];
+        const double ha = k < proto.n_fluids ? proto.h[k] : 1.0;
+        const double c = SG_SQRT2 / SG_SQRT_PI / (4.0 * ha * ha * ha) * sg_F64(0.25 / (ha * ha), w) * du * dphi;
+        hd->ind_coef[k] = k < proto.n_fluids ? c : 0.0;
     }
-    *hd = h;
+    if (k < 16) {
+        const bool in = k < npair;
+        hd->self_r[k] = in ? self(k) : 0.0;
+        hd->dself_r[k][0] = in && with_dh ? self(npair + 2 * k) : 0.0;
+        hd->dself_r[k][1] = in && with_dh ? self(npair + 2 * k + 1) : 0.0;
+    }
 }
 
 // ------------------------------------------------------------- F for tests
@@ -720,67 +866,72 @@ void sg_gl_nodes(GLNodes &gl, double aspect)
     gl = cache.g[aspect <= 8.0 && aspect >= 0.125 ? 0 : 1];
 }
 
-template <int NPHI>
-static void launch_tab_phi(const double2 *A, double2 *B, int rows, hipStream_t s)
+static bool launch_tab_rows(const TabArgs &A, hipStream_t s)
 {
-    using Sh = FftShape<NPHI>;
-    constexpr int WGS = Sh::T > 256 ? Sh::T : 256;
-    constexpr int G = WGS / Sh::T;
-    hipLaunchKernelGGL(k_tab_phi<NPHI>, dim3((rows + G - 1) / G), dim3(WGS), 0, s, A, B, rows);
-}
-
-template <int NU>
-static void launch_tab_u(const double2 *B, float2 *dst, int ncol, size_t col_stride, size_t o0,
-                         size_t o1, double scale, hipStream_t s)
-{
-    using Sh = FftShape<NU>;
-    constexpr int WGS = Sh::T > 256 ? Sh::T : 256;
-    constexpr int G = WGS / Sh::T;
-    hipLaunchKernelGGL(k_tab_u<NU>, dim3((2 * ncol + G - 1) / G), dim3(WGS), 0, s, B, dst, ncol,
-                       col_stride, o0, o1, scale);
-}
-
-static bool dispatch_tab_phi(int nphi, const double2 *A, double2 *B, int rows, hipStream_t s)
-{
-    switch (nphi) {
-    case 4: launch_tab_phi<4>(A, B, rows, s); return true;
-    case 8: launch_tab_phi<8>(A, B, rows, s); return true;
-    case 16: launch_tab_phi<16>(A, B, rows, s); return true;
-    case 32: launch_tab_phi<32>(A, B, rows, s); return true;
-    case 64: launch_tab_phi<64>(A, B, rows, s); return true;
-    case 128: launch_tab_phi<128>(A, B, rows, s); return true;
-    case 256: launch_tab_phi<256>(A, B, rows, s); return true;
-    case 512: launch_tab_phi<512>(A, B, rows, s); return true;
-    case 1024: launch_tab_phi<1024>(A, B, rows, s); return true;
-    case 2048: launch_tab_phi<2048>(A, B, rows, s); return true;
-    default: return false;
+    const dim3 grid((unsigned)A.blk0[A.ncls], (unsigned)A.nit);
+    switch (A.nphi) {
+#define SG_ROWS(N) \
+    case N: hipLaunchKernelGGL(k_tab_rows<N>, grid, dim3(256), 0, s, A); return true;
+        SG_ROWS(4) SG_ROWS(8) SG_ROWS(16) SG_ROWS(32) SG_ROWS(64) SG_ROWS(128) SG_ROWS(256) SG_ROWS(512)
+        SG_ROWS(1024) SG_ROWS(2048)
+#undef SG_ROWS
     }
+    return false;
 }
 
-static bool dispatch_tab_u(int nu, const double2 *B, float2 *dst, int ncol, size_t cs, size_t o0,
-                           size_t o1, double scale, hipStream_t s)
+template <int NU> static void launch_tab_u(const TabArgs &A, hipStream_t s)
 {
-    switch (nu) {
-    case 4: launch_tab_u<4>(B, dst, ncol, cs, o0, o1, scale, s); return true;
-    case 8: launch_tab_u<8>(B, dst, ncol, cs, o0, o1, scale, s); return true;
-    case 16: launch_tab_u<16>(B, dst, ncol, cs, o0, o1, scale, s); return true;
-    case 32: launch_tab_u<32>(B, dst, ncol, cs, o0, o1, scale, s); return true;
-    case 64: launch_tab_u<64>(B, dst, ncol, cs, o0, o1, scale, s); return true;
-    case 128: launch_tab_u<128>(B, dst, ncol, cs, o0, o1, scale, s); return true;
-    case 256: launch_tab_u<256>(B, dst, ncol, cs, o0, o1, scale, s); return true;
-    case 512: launch_tab_u<512>(B, dst, ncol, cs, o0, o1, scale, s); return true;
-    case 1024: launch_tab_u<1024>(B, dst, ncol, cs, o0, o1, scale, s); return true;
-    case 2048: launch_tab_u<2048>(B, dst, ncol, cs, o0, o1, scale, s); return true;
-    case 4096: launch_tab_u<4096>(B, dst, ncol, cs, o0, o1, scale, s); return true;
-    default: return false;
-    }
+    constexpr int T = FftShape<NU>::T, WGS = T > 256 ? T : 256, G = WGS / T, K = 4 / G > 0 ? 4 / G : 1;
+    const int nwg = (A.nphi / 2 + G - 1) / G;  // whole XCD clusters of 8 K
+    hipLaunchKernelGGL(k_tab_u<NU>, dim3((unsigned)((nwg + 8 * K - 1) / (8 * K) * (8 * K)), (unsigned)A.nit), dim3(WGS),
+                       0, s, A);
 }
+
+static bool dispatch_tab_u(const TabArgs &A, hipStream_t s)
+{
+    switch (2 * A.nr) {
+#define SG_COLS(N) \
+    case N: launch_tab_u<N>(A, s); return true;
+        SG_COLS(4) SG_COLS(8) SG_COLS(16) SG_COLS(32) SG_COLS(64) SG_COLS(128) SG_COLS(256) SG_COLS(512)
+        SG_COLS(1024) SG_COLS(2048) SG_COLS(4096)
+#undef SG_COLS
+    }
+    return false;
+}
+
+// Own-cell parts, then the intermediate columns (with SG_SECOND_ORDER the
+// samples before them).
+static size_t tab_self_bytes() { return sg_align256(sizeof(double) * SG_SELF_MAX * SG_SELF_PARTS); }
 
 size_t sg_table_ws_bytes(int nr, int nphi)
 {
     const size_t A = sizeof(double2) * 2 * (size_t)nr * nphi;
     const size_t B = sizeof(double2) * 2 * (size_t)(nphi / 2 + 1) * 2 * nr;
-    return sg_align256(A) + sg_align256(B) + 256;
+    const size_t item = sizeof(double2) * tab_item_elems(nr, nphi);
+    return sg_align256(A) + sg_align256(B > item ? B : item) + tab_self_bytes();
+}
+
+// Row classes of the grid: M azimuths for the offsets K1 <= |k| < K2 with
+// M |k| du >= SG_SS_ALIAS; one class of all rows where that saves nothing (and
+// with second-order samples, which exist on the full grid).
+static void tab_classes(TabArgs &A, bool second)
+{
+    A.ncls = 0;
+    A.blk0[0] = 0;
+    for (int M = A.nphi;; M /= 2) {
+        const bool last = second || M / 2 < SG_SS_MIN_M;
+        const int K1 = M == A.nphi ? 0 : (int)fmin(ceil(SG_SS_ALIAS / M / A.du), (double)A.nr);
+        const int K2 = last ? A.nr : (int)fmin(ceil(SG_SS_ALIAS / (M / 2) / A.du), (double)A.nr);
+        if (K1 < K2) {
+            const int c = A.ncls++;
+            const int nk = K1 == 0 ? 2 * K2 - 1 : 2 * (K2 - K1), T = M >= 8 ? M / 8 : 1, G = 256 / T;
+            A.M[c] = M;
+            A.K1[c] = K1;
+            A.K2[c] = K2;
+            A.blk0[c + 1] = A.blk0[c] + ((nk + 1) / 2 + G - 1) / G;
+        }
+        if (last) break;
+    }
 }
 
 sg_status sg_table_build(const sg_grid *grid, const sg_fluids *fl, uint32_t flags, void *d_table,
@@ -792,97 +943,80 @@ sg_status sg_table_build(const sg_grid *grid, const sg_fluids *fl, uint32_t flag
     const double dphi = 2.0 * SG_PI / nphi;
     char *tb = (char *)d_table;
     char *ws = (char *)d_ws;
-    double2 *A = (double2 *)ws;
-    double2 *B = (double2 *)(ws + sg_align256(sizeof(double2) * 2 * (size_t)nr * nphi));
-    double *selfbuf = (double *)((char *)B + sg_align256(sizeof(double2) * 2 * (size_t)L.ncol * 2 * nr));
+    double *selfbuf = (double *)ws;
+    double2 *A0 = (double2 *)(ws + tab_self_bytes());
+    const size_t bytes = sg_table_ws_bytes(nr, nphi) - tab_self_bytes();
     const bool with_dh = (flags & SG_WITH_DH) != 0;
     const bool excl = (flags & SG_SELF_CELL_EXCLUDE) != 0;
     const bool second = (flags & SG_SECOND_ORDER) != 0;  // no own-cell switch
 
-    // twiddle tables
-    {
-        const int n = 2 * nr > nphi ? 2 * nr : nphi;
-        hipLaunchKernelGGL(k_twiddles, dim3((n + 255) / 256), dim3(256), 0, s,
-                           (float2 *)(tb + L.off_tw_u), 2 * nr, (float2 *)(tb + L.off_tw_phi), nphi);
-        SG_HIP(hipGetLastError());
-    }
-    // self-cell items: [pair] for which = 0, then [pair][d] for the derivatives
-    SelfItems items{};
-    int nit = 0;
-    for (int a = 0; a < nf; ++a)
-        for (int b = 0; b < nf; ++b) {
-            items.ha[nit] = fl->h[a];
-            items.hb[nit] = fl->h[b];
-            items.which[nit] = 0;
-            ++nit;
-        }
-    if (with_dh)
-        for (int a = 0; a < nf; ++a)
-            for (int b = 0; b < nf; ++b)
-                for (int d = 0; d < 2; ++d) {
-                    items.ha[nit] = fl->h[a];
-                    items.hb[nit] = fl->h[b];
-                    items.which[nit] = 1 + d;
-                    ++nit;
-                }
-    if (excl) {
-        hipLaunchKernelGGL(k_fill_f64, dim3(1), dim3(64), 0, s, selfbuf, (int64_t)nit, 0.0);
-        SG_HIP(hipGetLastError());
-    } else if (!second) {  // second order: W_r(0, 0) is copied in per pair below
-        GLNodes gl;
-        sg_gl_nodes(gl, du / dphi);
-        hipLaunchKernelGGL(k_self_cell, dim3(nit), dim3(256), 0, s, items, selfbuf, du, dphi, gl);
-        SG_HIP(hipGetLastError());
-    }
-
-    const double scale = -du * dphi / (2.0 * nr * (double)nphi);
-    const size_t col_stride = (size_t)L.npair * 2 * L.kk;        // spec: [m][pair][c][k]
-    const size_t dcol_stride = (size_t)L.npair * 4 * L.kk;       // dspec: [m][pair][d][c][k]
+    // items: [pair] for which = 0, then [pair][d] for the derivatives
     float2 *spec = (float2 *)(tb + L.off_spec);
     float2 *dspec = (float2 *)(tb + L.off_dspec);
-    const int nwhich = with_dh ? 3 : 1;
-    for (int a = 0; a < nf; ++a)
-        for (int b = 0; b < nf; ++b) {
-            const int pair = a * nf + b;
-            for (int w = 0; w < nwhich; ++w) {
-                const double *sv = w == 0 ? selfbuf + pair : selfbuf + L.npair + 2 * pair + (w - 1);
-                if (second) {
-                    GLNodes gl;
-                    sg_gl_nodes(gl, du / dphi);
-                    hipLaunchKernelGGL(k_sample_hat_far, dim3((nphi + 255) / 256, 2 * nr), dim3(256), 0, s, A, nr,
-                                       nphi, du, fl->h[a], fl->h[b], w);
-                    hipLaunchKernelGGL(k_sample_hat_near, dim3(9), dim3(256), 0, s, A, nr, nphi, du, fl->h[a],
-                                       fl->h[b], w, gl);
-                    // the header's own-cell value of this pair (or its derivative): W_r(0, 0)
-                    hipLaunchKernelGGL(k_copy_w00, dim3(1), dim3(1), 0, s, (const double2 *)A, (double *)sv);
-                } else {
-                    hipLaunchKernelGGL(k_sample, dim3((nphi + 255) / 256, 2 * nr), dim3(256), 0, s, A,
-                                       nr, nphi, du, fl->h[a], fl->h[b], w, sv);
+    SelfItems items{};
+    std::vector<TabItem> its;
+    for (int w = 0; w < (with_dh ? 2 : 1); ++w)
+        for (int a = 0; a < nf; ++a)
+            for (int b = 0; b < nf; ++b)
+                for (int d = 0; d < (w ? 2 : 1); ++d) {
+                    const int pair = a * nf + b, n = (int)its.size();
+                    TabItem it;
+                    it.ha = fl->h[a];
+                    it.hb = fl->h[b];
+                    it.which = w ? 1 + d : 0;
+                    it.comp = (uint32_t)L.kk;
+                    it.cs = (uint32_t)(L.npair * (w ? 4 : 2) * L.kk);                  // dspec: [m][pair][d][c][k]
+                    it.dst = w ? dspec + (size_t)(pair * 2 + d) * 2 * L.kk : spec + (size_t)pair * 2 * L.kk;
+                    its.push_back(it);
+                    items.ha[n] = it.ha;
+                    items.hb[n] = it.hb;
+                    items.which[n] = it.which;
                 }
-                SG_HIP(hipGetLastError());
-                if (!dispatch_tab_phi(nphi, A, B, 2 * nr, s)) return SG_ERR_UNSUPPORTED;
-                SG_HIP(hipGetLastError());
-                float2 *dst;
-                size_t cs, o0, o1;
-                if (w == 0) {
-                    dst = spec;
-                    cs = col_stride;
-                    o0 = ((size_t)pair * 2 + 0) * L.kk;
-                    o1 = ((size_t)pair * 2 + 1) * L.kk;
-                } else {
-                    dst = dspec;
-                    cs = dcol_stride;
-                    o0 = (((size_t)pair * 2 + (w - 1)) * 2 + 0) * L.kk;
-                    o1 = (((size_t)pair * 2 + (w - 1)) * 2 + 1) * L.kk;
-                }
-                if (!dispatch_tab_u(2 * nr, B, dst, L.ncol, cs, o0, o1, scale, s))
-                    return SG_ERR_UNSUPPORTED;
-                SG_HIP(hipGetLastError());
-            }
+    const int nit = (int)its.size();
+    const bool own = !excl && !second;  // second order: W_r(0, 0) is copied in per item below
+    GLNodes gl;
+    sg_gl_nodes(gl, du / dphi);
+    if (excl) {
+        hipLaunchKernelGGL(k_fill_f64, dim3(4), dim3(256), 0, s, selfbuf, (int64_t)nit * SG_SELF_PARTS, 0.0);
+        SG_HIP(hipGetLastError());
+    }
+    {
+        const int n = 2 * nr > nphi ? 2 * nr : nphi, nself = own ? nit : 0;
+        hipLaunchKernelGGL(k_tab_pre, dim3((unsigned)(nself * SG_SELF_PARTS + (n + 255) / 256)), dim3(256), 0, s, items,
+                           nself, selfbuf, du, dphi, gl, (float2 *)(tb + L.off_tw_u), 2 * nr,
+                           (float2 *)(tb + L.off_tw_phi), nphi);
+        SG_HIP(hipGetLastError());
+    }
+    TabArgs T{};
+    T.nr = nr;
+    T.nphi = nphi;
+    T.du = du;
+    T.dphi = dphi;
+    T.scale = -du * dphi / (2.0 * nr * (double)nphi);
+    tab_classes(T, second);
+    const size_t item = sizeof(double2) * tab_item_elems(nr, nphi);
+    T.B = second ? (double2 *)((char *)A0 + sg_align256(sizeof(double2) * 2 * (size_t)nr * nphi)) : A0;
+    const int batch = second ? 1 : std::max(1, (int)std::min<size_t>(SG_TAB_ITEMS, bytes / item));
+    for (int i0 = 0; i0 < nit; i0 += batch) {
+        T.nit = std::min(batch, nit - i0);
+        for (int i = 0; i < T.nit; ++i) T.it[i] = its[i0 + i];
+        T.self = own ? selfbuf + (size_t)i0 * SG_SELF_PARTS : nullptr;
+        if (second) {
+            const TabItem &it = its[i0];
+            T.A = A0;
+            hipLaunchKernelGGL(k_sample_hat_far, dim3((nphi + 255) / 256, 2 * nr), dim3(256), 0, s, A0, nr, nphi, du,
+                               it.ha, it.hb, it.which);
+            hipLaunchKernelGGL(k_sample_hat_near, dim3(9), dim3(256), 0, s, A0, nr, nphi, du, it.ha, it.hb, it.which,
+                               gl);
+            // the header's own-cell value of this pair (or its derivative): W_r(0, 0)
+            hipLaunchKernelGGL(k_copy_w00, dim3(1), dim3(1), 0, s, (const double2 *)A0, selfbuf + (size_t)i0 * SG_SELF_PARTS);
+            SG_HIP(hipGetLastError());
         }
-    hipLaunchKernelGGL(k_pair_col, dim3((L.npair * L.kk + 255) / 256), dim3(256), 0, s, spec, L.ncol, L.npair,
-                       L.kk);
-    SG_HIP(hipGetLastError());
+        if (!launch_tab_rows(T, s)) return SG_ERR_UNSUPPORTED;
+        SG_HIP(hipGetLastError());
+        if (!dispatch_tab_u(T, s)) return SG_ERR_UNSUPPORTED;
+        SG_HIP(hipGetLastError());
+    }
     sg_table_header proto{};
     proto.magic = SG_TABLE_MAGIC;
     proto.version = 1;
@@ -894,8 +1028,8 @@ sg_status sg_table_build(const sg_grid *grid, const sg_fluids *fl, uint32_t flag
     proto.r_min = grid->r_min;
     proto.r_max = grid->r_max;
     proto.total_bytes = L.total;
-    hipLaunchKernelGGL(k_header, dim3(1), dim3(64), 0, s, (sg_table_header *)tb, proto, selfbuf,
-                       L.npair, with_dh ? 1 : 0);
+    hipLaunchKernelGGL(k_header, dim3(1), dim3(256), 0, s, (sg_table_header *)tb, proto, selfbuf, L.npair,
+                       with_dh ? 1 : 0);
     SG_HIP(hipGetLastError());
     return SG_OK;
 }
