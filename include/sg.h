@@ -281,10 +281,12 @@ typedef struct sg_disc {
  * latency).  The plan, the graph where used and a device copy of the batch
  * descriptors are cached per (sizes, pointers) signature on the first call
  * (that call allocates and synchronises once); later calls with the same
- * signature only launch.  At most 256 signatures are kept; a new one
+ * signature only launch.  A single disc (without species) passes its
+ * descriptor by value: its plan is kept by grid, fluid count and flags, holds
+ * no device memory, and serves any buffers without a synchronisation.  At most 256 signatures are kept; a new one
  * beyond that releases the least recently used (after a device
  * synchronisation).  d_ws: sg_field_fft_workspace_bytes(discs, n)
- * bytes, 256-byte aligned; its address is part of the signature.
+ * bytes, 256-byte aligned; its address is part of a batch's signature.
  * n_discs in [1, 4096].  Outputs overwritten.
  * --------------------------------------------------------------------- */
 size_t sg_field_fft_workspace_bytes(const sg_disc *discs, int n_discs);
@@ -509,7 +511,7 @@ sg_status sg_self_cell(const sg_grid *grid, const double *ha, const double *hb, 
 void sg_release(void);
 
 /* Number of batch signatures (discs' shapes and buffer addresses, workspace,
- * device) whose plan (and graph, where used) sg_field_fft currently caches; a caller that
+ * device; of a single disc without species its shape and device) whose plan (and graph, where used) sg_field_fft currently caches; a caller that
  * keeps its buffers sees it stay constant after the first call. */
 int sg_field_fft_cache_entries(void);
 

@@ -5,9 +5,11 @@
 #include <cstddef>
 #include <cmath>
 #include <cstdio>
+#include <cstring>
 #include <tuple>
 #include <map>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include <hip/hip_ext.h>
@@ -41,7 +43,7 @@ template <int N, int GM> struct P1Shape {
 
 template <int N, int NF, bool SF, int GM>
 __global__ void __launch_bounds__((P1Shape<N, GM>::WGS))
-k_pass1(const DiscDev *discs, const WJob *wj, int nj, const float2 *twp, int kc)
+k_pass1(const DiscDev *discs, const WJob *wj, int nj, const float2 *twp, int kc, OneDisc one)
 {
     using S = P1Shape<N, GM>;
     constexpr int P = S::P, T = S::T, G = S::G, W = LdsPlane<float>::elems(N);
@@ -50,9 +52,10 @@ k_pass1(const DiscDev *discs, const WJob *wj, int nj, const float2 *twp, int kc)
     const int g = threadIdx.x / T, t = threadIdx.x % T;
     const int w = sg_uniform(sg_xcd_remap(blockIdx.x, kc));
     if (w >= nj) return;
-    const int cd = sg_uniform(wj[w].disc), cb = sg_uniform(wj[w].base), cn = sg_uniform(wj[w].n);
-    const DiscDev *D = discs + cd;
-    const int nr = D->nr, half = sg_blk_rows(nr) / 2;  // row pairs per fluid
+    DiscDev D;
+    const WJob job = pass_job(discs, wj, one, w, G, D);
+    const int cb = job.base, cn = job.n;
+    const int nr = D.nr, half = sg_blk_rows(nr) / 2;  // row pairs per fluid
     const LdsPlane<float> pl{lds + W * g};
     TwRegC<N, SF> tw;
     tw.load(twp, t);
@@ -64,21 +67,22 @@ k_pass1(const DiscDev *discs, const WJob *wj, int nj, const float2 *twp, int kc)
         const int f = idx / half, j = idx % half;
         const uint32_t r1 = (uint32_t)min(2 * j, nr - 1) * N + t;
         const uint32_t r2 = (uint32_t)min(2 * j + 1, nr - 1) * N + t;
-        if (sg_uniform(D->ns) == 0) {
+        if (sg_uniform(D.ns) == 0) {
             const uint32_t o = (uint32_t)f * nr * N;
 #pragma unroll
             for (int p = 0; p < P; ++p)
-                z[p] = make_float2(gld1(D->sigma, o + r1 + T * p), gld1(D->sigma, o + r2 + T * p));
+                z[p] = make_float2(gld1(D.sigma, o + r1 + T * p), gld1(D.sigma, o + r2 + T * p));
         } else {
 #pragma unroll
             for (int p = 0; p < P; ++p) z[p] = make_float2(0.f, 0.f);
-            const int cnt = D->gcount[f];
+            const DiscDev *sp = discs + job.disc;
+            const int cnt = sp->gcount[f];
             for (int k = 0; k < cnt; ++k) {
-                const uint32_t o = (uint32_t)D->gsp[f][k] * nr * N;
+                const uint32_t o = (uint32_t)sp->gsp[f][k] * nr * N;
 #pragma unroll
                 for (int p = 0; p < P; ++p) {
-                    z[p].x += gld1(D->sigma, o + r1 + T * p);
-                    z[p].y += gld1(D->sigma, o + r2 + T * p);
+                    z[p].x += gld1(D.sigma, o + r1 + T * p);
+                    z[p].y += gld1(D.sigma, o + r2 + T * p);
                 }
             }
         }
@@ -124,7 +128,7 @@ k_pass1(const DiscDev *discs, const WJob *wj, int nj, const float2 *twp, int kc)
             v0 = make_float2(Z0.x, ZN.x);
             v1 = make_float2(Z0.y, ZN.y);
         }
-        gst2x2(D->st + f * fs + sg_blk_tile(q, i0, nr) + 2 * l, v0, v1);
+        gst2x2(D.st + f * fs + sg_blk_tile(q, i0, nr) + 2 * l, v0, v1);
     }
 }
 
@@ -148,17 +152,17 @@ template <int NU, int NF, int GM> struct P2Shape {
 // table holds (K0 + KN)/2 and (K0 - KN)/2 (K_r of the two columns) in that
 // slot's K_r and K_phi places, so the job loads from slot n_phi/2 + 1.
 template <int NU>
-__device__ inline void p2_load_sh(const DiscDev *D, int m, int h, int t, float2 (&sh)[FftShape<NU>::P / 2])
+__device__ inline void p2_load_sh(const DiscDev &D, int m, int h, int t, float2 (&sh)[FftShape<NU>::P / 2])
 {
     constexpr int P = FftShape<NU>::P, T = FftShape<NU>::T, H = P / 2, NR = NU / 2;
-    const uint32_t fs = (uint32_t)sg_blk_field_elems(D->nphi, NR);
+    const uint32_t fs = (uint32_t)sg_blk_field_elems(D.nphi, NR);
 #pragma unroll
-    for (int p = 0; p < H; ++p) sh[p] = gld2(D->st, h * fs + (uint32_t)sg_blk_index(m, t + T * p, NR));
+    for (int p = 0; p < H; ++p) sh[p] = gld2(D.st, h * fs + (uint32_t)sg_blk_index(m, t + T * p, NR));
 }
 
 // spectra of source a for target h
 template <int NU, int NF>
-__device__ inline void p2_load_k(const DiscDev *D, int m, int a, int h, int t, float2 (&K)[2][FftShape<NU>::P / 2],
+__device__ inline void p2_load_k(const DiscDev &D, int m, int a, int h, int t, float2 (&K)[2][FftShape<NU>::P / 2],
                                  float2 (&KN)[2])
 {
     constexpr int P = FftShape<NU>::P, T = FftShape<NU>::T, H = P / 2, NR = NU / 2;
@@ -167,13 +171,13 @@ __device__ inline void p2_load_k(const DiscDev *D, int m, int a, int h, int t, f
     for (int cc = 0; cc < 2; ++cc) {
         const uint32_t o = (((uint32_t)m * (NF * NF) + a * NF + h) * 2 + cc) * kk;
 #pragma unroll
-        for (int j = 0; j < H; ++j) K[cc][j] = gld2(D->spec, o + t + T * j);
-        KN[cc] = gld2(D->spec, o + NR);
+        for (int j = 0; j < H; ++j) K[cc][j] = gld2(D.spec, o + t + T * j);
+        KN[cc] = gld2(D.spec, o + NR);
     }
 }
 
 template <int NU, int NF>
-__device__ inline void p2_issue(const DiscDev *D, int m, int h, int t, float2 (&sh)[FftShape<NU>::P / 2],
+__device__ inline void p2_issue(const DiscDev &D, int m, int h, int t, float2 (&sh)[FftShape<NU>::P / 2],
                                 float2 (&K)[NF][2][FftShape<NU>::P / 2], float2 (&KN)[NF][2])
 {
     p2_load_sh<NU>(D, m, h, t, sh);
@@ -197,7 +201,7 @@ __device__ inline void p2_issue(const DiscDev *D, int m, int h, int t, float2 (&
 //      first n_r outputs are stored.
 template <int NU, int NF, bool SF, int GM>
 __global__ void __launch_bounds__((P2Shape<NU, NF, GM>::WGS)) __attribute__((amdgpu_waves_per_eu(4)))
-k_pass2(const DiscDev *discs, const WJob *wj, int nj, const float2 *twu, int kc)
+k_pass2(const DiscDev *discs, const WJob *wj, int nj, const float2 *twu, int kc, OneDisc one)
 {
     using S = P2Shape<NU, NF, GM>;
     constexpr int P = S::P, T = S::T, H = P / 2;
@@ -213,11 +217,12 @@ k_pass2(const DiscDev *discs, const WJob *wj, int nj, const float2 *twu, int kc)
     // planes: F_h (forward / output r) and X_h (spectrum / output phi)
     const LdsPlane<float> pl[2] = {LdsPlane<float>{base + W * (2 * h)},
                                    LdsPlane<float>{base + W * (2 * h + 1)}};
-    const int cd = sg_uniform(wj[w].disc), cb = sg_uniform(wj[w].base), cn = sg_uniform(wj[w].n);
-    const DiscDev *D = discs + cd;
+    DiscDev D;
+    const WJob job = pass_job(discs, wj, one, w, S::G, D);
+    const int cb = job.base, cn = job.n;
     const int m = g < cn ? cb + g : cb;
     const bool pr = m == 0;  // columns 0 and n_phi/2 as one job
-    const int mm = pr ? D->nphi / 2 + 1 : m;
+    const int mm = pr ? D.nphi / 2 + 1 : m;
     // 1. loads (three or four groups: the spectra of one source at a time,
     //    the next source's loaded while the current one is multiplied)
     constexpr int KA = NF <= 2 ? NF : 1;
@@ -236,7 +241,7 @@ k_pass2(const DiscDev *discs, const WJob *wj, int nj, const float2 *twu, int kc)
     // target (see ind_add below).  Uniform branch: the whole workgroup takes
     // part in the reduction.
     float2 dr = make_float2(0.f, 0.f), dp = make_float2(0.f, 0.f);
-    const bool ind = (D->flags & SG_INDIRECT) && cb <= 1 && 1 < cb + cn;
+    const bool ind = (D.flags & SG_INDIRECT) && cb <= 1 && 1 < cb + cn;
     if (ind) {
         float2 ps = make_float2(0.f, 0.f);
 #pragma unroll
@@ -249,13 +254,13 @@ k_pass2(const DiscDev *discs, const WJob *wj, int nj, const float2 *twu, int kc)
             __syncthreads();
         }
         if (m == 1) {
-            const double half = SG_PI / D->nphi;  // dphi / 2
+            const double half = SG_PI / D.nphi;  // dphi / 2
             const double ce = cos(half), se = sin(half);
             double A = 0.0, B = 0.0;
 #pragma unroll
             for (int a = 0; a < NF; ++a) {
                 const float2 S = red[g * S::CT + a * T];
-                const double ca = D->ind[a];
+                const double ca = D.ind[a];
                 // c_a e^{i dphi/2} conj(S)
                 A += ca * (ce * S.x + se * S.y);
                 B += ca * (se * S.x - ce * S.y);
@@ -414,27 +419,27 @@ k_pass2(const DiscDev *discs, const WJob *wj, int nj, const float2 *twu, int kc)
         }
     }
     if (g < cn) {
-        const uint32_t fs = (uint32_t)sg_blk_field_elems(D->nphi, NR);
+        const uint32_t fs = (uint32_t)sg_blk_field_elems(D.nphi, NR);
         if (pr) {
             // y = g0 + i gN; the phi outputs of both columns are zero
-            const int mh = D->nphi / 2;
+            const int mh = D.nphi / 2;
             const uint32_t orr = (h * 2) * fs, op = (h * 2 + 1) * fs;
 #pragma unroll
             for (int p = 0; p < H; ++p) {
                 const float2 y = acc[0][p];
                 const uint32_t i0 = (uint32_t)sg_blk_index(0, t + T * p, NR);
                 const uint32_t i1 = (uint32_t)sg_blk_index(mh, t + T * p, NR);
-                gst2(D->gh, orr + i0, make_float2(y.x, 0.f));
-                gst2(D->gh, orr + i1, make_float2(y.y, 0.f));
-                gst2(D->gh, op + i0, make_float2(0.f, 0.f));
-                gst2(D->gh, op + i1, make_float2(0.f, 0.f));
+                gst2(D.gh, orr + i0, make_float2(y.x, 0.f));
+                gst2(D.gh, orr + i1, make_float2(y.y, 0.f));
+                gst2(D.gh, op + i0, make_float2(0.f, 0.f));
+                gst2(D.gh, op + i1, make_float2(0.f, 0.f));
             }
         } else {
 #pragma unroll
             for (int cc = 0; cc < 2; ++cc)
 #pragma unroll
                 for (int p = 0; p < H; ++p)
-                    gst2(D->gh, (h * 2 + cc) * fs + (uint32_t)sg_blk_index(m, t + T * p, NR), acc[cc][p]);
+                    gst2(D.gh, (h * 2 + cc) * fs + (uint32_t)sg_blk_index(m, t + T * p, NR), acc[cc][p]);
         }
     }
 }
@@ -445,7 +450,7 @@ k_pass2(const DiscDev *discs, const WJob *wj, int nj, const float2 *twu, int kc)
 // group's plane: z[m] = A[m] + i B[m], z[N - m] = conj A[m] + i conj B[m].
 template <int N, int NF, bool SF, int GM>
 __global__ void __launch_bounds__((PassShape<N, GM>::WGS))
-k_pass3(const DiscDev *discs, const WJob *wj, int nj, const float2 *twp, int kc)
+k_pass3(const DiscDev *discs, const WJob *wj, int nj, const float2 *twp, int kc, OneDisc one)
 {
     using S = PassShape<N, GM>;
     constexpr int P = S::P, T = S::T, G = S::G, W = LdsPlane<float>::elems(N);
@@ -454,9 +459,10 @@ k_pass3(const DiscDev *discs, const WJob *wj, int nj, const float2 *twp, int kc)
     const int g = threadIdx.x / T, t = threadIdx.x % T;
     const int w = sg_uniform(sg_xcd_remap(blockIdx.x, kc));
     if (w >= nj) return;
-    const int cd = sg_uniform(wj[w].disc), cb = sg_uniform(wj[w].base), cn = sg_uniform(wj[w].n);
-    const DiscDev *D = discs + cd;
-    const int nr = D->nr, nrp = sg_blk_rows(nr);
+    DiscDev D;
+    const WJob job = pass_job(discs, wj, one, w, G, D);
+    const int cb = job.base, cn = job.n;
+    const int nr = D.nr, nrp = sg_blk_rows(nr);
     const size_t fs = sg_blk_field_elems(N, nr);
     // 1. tile loads of the row quads into the planes
     for (int e = threadIdx.x; e < (G / 4) * NG * 8; e += S::WGS) {
@@ -464,7 +470,7 @@ k_pass3(const DiscDev *discs, const WJob *wj, int nj, const float2 *twp, int kc)
         if (4 * k >= cn) continue;
         const int j0 = cb + 4 * k;  // first job of the quad: same fluid for all 4
         const int b = j0 / nrp, i0 = j0 % nrp;
-        const float2 *A = D->gh + (size_t)(b * 2) * fs + sg_blk_tile(q, i0, nr) + 2 * l;
+        const float2 *A = D.gh + (size_t)(b * 2) * fs + sg_blk_tile(q, i0, nr) + 2 * l;
         float2 va[2], vb[2];
         gld2x2(A, va[0], va[1]);
         gld2x2(A + fs, vb[0], vb[1]);
@@ -494,15 +500,15 @@ k_pass3(const DiscDev *discs, const WJob *wj, int nj, const float2 *twp, int kc)
         const size_t o = (size_t)b * nr * N + (size_t)i * N;
 #pragma unroll
         for (int p = 0; p < P; ++p) {
-            gst1nt(D->gr + o, t + T * p, z[p].x);  // outputs: streamed past the caches
-            gst1nt(D->gp + o, t + T * p, z[p].y);
+            gst1nt(D.gr + o, t + T * p, z[p].x);  // outputs: streamed past the caches
+            gst1nt(D.gp + o, t + T * p, z[p].y);
         }
     }
 }
 
 // ------------------------------------------------------------- launching
 
-using KernelFn = void (*)(const DiscDev *, const WJob *, int, const float2 *, int);
+using KernelFn = void (*)(const DiscDev *, const WJob *, int, const float2 *, int, OneDisc);
 
 struct PassKernel {
     KernelFn fn;
@@ -604,6 +610,7 @@ struct Launch {
     int K;            // cluster size in use
     size_t wj_off;    // offset (in WJob units) into the workgroup-job table
     int nj;           // workgroup jobs of this launch
+    int jobs;         // jobs of its first disc (of a one-disc batch: all)
     int grid;         // workgroups (a multiple of 8 K)
     const float2 *tw; // twiddles of this launch's transform length
     int pass;
@@ -725,6 +732,7 @@ static bool make_launch(const sg_disc *discs, const Plan &P, const ClassSpec &c,
     }
     class_wjobs(discs, c, k.G, La.K, k.tb, wj);
     La.nj = (int)wj.size();
+    La.jobs = pass_jobs(discs[c.discs[0]], c.pass, k.tb);
     La.grid = launch_grid(La.nj, La.K);
     const DiscDev &D0 = P.discs[c.discs[0]];
     La.tw = c.pass == 2 ? D0.tw_u : D0.tw_phi;
@@ -802,7 +810,7 @@ static bool build_plan(const sg_disc *discs, int n, char *ws, Plan &P)
 }
 
 struct Cached {
-    void *dmem = nullptr;      // descriptors + jobs on the device
+    void *dmem = nullptr;      // descriptors + jobs on the device (none for a one-disc plan)
     hipGraphExec_t exec = nullptr;
     hipGraph_t graph = nullptr;
     uint64_t last_use = 0;
@@ -817,6 +825,25 @@ struct Cached {
 static std::mutex g_mu;
 static std::map<std::vector<uint64_t>, Cached *> g_cache;
 static uint64_t g_tick = 0;
+
+// Batches of one disc (without species) are cached by shape alone: nothing of
+// theirs is kept on the device, and each call fills the descriptor that its
+// launches take by value with the addresses it was given.  (With the radii,
+// on which the semi-spectral band and so the staged column depends.)
+static bool one_disc(const sg_disc *discs, int n) { return n == 1 && discs[0].n_species == 0; }
+
+static std::vector<uint64_t> shape_signature(const sg_disc &d)
+{
+    std::vector<uint64_t> k(6);
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    k[0] = (1ull << 40) | (uint64_t)dev;  // no batch signature has this length
+    k[1] = ((uint64_t)d.grid.n_r << 32) | (uint32_t)d.grid.n_phi;
+    k[2] = ((uint64_t)d.fluids.n_fluids << 32) | d.flags;
+    memcpy(&k[3], &d.grid.r_min, 8);
+    memcpy(&k[4], &d.grid.r_max, 8);
+    return k;
+}
 
 static std::vector<uint64_t> signature(const sg_disc *discs, int n, void *ws)
 {
@@ -844,9 +871,33 @@ static std::vector<uint64_t> signature(const sg_disc *discs, int n, void *ws)
 static sg_status launch_one(const DiscDev *dd, const WJob *wj, const Launch &L, hipStream_t s)
 {
     hipLaunchKernelGGL(L.k.fn, dim3(L.grid), dim3(L.k.wgs), (unsigned)L.lds, s, dd, wj + L.wj_off, L.nj, L.tw,
-                       L.K);
+                       L.K, OneDisc{});
     SG_HIP(hipGetLastError());
     return SG_OK;
+}
+
+// The descriptor of a one-disc call: its plan's, moved to the call's addresses.
+static OneDisc one_disc_at(const Cached &C, const sg_disc &d, void *ws)
+{
+    OneDisc o;
+    o.jobs = 0;
+    o.D = C.plan.discs[0];
+    const char *tb = (const char *)d.table;
+    auto move = [](auto &p, const void *base) {  // offsets within a table are never 0
+        if (p) p = (std::remove_reference_t<decltype(p)>)((const char *)base + (uintptr_t)p);
+    };
+    o.D.sigma = d.sigma;
+    o.D.gr = d.g_r;
+    o.D.gp = d.g_phi;
+    move(o.D.spec, tb);
+    move(o.D.dspec, tb);
+    move(o.D.tw_u, tb);
+    move(o.D.tw_phi, tb);
+    move(o.D.ind, tb);
+    move(o.D.modes, tb);
+    o.D.gh = (float2 *)((char *)ws + (uintptr_t)o.D.gh);
+    o.D.st = (float2 *)ws;
+    return o;
 }
 
 static const WJob *cached_wjobs(const Cached &C)
@@ -854,10 +905,32 @@ static const WJob *cached_wjobs(const Cached &C)
     return (const WJob *)((const char *)C.dmem + sg_align256(sizeof(DiscDev) * C.plan.discs.size()));
 }
 
-static sg_status enqueue(const Cached &C, hipStream_t s)
+// Launch L of a plan, of a one-disc plan with the call's descriptor; events
+// (may be null) take the kernel's own start and end.
+static sg_status launch_plan(const Cached &C, const OneDisc &one, const Launch &L, hipStream_t s,
+                             hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr)
+{
+    OneDisc o = one;
+    const DiscDev *dd = (const DiscDev *)C.dmem;
+    const WJob *wj = dd ? cached_wjobs(C) + L.wj_off : nullptr;
+    const float2 *tw = L.tw;
+    if (!dd) {
+        o.jobs = L.jobs;
+        tw = L.pass == 2 ? o.D.tw_u : o.D.tw_phi;
+    }
+    if (e0)
+        hipExtLaunchKernelGGL(L.k.fn, dim3(L.grid), dim3(L.k.wgs), (uint32_t)L.lds, s, e0, e1, 0, dd, wj, L.nj, tw,
+                              L.K, o);
+    else
+        hipLaunchKernelGGL(L.k.fn, dim3(L.grid), dim3(L.k.wgs), (unsigned)L.lds, s, dd, wj, L.nj, tw, L.K, o);
+    SG_HIP(hipGetLastError());
+    return SG_OK;
+}
+
+static sg_status enqueue(const Cached &C, const OneDisc &one, hipStream_t s)
 {
     for (const Launch &L : C.plan.launches) {
-        const sg_status st = launch_one((const DiscDev *)C.dmem, cached_wjobs(C), L, s);
+        const sg_status st = launch_plan(C, one, L, s);
         if (st != SG_OK) return st;
     }
     return SG_OK;
@@ -963,15 +1036,19 @@ static void destroy(Cached *C)
     delete C;
 }
 
-// Plan, device tables and graph of a batch signature (built on first use).
-// Caller holds g_mu.
-static sg_status get_cached(const sg_disc *discs, int n, void *ws, Cached *&out)
+// Plan, device tables and graph of a batch signature (built on first use), and
+// for a one-disc plan the call's descriptor.  Caller holds g_mu.
+static sg_status get_cached(const sg_disc *discs, int n, void *ws, Cached *&out, OneDisc &one)
 {
-    auto key = signature(discs, n, ws);
+    const bool single = one_disc(discs, n);
+    sg_disc at0 = discs[0];  // a one-disc plan holds offsets
+    at0.table = nullptr;
+    auto key = single ? shape_signature(discs[0]) : signature(discs, n, ws);
     auto it = g_cache.find(key);
     if (it != g_cache.end()) {
         out = it->second;
         out->last_use = ++g_tick;
+        if (single) one = one_disc_at(*out, discs[0], ws);
         return SG_OK;
     }
     if (g_cache.size() >= SG_CACHE_MAX) {
@@ -984,9 +1061,15 @@ static sg_status get_cached(const sg_disc *discs, int n, void *ws, Cached *&out)
     }
     Cached *C = new Cached;
     C->last_use = ++g_tick;
-    if (!build_plan(discs, n, (char *)ws, C->plan)) {
+    if (!build_plan(single ? &at0 : discs, n, single ? nullptr : (char *)ws, C->plan)) {
         delete C;
         return SG_ERR_UNSUPPORTED;
+    }
+    if (single) {
+        g_cache[key] = C;
+        out = C;
+        one = one_disc_at(*C, discs[0], ws);
+        return SG_OK;
     }
     const size_t bd = sg_align256(sizeof(DiscDev) * n);
     const size_t bytes = bd + sizeof(WJob) * C->plan.wjobs.size();
@@ -1029,13 +1112,14 @@ sg_status sg_fft_run(const sg_disc *discs, int n, void *ws, hipStream_t s)
 {
     std::lock_guard<std::mutex> lk(g_mu);
     Cached *C = nullptr;
-    const sg_status st = get_cached(discs, n, ws, C);
+    OneDisc one;
+    const sg_status st = get_cached(discs, n, ws, C, one);
     if (st != SG_OK) return st;
     if (C->exec) {
         SG_HIP(hipGraphLaunch(C->exec, s));
         return SG_OK;
     }
-    return enqueue(*C, s);
+    return enqueue(*C, one, s);
 }
 
 // One step, every launch in plan order with a start and a stop event
@@ -1043,21 +1127,15 @@ sg_status sg_fft_run(const sg_disc *discs, int n, void *ws, hipStream_t s)
 // kernel's own start and end, not a marker between launches), with nothing
 // run before it: a caller that evicts the caches first times a cold step.
 // ms[p] = the summed kernel time of pass p's launches.
-static sg_status profile_one_step(const Cached &C, hipStream_t s, float *ms)
+static sg_status profile_one_step(const Cached &C, const OneDisc &one, hipStream_t s, float *ms)
 {
     const size_t nl = C.plan.launches.size();
     std::vector<hipEvent_t> ev(2 * nl, nullptr);
     sg_status st = SG_OK;
     for (auto &e : ev)
         if (st == SG_OK && hipEventCreate(&e) != hipSuccess) st = SG_ERR_HIP;
-    const DiscDev *dd = (const DiscDev *)C.dmem;
-    const WJob *wj = cached_wjobs(C);
-    for (size_t i = 0; i < nl && st == SG_OK; ++i) {
-        const Launch &L = C.plan.launches[i];
-        hipExtLaunchKernelGGL(L.k.fn, dim3(L.grid), dim3(L.k.wgs), (uint32_t)L.lds, s, ev[2 * i],
-                              ev[2 * i + 1], 0, dd, wj + L.wj_off, L.nj, L.tw, L.K);
-        if (hipGetLastError() != hipSuccess) st = SG_ERR_HIP;
-    }
+    for (size_t i = 0; i < nl && st == SG_OK; ++i)
+        st = launch_plan(C, one, C.plan.launches[i], s, ev[2 * i], ev[2 * i + 1]);
     if (st == SG_OK && nl && hipEventSynchronize(ev[2 * nl - 1]) != hipSuccess) st = SG_ERR_HIP;
     for (int p = 0; p < 3; ++p) ms[p] = 0.f;
     for (size_t i = 0; i < nl && st == SG_OK; ++i) {
@@ -1081,10 +1159,11 @@ sg_status sg_fft_profile(const sg_disc *discs, int n, void *ws, hipStream_t s, i
 {
     std::lock_guard<std::mutex> lk(g_mu);
     Cached *C = nullptr;
-    sg_status st = get_cached(discs, n, ws, C);
+    OneDisc one;
+    sg_status st = get_cached(discs, n, ws, C, one);
     if (st != SG_OK) return st;
-    if (reps == 1) return profile_one_step(*C, s, ms);
-    st = enqueue(*C, s);
+    if (reps == 1) return profile_one_step(*C, one, s, ms);
+    st = enqueue(*C, one, s);
     if (st != SG_OK) return st;
     hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
     for (auto &e : ev) SG_HIP(hipEventCreate(&e));
@@ -1092,7 +1171,7 @@ sg_status sg_fft_profile(const sg_disc *discs, int n, void *ws, hipStream_t s, i
         if (pass == 1 && hipEventRecord(ev[0], s) != hipSuccess) st = SG_ERR_HIP;
         for (int r = 0; r < reps && st == SG_OK; ++r)
             for (const Launch &L : C->plan.launches)
-                if (L.pass == pass && st == SG_OK) st = launch_one((const DiscDev *)C->dmem, cached_wjobs(*C), L, s);
+                if (L.pass == pass && st == SG_OK) st = launch_plan(*C, one, L, s);
         if (st == SG_OK && hipEventRecord(ev[pass], s) != hipSuccess) st = SG_ERR_HIP;
     }
     if (st == SG_OK && hipEventSynchronize(ev[3]) != hipSuccess) st = SG_ERR_HIP;

@@ -126,6 +126,12 @@ __device__ inline void gst2x2(float2 *p, float2 a, float2 b)
 
 // Forces a value that is equal in all lanes into a scalar register.
 __device__ inline int sg_uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+template <typename P> __device__ inline P *sg_uniform(P *p)
+{
+    const uint64_t v = (uint64_t)p;
+    const uint32_t lo = (uint32_t)sg_uniform((int)(uint32_t)v), hi = (uint32_t)sg_uniform((int)(uint32_t)(v >> 32));
+    return (P *)(((uint64_t)hi << 32) | lo);
+}
 
 // ------------------------------------------------------------ table layout
 // Device kernel-table layout (all offsets 256-byte aligned, computable on the

@@ -872,20 +872,21 @@ __device__ inline void ss_ld4(const float2 *p, uint32_t i, float2 &x, float2 &y)
 // by reading the table.
 template <int NF, int V, int S, bool NT, int U>
 __global__ void __launch_bounds__(256) k_ss_pass(const DiscDev *discs, const WJob *wj, int nj, const float2 *,
-                                                 int kc)
+                                                 int kc, OneDisc one)
 {
     extern __shared__ __attribute__((aligned(16))) float2 ssh[];
     constexpr int LN = 256 / S, TB = LN * V;
     static_assert(V % 2 == 0, "targets per lane come in 16-byte pairs");
     const int w = sg_uniform(sg_xcd_remap(blockIdx.x, kc));
     if (w >= nj) return;
-    if (sg_uniform(wj[w].n) == 0) return;  // cluster padding
-    const int cd = sg_uniform(wj[w].disc), idx = sg_uniform(wj[w].base);
-    const DiscDev *D = discs + cd;
-    const int nr = D->nr, nrt = (nr + 1) & ~1, nb = (nr + TB - 1) / TB;
+    DiscDev D;
+    const WJob job = pass_job(discs, wj, one, w, 1, D);
+    if (job.n == 0) return;  // cluster padding
+    const int idx = job.base;
+    const int nr = D.nr, nrt = (nr + 1) & ~1, nb = (nr + TB - 1) / TB;
     const int blk = idx % nb, mb = idx / nb, b = mb % NF, m = mb / NF;
-    const size_t fs = sg_blk_field_elems(D->nphi, nr);
-    const SsMode md = D->modes[m];
+    const size_t fs = sg_blk_field_elems(D.nphi, nr);
+    const SsMode md = D.modes[m];
     const bool banded = sg_uniform(md.banded) != 0;
     const int bw = banded ? sg_uniform(md.w) : 0;
     // staged sources: a full mode's whole column, a banded mode's window
@@ -893,10 +894,10 @@ __global__ void __launch_bounds__(256) k_ss_pass(const DiscDev *discs, const WJo
     const int cs = banded ? TB + 2 * bw + 4 : nr;
     const int nk = banded ? 2 * bw + 1 : nr;        // operator rows per (b, a)
     const int base = banded ? blk * TB - bw : 0;
-    if (banded && bw > D->ss_wmax) return;  // table not built for this grid: never overrun the LDS
+    if (banded && bw > D.ss_wmax) return;  // table not built for this grid: never overrun the LDS
     for (int e = threadIdx.x; e < NF * cs; e += 256) {
         const int a = e / cs, ip = e - a * cs + base;
-        ssh[e] = (ip >= 0 && ip < nr) ? gld2(D->st + a * fs, (uint32_t)sg_blk_index(m, ip, nr))
+        ssh[e] = (ip >= 0 && ip < nr) ? gld2(D.st + a * fs, (uint32_t)sg_blk_index(m, ip, nr))
                                       : make_float2(0.f, 0.f);
     }
     __syncthreads();
@@ -913,7 +914,7 @@ __global__ void __launch_bounds__(256) k_ss_pass(const DiscDev *discs, const WJo
     float2 ar[V], ap[V];
 #pragma unroll
     for (int v = 0; v < V; ++v) ar[v] = ap[v] = make_float2(0.f, 0.f);
-    const float2 *C = D->spec + md.off;
+    const float2 *C = D.spec + md.off;
     for (int a = 0; a < NF; ++a) {
         const float2 *Tm = C + (size_t)(b * NF + a) * nk * nrt;
         const float2 *sa = ssh + a * cs;
@@ -975,7 +976,7 @@ __global__ void __launch_bounds__(256) k_ss_pass(const DiscDev *discs, const WJo
                 ap[v].y += y.y;
             }
     }
-    float2 *gr = D->gh + (size_t)(b * 2) * fs, *gp = gr + fs;
+    float2 *gr = D.gh + (size_t)(b * 2) * fs, *gp = gr + fs;
 #pragma unroll
     for (int v = 0; v < V; ++v) {
         const int i = i0 + v;
