@@ -33,6 +33,7 @@ struct AdjDev {
     float2 *st;     // Sigma~ [F][blk]  (for dh)
     float2 *dt;     // dSigma~ [F][blk]
     double *part;   // [ncol][F] dh partials
+    double *dh;     // dL/dh (null: not wanted)
     int count;      // jobs of the launch
 };
 
@@ -54,26 +55,6 @@ __device__ inline int adj_job(int G, int K, int g, bool &whole_invalid, int coun
     const int idx = wl * G + g;
     valid = idx < count;
     return idx;
-}
-
-// pass 1 on lam: job (b, i): z = lam_r[b][i] + i lam_phi[b][i]
-template <int N>
-__global__ void __launch_bounds__(AdjShape<N>::WGS) k_adj_lam(AdjDev A)
-{
-    using S = AdjShape<N>;
-    constexpr int W = LdsPlane<float>::elems(N);
-    __shared__ __attribute__((aligned(16))) float2 lds[W * S::G];
-    const int g = threadIdx.x / S::T, t = threadIdx.x % S::T;
-    bool none, valid;
-    const int idx = adj_job(S::G, S::K, g, none, A.count, valid);
-    if (none) return;
-    LdsPlane<float> pl{lds + W * g};
-    const int nr = A.D.nr;
-    const int b = valid ? idx / nr : 0, i = valid ? idx % nr : 0;
-    const size_t fs = sg_blk_field_elems(N, nr);
-    const size_t row = (size_t)b * nr * N + (size_t)i * N;
-    phi_fwd_pair<N>(A.lam_r + row, A.lam_p + row, A.lt + (b * 2 + 0) * fs, i,
-                    A.lt + (b * 2 + 1) * fs, i, nr, TwTable{A.D.tw_phi}, t, pl, valid);
 }
 
 // Row pairs of the phi transforms of Sigma (adjoint pass 1) and dSigma (pass
@@ -99,9 +80,11 @@ template <int NF> __device__ inline void adj_pair(int j, int nr, int &f1, int &f
     }
 }
 
-// pass 1 on Sigma (only when dh is requested)
+// pass 1, both inputs in one launch: job (b, i) < NF n_r transforms
+// lam_r[b][i] + i lam_phi[b][i]; the jobs beyond (only when dh is requested)
+// transform Sigma row pairs.
 template <int N, int NF>
-__global__ void __launch_bounds__(AdjShape<N>::WGS) k_adj_sig(AdjDev A)
+__global__ void __launch_bounds__(AdjShape<N>::WGS) k_adj_fwd(AdjDev A)
 {
     using S = AdjShape<N>;
     constexpr int W = LdsPlane<float>::elems(N);
@@ -111,18 +94,185 @@ __global__ void __launch_bounds__(AdjShape<N>::WGS) k_adj_sig(AdjDev A)
     const int idx = adj_job(S::G, S::K, g, none, A.count, valid);
     if (none) return;
     LdsPlane<float> pl{lds + W * g};
-    const int nr = A.D.nr;
+    TwReg<N> tw;
+    tw.load(A.D.tw_phi, t);
+    const int nr = A.D.nr, nl = NF * nr;
     const size_t fs = sg_blk_field_elems(N, nr);
     const size_t plane = (size_t)nr * N;
     const int j = valid ? idx : 0;
-    int f1, f2, i1, i2;
-    adj_pair<NF>(j, nr, f1, f2, i1, i2);
-    phi_fwd_pair<N>(A.D.sigma + f1 * plane + (size_t)i1 * N, A.D.sigma + f2 * plane + (size_t)i2 * N,
-                    A.st + f1 * fs, i1, A.st + f2 * fs, i2, nr, TwTable{A.D.tw_phi}, t, pl, valid);
+    const float *x1, *x2;
+    float2 *d1, *d2;
+    int i1, i2;
+    if (j < nl) {
+        const int b = j / nr;
+        i1 = i2 = j - b * nr;
+        x1 = A.lam_r + (size_t)j * N;
+        x2 = A.lam_p + (size_t)j * N;
+        d1 = A.lt + (b * 2 + 0) * fs;
+        d2 = A.lt + (b * 2 + 1) * fs;
+    } else {
+        int f1, f2;
+        adj_pair<NF>(j - nl, nr, f1, f2, i1, i2);
+        x1 = A.D.sigma + f1 * plane + (size_t)i1 * N;
+        x2 = A.D.sigma + f2 * plane + (size_t)i2 * N;
+        d1 = A.st + f1 * fs;
+        d2 = A.st + f2 * fs;
+    }
+    phi_fwd_pair<N>(x1, x2, d1, i1, d2, i2, nr, tw, t, pl, valid);
 }
 
-// pass 2: column m.  dSigma^_a = sum_{b,c} conj(K'_c^{ab}) lam^_{b,c}; with DH,
-// also the Parseval partials of lam^ against D' Sigma^ for this column.
+// Pass 2 with the transforms of a column side by side: 2 NF slots of T threads
+// per column, slot (b, c) transforms lam_{b,c} and keeps lam^ in registers;
+// through LDS slot a < NF gathers dSigma^_a = sum_{b,c} conj(K'_c^{ab}) lam^
+// and transforms it back while slot NF + a transforms Sigma_a; its spectrum
+// then goes through LDS to all slots, each of which adds its own (b, c) to
+// the Parseval sums.  The inverse transform is taken as the conjugate of the
+// forward transform of the conjugate, so that both run the same instructions.
+//
+// A column is a chain of 3 NF transforms when one group does them in turn
+// (k_adj_col below), which bounds grids of few columns: they leave the chip
+// idle and each transform is a chain of exchanges and spectrum reads.  Here
+// the chain is two transforms, with twiddles and spectra loaded ahead of them.
+// Whole adjoint with dL/dh, before -> now: 256 x 128 two-fluid 41 -> 15 us,
+// 256 x 512 46 -> 20, four fluids 64 x 128 132 -> 17, 512 x 512 208 -> 135.
+template <int NU, int NF> struct AdjSlots {
+    static constexpr int P = FftShape<NU>::P;
+    static constexpr int T = FftShape<NU>::T;
+    static constexpr int SL = 2 * NF;            // slots of a column
+    static constexpr int CT = SL * T;            // threads of a column
+    static constexpr bool FITS = CT <= 1024;
+    static constexpr int G = CT < 256 ? 256 / CT : 1;
+    static constexpr int WGS = CT * G;
+    static constexpr int K = G >= 4 ? 1 : 4 / G;
+    static constexpr int SUB = T < 64 ? T : 64;  // lanes of a partial sum
+};
+
+template <int NU, int NF, bool DH>
+__global__ void __launch_bounds__((AdjSlots<NU, NF>::WGS)) k_adj_col_slots(AdjDev A)
+{
+    using S = AdjSlots<NU, NF>;
+    constexpr int P = S::P, T = S::T, G = S::G, SL = S::SL;
+    constexpr int W = LdsPlane<float>::elems(NU);
+    constexpr int NR = NU / 2;
+    constexpr int NS = S::CT / S::SUB;
+    constexpr bool AHEAD = S::WGS <= 512;  // registers for spectra in flight
+    __shared__ __attribute__((aligned(16))) float2 lds[W * SL * G];
+    __shared__ double red[DH ? G * NS * NF : 1];
+    const int g = threadIdx.x / S::CT, u = threadIdx.x % S::CT;
+    const int slot = T >= 64 ? sg_uniform(u / T) : u / T, t = u % T;
+    const int wl = sg_xcd_remap(blockIdx.x, S::K);
+    if (wl * G >= A.count) return;
+    const int m = wl * G + g;
+    const bool valid = m < A.count;
+    const int mm = valid ? m : 0;
+    float2 *const col0 = lds + W * SL * g;  // the column's planes, one a slot
+    const LdsPlane<float> pl{col0 + W * slot};
+    const size_t fs = sg_blk_field_elems(A.D.nphi, NR);
+    const size_t kk = NR + 1;
+    const float2 *col = A.D.spec + (size_t)mm * (NF * NF) * 2 * kk;
+    const float2 *dcol = DH ? A.D.dspec + (size_t)mm * (NF * NF) * 4 * kk : nullptr;
+    const int b = slot >> 1, c = slot & 1;
+
+    TwReg<NU> tw;
+    tw.load(A.D.tw_u, t);
+    float2 lh[P], v[P], Kv[AHEAD ? SL : 1][P];
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+        lh[p] = p < P / 2 ? gload2(A.lt + slot * fs, sg_blk_index(mm, t + T * p, NR)) : make_float2(0.f, 0.f);
+#pragma unroll
+    for (int p = 0; p < P; ++p) v[p] = make_float2(0.f, 0.f);
+    if (slot < NF) {
+        if constexpr (AHEAD)
+#pragma unroll
+            for (int q = 0; q < SL; ++q)
+#pragma unroll
+                for (int p = 0; p < P; ++p)
+                    Kv[q][p] = kspec_g<NU>(col + ((slot * NF + (q >> 1)) * 2 + (q & 1)) * kk, t + T * p, q & 1);
+    } else if constexpr (DH) {
+#pragma unroll
+        for (int p = 0; p < P / 2; ++p) v[p] = gload2(A.st + (slot - NF) * fs, sg_blk_index(mm, t + T * p, NR));
+    }
+    fft<NU, false>(lh, t, pl, tw);
+#pragma unroll
+    for (int p = 0; p < P; ++p) pl.st(t + T * p, lh[p]);
+    __syncthreads();
+    if (slot < NF) {
+#pragma unroll
+        for (int q = 0; q < SL; ++q) {
+            const LdsPlane<float> x{col0 + W * q};
+#pragma unroll
+            for (int p = 0; p < P; ++p) {
+                // conj(K) * lam^, the result conjugated
+                const float2 K = AHEAD ? Kv[AHEAD ? q : 0][p]
+                                       : kspec_g<NU>(col + ((slot * NF + (q >> 1)) * 2 + (q & 1)) * kk, t + T * p,
+                                                     q & 1);
+                const float2 l = x.ld(t + T * p);
+                v[p].x += K.x * l.x + K.y * l.y;
+                v[p].y -= K.x * l.y - K.y * l.x;
+            }
+        }
+    }
+    float2 Dv[DH && AHEAD ? NF * 2 : 1][P];
+    if constexpr (DH && AHEAD)
+#pragma unroll
+        for (int e = 0; e < NF * 2; ++e)
+#pragma unroll
+            for (int p = 0; p < P; ++p)
+                Dv[e][p] = kspec_g<NU>(dcol + ((((e >> 1) * NF + b) * 2 + (e & 1)) * 2 + c) * kk, t + T * p, c);
+    __syncthreads();
+    fft<NU, false>(v, t, pl, tw);
+    if (slot < NF && valid) {
+#pragma unroll
+        for (int p = 0; p < P / 2; ++p)
+            gstore2(A.dt + slot * fs, sg_blk_index(mm, t + T * p, NR), make_float2(v[p].x, -v[p].y));
+    }
+    if constexpr (DH) {
+        if (slot >= NF) {
+#pragma unroll
+            for (int p = 0; p < P; ++p) pl.st(t + T * p, v[p]);
+        }
+        __syncthreads();
+        double src[NF], tgt = 0.0;  // d = 0: to the source fluid, d = 1: to the target
+#pragma unroll
+        for (int a = 0; a < NF; ++a) {
+            src[a] = 0.0;
+            const LdsPlane<float> x{col0 + W * (NF + a)};
+#pragma unroll
+            for (int p = 0; p < P; ++p) {
+                const float2 sh = x.ld(t + T * p);
+                const double lr = lh[p].x, li = lh[p].y, sr = sh.x, si = sh.y;
+#pragma unroll
+                for (int d = 0; d < 2; ++d) {
+                    // q = D' Sigma^ ; Re(conj(lam^) q)
+                    const float2 Dk = AHEAD ? Dv[AHEAD ? a * 2 + d : 0][p]
+                                            : kspec_g<NU>(dcol + (((a * NF + b) * 2 + d) * 2 + c) * kk, t + T * p, c);
+                    const double qr = Dk.x * sr - Dk.y * si, qi = Dk.x * si + Dk.y * sr;
+                    (d == 0 ? src[a] : tgt) += lr * qr + li * qi;
+                }
+            }
+        }
+        const double wm = !valid ? 0.0 : (mm == 0 || mm == A.D.nphi / 2) ? 1.0 : 2.0;
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            double x = src[f] + (f == b ? tgt : 0.0);
+#pragma unroll
+            for (int o = S::SUB / 2; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+            if (u % S::SUB == 0) red[(g * NS + u / S::SUB) * NF + f] = wm * x;
+        }
+        __syncthreads();
+        if (u < NF && valid) {
+            double x = 0.0;
+            for (int w = 0; w < NS; ++w) x += red[(g * NS + w) * NF + u];
+            A.part[(size_t)m * NF + u] = x;
+        }
+    }
+}
+
+// pass 2, a column's transforms in turn (one group of T threads holds them
+// all): dSigma^_a = sum_{b,c} conj(K'_c^{ab}) lam^_{b,c}; with DH, also the
+// Parseval partials of lam^ against D' Sigma^ for this column.  Twiddles in
+// registers and unconditional loads: 1024 x 2048 two-fluid adjoint 117 -> 72
+// us, with dL/dh 269 -> 150.
 template <int NU, int NF, bool DH>
 __global__ void __launch_bounds__(AdjShape<NU>::WGS) k_adj_col(AdjDev A)
 {
@@ -137,7 +287,8 @@ __global__ void __launch_bounds__(AdjShape<NU>::WGS) k_adj_col(AdjDev A)
     const int m = adj_job(G, S::K, g, none, A.count, valid);
     if (none) return;
     LdsPlane<float> pl{lds + W * g};
-    const TwTable tw{A.D.tw_u};
+    TwReg<NU> tw;
+    tw.load(A.D.tw_u, t);
     const size_t fs = sg_blk_field_elems(A.D.nphi, NR);
     const int mm = valid ? m : 0;
 
@@ -149,8 +300,7 @@ __global__ void __launch_bounds__(AdjShape<NU>::WGS) k_adj_col(AdjDev A)
 #pragma unroll
             for (int p = 0; p < P; ++p) {
                 lh[b][c][p] = make_float2(0.f, 0.f);
-                if (valid && p < P / 2)
-                    lh[b][c][p] = A.lt[(b * 2 + c) * fs + sg_blk_index(mm, t + T * p, NR)];
+                if (p < P / 2) lh[b][c][p] = gload2(A.lt + (b * 2 + c) * fs, sg_blk_index(mm, t + T * p, NR));
             }
             fft<NU, false>(lh[b][c], t, pl, tw);
         }
@@ -168,7 +318,7 @@ __global__ void __launch_bounds__(AdjShape<NU>::WGS) k_adj_col(AdjDev A)
 #pragma unroll
                 for (int c = 0; c < 2; ++c) {
                     // conj(K) * lam^
-                    const float2 K = kspec<NU>(col + ((a * NF + b) * 2 + c) * kk, k, c);
+                    const float2 K = kspec_g<NU>(col + ((a * NF + b) * 2 + c) * kk, k, c);
                     acc[p].x += K.x * lh[b][c][p].x + K.y * lh[b][c][p].y;
                     acc[p].y += K.x * lh[b][c][p].y - K.y * lh[b][c][p].x;
                 }
@@ -191,7 +341,7 @@ __global__ void __launch_bounds__(AdjShape<NU>::WGS) k_adj_col(AdjDev A)
 #pragma unroll
             for (int p = 0; p < P; ++p) {
                 sh[p] = make_float2(0.f, 0.f);
-                if (valid && p < P / 2) sh[p] = A.st[a * fs + sg_blk_index(mm, t + T * p, NR)];
+                if (p < P / 2) sh[p] = gload2(A.st + a * fs, sg_blk_index(mm, t + T * p, NR));
             }
             fft<NU, false>(sh, t, pl, tw);
 #pragma unroll
@@ -207,7 +357,7 @@ __global__ void __launch_bounds__(AdjShape<NU>::WGS) k_adj_col(AdjDev A)
 #pragma unroll
                         for (int d = 0; d < 2; ++d) {
                             const float2 Dk =
-                                kspec<NU>(dcol + (((a * NF + b) * 2 + d) * 2 + c) * kk, k, c);
+                                kspec_g<NU>(dcol + (((a * NF + b) * 2 + d) * 2 + c) * kk, k, c);
                             const double qr = Dk.x * sr - Dk.y * si, qi = Dk.x * si + Dk.y * sr;
                             const double v = lr * qr + li * qi;
                             dh[d == 0 ? a : b] += v;
@@ -249,7 +399,12 @@ __global__ void __launch_bounds__(AdjShape<NU>::WGS) k_adj_col_many(AdjDev A)
     const int m = adj_job(G, S::K, g, none, A.count, valid);
     if (none) return;
     LdsPlane<float> pl{lds + W * g};
-    const TwTable tw{A.D.tw_u};
+    // The widest form without dh has no registers for twiddles and spectra in
+    // flight (1024 x 256: 66 us, with them 86).
+    constexpr bool LEAN = NF == 4 && !DH;
+    std::conditional_t<LEAN, TwTable, TwReg<NU>> tw;
+    if constexpr (LEAN) tw.tab = A.D.tw_u;
+    else tw.load(A.D.tw_u, t);
     const size_t fs = sg_blk_field_elems(A.D.nphi, NR);
     const int mm = valid ? m : 0;
     const size_t kk = NR + 1;
@@ -269,7 +424,7 @@ __global__ void __launch_bounds__(AdjShape<NU>::WGS) k_adj_col_many(AdjDev A)
 #pragma unroll
             for (int p = 0; p < P; ++p) {
                 lh[p] = make_float2(0.f, 0.f);
-                if (valid && p < P / 2) lh[p] = A.lt[(b * 2 + c) * fs + sg_blk_index(mm, t + T * p, NR)];
+                if (p < P / 2) lh[p] = gload2(A.lt + (b * 2 + c) * fs, sg_blk_index(mm, t + T * p, NR));
             }
             fft<NU, false>(lh, t, pl, tw);
 #pragma unroll
@@ -277,7 +432,8 @@ __global__ void __launch_bounds__(AdjShape<NU>::WGS) k_adj_col_many(AdjDev A)
 #pragma unroll
                 for (int p = 0; p < P; ++p) {
                     // conj(K) * lam^
-                    const float2 K = kspec<NU>(col + ((a * NF + b) * 2 + c) * kk, t + T * p, c);
+                    const float2 *kc = col + ((a * NF + b) * 2 + c) * kk;
+                    const float2 K = LEAN ? kspec<NU>(kc, t + T * p, c) : kspec_g<NU>(kc, t + T * p, c);
                     acc[a][p].x += K.x * lh[p].x + K.y * lh[p].y;
                     acc[a][p].y += K.x * lh[p].y - K.y * lh[p].x;
                 }
@@ -287,7 +443,7 @@ __global__ void __launch_bounds__(AdjShape<NU>::WGS) k_adj_col_many(AdjDev A)
 #pragma unroll
                     for (int p = 0; p < P; ++p) {
                         sh[p] = make_float2(0.f, 0.f);
-                        if (valid && p < P / 2) sh[p] = A.st[a * fs + sg_blk_index(mm, t + T * p, NR)];
+                        if (p < P / 2) sh[p] = gload2(A.st + a * fs, sg_blk_index(mm, t + T * p, NR));
                     }
                     fft<NU, false>(sh, t, pl, tw);
 #pragma unroll
@@ -298,7 +454,7 @@ __global__ void __launch_bounds__(AdjShape<NU>::WGS) k_adj_col_many(AdjDev A)
                         const double sr = sh[p].x, si = sh[p].y;
 #pragma unroll
                         for (int d = 0; d < 2; ++d) {
-                            const float2 Dk = kspec<NU>(dcol + (((a * NF + b) * 2 + d) * 2 + c) * kk, k, c);
+                            const float2 Dk = kspec_g<NU>(dcol + (((a * NF + b) * 2 + d) * 2 + c) * kk, k, c);
                             const double qr = Dk.x * sr - Dk.y * si, qi = Dk.x * si + Dk.y * sr;
                             const double v = lr * qr + li * qi;
                             if (d == 0) dh[a] += v;
@@ -427,43 +583,53 @@ __global__ void __launch_bounds__(256) k_ss_adj_band(AdjDev A, int m0, int ncol)
     if (ip < nr) A.dt[a * fs + sg_blk_index(m, ip, nr)] = acc;
 }
 
-// pass 3: inverse phi transform of dSigma~ pairs (as the forward pass 1 pairing)
+// pass 3: inverse phi transform of dSigma~ pairs (as the forward pass 1
+// pairing).  With dh one more workgroup, the last, adds the columns' Parseval
+// partials (in a fixed order), which were a launch of their own.
 template <int N, int NF>
 __global__ void __launch_bounds__(AdjShape<N>::WGS) k_adj_out(AdjDev A)
 {
     using S = AdjShape<N>;
     constexpr int W = LdsPlane<float>::elems(N);
     __shared__ __attribute__((aligned(16))) float2 lds[W * S::G];
+    if (A.dh && blockIdx.x == gridDim.x - 1) {
+        __shared__ double red[S::WGS / 64 * NF];
+        const int ncol = N / 2 + 1;
+        double x[NF];
+#pragma unroll
+        for (int f = 0; f < NF; ++f) x[f] = 0.0;
+        for (int m = threadIdx.x; m < ncol; m += S::WGS)
+#pragma unroll
+            for (int f = 0; f < NF; ++f) x[f] += A.part[(size_t)m * NF + f];
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) x[f] += __shfl_xor(x[f], o, 64);
+            if (threadIdx.x % 64 == 0) red[threadIdx.x / 64 * NF + f] = x[f];
+        }
+        __syncthreads();
+        if (threadIdx.x < NF) {
+            double y = 0.0;
+            for (int w = 0; w < S::WGS / 64; ++w) y += red[w * NF + threadIdx.x];
+            A.dh[threadIdx.x] = y;
+        }
+        return;
+    }
     const int g = threadIdx.x / S::T, t = threadIdx.x % S::T;
     bool none, valid;
     const int idx = adj_job(S::G, S::K, g, none, A.count, valid);
     if (none) return;
     LdsPlane<float> pl{lds + W * g};
+    TwReg<N> tw;
+    tw.load(A.D.tw_phi, t);
     const int nr = A.D.nr;
     const size_t fs = sg_blk_field_elems(N, nr);
     const size_t plane = (size_t)nr * N;
     const int j = valid ? idx : 0;
     int f1, f2, i1, i2;
     adj_pair<NF>(j, nr, f1, f2, i1, i2);
-    phi_inv_pair<N>(A.dt + f1 * fs, i1, A.dt + f2 * fs, i2, nr, TwTable{A.D.tw_phi},
-                    A.dsig + f1 * plane + (size_t)i1 * N, A.dsig + f2 * plane + (size_t)i2 * N, t, pl, valid);
-}
-
-__global__ void k_adj_dh_reduce(const double *part, int ncol, int nf, double *dh)
-{
-    __shared__ double red[256];
-    for (int f = 0; f < nf; ++f) {
-        double s = 0.0;
-        for (int m = threadIdx.x; m < ncol; m += blockDim.x) s += part[(size_t)m * nf + f];
-        red[threadIdx.x] = s;
-        __syncthreads();
-        for (int w = blockDim.x / 2; w > 0; w >>= 1) {
-            if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) dh[f] = red[0];
-        __syncthreads();
-    }
+    phi_inv_pair<N>(A.dt + f1 * fs, i1, A.dt + f2 * fs, i2, nr, tw, A.dsig + f1 * plane + (size_t)i1 * N,
+                    A.dsig + f2 * plane + (size_t)i2 * N, t, pl, valid);
 }
 
 // ------------------------------------------------------------------- host
@@ -698,73 +864,84 @@ static sg_status adjoint_species(const sg_disc &d, const float *lam_r, const flo
     return SG_OK;
 }
 
-template <int N> static int nwg_for(int count)
+template <class S> static int adj_grid(int count)
 {
-    using S = AdjShape<N>;
-    int nwg = (count + S::G - 1) / S::G;
-    const int q = 8 * S::K;
+    const int nwg = (count + S::G - 1) / S::G, q = 8 * S::K;
     return (nwg + q - 1) / q * q;
 }
 
-template <int NPHI, int NU, int NF>
-static sg_status adj_launch(AdjDev A, bool dh, double *d_dh, int ncol, hipStream_t s)
+template <int NPHI, int NF> static sg_status adj_fwd(AdjDev A, bool dh, hipStream_t s)
 {
-    const int nr = A.D.nr;
-    A.count = NF * nr;
-    hipLaunchKernelGGL(k_adj_lam<NPHI>, dim3(nwg_for<NPHI>(A.count)), dim3(AdjShape<NPHI>::WGS), 0,
-                       s, A);
+    using S = AdjShape<NPHI>;
+    A.count = NF * A.D.nr + (dh ? adj_pairs<NF>(A.D.nr) : 0);
+    hipLaunchKernelGGL((k_adj_fwd<NPHI, NF>), dim3(adj_grid<S>(A.count)), dim3(S::WGS), 0, s, A);
     SG_HIP(hipGetLastError());
-    const int pairs = adj_pairs<NF>(nr);
-    if (dh) {
-        A.count = pairs;
-        hipLaunchKernelGGL((k_adj_sig<NPHI, NF>), dim3(nwg_for<NPHI>(pairs)),
-                           dim3(AdjShape<NPHI>::WGS), 0, s, A);
-        SG_HIP(hipGetLastError());
-    }
-    A.count = ncol;
-    if constexpr (NF <= 2) {
-        if (dh)
-            hipLaunchKernelGGL((k_adj_col<NU, NF, true>), dim3(nwg_for<NU>(ncol)),
-                               dim3(AdjShape<NU>::WGS), 0, s, A);
-        else
-            hipLaunchKernelGGL((k_adj_col<NU, NF, false>), dim3(nwg_for<NU>(ncol)),
-                               dim3(AdjShape<NU>::WGS), 0, s, A);
-    } else {
-        if (dh)
-            hipLaunchKernelGGL((k_adj_col_many<NU, NF, true>), dim3(nwg_for<NU>(ncol)),
-                               dim3(AdjShape<NU>::WGS), 0, s, A);
-        else
-            hipLaunchKernelGGL((k_adj_col_many<NU, NF, false>), dim3(nwg_for<NU>(ncol)),
-                               dim3(AdjShape<NU>::WGS), 0, s, A);
-    }
-    SG_HIP(hipGetLastError());
-    A.count = pairs;
-    hipLaunchKernelGGL((k_adj_out<NPHI, NF>), dim3(nwg_for<NPHI>(pairs)),
-                       dim3(AdjShape<NPHI>::WGS), 0, s, A);
-    SG_HIP(hipGetLastError());
-    if (dh) {
-        hipLaunchKernelGGL(k_adj_dh_reduce, dim3(1), dim3(256), 0, s, A.part, ncol, NF, d_dh);
-        SG_HIP(hipGetLastError());
-    }
     return SG_OK;
 }
 
+template <int NPHI, int NF> static sg_status adj_out(AdjDev A, hipStream_t s)
+{
+    using S = AdjShape<NPHI>;
+    A.count = adj_pairs<NF>(A.D.nr);
+    hipLaunchKernelGGL((k_adj_out<NPHI, NF>), dim3(adj_grid<S>(A.count) + (A.dh ? 1 : 0)), dim3(S::WGS), 0, s, A);
+    SG_HIP(hipGetLastError());
+    return SG_OK;
+}
+
+template <int NPHI, int NU, int NF>
+static sg_status adj_launch(AdjDev A, int ncol, hipStream_t s)
+{
+    const bool dh = A.dh != nullptr;
+    sg_status st = adj_fwd<NPHI, NF>(A, dh, s);
+    if (st != SG_OK) return st;
+    A.count = ncol;
+    using SH = AdjShape<NU>;
+    using SS = AdjSlots<NU, NF>;
+    // Side by side where a column fits a workgroup.  Two fluids only while
+    // the columns give at most 512 threads per CU, or with dh in workgroups of
+    // 256: beyond, the columns taken in turn fill the chip by themselves and
+    // the slots left idle by the inverse transforms cost more than the chain
+    // (whole adjoint without / with dh, side by side against in turn:
+    // 256 x 512 16.6 / 20 us against 25 / 46; 512 x 1024 40 / 52 against
+    // 32 / 47; 1024 x 512 46 / 62 against 31 / 48; 1024 x 2048 120 / 196
+    // against 72 / 150; 256 x 2048 - / 39 against 29 / 44).  One fluid: 1024 x
+    // 2048 47 / 74 against 58 / 89.  Three and four: 512 x 512 x 4 57 / 135
+    // against 82 / 178.
+    const bool slots = SS::FITS && (NF != 2 || ncol * SS::CT <= 256 * 512 || (dh && SS::WGS <= 256));
+    auto go = [&](void (*fn)(AdjDev), int grid, int wgs) {
+        hipLaunchKernelGGL(fn, dim3(grid), dim3(wgs), 0, s, A);
+    };
+    if constexpr (SS::FITS) {
+        if (slots) go(dh ? k_adj_col_slots<NU, NF, true> : k_adj_col_slots<NU, NF, false>, adj_grid<SS>(ncol), SS::WGS);
+    }
+    if constexpr (!SS::FITS || NF == 2) {
+        if (!slots) {
+            if constexpr (NF > 2)
+                go(dh ? k_adj_col_many<NU, NF, true> : k_adj_col_many<NU, NF, false>, adj_grid<SH>(ncol), SH::WGS);
+            else
+                go(dh ? k_adj_col<NU, NF, true> : k_adj_col<NU, NF, false>, adj_grid<SH>(ncol), SH::WGS);
+        }
+    }
+    SG_HIP(hipGetLastError());
+    return adj_out<NPHI, NF>(A, s);
+}
+
 template <int NPHI, int NF>
-static sg_status adj_nu(int nu, AdjDev A, bool dh, double *d_dh, int ncol, hipStream_t s)
+static sg_status adj_nu(int nu, AdjDev A, int ncol, hipStream_t s)
 {
     switch (nu) {
-    case 4: return adj_launch<NPHI, 4, NF>(A, dh, d_dh, ncol, s);
-    case 8: return adj_launch<NPHI, 8, NF>(A, dh, d_dh, ncol, s);
-    case 16: return adj_launch<NPHI, 16, NF>(A, dh, d_dh, ncol, s);
-    case 32: return adj_launch<NPHI, 32, NF>(A, dh, d_dh, ncol, s);
-    case 64: return adj_launch<NPHI, 64, NF>(A, dh, d_dh, ncol, s);
-    case 128: return adj_launch<NPHI, 128, NF>(A, dh, d_dh, ncol, s);
-    case 256: return adj_launch<NPHI, 256, NF>(A, dh, d_dh, ncol, s);
-    case 512: return adj_launch<NPHI, 512, NF>(A, dh, d_dh, ncol, s);
-    case 1024: return adj_launch<NPHI, 1024, NF>(A, dh, d_dh, ncol, s);
-    case 2048: return adj_launch<NPHI, 2048, NF>(A, dh, d_dh, ncol, s);
+    case 4: return adj_launch<NPHI, 4, NF>(A, ncol, s);
+    case 8: return adj_launch<NPHI, 8, NF>(A, ncol, s);
+    case 16: return adj_launch<NPHI, 16, NF>(A, ncol, s);
+    case 32: return adj_launch<NPHI, 32, NF>(A, ncol, s);
+    case 64: return adj_launch<NPHI, 64, NF>(A, ncol, s);
+    case 128: return adj_launch<NPHI, 128, NF>(A, ncol, s);
+    case 256: return adj_launch<NPHI, 256, NF>(A, ncol, s);
+    case 512: return adj_launch<NPHI, 512, NF>(A, ncol, s);
+    case 1024: return adj_launch<NPHI, 1024, NF>(A, ncol, s);
+    case 2048: return adj_launch<NPHI, 2048, NF>(A, ncol, s);
     case 4096:
-        if constexpr (NF <= 2) return adj_launch<NPHI, 4096, NF>(A, dh, d_dh, ncol, s);
+        if constexpr (NF <= 2) return adj_launch<NPHI, 4096, NF>(A, ncol, s);
         else return SG_ERR_UNSUPPORTED;  // beyond two groups n_r <= 1024
     }
     return SG_ERR_UNSUPPORTED;
@@ -775,9 +952,8 @@ template <int NPHI, int NF>
 static sg_status adj_ss_launch(AdjDev A, int m0, int ncol, hipStream_t s)
 {
     const int nr = A.D.nr;
-    A.count = NF * nr;
-    hipLaunchKernelGGL(k_adj_lam<NPHI>, dim3(nwg_for<NPHI>(A.count)), dim3(AdjShape<NPHI>::WGS), 0, s, A);
-    SG_HIP(hipGetLastError());
+    const sg_status st = adj_fwd<NPHI, NF>(A, false, s);
+    if (st != SG_OK) return st;
     if (m0 > 0) {
         hipLaunchKernelGGL(k_ss_adj_full<NF>, dim3(m0 * NF * ((nr + 15) / 16)), dim3(256), 0, s, A, m0);
         SG_HIP(hipGetLastError());
@@ -787,11 +963,7 @@ static sg_status adj_ss_launch(AdjDev A, int m0, int ncol, hipStream_t s)
                            ncol);
         SG_HIP(hipGetLastError());
     }
-    const int pairs = adj_pairs<NF>(nr);
-    A.count = pairs;
-    hipLaunchKernelGGL((k_adj_out<NPHI, NF>), dim3(nwg_for<NPHI>(pairs)), dim3(AdjShape<NPHI>::WGS), 0, s, A);
-    SG_HIP(hipGetLastError());
-    return SG_OK;
+    return adj_out<NPHI, NF>(A, s);
 }
 
 template <int NF>
@@ -813,19 +985,19 @@ static sg_status adj_ss_phi(int nphi, AdjDev A, int m0, int ncol, hipStream_t s)
 }
 
 template <int NF>
-static sg_status adj_phi(int nphi, int nu, AdjDev A, bool dh, double *d_dh, int ncol, hipStream_t s)
+static sg_status adj_phi(int nphi, int nu, AdjDev A, int ncol, hipStream_t s)
 {
     switch (nphi) {
-    case 4: return adj_nu<4, NF>(nu, A, dh, d_dh, ncol, s);
-    case 8: return adj_nu<8, NF>(nu, A, dh, d_dh, ncol, s);
-    case 16: return adj_nu<16, NF>(nu, A, dh, d_dh, ncol, s);
-    case 32: return adj_nu<32, NF>(nu, A, dh, d_dh, ncol, s);
-    case 64: return adj_nu<64, NF>(nu, A, dh, d_dh, ncol, s);
-    case 128: return adj_nu<128, NF>(nu, A, dh, d_dh, ncol, s);
-    case 256: return adj_nu<256, NF>(nu, A, dh, d_dh, ncol, s);
-    case 512: return adj_nu<512, NF>(nu, A, dh, d_dh, ncol, s);
-    case 1024: return adj_nu<1024, NF>(nu, A, dh, d_dh, ncol, s);
-    case 2048: return adj_nu<2048, NF>(nu, A, dh, d_dh, ncol, s);
+    case 4: return adj_nu<4, NF>(nu, A, ncol, s);
+    case 8: return adj_nu<8, NF>(nu, A, ncol, s);
+    case 16: return adj_nu<16, NF>(nu, A, ncol, s);
+    case 32: return adj_nu<32, NF>(nu, A, ncol, s);
+    case 64: return adj_nu<64, NF>(nu, A, ncol, s);
+    case 128: return adj_nu<128, NF>(nu, A, ncol, s);
+    case 256: return adj_nu<256, NF>(nu, A, ncol, s);
+    case 512: return adj_nu<512, NF>(nu, A, ncol, s);
+    case 1024: return adj_nu<1024, NF>(nu, A, ncol, s);
+    case 2048: return adj_nu<2048, NF>(nu, A, ncol, s);
     }
     return SG_ERR_UNSUPPORTED;
 }
@@ -888,13 +1060,13 @@ sg_status sg_adjoint_run(const sg_disc &d, const float *lam_r, const float *lam_
     A.part = (double *)o;
     const int ncol = nphi / 2 + 1;
     o += sg_align256(sizeof(double) * ncol * nf);
-    const bool want_dh = dh != nullptr;
+    A.dh = dh;
     sg_status st = SG_ERR_UNSUPPORTED;
     switch (nf) {
-    case 1: st = adj_phi<1>(nphi, 2 * nr, A, want_dh, dh, ncol, s); break;
-    case 2: st = adj_phi<2>(nphi, 2 * nr, A, want_dh, dh, ncol, s); break;
-    case 3: st = adj_phi<3>(nphi, 2 * nr, A, want_dh, dh, ncol, s); break;
-    case 4: st = adj_phi<4>(nphi, 2 * nr, A, want_dh, dh, ncol, s); break;
+    case 1: st = adj_phi<1>(nphi, 2 * nr, A, ncol, s); break;
+    case 2: st = adj_phi<2>(nphi, 2 * nr, A, ncol, s); break;
+    case 3: st = adj_phi<3>(nphi, 2 * nr, A, ncol, s); break;
+    case 4: st = adj_phi<4>(nphi, 2 * nr, A, ncol, s); break;
     }
     if (st != SG_OK || !(d.flags & SG_INDIRECT)) return st;
     return adjoint_indirect(d, lam_r, lam_p, dsig, dh, o, s);
