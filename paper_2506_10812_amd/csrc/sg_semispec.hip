@@ -101,12 +101,14 @@ struct SsClass {
     int on;          // 0: every row, in the plain (b, a, i', i) order
     int nt;          // tiles of target rings
     int K1, K2;      // |k| of the class in [K1, K2) (K1 = 0: all of -K2 < k < K2)
-    int nk;          // offsets: 2 K2 - 1 or 2 (K2 - K1)
+    int nk;          // offsets: 2 K2 - 1 or 2 (K2 - K1); half: K2 - K1
+    int half;        // offsets k >= 0 only
     double x1, x2;   // the class's range of |X| (x2 infinite in the last)
 };
 
 __device__ inline int ss_class_offset(const SsClass &C, int q)
 {
+    if (C.half) return C.K1 + q;
     if (C.K1 == 0) return q - (C.K2 - 1);
     const int half = C.K2 - C.K1;
     return q < half ? C.K1 + q : -(C.K1 + q - half);
@@ -1043,56 +1045,269 @@ int sg_ss_default_variant(int) { return 1; }
 // derivative rows are sampled and transformed on the fly (the table's own
 // construction with the kernels' h derivatives), never stored.
 
-// Half spectra of lam rows (b, i) (r and phi parts) and of Sigma row pairs.
+// Half spectra of lam rows (b, i) (r and phi parts) and of Sigma row pairs, by
+// rings: lt [b][i][m] (lam_r~, lam_phi~) and st [a][i][m].  (The contraction
+// reads them along m, once per ring pair; in the passes' tiles of 4 x 4, one
+// 8-byte value from each 32-byte sector, those reads were a third of the
+// kernel.)
 template <int N>
 __global__ void __launch_bounds__(SsRowShape<N>::WGS)
-k_ssg_phi(const float *lam_r, const float *lam_p, const float *sigma, const float2 *tw, float2 *lt, float2 *st,
+k_ssg_phi(const float *lam_r, const float *lam_p, const float *sigma, const float2 *tw, float4 *lt, float2 *st,
           int nr, int nf)
 {
     using S = SsRowShape<N>;
-    constexpr int T = S::T, G = S::G, W = LdsPlane<float>::elems(N);
+    constexpr int P = S::P, T = S::T, G = S::G, W = LdsPlane<float>::elems(N), NC = N / 2 + 1;
     __shared__ __attribute__((aligned(16))) float2 lds[W * G];
     const int g = threadIdx.x / T, t = threadIdx.x % T;
     const int hp = (nr + 1) / 2, nl = nf * nr, count = nl + nf * hp;
     const int idx = blockIdx.x * G + g;
     const bool valid = idx < count;
     const int j = valid ? idx : 0;
-    const size_t fs = sg_blk_field_elems(N, nr);
     const LdsPlane<float> pl{lds + W * g};
     const float *x1, *x2;
-    float2 *d1, *d2;
-    int i1, i2;
+    size_t r1, r2;  // rows of st
     if (j < nl) {
-        const int b = j / nr, i = j % nr;
-        x1 = lam_r + ((size_t)b * nr + i) * N;
-        x2 = lam_p + ((size_t)b * nr + i) * N;
-        d1 = lt + (size_t)(2 * b) * fs;
-        d2 = d1 + fs;
-        i1 = i2 = i;
+        x1 = lam_r + (size_t)j * N;
+        x2 = lam_p + (size_t)j * N;
+        r1 = r2 = (size_t)j;
     } else {
         const int q = j - nl, a = q / hp, jj = q % hp;
-        i1 = 2 * jj;
-        i2 = min(2 * jj + 1, nr - 1);
-        x1 = sigma + ((size_t)a * nr + i1) * N;
-        x2 = sigma + ((size_t)a * nr + i2) * N;
-        d1 = d2 = st + (size_t)a * fs;
+        r1 = (size_t)a * nr + 2 * jj;
+        r2 = (size_t)a * nr + min(2 * jj + 1, nr - 1);
+        x1 = sigma + r1 * N;
+        x2 = sigma + r2 * N;
     }
-    phi_fwd_pair<N>(x1, x2, d1, i1, d2, i2, nr, TwTable{tw}, t, pl, valid);
+    float2 z[P];
+    p1_load<N>(x1, x2, z, t);
+    fft<N, false>(z, t, pl, TwTable{tw});
+#pragma unroll
+    for (int p = 0; p < P; ++p) pl.st(t + T * p, z[p]);
+    __syncthreads();
+    if (!valid) return;
+    for (int m = t; m < NC; m += T) {
+        // the Hermitian split of pass 1
+        const float2 Z = pl.ld(m), C = pl.ld((N - m) & (N - 1));
+        const float2 v1 = make_float2(0.5f * (Z.x + C.x), 0.5f * (Z.y - C.y));
+        const float2 v2 = make_float2(0.5f * (Z.y + C.y), -0.5f * (Z.x - C.x));
+        if (j < nl) {
+            lt[r1 * NC + m] = make_float4(v1.x, v1.y, v2.x, v2.y);
+        } else {
+            gstore2(st, r1 * NC + m, v1);
+            gstore2(st, r2 * NC + m, v2);  // (an odd last row is its own partner)
+        }
+    }
 }
 
-// One group of T threads per (b, a, i', i) row: for which = 1 (d/dh_a,
-// source) and 2 (d/dh_b, target) the derivative samples are transformed as
-// in k_ss_rows and contracted with lam~ and Sigma~ of the row's mode column.
-// SO: the rows of second-order operators, whose samples are the h
-// derivatives of the hat weights (k_ss_rows<N, true>: integrated near the
-// singular point, point value plus second moments beyond; both are linear
-// in the kernel, so they apply to its derivatives sample by sample).
+// Contraction of one mode of the row with lam~ and Sigma~:
+// Re[conj(lr) T_r s] + Re[conj(lp) i t_phi s] = T_r cr + t_phi cp.
+__device__ inline void ssg_mode(const float4 *lt, const float2 *st, size_t ro, size_t so, int m, double &cr, double &cp)
+{
+    typedef float v4 __attribute__((ext_vector_type(4)));
+    const v4 l = ((const __attribute__((address_space(1))) v4 *)lt)[ro + m];
+    const float2 sv = gload2(st, so + m);
+    cr = (double)l.x * sv.x + (double)l.y * sv.y;
+    cp = -(double)l.z * sv.y + (double)l.w * sv.x;
+}
+
+// Point-sampled rows, a ring pair at a time.  Both h derivatives of both
+// operators of a ring pair, (b, a, i', i) and its mirror (a, b, i, i'), are
+// one even function of phi, S = D(x(phi)) (E for the potential), times
+//   K_r = p (e^X - cos phi) = p ((e^X - 1) + (1 - cos phi)),  K_phi = p sin phi
+// with p and X of the row and the derivative.  The products with 1 - cos phi
+// and sin phi are differences of neighbouring modes of S~ (exact for the
+// sampled sequences), so a ring pair takes one real transform where its two
+// rows and two derivatives took four, and one evaluation per azimuth of half
+// the circle where the rows took two; a group transforms two ring pairs at
+// once as z_A + i z_B (S~ is real).  The differences cost digits of the double
+// rounding: 1e-16/|X| of a row's largest coefficient, for i' = i 1e-16/dphi^2
+// (dL/dH itself moved by 5e-13 of its largest at 600 x 1024).
+// The own-cell sample of i = i' enters as a constant of all modes.
+// On a uniform grid the classes of a row and of its mirror differ: rows then
+// stand alone (both signs of k).  Index: as ss_row's with offsets k >= 0.
+// The transforms bound it with the evaluations (both FP64 with LDS traffic).
+// 600 x 1024 two-fluid, all rows: 3.86 -> 1.90 ms.
+template <int N>
+__global__ void __launch_bounds__(SsRowShape<N>::WGS)
+k_ssg_pairs(const double *H, const double *dself, SsRowArgs A, SsClass C, int nphi, const float4 *lt,
+            const float2 *st, size_t r0, int nrows, double *rowpart)
+{
+    using S = SsRowShape<N>;
+    constexpr int P = S::P, T = S::T, G = S::G, W = LdsPlane<double>::elems(N);
+    constexpr int NC = N / 2 + 1, SUB = T < 64 ? T : 64, NS = T / SUB;
+    __shared__ __attribute__((aligned(16))) double2 lds[W * G];
+    __shared__ __attribute__((aligned(16))) double wq[FQuad<double>::TABLE];
+    __shared__ double red[G * NS * 4];
+    __shared__ double ext[G * 4];  // cr + cp of mode 1 (the indirect term), by ring pair and direction
+    const int g = threadIdx.x / T, t = threadIdx.x % T;
+    const LdsPlane<double> pl{lds + W * g};
+    const int row = (blockIdx.x * G + g) * 2;
+    int ic[2], ip[2], a = 0, b = 0;
+    bool live[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        int ua, ub;
+        live[u] = ss_row(A, C, (uint32_t)r0 + (row + u < nrows ? row + u : 0), ub, ua, ip[u], ic[u]) && row + u < nrows;
+        if (live[u]) {
+            a = ua;  // a unit's rows are of one fluid pair
+            b = ub;
+        } else {
+            ic[u] = ip[u] = 0;
+        }
+    }
+    if (!__syncthreads_or(live[0] || live[1] ? 1 : 0)) return;
+    sg_fill64(wq, A.pot ? SG_FN_E : SG_FN_D);
+    // x(phi) = xa (x0 + 2 sin^2(phi / 2)), also the potential's s^2 / (8 H_ab^2)
+    double x0[2], xa[2], ri[2], rp[2], X[2], ha[2], hb[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        ri[u] = A.lin ? A.rmin + (ic[u] + 0.5) * A.dr : exp(A.lnrmin + (ic[u] + 0.5) * A.du);
+        rp[u] = A.lin ? A.rmin + (ip[u] + 0.5) * A.dr : exp(A.lnrmin + (ip[u] + 0.5) * A.du);
+        ha[u] = H[a * A.nr + ip[u]] / rp[u];
+        hb[u] = H[b * A.nr + ic[u]] / ri[u];
+        X[u] = A.lin ? log(ri[u] / rp[u]) : (double)(ic[u] - ip[u]) * A.du;
+        const ConvRowDh64 d = sg_conv_row64_dh(X[u], ha[u], hb[u]);
+        x0[u] = d.two_sxh2;
+        xa[u] = d.inv4h2;
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int q = t; q <= N / 2; q += T) {
+        double sh, ch, v[2];
+        ss_half_angle<N>(q, sh, ch);
+        const double two_s2 = 2.0 * sh * sh;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            v[u] = 0.0;
+            if (!live[u] || (ic[u] == ip[u] && q == 0)) continue;
+            const double x = (x0[u] + two_s2) * xa[u];
+            v[u] = A.pot ? sg_E64(x, wq) : sg_D64(x, wq);
+        }
+        const double2 z = make_double2(v[0], v[1]);
+        pl.st(q, z);
+        if (q != 0 && q != N / 2) pl.st(N - q, z);
+    }
+    __syncthreads();
+    double2 z[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) z[p] = pl.ld(t + T * p);
+    __syncthreads();
+    fft<N, false>(z, t, pl, TwPow64<N>{t});
+#pragma unroll
+    for (int p = 0; p < P; ++p) pl.st(t + T * p, z[p]);
+    __syncthreads();
+    // acc[u][0]: the row; [u][1]: its mirror, or (i = i') the sum of w cr
+    double acc[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
+    const double b1 = A.pot ? 0.0 : 1.0;
+    double c0[2][2];  // K_r = p (c0 S + b1 (1 - cos) S)
+    size_t ro[2][2], so[2][2];
+    const int ncol = nphi / 2 + 1;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        double sx, ep, em;
+        sg_exp_half(X[u], sx, ep, em);
+        c0[u][0] = A.pot ? 1.0 : 2.0 * sx * ep;
+        c0[u][1] = A.pot ? 1.0 : -2.0 * sx * em;
+        ro[u][0] = ((size_t)b * A.nr + ic[u]) * ncol;
+        so[u][0] = ((size_t)a * A.nr + ip[u]) * ncol;
+        ro[u][1] = ((size_t)a * A.nr + ip[u]) * ncol;
+        so[u][1] = ((size_t)b * A.nr + ic[u]) * ncol;
+    }
+    for (int m = t; m < NC; m += T) {
+        const double2 z0 = pl.ld(m), zl = pl.ld(m == 0 ? 1 : m - 1), zh = pl.ld((m + 1) & (N - 1));
+        const double wm = (m == 0 || m == nphi / 2) ? 1.0 : 2.0;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            if (!live[u]) continue;
+            const double s0 = u ? z0.y : z0.x, sl = u ? zl.y : zl.x, sh = u ? zh.y : zh.x;
+            const double B = b1 * (s0 - 0.5 * (sl + sh)), tp = b1 * 0.5 * (sh - sl);
+            double cr, cp;
+            ssg_mode(lt, st, ro[u][0], so[u][0], m, cr, cp);
+            acc[u][0] += wm * ((c0[u][0] * s0 + B) * cr + tp * cp);
+            if (m == 1) ext[(g * 2 + u) * 2] = cr + cp;
+            if (ic[u] == ip[u]) {
+                acc[u][1] += wm * cr;
+            } else if (!A.lin) {
+                ssg_mode(lt, st, ro[u][1], so[u][1], m, cr, cp);
+                acc[u][1] += wm * ((c0[u][1] * s0 + B) * cr + tp * cp);
+                if (m == 1) ext[(g * 2 + u) * 2 + 1] = cr + cp;
+            }
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        double x = acc[e >> 1][e & 1];
+#pragma unroll
+        for (int o = SUB / 2; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+        if (t % SUB == 0) red[(g * NS + t / SUB) * 4 + e] = x;
+    }
+    __syncthreads();
+    // thread (u, dir) of the group writes the row's partials (part 0 belongs
+    // to dL/dh_a at the source ring, part 1 to dL/dh_b at the target ring);
+    // k_ssg_finish adds them up
+    for (int e = t; e < 4; e += T) {
+        const int dir = e & 1;
+        const bool second = e >= 2;
+        if (!(second ? live[1] : live[0])) continue;
+        const int ii = second ? ic[1] : ic[0], jj = second ? ip[1] : ip[0];
+        if (dir && (ii == jj || A.lin)) continue;
+        double sum = 0.0, own = 0.0;
+        for (int w = 0; w < NS; ++w) {
+            sum += red[(g * NS + w) * 4 + e];
+            if (ii == jj) own += red[(g * NS + w) * 4 + e + 1];
+        }
+        const double r1 = second ? ri[1] : ri[0], r2 = second ? rp[1] : rp[0];
+        const double h1 = second ? ha[1] : ha[0], h2 = second ? hb[1] : hb[0], Xr = second ? X[1] : X[0];
+        const int tb = dir ? a : b, ta = dir ? b : a, ti = dir ? jj : ii, tj = dir ? ii : jj;
+        const double tr = dir ? r2 : r1, tq = dir ? r1 : r2;    // target and source radius
+        const double sa = dir ? h2 : h1, sb = dir ? h1 : h2;    // their h: source, target
+        double p1, p2;
+        if (A.pot) {
+            // d/dh of r'^2 G0(y) / (2 sqrt(pi) H_ab) (the forward's sample):
+            // d(G0/H)/dH = (2 y F(y) - G0(y)) / H^2, dH_ab/dh_a = H_a r' / (2 H_ab),
+            // dH_ab/dh_b = H_b r_i / (2 H_ab); even in phi (no K_phi part)
+            const double Ha = sa * tq, Hb = sb * tr, Hab2 = 0.5 * (Ha * Ha + Hb * Hb), Hab = sqrt(Hab2);
+            const double dq = tq * tq / (2.0 * SG_SQRT_PI * Hab2);
+            p1 = dq * Ha * tq / (2.0 * Hab);
+            p2 = dq * Hb * tr / (2.0 * Hab);
+        } else {
+            const ConvRowDh64 d = sg_conv_row64_dh(dir ? -Xr : Xr, sa, sb);
+            p1 = d.p1;
+            p2 = d.p2;
+        }
+        const double scale = -(A.lin ? A.dr / tq : A.du) * A.dphi / N;
+        double v1 = p1 * sum, v2 = p2 * sum;
+        if (ii == jj && !A.excl) {
+            const size_t o = (size_t)(ta * A.nf + tb) * A.nr + ti, wst = (size_t)A.nf * A.nf * A.nr;
+            v1 += dself[o] * own;
+            v2 += dself[wst + o] * own;
+        }
+        if (A.ind) {
+            // d/dh_a of r'^2 sqrt(2) K_a(r'/H_a) n_phi / 2, H_a = h_a r':
+            // dK_a/dH = pi^{-1/2} r' / (4 H^4) (-3 F(x) - 2 x F'(x)), x = r'^2 / (4 H^2)
+            const double Ha = sa * tq, x = tq * tq / (4.0 * Ha * Ha);
+            const double dK = (1.0 / SG_SQRT_PI) * tq / (2.0 * Ha * Ha * Ha * Ha) * sg_D64(x, wq);
+            v1 += 2.0 * tq * tq * SG_SQRT2 * dK * tq * (0.5 * N) *
+                  ext[(g * 2 + (second ? 1 : 0)) * 2 + dir];
+        }
+        double *o = rowpart + 2 * ((((size_t)tb * A.nf + ta) * A.nr + tj) * A.nrt + ti);
+        o[0] = scale * v1;
+        o[1] = scale * v2;
+    }
+}
+
+// The rows of second-order operators: one group of T threads per (b, a, i', i)
+// row, for which = 1 (d/dh_a, source) and 2 (d/dh_b, target) the derivative
+// samples are transformed as in k_ss_rows and contracted with lam~ and Sigma~
+// of the row's mode column.  The samples are the h derivatives of the hat
+// weights (k_ss_rows<N, 1>: integrated near the singular point, point value
+// plus second moments beyond; both are linear in the kernel, so they apply to
+// its derivatives sample by sample).
 // N: samples of the rows, as in k_ss_rows; the contraction runs over the modes
 // they resolve (m <= N/2; the others' derivatives are below e^{-48} of the
 // axisymmetric one).  nphi: the grid's.  SO as in k_ss_rows.
 template <int N, int SO>
 __global__ void __launch_bounds__(SsRowShape<N>::WGS)
-k_ssg_rows(const double *H, const double *dself, SsRowArgs A, SsClass C, int nphi, const float2 *lt,
+k_ssg_rows(const double *H, const double *dself, SsRowArgs A, SsClass C, int nphi, const float4 *lt,
            const float2 *st, size_t r0, int nrows, double *rowpart)
 {
     using S = SsRowShape<N>;
@@ -1110,7 +1325,7 @@ k_ssg_rows(const double *H, const double *dself, SsRowArgs A, SsClass C, int nph
     const bool valid = ss_row(A, C, (uint32_t)r0 + (row < nrows ? row : 0), b, a, ip, i) && row < nrows;
     if (!__syncthreads_or(valid ? 1 : 0)) return;
     if (!valid) b = a = ip = i = 0;
-    sg_fill64(wq, A.pot ? SG_FN_E : SG_FN_D);
+    sg_fill64(wq, SG_FN_D);
     const bool live = valid && i < A.nr;
     const int ic = i < A.nr ? i : A.nr - 1;
     const double ri = A.lin ? A.rmin + (ic + 0.5) * A.dr : exp(A.lnrmin + (ic + 0.5) * A.du);
@@ -1118,7 +1333,7 @@ k_ssg_rows(const double *H, const double *dself, SsRowArgs A, SsClass C, int nph
     const double ha = H[a * A.nr + ip] / rp, hb = H[b * A.nr + ic] / ri;
     const double X = A.lin ? log(ri / rp) : (double)(ic - ip) * A.du;
     const double scale = -(A.lin ? A.dr / rp : A.du) * A.dphi / N;
-    const uint32_t fs = (uint32_t)sg_blk_field_elems(nphi, A.nr);
+    const int ncol = nphi / 2 + 1;
     __syncthreads();
     // Both derivatives are sampled in one sweep (one F, F' evaluation per
     // azimuth) and transformed together.  Row d is z_d = K_r,d + i K_phi,d
@@ -1126,12 +1341,9 @@ k_ssg_rows(const double *H, const double *dself, SsRowArgs A, SsClass C, int nph
     // plane holds z = z_1 + i z_2, whose transform carries Z_1 (d/dh_a) in
     // its real part and Z_2 (d/dh_b) in its imaginary part.
     constexpr int Q = P / 2 + 1;
-    const ConvRowDh64 d0 = sg_conv_row64_dh(X, ha, hb);
-    ConvRowDh64 dp = d0, dm = d0;  // the D_X neighbours of second-order rows
-    if constexpr (SO != 0) {
-        dp = sg_conv_row64_dh(X + A.du, ha, hb);
-        dm = sg_conv_row64_dh(X - A.du, ha, hb);
-    }
+    // the row and its D_X neighbours
+    const ConvRowDh64 d0 = sg_conv_row64_dh(X, ha, hb), dp = sg_conv_row64_dh(X + A.du, ha, hb),
+                      dm = sg_conv_row64_dh(X - A.du, ha, hb);
     if constexpr (SO == 1) {
         // integrated samples, cooperatively (as in k_ss_rows<N, true>)
         const int Pr = ic - ip;
@@ -1226,43 +1438,18 @@ k_ssg_rows(const double *H, const double *dself, SsRowArgs A, SsClass C, int nph
         const int q = t + T * u;
         if (q > N / 2) break;
         double kr1 = 0.0, kp1 = 0.0, kr2 = 0.0, kp2 = 0.0;
-        if constexpr (SO == 2) {
-            // K + (D_X^2 K + D_phi^2 K)/12 of both derivatives
+        // K + (D_X^2 K + D_phi^2 K)/12 of both derivatives
 #pragma unroll 1
-            for (int k = 0; k < 5; ++k) {
-                const double ph = 2.0 * q / N + (k == 3 ? A.dphi : k == 4 ? -A.dphi : 0.0) / SG_PI;
-                double sh, ch, a1, b1, a2, b2;
-                sincospi(0.5 * ph, &sh, &ch);
-                sg_conv_kernel64_dh(k == 1 ? dp : k == 2 ? dm : d0, sh, 2.0 * sh * ch, wq, a1, b1, a2, b2);
-                const double w = k == 0 ? 2.0 / 3.0 : 1.0 / 12.0;
-                kr1 += w * a1;
-                kp1 += w * b1;
-                kr2 += w * a2;
-                kp2 += w * b2;
-            }
-        } else if (ic == ip && q == 0) {
-            if (!A.excl) {
-                const size_t o = (size_t)(a * A.nf + b) * A.nr + ic, wst = (size_t)A.nf * A.nf * A.nr;
-                kr1 = dself[o];
-                kr2 = dself[wst + o];
-            }
-        } else if (A.pot) {
-            // d/dh of r'^2 G0(y) / (2 sqrt(pi) H_ab) (the forward's sample):
-            // d(G0/H)/dH = (2 y F(y) - G0(y)) / H^2, dH_ab/dh_a = H_a r' / (2 H_ab),
-            // dH_ab/dh_b = H_b r_i / (2 H_ab); even in phi (no K_phi part)
-            double sp, cp;
-            ss_half_angle<N>(q, sp, cp);
-            const double sx = sinh(0.5 * X);
-            const double s2 = 4.0 * ri * rp * (sx * sx + sp * sp);
-            const double Ha = ha * rp, Hb = hb * ri, Hab2 = 0.5 * (Ha * Ha + Hb * Hb), Hab = sqrt(Hab2);
-            const double y = s2 / (8.0 * Hab2);
-            const double dq = rp * rp * sg_E64(y, wq) / (2.0 * SG_SQRT_PI * Hab2);
-            kr1 = dq * Ha * rp / (2.0 * Hab);
-            kr2 = dq * Hb * ri / (2.0 * Hab);
-        } else {
-            double sh, ch;
-            ss_half_angle<N>(q, sh, ch);
-            sg_conv_kernel64_dh(d0, sh, 2.0 * sh * ch, wq, kr1, kp1, kr2, kp2);
+        for (int k = 0; k < 5; ++k) {
+            const double ph = 2.0 * q / N + (k == 3 ? A.dphi : k == 4 ? -A.dphi : 0.0) / SG_PI;
+            double sh, ch, a1, b1, a2, b2;
+            sincospi(0.5 * ph, &sh, &ch);
+            sg_conv_kernel64_dh(k == 1 ? dp : k == 2 ? dm : d0, sh, 2.0 * sh * ch, wq, a1, b1, a2, b2);
+            const double w = k == 0 ? 2.0 / 3.0 : 1.0 / 12.0;
+            kr1 += w * a1;
+            kp1 += w * b1;
+            kr2 += w * a2;
+            kp2 += w * b2;
         }
         pl.st(q, make_double2(kr1 - kp2, kp1 + kr2));
         if (q != 0 && q != N / 2) pl.st(N - q, make_double2(kr1 + kp2, kr2 - kp1));
@@ -1289,20 +1476,16 @@ k_ssg_rows(const double *H, const double *dself, SsRowArgs A, SsClass C, int nph
     if (live) {
         for (int m = t; m < NC; m += T) {
             const double2 zm = pl.ld(m), zn = pl.ld((N - m) & (N - 1));
-            const uint32_t oi = (uint32_t)sg_blk_index(m, ic, A.nr), op = (uint32_t)sg_blk_index(m, ip, A.nr);
-            const float2 lr = gld2(lt, (uint32_t)(2 * b) * fs + oi), lp = gld2(lt, (uint32_t)(2 * b + 1) * fs + oi);
-            const float2 sv = gld2(st, (uint32_t)a * fs + op);
-            // Re[conj(lr) T_r s] + Re[conj(lp) i t_phi s]
-            const double cr = (double)lr.x * sv.x + (double)lr.y * sv.y;
-            const double cp = -(double)lp.x * sv.y + (double)lp.y * sv.x;
+            double cr, cp;
+            ssg_mode(lt, st, ((size_t)b * A.nr + ic) * ncol, ((size_t)a * A.nr + ip) * ncol, m, cr, cp);
             const double wm = ((m == 0 || m == nphi / 2) ? 1.0 : 2.0) * scale;
-            double tr = 0.5 * (zm.x + zn.x), tp = A.pot ? 0.0 : 0.5 * (zn.x - zm.x);
+            double tr = 0.5 * (zm.x + zn.x), tp = 0.5 * (zn.x - zm.x);
             if (m == 1) {
                 tr += dind;
                 tp += dind;
             }
             part[0] += wm * (tr * cr + tp * cp);
-            part[1] += wm * (0.5 * (zm.y + zn.y) * cr + (A.pot ? 0.0 : 0.5 * (zn.y - zm.y)) * cp);
+            part[1] += wm * (0.5 * (zm.y + zn.y) * cr + 0.5 * (zn.y - zm.y) * cp);
         }
     }
     __syncthreads();
@@ -1368,7 +1551,7 @@ size_t sg_ss_grad_ws_bytes(int nr, int nphi, int nf) { return ssg_ws(nr, nphi, n
 
 template <int N>
 static void launch_ssg_phi(const SsRowArgs &A, const float *lam_r, const float *lam_p, const float *sigma,
-                           const float2 *tw, float2 *lt, float2 *st, hipStream_t s)
+                           const float2 *tw, float4 *lt, float2 *st, hipStream_t s)
 {
     using S = SsRowShape<N>;
     const int jobs = A.nf * A.nr + A.nf * ((A.nr + 1) / 2);
@@ -1378,23 +1561,36 @@ static void launch_ssg_phi(const SsRowArgs &A, const float *lam_r, const float *
 
 template <int N>
 static void launch_ssg_rows(const double *H, const double *dself, const SsRowArgs &A, const SsPart &P, int nphi,
-                            const float2 *lt, const float2 *st, double *rowpart, hipStream_t s)
+                            const float4 *lt, const float2 *st, double *rowpart, hipStream_t s)
 {
     using S = SsRowShape<N>;
-    const size_t rows = P.C.on ? ss_class_rows(A, P.C) : (size_t)A.nf * A.nf * A.nr * A.nrt;
+    SsClass C = P.C;
+    if (P.kind == 0) {
+        if (!C.on) {  // all ring pairs as one class
+            C.on = 1;
+            C.nt = (A.nr + SG_SS_TI - 1) / SG_SS_TI;
+            C.K1 = 0;
+            C.K2 = A.nr;
+            C.nk = 2 * C.K2 - 1;
+            C.x1 = 0.0;
+            C.x2 = INFINITY;
+        }
+        if (!A.lin) C.half = 1;  // offsets k >= 0, the mirrors along
+        if (C.half) C.nk = C.K2 - C.K1;
+    }
+    const size_t rows = C.on ? ss_class_rows(A, C) : (size_t)A.nf * A.nf * A.nr * A.nrt;
     const size_t chunk = (size_t)1 << 22;
     for (size_t r0 = 0; r0 < rows; r0 += chunk) {
         const int n = (int)std::min(chunk, rows - r0);
-        const dim3 grid((n + S::G - 1) / S::G);
+        const dim3 one((n + S::G - 1) / S::G), two((n / 2 + S::G - 1) / S::G);
         if (P.kind == 1)
-            hipLaunchKernelGGL((k_ssg_rows<N, 1>), grid, dim3(S::WGS), 0, s, H, dself, A, P.C, nphi, lt, st, r0, n,
+            hipLaunchKernelGGL((k_ssg_rows<N, 1>), one, dim3(S::WGS), 0, s, H, dself, A, C, nphi, lt, st, r0, n,
                                rowpart);
         else if (P.kind == 2)
-            hipLaunchKernelGGL((k_ssg_rows<N, 2>), grid, dim3(S::WGS), 0, s, H, dself, A, P.C, nphi, lt, st, r0, n,
+            hipLaunchKernelGGL((k_ssg_rows<N, 2>), one, dim3(S::WGS), 0, s, H, dself, A, C, nphi, lt, st, r0, n,
                                rowpart);
         else
-            hipLaunchKernelGGL((k_ssg_rows<N, 0>), grid, dim3(S::WGS), 0, s, H, dself, A, P.C, nphi, lt, st, r0, n,
-                               rowpart);
+            hipLaunchKernelGGL(k_ssg_pairs<N>, two, dim3(S::WGS), 0, s, H, dself, A, C, nphi, lt, st, r0, n, rowpart);
     }
 }
 
@@ -1419,7 +1615,8 @@ sg_status sg_ss_grad_run(const sg_disc &d0, const double *d_H, const float *lam_
     const float2 *tw = (const float2 *)((const char *)d.table + L.off_tw_phi);
     const SsGradWs W = ssg_ws(nr, nphi, nf);
     char *ws = (char *)d_ws;
-    float2 *lt = (float2 *)(ws + W.lt), *st = (float2 *)(ws + W.st);
+    float4 *lt = (float4 *)(ws + W.lt);
+    float2 *st = (float2 *)(ws + W.st);
     double *dself = (double *)(ws + W.dself), *rowpart = (double *)(ws + W.rowpart);
     const double dphi = 2.0 * SG_PI / nphi;
     SsRowArgs A;
