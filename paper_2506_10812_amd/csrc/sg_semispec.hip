@@ -416,6 +416,90 @@ k_ss_rows(const double *H, const double *self, SsRowArgs A, SsClass C, size_t r0
     }
 }
 
+// Point-sampled rows of a class on the log grid, a ring pair at a time: a row
+// (b, a, i', i) and its mirror (a, b, i, i') are one even function of phi,
+// S = F(x(phi)) (G0 for the potential), times
+//   K_r = p (e^X - cos phi) = p ((e^X - 1) + (1 - cos phi)),  K_phi = p sin phi
+// with p and X of the row, and the products with 1 - cos phi and sin phi are
+// differences of neighbouring modes of S~ (exact for the sampled sequence).
+// So a pair takes one evaluation per azimuth of half the circle and half a
+// transform, where its rows took two and one; the table's entries are formed
+// from S~, held in double, by k_ss_scatter_pairs.  The differences cost
+// 1e-16/|X| of a row's largest coefficient (1e-16/dphi^2 for i' = i, whose
+// own-cell sample enters as a constant of all modes); the table holds floats.
+// C: offsets k >= 0 only.  out: [nrows][ld] double S~, m < ld <= N/2 + 1.
+// 1200 x 2048 one fluid, all rows 2.74 -> 1.14 ms, whole build and solve 3.84
+// -> 2.40 ms.
+template <int N>
+__global__ void __launch_bounds__(SsRowShape<N>::WGS)
+k_ss_pairs(const double *H, SsRowArgs A, SsClass C, size_t r0, int nrows, int ld, double *out)
+{
+    using S = SsRowShape<N>;
+    constexpr int P = S::P, T = S::T, G = S::G, W = LdsPlane<double>::elems(N);
+    __shared__ __attribute__((aligned(16))) double2 lds[W * G];
+    __shared__ __attribute__((aligned(16))) double wq[FQuad<double>::TABLE];
+    const int g = threadIdx.x / T, t = threadIdx.x % T;
+    const LdsPlane<double> pl{lds + W * g};
+    const int row = (blockIdx.x * G + g) * 2;
+    int ic[2], ip[2], a = 0, b = 0;
+    bool live[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        int ua, ub;
+        live[u] = ss_row(A, C, (uint32_t)r0 + (row + u < nrows ? row + u : 0), ub, ua, ip[u], ic[u]) && row + u < nrows;
+        if (live[u]) {
+            a = ua;  // a unit's rows are of one fluid pair
+            b = ub;
+        } else {
+            ic[u] = ip[u] = 0;
+        }
+    }
+    if (!__syncthreads_or(live[0] || live[1] ? 1 : 0)) return;
+    sg_fill64(wq, A.pot ? SG_FN_G0 : SG_FN_F);
+    // x(phi) = xa (x0 + 2 sin^2(phi / 2)), also the potential's s^2 / (8 H_ab^2)
+    double x0[2], xa[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const double ri = exp(A.lnrmin + (ic[u] + 0.5) * A.du), rp = exp(A.lnrmin + (ip[u] + 0.5) * A.du);
+        const ConvRow64 c = sg_conv_row64((double)(ic[u] - ip[u]) * A.du, H[a * A.nr + ip[u]] / rp,
+                                          H[b * A.nr + ic[u]] / ri);
+        x0[u] = c.two_sxh2;
+        xa[u] = c.inv4h2;
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int q = t; q <= N / 2; q += T) {
+        double sh, ch, v[2];
+        ss_half_angle<N>(q, sh, ch);
+        const double two_s2 = 2.0 * sh * sh;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            v[u] = 0.0;
+            if (!live[u] || (ic[u] == ip[u] && q == 0)) continue;
+            const double x = (x0[u] + two_s2) * xa[u];
+            v[u] = A.pot ? sg_G0_64(x, wq) : sg_F64(x, wq);
+        }
+        const double2 z = make_double2(v[0], v[1]);
+        pl.st(q, z);
+        if (q != 0 && q != N / 2) pl.st(N - q, z);
+    }
+    __syncthreads();
+    double2 z[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) z[p] = pl.ld(t + T * p);
+    __syncthreads();
+    fft<N, false>(z, t, pl, TwPow64<N>{t});
+    if (row >= nrows) return;
+    double *o = out + (size_t)row * ld;
+#pragma unroll
+    for (int p = 0; p <= P / 2; ++p) {
+        const int m = t + T * p;
+        if (m >= ld) break;
+        o[m] = z[p].x;
+        o[ld + m] = z[p].y;
+    }
+}
+
 // ------------------------------------------------------- table: transpose
 // src [nrows][ld] (rows r0 + row of a class or of the plain order) into the layouts of modes m0 <= m < ncol, in 32 x 32 tiles of
 // rows and modes.  The 32 rows of a block are written as runs of consecutive
@@ -486,6 +570,118 @@ k_ss_scatter(const float2 *src, int ld, int nrows, int ncol, int m0, float2 *coe
                 dst = md.off + (size_t)(pair * A.nr + ip) * A.nrt + i;
             }
             gstore2(coef, dst, tile[tx][k]);
+        }
+    }
+}
+
+// The entries of a class's ring pairs from their S~ (k_ss_pairs; src
+// [nrows][ld], modes m0 <= m < m1 of rows of N samples), both rows of a pair.
+// The banded modes (!FULL) go by 32 consecutive rows, whose targets, i and
+// i + k, are runs of two diagonals.  The full modes go by a source ring times
+// 16 target rings of a tile, gathered from the rows of their offsets: rows
+// i' >= i by (tile of i, i'), their mirrors by (source i, tile of i').  Every
+// block forms its rows' factors once and goes through all its modes, 32 and
+// one neighbour on each side at a time.
+template <bool FULL>
+__global__ void __launch_bounds__(256)
+k_ss_scatter_pairs(const double *src, int ld, int nrows, int N, int m0, int m1, float2 *coef, const SsMode *modes,
+                   const double *H, const double *self, SsRowArgs A, SsClass C, size_t r0, int tile0)
+{
+    __shared__ double tile[32][35];
+    __shared__ double fc[2][32], fp[2][32], fown[2][32], find[2][32];
+    __shared__ int srow[32];
+    __shared__ __attribute__((aligned(16))) double wq[FQuad<double>::TABLE];
+    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+    int i, ip, a, b, row, edir = 0;
+    bool ok;
+    if constexpr (FULL) {
+        const int n0 = C.nk + SG_SS_TI - 1;                                      // source rings of a tile's rows
+        const int n1 = SG_SS_TI * ((C.nk + 2 * SG_SS_TI - 2) / SG_SS_TI);        // (source, tile) of their mirrors
+        const int h0 = (n0 + 1) / 2, half = h0 + n1 / 2;                         // blocks per tile
+        const int pt = tile0 + (int)(blockIdx.x / half), e = (int)(blockIdx.x % half), l = tx & 15;
+        const int t = pt % C.nt, pair = pt / C.nt;
+        a = pair % A.nf;
+        b = pair / A.nf;
+        edir = e >= h0 ? 1 : 0;
+        const int v = 2 * (edir ? e - h0 : e) + (tx >> 4);
+        if (!edir) {
+            i = t * SG_SS_TI + l;
+            ip = t * SG_SS_TI + C.K1 + v;
+            ok = v < n0;
+        } else {
+            i = t * SG_SS_TI + (v & 15);
+            ip = (((i + C.K1) & ~15) + 16 * (v >> 4)) + l;
+            ok = v < n1;
+        }
+        const int k = ip - i;
+        ok = ok && b < A.nf && i < A.nr && ip < A.nr && k >= C.K1 && k < C.K2 && !(edir && k == 0);
+        const int64_t rr = (((int64_t)pt * C.nk + (k - C.K1)) * SG_SS_TI + (i & 15)) - (int64_t)r0;
+        ok = ok && rr >= 0 && rr < nrows;
+        row = ok ? (int)rr : 0;
+    } else {
+        row = blockIdx.x * 32 + tx;
+        ok = ss_row(A, C, (uint32_t)r0 + (row < nrows ? row : 0), b, a, ip, i) && row < nrows;
+        row = ok ? row : 0;
+    }
+    if (!__syncthreads_or(ok ? 1 : 0)) return;
+    const bool ind = A.ind && m0 + (int)blockIdx.y * 32 <= 1;  // the block forms mode 1
+    if (ind) {
+        sg_fill64(wq, SG_FN_F);
+        __syncthreads();
+    }
+    if (ty == 0) srow[tx] = row;
+    if (ty < (FULL ? 1 : 2)) {
+        const int dir = FULL ? edir : ty;
+        const int ii = ok ? i : 0, jj = ok ? ip : 0, fa = ok ? a : 0, fb = ok ? b : 0;
+        const int ti = dir ? jj : ii, si = dir ? ii : jj, tf = dir ? fa : fb, sf = dir ? fb : fa;  // target, source
+        const double rt = exp(A.lnrmin + (ti + 0.5) * A.du), rs = exp(A.lnrmin + (si + 0.5) * A.du);
+        const double Ht = H[tf * A.nr + ti], Hs = H[sf * A.nr + si];
+        const double scale = -A.du * A.dphi / N;  // the source cell's measure r'^2 du dphi is in p
+        const ConvRow64 c = sg_conv_row64((double)(ti - si) * A.du, Hs / rs, Ht / rt);
+        fc[dir && !FULL][tx] = A.pot ? 1.0 : c.em1;
+        fp[dir && !FULL][tx] =
+            scale * (A.pot ? rs * rs / (2.0 * SG_SQRT_PI * sqrt(0.5 * (Hs * Hs + Ht * Ht))) : c.pref);
+        fown[dir && !FULL][tx] = ti == si && !A.excl ? scale * self[(size_t)(sf * A.nf + tf) * A.nr + ti] : 0.0;
+        double w = 0.0;
+        if (ind) {
+            // r'^2 sqrt(2) K_a(d) N / 2, K_a(d) = pi^{-1/2} H^{-2} (d/4) F(d^2/4)
+            const double d = rs / Hs;
+            w = scale * rs * rs * SG_SQRT2 * (1.0 / SG_SQRT_PI) / (Hs * Hs) * (0.25 * d) * sg_F64(0.25 * d * d, wq) *
+                (0.5 * N);
+        }
+        find[dir && !FULL][tx] = w;
+    }
+    const double b1 = A.pot ? 0.0 : 1.0;
+    const int k = ip - i;
+    for (int mb = m0 + blockIdx.y * 32; mb < m1; mb += gridDim.y * 32) {
+        __syncthreads();  // the rows' factors; the previous tile has been read
+        for (int e = threadIdx.x; e < 32 * 34; e += 256) {
+            const int r = e / 34, c = e - 34 * r;
+            int m = abs(mb - 1 + c);           // S~(-1) = S~(1)
+            m = m > N / 2 ? N - m : m;         // and S~(N/2 + 1) = S~(N/2 - 1)
+            tile[r][c] = src[(size_t)srow[r] * ld + min(m, ld - 1)];
+        }
+        __syncthreads();
+        if (!ok) continue;
+        for (int q = ty; q < 32 && mb + q < m1; q += 8) {
+            const int m = mb + q;
+            const SsMode md = modes[m];
+            if (md.banded && k > md.w) continue;
+            const double sl = tile[tx][q], s0 = tile[tx][q + 1], sh = tile[tx][q + 2];
+            const double B = b1 * (s0 - 0.5 * (sl + sh)), Cp = b1 * 0.5 * (sh - sl);
+#pragma unroll
+            for (int u = 0; u < (FULL ? 1 : 2); ++u) {
+                const int dir = FULL ? edir : u;
+                if (dir && k == 0) continue;
+                const double add = m == 1 ? find[u][tx] : 0.0;
+                const double tr = fp[u][tx] * (fc[u][tx] * s0 + B) + fown[u][tx] + add, tp = fp[u][tx] * Cp + add;
+                const uint32_t pair = dir ? a * A.nf + b : b * A.nf + a;
+                const int ti = dir ? ip : i, si = dir ? i : ip;
+                const size_t dst = md.banded
+                                       ? md.off + (size_t)(pair * (2 * md.w + 1) + (si - ti + md.w)) * A.nrt + ti
+                                       : md.off + (size_t)(pair * A.nr + si) * A.nrt + ti;
+                gstore2(coef, dst, make_float2((float)tr, A.pot ? 0.f : (float)tp));
+            }
         }
     }
 }
@@ -730,6 +926,44 @@ static bool dispatch_ss_rows(const double *H, const double *self, const SsRowArg
     return false;
 }
 
+// S~ of a class's ring pairs and their entries, a chunk buffer at a time.
+static bool build_pairs(const double *H, const double *self, const SsRowArgs &A, const SsPart &P, int mc, int mfull,
+                        void *chunk, size_t cbytes, float2 *coef, const SsMode *modes, hipStream_t s)
+{
+    SsClass C = P.C;
+    C.half = 1;
+    C.nk = C.K2 - C.K1;
+    const int N = P.M, ld = std::min(mc + 1, N / 2 + 1);  // one mode more, for the last one's difference
+    const size_t rows = ss_class_rows(A, C);
+    size_t crows = cbytes / (sizeof(double) * ld) / SG_SS_TI * SG_SS_TI;
+    if (crows > (size_t)1 << 30) crows = (size_t)1 << 30;
+    double *out = (double *)chunk;
+    for (size_t r0 = 0; r0 < rows; r0 += crows) {
+        const int n = (int)std::min(crows, rows - r0);
+        switch (N) {
+#define SG_PAIRS(M)                                                                                              \
+    case M:                                                                                                      \
+        hipLaunchKernelGGL(k_ss_pairs<M>, dim3((n / 2 + SsRowShape<M>::G - 1) / SsRowShape<M>::G),               \
+                           dim3(SsRowShape<M>::WGS), 0, s, H, A, C, r0, n, ld, out);                             \
+        break;
+            SG_PAIRS(128) SG_PAIRS(256) SG_PAIRS(512) SG_PAIRS(1024) SG_PAIRS(2048)
+#undef SG_PAIRS
+        default: return false;
+        }
+        if (mfull < mc)
+            hipLaunchKernelGGL(k_ss_scatter_pairs<false>, dim3((n + 31) / 32, (mc - mfull + 255) / 256), dim3(256), 0, s,
+                               out, ld, n, N, mfull, mc, coef, modes, H, self, A, C, r0, 0);
+        if (mfull > 0) {
+            const size_t per_tile = (size_t)C.nk * SG_SS_TI;
+            const int t0 = (int)(r0 / per_tile), t1 = (int)((r0 + n - 1) / per_tile) + 1;
+            const int half = (C.nk + SG_SS_TI) / 2 + SG_SS_TI * ((C.nk + 2 * SG_SS_TI - 2) / SG_SS_TI) / 2;
+            hipLaunchKernelGGL(k_ss_scatter_pairs<true>, dim3((unsigned)(half * (t1 - t0)), (mfull + 255) / 256),
+                               dim3(256), 0, s, out, ld, n, N, 0, mfull, coef, modes, H, self, A, C, r0, t0);
+        }
+    }
+    return true;
+}
+
 sg_status sg_ss_table_build(const sg_grid *grid, int nf, const double *d_H, uint32_t flags, void *d_table,
                             void *d_ws, hipStream_t s)
 {
@@ -809,6 +1043,11 @@ sg_status sg_ss_table_build(const sg_grid *grid, int nf, const double *d_H, uint
         }
         int mfull = 0;  // the leading full modes
         while (mfull < mc && !sg_ss_is_banded(sg_ss_band(mfull, nr, du, full), nr)) ++mfull;
+        if (P.C.on && P.kind == 0 && !lin) {
+            if (!build_pairs(d_H, self, A, P, mc, mfull, chunk, cbytes, coef, modes, s)) return SG_ERR_UNSUPPORTED;
+            SG_HIP(hipGetLastError());
+            continue;
+        }
         const size_t rows = P.C.on ? ss_class_rows(A, P.C) : L.rows;
         size_t crows = P.C.on ? cbytes / (sizeof(float2) * mc) / SG_SS_TI * SG_SS_TI : ss_chunk_rows(L);
         if (crows > (size_t)1 << 30) crows = (size_t)1 << 30;
