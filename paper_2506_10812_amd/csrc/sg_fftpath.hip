@@ -9,7 +9,6 @@
 #include <tuple>
 #include <map>
 #include <mutex>
-#include <type_traits>
 #include <vector>
 
 #include <hip/hip_ext.h>
@@ -53,7 +52,7 @@ k_pass1(const DiscDev *discs, const WJob *wj, int nj, const float2 *twp, int kc,
     const int w = sg_uniform(sg_xcd_remap(blockIdx.x, kc));
     if (w >= nj) return;
     DiscDev D;
-    const WJob job = pass_job(discs, wj, one, w, G, D);
+    const WJob job = pass_job<1>(discs, wj, one, w, G, D);
     const int cb = job.base, cn = job.n;
     const int nr = D.nr, half = sg_blk_rows(nr) / 2;  // row pairs per fluid
     const LdsPlane<float> pl{lds + W * g};
@@ -218,7 +217,7 @@ k_pass2(const DiscDev *discs, const WJob *wj, int nj, const float2 *twu, int kc,
     const LdsPlane<float> pl[2] = {LdsPlane<float>{base + W * (2 * h)},
                                    LdsPlane<float>{base + W * (2 * h + 1)}};
     DiscDev D;
-    const WJob job = pass_job(discs, wj, one, w, S::G, D);
+    const WJob job = pass_job<2>(discs, wj, one, w, S::G, D);
     const int cb = job.base, cn = job.n;
     const int m = g < cn ? cb + g : cb;
     const bool pr = m == 0;  // columns 0 and n_phi/2 as one job
@@ -460,7 +459,7 @@ k_pass3(const DiscDev *discs, const WJob *wj, int nj, const float2 *twp, int kc,
     const int w = sg_uniform(sg_xcd_remap(blockIdx.x, kc));
     if (w >= nj) return;
     DiscDev D;
-    const WJob job = pass_job(discs, wj, one, w, G, D);
+    const WJob job = pass_job<3>(discs, wj, one, w, G, D);
     const int cb = job.base, cn = job.n;
     const int nr = D.nr, nrp = sg_blk_rows(nr);
     const size_t fs = sg_blk_field_elems(N, nr);
@@ -876,27 +875,46 @@ static sg_status launch_one(const DiscDev *dd, const WJob *wj, const Launch &L, 
     return SG_OK;
 }
 
-// The descriptor of a one-disc call: its plan's, moved to the call's addresses.
-static OneDisc one_disc_at(const Cached &C, const sg_disc &d, void *ws)
+// The addresses of a one-disc call.
+struct OneCall {
+    const char *table;
+    char *ws;
+    const float *sigma;
+    float *gr, *gp;
+};
+
+static OneCall one_call(const sg_disc &d, void *ws)
 {
-    OneDisc o;
-    o.jobs = 0;
-    o.D = C.plan.discs[0];
-    const char *tb = (const char *)d.table;
-    auto move = [](auto &p, const void *base) {  // offsets within a table are never 0
-        if (p) p = (std::remove_reference_t<decltype(p)>)((const char *)base + (uintptr_t)p);
-    };
-    o.D.sigma = d.sigma;
-    o.D.gr = d.g_r;
-    o.D.gp = d.g_phi;
-    move(o.D.spec, tb);
-    move(o.D.dspec, tb);
-    move(o.D.tw_u, tb);
-    move(o.D.tw_phi, tb);
-    move(o.D.ind, tb);
-    move(o.D.modes, tb);
-    o.D.gh = (float2 *)((char *)ws + (uintptr_t)o.D.gh);
-    o.D.st = (float2 *)ws;
+    return {(const char *)d.table, (char *)ws, d.sigma, d.g_r, d.g_phi};
+}
+
+// What launch L of a one-disc plan passes: the plan's offsets at the call's
+// addresses.  tw: the pass's twiddles.
+static OneDisc one_disc_at(const DiscDev &P, const OneCall &c, const Launch &L, const float2 *&tw)
+{
+    auto tab = [&](const void *p) -> const char * { return c.table + (uintptr_t)p; };
+    float2 *const st = (float2 *)c.ws, *const gh = (float2 *)(c.ws + (uintptr_t)P.gh);
+    OneDisc o{};
+    if (L.pass == 1) {
+        o.in = c.sigma;
+        o.out = st;
+    } else if (L.pass == 3) {
+        o.in = gh;
+        o.out = c.gr;
+        o.out2 = c.gp;
+    } else {
+        o.in = tab(P.spec);
+        o.in2 = tab((P.flags & SG_SEMI_SPECTRAL) ? (const void *)P.modes : (const void *)P.ind);
+        o.out = st;
+        o.out2 = gh;
+    }
+    o.nr = P.nr;
+    o.nphi = P.nphi;
+    o.nf = P.nf;
+    o.flags = P.flags;
+    o.ss_wmax = P.ss_wmax;
+    o.jobs = L.jobs;
+    tw = (const float2 *)tab(L.tw);
     return o;
 }
 
@@ -907,17 +925,13 @@ static const WJob *cached_wjobs(const Cached &C)
 
 // Launch L of a plan, of a one-disc plan with the call's descriptor; events
 // (may be null) take the kernel's own start and end.
-static sg_status launch_plan(const Cached &C, const OneDisc &one, const Launch &L, hipStream_t s,
+static sg_status launch_plan(const Cached &C, const OneCall &one, const Launch &L, hipStream_t s,
                              hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr)
 {
-    OneDisc o = one;
     const DiscDev *dd = (const DiscDev *)C.dmem;
     const WJob *wj = dd ? cached_wjobs(C) + L.wj_off : nullptr;
     const float2 *tw = L.tw;
-    if (!dd) {
-        o.jobs = L.jobs;
-        tw = L.pass == 2 ? o.D.tw_u : o.D.tw_phi;
-    }
+    const OneDisc o = dd ? OneDisc{} : one_disc_at(C.plan.discs[0], one, L, tw);
     if (e0)
         hipExtLaunchKernelGGL(L.k.fn, dim3(L.grid), dim3(L.k.wgs), (uint32_t)L.lds, s, e0, e1, 0, dd, wj, L.nj, tw,
                               L.K, o);
@@ -927,7 +941,7 @@ static sg_status launch_plan(const Cached &C, const OneDisc &one, const Launch &
     return SG_OK;
 }
 
-static sg_status enqueue(const Cached &C, const OneDisc &one, hipStream_t s)
+static sg_status enqueue(const Cached &C, const OneCall &one, hipStream_t s)
 {
     for (const Launch &L : C.plan.launches) {
         const sg_status st = launch_plan(C, one, L, s);
@@ -1036,19 +1050,16 @@ static void destroy(Cached *C)
     delete C;
 }
 
-// Plan, device tables and graph of a batch signature (built on first use), and
-// for a one-disc plan the call's descriptor.  Caller holds g_mu.
-static sg_status get_cached(const sg_disc *discs, int n, void *ws, Cached *&out, OneDisc &one)
+// Plan, device tables and graph of a batch signature (built on first use).
+// Caller holds g_mu.
+static sg_status get_cached(const sg_disc *discs, int n, void *ws, Cached *&out)
 {
     const bool single = one_disc(discs, n);
-    sg_disc at0 = discs[0];  // a one-disc plan holds offsets
-    at0.table = nullptr;
     auto key = single ? shape_signature(discs[0]) : signature(discs, n, ws);
     auto it = g_cache.find(key);
     if (it != g_cache.end()) {
         out = it->second;
         out->last_use = ++g_tick;
-        if (single) one = one_disc_at(*out, discs[0], ws);
         return SG_OK;
     }
     if (g_cache.size() >= SG_CACHE_MAX) {
@@ -1061,6 +1072,8 @@ static sg_status get_cached(const sg_disc *discs, int n, void *ws, Cached *&out,
     }
     Cached *C = new Cached;
     C->last_use = ++g_tick;
+    sg_disc at0 = discs[0];  // a one-disc plan holds offsets
+    at0.table = nullptr;
     if (!build_plan(single ? &at0 : discs, n, single ? nullptr : (char *)ws, C->plan)) {
         delete C;
         return SG_ERR_UNSUPPORTED;
@@ -1068,7 +1081,6 @@ static sg_status get_cached(const sg_disc *discs, int n, void *ws, Cached *&out,
     if (single) {
         g_cache[key] = C;
         out = C;
-        one = one_disc_at(*C, discs[0], ws);
         return SG_OK;
     }
     const size_t bd = sg_align256(sizeof(DiscDev) * n);
@@ -1112,8 +1124,8 @@ sg_status sg_fft_run(const sg_disc *discs, int n, void *ws, hipStream_t s)
 {
     std::lock_guard<std::mutex> lk(g_mu);
     Cached *C = nullptr;
-    OneDisc one;
-    const sg_status st = get_cached(discs, n, ws, C, one);
+    const OneCall one = one_call(discs[0], ws);
+    const sg_status st = get_cached(discs, n, ws, C);
     if (st != SG_OK) return st;
     if (C->exec) {
         SG_HIP(hipGraphLaunch(C->exec, s));
@@ -1127,7 +1139,7 @@ sg_status sg_fft_run(const sg_disc *discs, int n, void *ws, hipStream_t s)
 // kernel's own start and end, not a marker between launches), with nothing
 // run before it: a caller that evicts the caches first times a cold step.
 // ms[p] = the summed kernel time of pass p's launches.
-static sg_status profile_one_step(const Cached &C, const OneDisc &one, hipStream_t s, float *ms)
+static sg_status profile_one_step(const Cached &C, const OneCall &one, hipStream_t s, float *ms)
 {
     const size_t nl = C.plan.launches.size();
     std::vector<hipEvent_t> ev(2 * nl, nullptr);
@@ -1159,8 +1171,8 @@ sg_status sg_fft_profile(const sg_disc *discs, int n, void *ws, hipStream_t s, i
 {
     std::lock_guard<std::mutex> lk(g_mu);
     Cached *C = nullptr;
-    OneDisc one;
-    sg_status st = get_cached(discs, n, ws, C, one);
+    const OneCall one = one_call(discs[0], ws);
+    sg_status st = get_cached(discs, n, ws, C);
     if (st != SG_OK) return st;
     if (reps == 1) return profile_one_step(*C, one, s, ms);
     st = enqueue(*C, one, s);

@@ -51,13 +51,23 @@ struct WJob {
 // job count) and its jobs are numbered in order, so a workgroup starts with
 // its data's addresses in its kernel arguments; in a batch it first reads its
 // workgroup job, then that job's descriptor (two dependent loads per pass).
-// Three passes of a 64 x 128 disc: 17.6 -> 15.3 us a call, of a two-fluid
+// Three passes of a 64 x 128 disc: 17.6 -> 14.8 us a call, of a two-fluid
 // 1024 x 2048 disc 62.4 -> 60.3.  Species discs keep the descriptor in memory.
+// Only what the pass reads is passed (56 bytes): whole descriptors, 168 bytes
+// a launch, cost more to enqueue than the loads took where the middle pass is
+// short (semi-spectral 86 x 128 two-fluid: 15.8 us a call with loads, 16.5 with
+// whole descriptors, 15.7 so).
 struct OneDisc {
-    DiscDev D;
-    int jobs;
+    const void *in, *in2;  // pass 1: Sigma; 2: spectra, indirect-term coefficients; 3: g^; semi-spectral: operators, modes
+    void *out, *out2;      // pass 1: Sigma~; 2 and semi-spectral: Sigma~, g^; 3: g_r, g_phi
+    int nr, nphi, nf, jobs;
+    uint32_t flags;
+    int ss_wmax;
 };
 
+#define SG_PASS_SS 4  // the semi-spectral middle pass, as pass_job's PASS
+
+template <int PASS>
 __device__ inline WJob pass_job(const DiscDev *discs, const WJob *wj, const OneDisc &one, int w, int G, DiscDev &D)
 {
     WJob j;
@@ -66,7 +76,26 @@ __device__ inline WJob pass_job(const DiscDev *discs, const WJob *wj, const OneD
         j.base = w * G;
         j.n = min(G, one.jobs - j.base);
         if (j.n <= 0) j.base = j.n = 0;
-        D = one.D;
+        if constexpr (PASS == 1) {
+            D.sigma = (const float *)one.in;
+            D.st = (float2 *)one.out;
+        } else if constexpr (PASS == 3) {
+            D.gh = (float2 *)one.in;
+            D.gr = (float *)one.out;
+            D.gp = (float *)one.out2;
+        } else {
+            D.spec = (const float2 *)one.in;
+            if constexpr (PASS == 2) D.ind = (const double *)one.in2;
+            else D.modes = (const SsMode *)one.in2;
+            D.st = (float2 *)one.out;
+            D.gh = (float2 *)one.out2;
+        }
+        D.nr = one.nr;
+        D.nphi = one.nphi;
+        D.nf = one.nf;
+        D.flags = one.flags;
+        D.ss_wmax = one.ss_wmax;
+        D.ns = 0;
     } else {
         j.disc = sg_uniform(wj[w].disc);
         j.base = sg_uniform(wj[w].base);

@@ -1121,7 +1121,7 @@ __global__ void __launch_bounds__(256) k_ss_pass(const DiscDev *discs, const WJo
     const int w = sg_uniform(sg_xcd_remap(blockIdx.x, kc));
     if (w >= nj) return;
     DiscDev D;
-    const WJob job = pass_job(discs, wj, one, w, 1, D);
+    const WJob job = pass_job<SG_PASS_SS>(discs, wj, one, w, 1, D);
     if (job.n == 0) return;  // cluster padding
     const int idx = job.base;
     const int nr = D.nr, nrt = (nr + 1) & ~1, nb = (nr + TB - 1) / TB;
