@@ -295,7 +295,7 @@ def summarize_rocprof(out):
         lines = ["# Kernel time, semi-spectral path, App. D flaring gas disc 1200x2048", "",
                  "Command (from /tmp, TMPDIR=/tmp; `<repo>` = repository root, `<out>` = output "
                  "root):", "", "    " + cmd["ss_kt"], "",
-                 "The run builds the radial operators twice (k_ss_rows, k_ss_scatter, self cells), "
+                 "The run builds the radial operators twice (k_ss_pairs, k_ss_scatter_pairs, self cells), "
                  "tunes the batch, then times solves (k_pass1, k_ss_pass, k_pass3) and per-pass "
                  "launches.", "",
                  "| Kernel | Calls | Average (us) | Min (us) | Max (us) | Share (%) |",
@@ -471,7 +471,7 @@ def summarize_direct(out, prof, cmd):
              "| Kernel | Time (us) | VALU instr. | per pair | FP add/mul/fma | Nominal issue ratio "
              "| TFLOP/s | of 78.6 |",
              "|---|---|---|---|---|---|---|---|"]
-    for kname, cells in (("k_direct<float, 1>", 256 * 512), ("k_direct<double, 1>", 64 * 128)):
+    for kname, cells in (("k_ring_sum<float, 2>", 256 * 512), ("k_ring_sum<double, 2>", 64 * 128)):
         st = stats.get(kname)
         vals = {}
         for r in rows:

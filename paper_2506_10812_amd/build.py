@@ -24,7 +24,8 @@ GEN = os.path.join(OBJ, "include")  # generated headers
 
 def _generate() -> None:
     """Host step: build and run gen_cheb64.cpp, which writes sg_cheb64.h (the
-    Chebyshev coefficients of the double mid-range F(x) branch)."""
+    polynomial tables of the kernel functions in double and float, and the
+    double twiddles)."""
     os.makedirs(GEN, exist_ok=True)
     exe = os.path.join(OBJ, "gen_cheb64")
     subprocess.check_call(["g++", "-O2", "-std=c++17", os.path.join(CSRC, "gen_cheb64.cpp"), "-o", exe])
