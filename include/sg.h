@@ -279,9 +279,9 @@ typedef struct sg_disc {
  * branches run those classes side by side; a batch with one class per pass
  * enqueues its three kernels directly (a graph launch would only add
  * latency).  The plan, the graph where used and a device copy of the batch
- * descriptors are cached per (sizes, pointers) signature on the first call
- * (that call allocates and synchronises once); later calls with the same
- * signature only launch.  A single disc (without species) passes its
+ * descriptors are cached per (sizes, pointers, and radii of semi-spectral
+ * discs) signature on the first call (that call allocates and synchronises
+ * once); later calls with the same signature only launch.  A single disc (without species) passes its
  * descriptor by value: its plan is kept by grid, fluid count and flags, holds
  * no device memory, and serves any buffers without a synchronisation.  At most 256 signatures are kept; a new one
  * beyond that releases the least recently used (after a device

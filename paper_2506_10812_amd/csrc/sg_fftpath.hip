@@ -831,6 +831,18 @@ static uint64_t g_tick = 0;
 // on which the semi-spectral band and so the staged column depends.)
 static bool one_disc(const sg_disc *discs, int n) { return n == 1 && discs[0].n_species == 0; }
 
+// The radii are part of a semi-spectral disc's key: they set the band of its
+// modes and so the staged column (ss_wmax).  A plan of narrower bands makes
+// the middle pass drop the modes that exceed it.
+static void push_radii(std::vector<uint64_t> &k, const sg_disc &d)
+{
+    if (!(d.flags & SG_SEMI_SPECTRAL)) return;
+    uint64_t w[2];
+    memcpy(&w[0], &d.grid.r_min, 8);
+    memcpy(&w[1], &d.grid.r_max, 8);
+    k.insert(k.end(), w, w + 2);
+}
+
 static std::vector<uint64_t> shape_signature(const sg_disc &d)
 {
     std::vector<uint64_t> k(6);
@@ -847,7 +859,7 @@ static std::vector<uint64_t> shape_signature(const sg_disc &d)
 static std::vector<uint64_t> signature(const sg_disc *discs, int n, void *ws)
 {
     std::vector<uint64_t> k;
-    k.reserve(n * 8 + 2);
+    k.reserve(n * 9 + 2);
     int dev = 0;
     (void)hipGetDevice(&dev);
     k.push_back((uint64_t)dev);
@@ -863,6 +875,7 @@ static std::vector<uint64_t> signature(const sg_disc *discs, int n, void *ws)
         k.push_back((uint64_t)(uintptr_t)d.g_r);
         k.push_back((uint64_t)(uintptr_t)d.g_phi);
         k.push_back((uint64_t)(uintptr_t)d.table);
+        push_radii(k, d);
     }
     return k;
 }
