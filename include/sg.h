@@ -282,8 +282,9 @@ typedef struct sg_disc {
  * descriptors are cached per (sizes, pointers, and radii of semi-spectral
  * discs) signature on the first call (that call allocates and synchronises
  * once); later calls with the same signature only launch.  A single disc (without species) passes its
- * descriptor by value: its plan is kept by grid, fluid count and flags, holds
- * no device memory, and serves any buffers without a synchronisation.  At most 256 signatures are kept; a new one
+ * descriptor by value: its plan is kept by sizes, fluid count and flags (and
+ * radii, if semi-spectral), holds no device memory, and serves any buffers
+ * without a synchronisation.  At most 256 signatures are kept; a new one
  * beyond that releases the least recently used (after a device
  * synchronisation).  d_ws: sg_field_fft_workspace_bytes(discs, n)
  * bytes, 256-byte aligned; its address is part of a batch's signature.

@@ -827,8 +827,7 @@ static uint64_t g_tick = 0;
 
 // Batches of one disc (without species) are cached by shape alone: nothing of
 // theirs is kept on the device, and each call fills the descriptor that its
-// launches take by value with the addresses it was given.  (With the radii,
-// on which the semi-spectral band and so the staged column depends.)
+// launches take by value with the addresses it was given.
 static bool one_disc(const sg_disc *discs, int n) { return n == 1 && discs[0].n_species == 0; }
 
 // The radii are part of a semi-spectral disc's key: they set the band of its
@@ -845,14 +844,13 @@ static void push_radii(std::vector<uint64_t> &k, const sg_disc &d)
 
 static std::vector<uint64_t> shape_signature(const sg_disc &d)
 {
-    std::vector<uint64_t> k(6);
+    std::vector<uint64_t> k(3);
     int dev = 0;
     (void)hipGetDevice(&dev);
-    k[0] = (1ull << 40) | (uint64_t)dev;  // no batch signature has this length
+    k[0] = (1ull << 40) | (uint64_t)dev;  // no batch signature begins so
     k[1] = ((uint64_t)d.grid.n_r << 32) | (uint32_t)d.grid.n_phi;
     k[2] = ((uint64_t)d.fluids.n_fluids << 32) | d.flags;
-    memcpy(&k[3], &d.grid.r_min, 8);
-    memcpy(&k[4], &d.grid.r_max, 8);
+    push_radii(k, d);
     return k;
 }
 

@@ -61,3 +61,26 @@ def test_semi_spectral_batches_follow_the_radii(sg, n_discs, groups, first, then
     for (a, b), (x, y) in zip(got, want):
         assert bool(torch.isfinite(x).all()) and float(x.abs().max()) > 0
         assert torch.equal(a, x) and torch.equal(b, y)
+
+
+@pytest.mark.parametrize("n_discs", [1, 2])
+def test_fft_plans_serve_any_radii(sg, n_discs):
+    """Nothing in an FFT-path plan depends on the radii: a grid that moves
+    between calls (a table per step, the same buffers) takes no further plan."""
+    from paper_2506_10812_amd import torch_ops as T
+    print(f"plan key fft {n_discs}", flush=True)
+    f, sig = sg.fluids([0.05]), torch.rand((n_discs, 1, 16, 32), device="cuda")
+    out, want = torch.empty((2, n_discs, 1, 16, 32), device="cuda"), []
+    ws = torch.empty(1 << 20, dtype=torch.uint8, device="cuda")
+    table = T.build_table(sg.grid(16, 32, 0.4, 2.5), f)
+    n = []
+    for r_max in (2.5, 2.6, 2.7, 25.0):
+        g = sg.grid(16, 32, 0.4, r_max)
+        table.copy_(T.build_table(g, f))
+        sg.field_fft([sg.make_disc(g, f, 0, sig[i], out[0, i], out[1, i], table) for i in range(n_discs)], ws)
+        torch.cuda.synchronize()
+        n.append(sg.field_fft_cache_entries())
+        want.append(out.clone())
+        assert bool(torch.isfinite(out).all())
+    assert n == [n[0]] * len(n)
+    assert all(not torch.equal(want[0], w) for w in want[1:])  # the tables were used
