@@ -294,16 +294,31 @@ template <int FN> __device__ inline float sg_v(float u, const float *w)
     return f;
 }
 
-// Float F(x) and G0(x); w: the table of V or Vg.
+// Float F(x) and G0(x) over the whole range of x; w: the table of V or Vg.
+// The power series gives them below 1/16: u^{3/2} overflows from x = 2e-26 down.
 __device__ inline float sg_F32(float x, const float *w)
 {
+    const bool ser = x < 0.0625f;
     const float u = sg_rcp(x);
-    return u * sqrtf(u) * sg_v<SG_FN_V>(u, w);
+    float f = u * sg_rsqrt(x) * sg_v<SG_FN_V>(ser ? 1.0f : u, w);
+    if (__any(ser)) {
+        SG_NO_SPECULATE();
+        float s;
+        sg_F_series<float, 5>(x, s, nullptr);
+        f = ser ? s : f;
+    }
+    return f;
 }
 __device__ inline float sg_G0_32(float x, const float *w)
 {
-    const float u = sg_rcp(x);
-    return sqrtf(u) * sg_v<SG_FN_VG>(u, w);
+    const bool ser = x < 0.0625f;
+    float g = sg_rsqrt(x) * sg_v<SG_FN_VG>(ser ? 1.0f : sg_rcp(x), w);
+    if (__any(ser)) {
+        SG_NO_SPECULATE();
+        const float s = sg_G0_series<float, 5>(x);
+        g = ser ? s : g;
+    }
+    return g;
 }
 
 // ------------------------------------------------------------------------
