@@ -66,6 +66,13 @@ template <typename T> __device__ inline void sg_two_sum_acc(T &s, T &c, T v)
     s = t;
 }
 
+// The sums take lengths in units of the power of two below r_min: a pair's
+// factor (s^2/8)^{-3/2} and the masses r^3 Sigma would otherwise leave float's
+// range where lengths are far from 1 (discs in metres or centimetres: subnormal
+// from s = 1e13 on).  The field does not depend on the unit of length, the
+// potential is proportional to it; a power of two costs no rounding.
+static double length_unit(const sg_grid &g) { return ldexp(1.0, ilogb(g.r_min)); }
+
 // Ring radius: log grid (lin = 0) or uniform grid (a = r_min, b = dr).
 __device__ inline double dir_radius(int lin, double lnrmin, double du, double rmin, double dr, int i)
 {
@@ -76,8 +83,9 @@ template <typename T>
 __global__ void k_direct_prep(int nr, int nphi, int nf, double lnrmin, double du, double dphi,
                               const double *h, const T *sigma, const T *H, T *rrow, T *sx, T *ex,
                               T *sph, T *snp, T *mass, T *H2, int lin, double rmin, double dr, double *Hd,
-                              int scaled)
+                              int scaled, double unit)
 {
+    // lnrmin, rmin, dr and the radii here in units of unit; sigma, H and Hd not
     const int64_t N = (int64_t)nr * nphi;
     const int64_t tid = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -101,15 +109,13 @@ __global__ void k_direct_prep(int nr, int nphi, int nf, double lnrmin, double du
         // or -1 / (2 sqrt(pi)) (potential, 2)
         const double c = scaled == 1 ? -r / (8.0 * SG_SQRT_PI) : scaled == 2 ? -0.5 / SG_SQRT_PI : 1.0;
         mass[k] = (T)((double)sigma[k] * (lin ? r * dr : r * r * du) * dphi * c);
-        double Hk;
-        if (H) Hk = (double)H[k];
-        else Hk = h[k / N] * r;
+        const double Hk = H ? (double)H[k] / unit : h[k / N] * r;
         H2[k] = (T)(0.5 * Hk * Hk);  // H_ab^2 = H2_a + H2_b
-        if (lin && H) Hd[k] = Hk;  // double H per cell for the own-cell integrals
+        if (lin && H) Hd[k] = (double)H[k];  // double H per cell for the own-cell integrals
     }
     if (lin && !H)  // double H per ring
         for (int64_t k = tid; k < (int64_t)nf * nr; k += stride)
-            Hd[k] = h[k / nr] * dir_radius(1, 0.0, 0.0, rmin, dr, (int)(k % nr));
+            Hd[k] = h[k / nr] * (dir_radius(1, 0.0, 0.0, rmin, dr, (int)(k % nr)) * unit);
 }
 
 // General sum (a scale height per cell): VALU bound.  Per source one
@@ -601,7 +607,7 @@ __global__ void __launch_bounds__(256) k_potential(DirectArgs<T> A)
 
 template <typename T, int NF>
 __global__ void k_potential_reduce(const T *partial, int S, int64_t N, int nphi, const double *self,
-                                   int per_row, int with_self, const T *sigma, T *pot)
+                                   int per_row, int with_self, const T *sigma, T *pot, double unit)
 {
     const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (t >= N) return;
@@ -615,7 +621,7 @@ __global__ void k_potential_reduce(const T *partial, int S, int64_t N, int nphi,
             sg_two_sum_acc(sum, e, (double)pp[0]);
             sg_two_sum_acc(sum, e, (double)pp[N]);
         }
-        sum += e;
+        sum = (sum + e) * unit;
         if (with_self) {
             double st = 0.0;
 #pragma unroll
@@ -696,7 +702,7 @@ static sg_status direct_run(const sg_grid *g, int nf, const double *h, const T *
     const int64_t N = (int64_t)nr * nphi;
     const double du = log(g->r_max / g->r_min) / nr;
     const double dphi = 2.0 * SG_PI / nphi;
-    const double lnrmin = log(g->r_min);
+    const double lnrmin = log(g->r_min), unit = length_unit(*g);
     const int lin = (flags & SG_LINEAR_R) ? 1 : 0;
     const double dr = (g->r_max - g->r_min) / nr;
     int S = direct_splits(nr, N);
@@ -734,8 +740,8 @@ static sg_status direct_run(const sg_grid *g, int nf, const double *h, const T *
         int64_t nb = (work + 255) / 256;
         if (nb > 65536) nb = 65536;
         hipLaunchKernelGGL(k_direct_prep<T>, dim3((unsigned)nb), dim3(256), 0, s, nr, nphi, nf,
-                           lnrmin, du, dphi, (const double *)dh, sigma, H, rrow, sx, ex, sph, snp,
-                           mass, H2, lin, g->r_min, dr, Hd, percell ? 1 : 0);
+                           log(g->r_min / unit), du, dphi, (const double *)dh, sigma, H, rrow, sx, ex, sph, snp,
+                           mass, H2, lin, g->r_min / unit, dr / unit, Hd, percell ? 1 : 0, unit);
         SG_HIP(hipGetLastError());
     }
     const int with_self = !(flags & SG_SELF_CELL_EXCLUDE);
@@ -837,7 +843,7 @@ static sg_status potential_run(const sg_grid *g, int nf, const double *h, const 
     const int64_t N = (int64_t)nr * nphi;
     const double du = log(g->r_max / g->r_min) / nr;
     const double dphi = 2.0 * SG_PI / nphi;
-    const double lnrmin = log(g->r_min);
+    const double lnrmin = log(g->r_min), unit = length_unit(*g);
     int S = direct_splits(nr, N);
     const int rps = (nr + S - 1) / S;
     char *o = (char *)ws;
@@ -866,8 +872,8 @@ static sg_status potential_run(const sg_grid *g, int nf, const double *h, const 
         int64_t nb = (work + 255) / 256;
         if (nb > 65536) nb = 65536;
         hipLaunchKernelGGL(k_direct_prep<T>, dim3((unsigned)nb), dim3(256), 0, s, nr, nphi, nf,
-                           lnrmin, du, dphi, (const double *)dh, sigma, H, rrow, sx, ex, sph, snp,
-                           mass, H2, 0, 0.0, 0.0, nullptr, percell ? 2 : 0);
+                           log(g->r_min / unit), du, dphi, (const double *)dh, sigma, H, rrow, sx, ex, sph, snp,
+                           mass, H2, 0, 0.0, 0.0, nullptr, percell ? 2 : 0, unit);
         SG_HIP(hipGetLastError());
     }
     const int with_self = !(flags & SG_SELF_CELL_EXCLUDE);
@@ -904,7 +910,7 @@ static sg_status potential_run(const sg_grid *g, int nf, const double *h, const 
     const unsigned nb = (unsigned)((N + 255) / 256);
 #define SG_PRED(NF)                                                                                      \
     hipLaunchKernelGGL((k_potential_reduce<T, NF>), dim3(nb), dim3(256), 0, s, partial, S, N, nphi, self, \
-                       percell ? 0 : 1, with_self, sigma, pot)
+                       percell ? 0 : 1, with_self, sigma, pot, unit)
     switch (nf) {
     case 1: SG_PRED(1); break;
     case 2: SG_PRED(2); break;
