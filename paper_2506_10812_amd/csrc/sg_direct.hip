@@ -20,7 +20,7 @@
 // H = h r (d_H == NULL) makes the kernel between two rings a function of the
 // azimuth offset alone: k_ring_sum evaluates it once per offset and sums it
 // against the source row as a Toeplitz product.  The rest of this comment is
-// about the general sum with a scale height per cell.
+// about the general sum with a scale height per cell (and of rings of few cells).
 //
 // Layout: one thread per target cell (256 per workgroup), all target fluids
 // in registers; the source loop runs over whole radial rows so every
@@ -684,6 +684,22 @@ size_t sg_direct_ws_bytes(int nr, int nphi, int nf, sg_dtype dt, int percell)
     return o;
 }
 
+// H = h r sums by the general kernels (one pair of cells at a time) on many
+// rings of few azimuths: a ring pair then has fewer terms than the 8 x 8 step of
+// the ring sums, whose staging is left (a barrier per KS rings of few
+// evaluations).  Ring sums / general kernels in us, one fluid: field in float
+// 6000 x 1 3010 / 163, 1000 x 6 193 / 150, 750 x 8 108 / 109; in double 6000 x 1
+// 4190 / 265, 1000 x 5 267 / 217, 1000 x 6 226 / 220 (four fluids 1640 / 1920);
+// potential 6000 x 1 1500 / 490, 1500 x 4 382 / 355, 4000 x 5 1240 / 1300.  On
+// fewer rings the general kernels' chains are the longer ones: 1000 x 1 213 /
+// 257, 250 x 4 91 / 162, potential 1000 x 1 247 / 349; four fluids 500 x 1 545 /
+// 815, 900 x 1 1390 / 787.
+template <typename T, int NC> static bool few_azimuths(int nr, int nphi, int nf)
+{
+    const int rings = NC == 1 ? 1500 : nphi == 1 ? 1100 - 100 * nf : 1000;
+    return nr >= rings && nphi < (NC == 1 ? 5 : sizeof(T) == 8 ? 6 : 8);
+}
+
 // H = h r: the ring sums into at most smax splits; returns the splits used.
 template <typename T, int NC> static int ring_sum(const DirectArgs<T> &A, int nf, int smax, hipStream_t s)
 {
@@ -721,6 +737,7 @@ static sg_status direct_run(const sg_grid *g, int nf, const double *h, const T *
     T *mass = (T *)take(sizeof(T) * nf * N);
     T *H2 = (T *)take(sizeof(T) * nf * N);
     const int percell = H != nullptr;
+    const bool by_cell = percell || few_azimuths<T, 2>(nr, nphi, nf);
     double *self = (double *)take(sizeof(double) * nf * nf * (percell ? N : nr));
     T *partial = (T *)take(sizeof(T) * (size_t)S * nf * 4 * N);
     // uniform grid: double H for the own-cell integrals, per cell or per ring,
@@ -741,7 +758,7 @@ static sg_status direct_run(const sg_grid *g, int nf, const double *h, const T *
         if (nb > 65536) nb = 65536;
         hipLaunchKernelGGL(k_direct_prep<T>, dim3((unsigned)nb), dim3(256), 0, s, nr, nphi, nf,
                            log(g->r_min / unit), du, dphi, (const double *)dh, sigma, H, rrow, sx, ex, sph, snp,
-                           mass, H2, lin, g->r_min / unit, dr / unit, Hd, percell ? 1 : 0, unit);
+                           mass, H2, lin, g->r_min / unit, dr / unit, Hd, by_cell ? 1 : 0, unit);
         SG_HIP(hipGetLastError());
     }
     const int with_self = !(flags & SG_SELF_CELL_EXCLUDE);
@@ -790,7 +807,7 @@ static sg_status direct_run(const sg_grid *g, int nf, const double *h, const T *
     A.mass = mass;
     A.H2 = H2;
     A.partial = partial;
-    if (percell) {
+    if (by_cell) {
         dim3 grid((unsigned)((N + 255) / 256), (unsigned)S);
         switch (nf) {
         case 1: hipLaunchKernelGGL((k_direct<T, 1>), grid, dim3(256), 0, s, A); break;
@@ -860,6 +877,7 @@ static sg_status potential_run(const sg_grid *g, int nf, const double *h, const 
     T *mass = (T *)take(sizeof(T) * nf * N);
     T *H2 = (T *)take(sizeof(T) * nf * N);
     const int percell = H != nullptr;
+    const bool by_cell = percell || few_azimuths<T, 1>(nr, nphi, nf);
     double *self = (double *)take(sizeof(double) * nf * nf * (percell ? N : nr));
     T *partial = (T *)take(sizeof(T) * (size_t)S * nf * 2 * N);
     double *dh = (double *)take(sizeof(double) * 4);
@@ -873,7 +891,7 @@ static sg_status potential_run(const sg_grid *g, int nf, const double *h, const 
         if (nb > 65536) nb = 65536;
         hipLaunchKernelGGL(k_direct_prep<T>, dim3((unsigned)nb), dim3(256), 0, s, nr, nphi, nf,
                            log(g->r_min / unit), du, dphi, (const double *)dh, sigma, H, rrow, sx, ex, sph, snp,
-                           mass, H2, 0, 0.0, 0.0, nullptr, percell ? 2 : 0, unit);
+                           mass, H2, 0, 0.0, 0.0, nullptr, by_cell ? 2 : 0, unit);
         SG_HIP(hipGetLastError());
     }
     const int with_self = !(flags & SG_SELF_CELL_EXCLUDE);
@@ -895,7 +913,7 @@ static sg_status potential_run(const sg_grid *g, int nf, const double *h, const 
     A.mass = mass;
     A.H2 = H2;
     A.partial = partial;
-    if (percell) {
+    if (by_cell) {
         dim3 grid((unsigned)((N + 255) / 256), (unsigned)S);
         switch (nf) {
         case 1: hipLaunchKernelGGL((k_potential<T, 1>), grid, dim3(256), 0, s, A); break;
