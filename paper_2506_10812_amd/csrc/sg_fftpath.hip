@@ -514,6 +514,7 @@ struct PassKernel {
     int wgs, G, K;    // K: default XCD cluster size
     int tb = 0;       // semi-spectral pass: target rows per workgroup job
     int lds_per_row = 0, lds_fixed = 0;  // its dynamic LDS: per radial row, fixed
+    KernelFn fn_one = nullptr;           // its kernel for one disc by value (null: fn takes both)
 };
 
 // Shapes above 1024 threads do not exist (null kernel).
@@ -570,7 +571,7 @@ static bool ss_pass_kernel(int nf, int gm, PassKernel &out)
 {
     SsPassInfo k;
     if (!sg_ss_pass_kernel(nf, gm, k)) return false;
-    out = PassKernel{k.fn, k.wgs, 1, 1, k.tb, k.lds_per_row, k.lds_fixed};
+    out = PassKernel{k.fn, k.wgs, 1, 1, k.tb, k.lds_per_row, k.lds_fixed, k.fn_one};
     return true;
 }
 
@@ -943,11 +944,11 @@ static sg_status launch_plan(const Cached &C, const OneCall &one, const Launch &
     const WJob *wj = dd ? cached_wjobs(C) + L.wj_off : nullptr;
     const float2 *tw = L.tw;
     const OneDisc o = dd ? OneDisc{} : one_disc_at(C.plan.discs[0], one, L, tw);
+    const KernelFn fn = !dd && L.k.fn_one ? L.k.fn_one : L.k.fn;
     if (e0)
-        hipExtLaunchKernelGGL(L.k.fn, dim3(L.grid), dim3(L.k.wgs), (uint32_t)L.lds, s, e0, e1, 0, dd, wj, L.nj, tw,
-                              L.K, o);
+        hipExtLaunchKernelGGL(fn, dim3(L.grid), dim3(L.k.wgs), (uint32_t)L.lds, s, e0, e1, 0, dd, wj, L.nj, tw, L.K, o);
     else
-        hipLaunchKernelGGL(L.k.fn, dim3(L.grid), dim3(L.k.wgs), (unsigned)L.lds, s, dd, wj, L.nj, tw, L.K, o);
+        hipLaunchKernelGGL(fn, dim3(L.grid), dim3(L.k.wgs), (unsigned)L.lds, s, dd, wj, L.nj, tw, L.K, o);
     SG_HIP(hipGetLastError());
     return SG_OK;
 }

@@ -55,8 +55,7 @@ struct WJob {
 // 1024 x 2048 disc 62.4 -> 60.3.  Species discs keep the descriptor in memory.
 // Only what the pass reads is passed (56 bytes): whole descriptors, 168 bytes
 // a launch, cost more to enqueue than the loads took where the middle pass is
-// short (semi-spectral 86 x 128 two-fluid: 15.8 us a call with loads, 16.5 with
-// whole descriptors, 15.7 so).
+// short.
 struct OneDisc {
     const void *in, *in2;  // pass 1: Sigma; 2: spectra, indirect-term coefficients; 3: g^; semi-spectral: operators, modes
     void *out, *out2;      // pass 1: Sigma~; 2 and semi-spectral: Sigma~, g^; 3: g_r, g_phi
@@ -67,11 +66,19 @@ struct OneDisc {
 
 #define SG_PASS_SS 4  // the semi-spectral middle pass, as pass_job's PASS
 
-template <int PASS>
+// Where a kernel takes its job and descriptor from: told by one.jobs, from
+// memory (a batch), by value (one disc).  The semi-spectral pass has a kernel
+// for each of the last two: deciding in the kernel put the read of one.jobs
+// before all other reads of a pass that is short (two fluids 64 x 512 17.3 us a
+// call with loads alone, 17.7 decided in the kernel, 17.0 so; 86 x 128 17.4,
+// 17.6, 17.2; one fluid 200 x 512 21.5, 21.5, 20.7).
+enum { SG_SRC_EITHER, SG_SRC_BATCH, SG_SRC_ONE };
+
+template <int PASS, int SRC = SG_SRC_EITHER>
 __device__ inline WJob pass_job(const DiscDev *discs, const WJob *wj, const OneDisc &one, int w, int G, DiscDev &D)
 {
     WJob j;
-    if (one.jobs > 0) {
+    if (SRC == SG_SRC_ONE || (SRC == SG_SRC_EITHER && one.jobs > 0)) {
         j.disc = 0;
         j.base = w * G;
         j.n = min(G, one.jobs - j.base);

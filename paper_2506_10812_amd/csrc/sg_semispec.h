@@ -13,7 +13,8 @@
 // lds_per_row * c + lds_fixed bytes of dynamic LDS, c the longest staged
 // column of a mode (n_r, or n_r + 2 w + 4 for a banded mode).
 struct SsPassInfo {
-    void (*fn)(const DiscDev *, const WJob *, int, const float2 *, int, OneDisc);
+    void (*fn)(const DiscDev *, const WJob *, int, const float2 *, int, OneDisc);      // of a batch
+    void (*fn_one)(const DiscDev *, const WJob *, int, const float2 *, int, OneDisc);  // of one disc by value
     int wgs, tb, lds_per_row, lds_fixed;
 };
 

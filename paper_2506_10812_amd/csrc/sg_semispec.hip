@@ -1111,7 +1111,7 @@ __device__ inline void ss_ld4(const float2 *p, uint32_t i, float2 &x, float2 &y)
 // that target i0 + v reads source i0 + v + d - w at window index V l + v + d.  The operator rows
 // are streamed once with 16-byte loads, U rows in flight: this pass is bound
 // by reading the table.
-template <int NF, int V, int S, bool NT, int U>
+template <int NF, int V, int S, bool NT, int U, int SRC>
 __global__ void __launch_bounds__(256) k_ss_pass(const DiscDev *discs, const WJob *wj, int nj, const float2 *,
                                                  int kc, OneDisc one)
 {
@@ -1121,7 +1121,7 @@ __global__ void __launch_bounds__(256) k_ss_pass(const DiscDev *discs, const WJo
     const int w = sg_uniform(sg_xcd_remap(blockIdx.x, kc));
     if (w >= nj) return;
     DiscDev D;
-    const WJob job = pass_job<SG_PASS_SS>(discs, wj, one, w, 1, D);
+    const WJob job = pass_job<SG_PASS_SS, SRC>(discs, wj, one, w, 1, D);
     if (job.n == 0) return;  // cluster padding
     const int idx = job.base;
     const int nr = D.nr, nrt = (nr + 1) & ~1, nb = (nr + TB - 1) / TB;
@@ -1233,7 +1233,8 @@ template <int NF, int V, int S, bool NT = false, int U = 8> static SsPassInfo ss
 {
     constexpr int LN = 256 / S;
     SsPassInfo k;
-    k.fn = k_ss_pass<NF, V, S, NT, U>;
+    k.fn = k_ss_pass<NF, V, S, NT, U, SG_SRC_BATCH>;
+    k.fn_one = k_ss_pass<NF, V, S, NT, U, SG_SRC_ONE>;
     k.wgs = 256;
     k.tb = LN * V;
     k.lds_per_row = NF * (int)sizeof(float2);
