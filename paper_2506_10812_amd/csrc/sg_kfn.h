@@ -19,7 +19,9 @@
 //     The same three branches give D(x) = -x F' - 3/2 F (what the derivatives
 //     with respect to the scale heights need; the difference of its two terms
 //     would lose log10(x) digits), G0(x) = e^x K0(x) (the potential's kernel)
-//     and E(x) = 2 x F - G0 (its derivative).  A block copies the one table
+//     and E(x) = 2 x F - G0 (its derivative).  The series of D and E begin at
+//     n = 1 and so go through n = 9: first omitted terms 1.3e-17 and 2e-18 of
+//     them (through n = 7 3e-14 and 5e-15).  A block copies the one table
 //     it needs (9 KB) into LDS.  Per wave an evaluation is 12 LDS reads and 11
 //     FMAs in a dependent chain; the Chebyshev series of 27 terms used before
 //     took 27 reads and 53 operations, and below 32 only.
@@ -112,15 +114,16 @@ __device__ inline void sg_F_series(R x, R &F, R *dF)
 template <int FN> __device__ inline double sg_series64(double x);
 template <typename R, int NT> __device__ inline R sg_G0_series(R x);
 
-// Asymptotic coefficients n = 0..7 of F / ((sqrt(2 pi)/4) x^{-3/2}), of D over
+// Asymptotic coefficients n = 0..N-1 of F / ((sqrt(2 pi)/4) x^{-3/2}), of D over
 // the same (n c_n), of G0 / sqrt(pi/(2x)) (a_n = -a_{n-1} (2n - 1)^2/(8n)) and
 // of E over the same (c_n - a_n).
 template <int FN> struct Asym64 {
-    double c[8];
+    static constexpr int N = FN == SG_FN_F || FN == SG_FN_G0 ? 8 : 10;
+    double c[N];
     constexpr Asym64() : c{}
     {
         double v = 1.0, g = 1.0;
-        for (int n = 0; n < 8; ++n) {
+        for (int n = 0; n < N; ++n) {
             if (n) {
                 v = -v * (4.0 * n * n - 1.0) / (8.0 * n);
                 g = -g * (2.0 * n - 1.0) * (2.0 * n - 1.0) / (8.0 * n);
@@ -153,9 +156,9 @@ template <int FN> __device__ inline double sg_fn64(double x, const double *w)
         SG_NO_SPECULATE();
         constexpr Asym64<FN> A;
         const double r = rsqrt(x), u = r * r;
-        double s = A.c[7];
+        double s = A.c[A.N - 1];
 #pragma unroll
-        for (int n = 6; n >= 0; --n) s = fma(s, u, A.c[n]);
+        for (int n = A.N - 2; n >= 0; --n) s = fma(s, u, A.c[n]);
         s *= FN == SG_FN_F || FN == SG_FN_D ? (SG_SQRT2 * SG_SQRT_PI * 0.25) * (u * r) : (SG_SQRT_PI / SG_SQRT2) * r;
         f = x < 256.0 ? f : s;
     }
