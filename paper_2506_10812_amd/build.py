@@ -29,7 +29,7 @@ def _generate() -> None:
     os.makedirs(GEN, exist_ok=True)
     exe = os.path.join(OBJ, "gen_cheb64")
     subprocess.check_call(["g++", "-O2", "-std=c++17", os.path.join(CSRC, "gen_cheb64.cpp"), "-o", exe])
-    r = subprocess.run([exe], capture_output=True, text=True)
+    r = subprocess.run([exe, "--header"], capture_output=True, text=True)
     if r.returncode != 0:
         sys.stderr.write(r.stderr)
         raise RuntimeError("gen_cheb64 failed")

@@ -1,43 +1,38 @@
-// gen_cheb64.cpp -- host build step: writes sg_cheb64.h, the Chebyshev
-// coefficients of the double-precision mid-range branch of
-//     F(x) = e^x [K1(x) - K0(x)],  F'(x) = dF/dx   and   G0(x) = e^x K0(x)
-// (the force kernel's function of Sect. 2.2 and App. A, and the potential
-// kernel's of Sect. 5.5) on the dyadic intervals
-// [2^(k-1), 2^k), k = 0 .. SG_CHEB_NI - 1, i.e. 1/2 <= x < 32.
+// gen_cheb64.cpp -- host build step: writes the tables of sg_cheb64.h.
 //
+// The kernel functions (the force kernel's of Sect. 2.2 and App. A, its
+// derivative's and the potential kernel's of Sect. 5.5) are
+//     F(x)  = e^x [K1(x) - K0(x)],   G0(x) = e^x K0(x),
+//     D(x)  = -x F'(x) - 3/2 F(x),   E(x)  = 2 x F(x) - G0(x).
 // Values come from the integral representation of the Macdonald functions,
 // K_nu(x) = int_0^inf e^{-x cosh t} cosh(nu t) dt, which gives
 //     F(x)  =  int_0^inf e^{-x (cosh t - 1)} (cosh t - 1) dt,
 //     F'(x) = -int_0^inf e^{-x (cosh t - 1)} (cosh t - 1)^2 dt,
+//     D(x)  = -1/2 int_0^inf e^{-x (cosh t - 1)} tanh^3(t/2) sinh t dt
+//             (the two terms of D cancel to O(1/x) of themselves, the integral
+//             does not),
 //     G0(x) =  int_0^inf e^{-x (cosh t - 1)} dt,
+//     E(x)  =  int_0^inf e^{-x (cosh t - 1)} (2 x (cosh t - 1) - 1) dt,
 // evaluated in long double with the trapezoid rule: the integrands are even,
 // entire and decay doubly exponentially, so the rule converges geometrically
 // in 1/step (step 1/64 here, far below what 64-bit mantissas need).
 //
-// On each interval x = a (3 + t) / 2, t in [-1, 1], a = 2^(k-1), and
-//     f(x) = sum_{j < M} c_j T_j(t)
-// with c_j from the discrete cosine transform of f at the NN Chebyshev points
-// of the first kind (c_0 already halved).  M = 27 terms leave a truncation
-// below 1e-17 of the interval's largest value (the nearest singularity, at
-// x = 0, lies one interval length below every interval, so all intervals
-// converge alike); the program checks that the last kept coefficients are
-// that small and fails otherwise.
-//
-// The kernels that evaluate many points take shorter local polynomials
-// instead: PSUB intervals per octave from 2^POCT0 to 2^POCT1, PNC monomial
-// coefficients each in the local variable t in [-1, 1) (fitted the same way,
-// the last ones below 1e-15 of the value, the dropped ones below 3e-17), of F, G0 and
-//     D(x) = -x F'(x) - 3/2 F(x)
-//          = -1/2 int_0^inf e^{-x (cosh t - 1)} tanh^3(t/2) sinh t dt,
-// the combination the derivatives with respect to the scale heights need (the
-// two terms cancel to O(1/x) of themselves, the integral does not), and of
-//     E(x) = 2 x F(x) - G0(x) = int_0^inf e^{-x (cosh t - 1)} (2 x (cosh t - 1) - 1) dt
-// likewise for the potential; and, for the direct sums, of
-//     V(u) = u^{-3/2} F(1/u),   Vg(u) = u^{-1/2} G0(1/u)
-// on the octaves of u = 1/x (2^UOCT0 to 2^UOCT1), in double and, on 4
-// intervals per octave with 7 terms, in float.  Also written: the double twiddles of the table
-// builds' transforms.  The library evaluates these; the Chebyshev
-// series above are the fits' reference, kept for the generator's own test.
+// The tables (all of the header, written with --header):
+//   sg_poly64   F, D, G0, E: PSUB intervals per octave from 2^POCT0 to
+//               2^POCT1, PNC monomial coefficients each in the local variable
+//               t in [-1, 1), from the Chebyshev interpolant on the interval
+//               (its last coefficients are checked to be below 1e-15 of the
+//               value; the dropped ones are below 3e-17);
+//   sg_polyu64  V(u) = u^{-3/2} F(1/u) and Vg(u) = u^{-1/2} G0(1/u) of the
+//               direct sums likewise, on the octaves of u = 1/x from 2^UOCT0 to
+//               2^UOCT1;
+//   sg_polyu32  the same in float, FSUB intervals per octave with FNC terms;
+//   sg_tw64     the double twiddles of the table builds' transforms.
+// Without --header they follow Chebyshev series of F, F' and G0 on the dyadic
+// intervals [2^(k-1), 2^k), k = 0 .. NI - 1 (M = 27 terms from the discrete
+// cosine transform at NN points of the first kind, truncated below 1e-17 of
+// an interval's largest value), which check the integrals' evaluation over
+// whole octaves; the library does not use them.
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -125,8 +120,9 @@ static void fdf(long double x, long double &F, long double &dF, long double &G)
     G = sg * h;
 }
 
-int main()
+int main(int argc, char **)
 {
+    const bool header = argc > 1;  // --header
     static double cf[NI][M], cd[NI][M], cg[NI][M];
     const long double pi = 3.141592653589793238462643383279502884L;
     for (int k = 0; k < NI; ++k) {
@@ -162,10 +158,11 @@ int main()
         }
     }
     printf("// sg_cheb64.h -- written by gen_cheb64.cpp at build time; do not edit.\n");
-    printf("#pragma once\n#define SG_CHEB_NI %d\n#define SG_CHEB_M %d\n", NI, M);
+    printf("#pragma once\n");
+    if (!header) printf("#define SG_CHEB_NI %d\n#define SG_CHEB_M %d\n", NI, M);
     const char *names[3] = {"sg_cheb_f", "sg_cheb_df", "sg_cheb_g0"};
     double(*tabs[3])[M] = {cf, cd, cg};
-    for (int q = 0; q < 3; ++q) {
+    for (int q = 0; q < 3 && !header; ++q) {
         printf("static constexpr double %s[SG_CHEB_NI * SG_CHEB_M] = {\n", names[q]);
         for (int k = 0; k < NI; ++k)
             for (int m = 0; m < M; ++m) printf("    %.17e,\n", tabs[q][k][m]);
