@@ -58,7 +58,7 @@ typedef enum sg_status {
     SG_OK = 0,
     SG_ERR_ARG = 1,         /* invalid argument (NULL pointer, size, range) */
     SG_ERR_UNSUPPORTED = 2, /* valid but not supported by this path        */
-    SG_ERR_HIP = 3,         /* a HIP runtime call failed                    */
+    SG_ERR_HIP = 3,         /* a HIP runtime call failed, or host memory ran out */
     SG_ERR_WORKSPACE = 4,   /* workspace pointer NULL or too small          */
     SG_ERR_TABLE = 5,       /* kernel table does not match the disc         */
     SG_ERR_SCRATCH = 6      /* larger than the no-allocation scratch array  */

@@ -10,6 +10,17 @@
 #include "sg_semispec.h"
 #include "sg_table.h"
 
+// No exception crosses the ABI: plans and the lists of a table build are
+// standard containers, whose allocations can fail.
+template <typename F> static sg_status no_throw(F f)
+{
+    try {
+        return f();
+    } catch (...) {
+        return SG_ERR_HIP;
+    }
+}
+
 static bool finite_pos(double v) { return isfinite(v) && v > 0.0; }
 
 static sg_status check_grid(const sg_grid *g)
@@ -111,7 +122,7 @@ sg_status sg_kernel_table(const sg_grid *grid, const sg_fluids *fluids, uint32_t
     if (!d_table || ((uintptr_t)d_table & 255)) return SG_ERR_ARG;
     if (!d_ws || ws_bytes < sg_table_ws_bytes(grid->n_r, grid->n_phi) || ((uintptr_t)d_ws & 255))
         return SG_ERR_WORKSPACE;
-    return sg_table_build(grid, fluids, flags, d_table, d_ws, (hipStream_t)stream);
+    return no_throw([&] { return sg_table_build(grid, fluids, flags, d_table, d_ws, (hipStream_t)stream); });
 }
 
 size_t sg_ss_table_bytes(const sg_grid *grid, int n_fluids, uint32_t flags)
@@ -137,7 +148,7 @@ sg_status sg_ss_table(const sg_grid *grid, int n_fluids, const double *d_H, uint
     if (!d_table || ((uintptr_t)d_table & 255)) return SG_ERR_ARG;
     if (!d_ws || ws_bytes < sg_ss_ws_bytes(grid->n_r, grid->n_phi, n_fluids) || ((uintptr_t)d_ws & 255))
         return SG_ERR_WORKSPACE;
-    return sg_ss_table_build(grid, n_fluids, d_H, flags, d_table, d_ws, (hipStream_t)stream);
+    return no_throw([&] { return sg_ss_table_build(grid, n_fluids, d_H, flags, d_table, d_ws, (hipStream_t)stream); });
 }
 
 // Species summed into kernel groups: 0 (one density per fluid) or 1..8
@@ -195,7 +206,7 @@ sg_status sg_field_fft(const sg_disc *discs, int n_discs, void *d_ws, size_t ws_
         need += sg_fft_disc_ws_bytes(discs[i]);
     }
     if (!d_ws || ws_bytes < need || ((uintptr_t)d_ws & 255)) return SG_ERR_WORKSPACE;
-    return sg_fft_run(discs, n_discs, d_ws, (hipStream_t)stream);
+    return no_throw([&] { return sg_fft_run(discs, n_discs, d_ws, (hipStream_t)stream); });
 }
 
 sg_status sg_field_fft_profile(const sg_disc *discs, int n_discs, void *d_ws, size_t ws_bytes,
@@ -210,7 +221,7 @@ sg_status sg_field_fft_profile(const sg_disc *discs, int n_discs, void *d_ws, si
         need += sg_fft_disc_ws_bytes(discs[i]);
     }
     if (!d_ws || ws_bytes < need || ((uintptr_t)d_ws & 255)) return SG_ERR_WORKSPACE;
-    return sg_fft_profile(discs, n_discs, d_ws, (hipStream_t)stream, reps, ms_per_pass);
+    return no_throw([&] { return sg_fft_profile(discs, n_discs, d_ws, (hipStream_t)stream, reps, ms_per_pass); });
 }
 
 sg_status sg_field_fft_tune(const sg_disc *discs, int n_discs, void *d_ws, size_t ws_bytes,
@@ -225,7 +236,8 @@ sg_status sg_field_fft_tune(const sg_disc *discs, int n_discs, void *d_ws, size_
         need += sg_fft_disc_ws_bytes(discs[i]);
     }
     if (!d_ws || ws_bytes < need || ((uintptr_t)d_ws & 255)) return SG_ERR_WORKSPACE;
-    return sg_fft_tune(discs, n_discs, d_ws, (hipStream_t)stream, results, capacity, n_results);
+    return no_throw(
+        [&] { return sg_fft_tune(discs, n_discs, d_ws, (hipStream_t)stream, results, capacity, n_results); });
 }
 
 size_t sg_field_direct_workspace_bytes(const sg_grid *grid, int n_fluids, sg_dtype dtype,
@@ -428,7 +440,7 @@ sg_status sg_ss_grad_H(const sg_disc *disc, const double *d_H, const float *d_la
     if (!ss_grad_ok(disc)) return SG_ERR_UNSUPPORTED;
     const size_t need = ss_grad_bytes(*disc);
     if (!d_ws || ws_bytes < need || ((uintptr_t)d_ws & 255)) return SG_ERR_WORKSPACE;
-    return sg_ss_grad_run(*disc, d_H, d_lam_r, d_lam_phi, d_dH, d_ws, (hipStream_t)stream);
+    return no_throw([&] { return sg_ss_grad_run(*disc, d_H, d_lam_r, d_lam_phi, d_dH, d_ws, (hipStream_t)stream); });
 }
 
 sg_status sg_eval_F(const void *d_x, void *d_F, void *d_dF, int64_t n, sg_dtype dtype, void *stream)

@@ -8,6 +8,7 @@
 #include <cstring>
 #include <tuple>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <vector>
 
@@ -1082,37 +1083,27 @@ static sg_status get_cached(const sg_disc *discs, int n, void *ws, Cached *&out)
         destroy(lru->second);
         g_cache.erase(lru);
     }
-    Cached *C = new Cached;
+    std::unique_ptr<Cached, void (*)(Cached *)> own(new Cached, destroy);
+    Cached *const C = own.get();
     C->last_use = ++g_tick;
     sg_disc at0 = discs[0];  // a one-disc plan holds offsets
     at0.table = nullptr;
-    if (!build_plan(single ? &at0 : discs, n, single ? nullptr : (char *)ws, C->plan)) {
-        delete C;
-        return SG_ERR_UNSUPPORTED;
-    }
+    if (!build_plan(single ? &at0 : discs, n, single ? nullptr : (char *)ws, C->plan)) return SG_ERR_UNSUPPORTED;
     if (single) {
         g_cache[key] = C;
-        out = C;
+        out = own.release();
         return SG_OK;
     }
     const size_t bd = sg_align256(sizeof(DiscDev) * n);
     const size_t bytes = bd + sizeof(WJob) * C->plan.wjobs.size();
-    if (hipMalloc(&C->dmem, bytes) != hipSuccess) {
-        delete C;
-        return SG_ERR_HIP;
-    }
+    SG_HIP(hipMalloc(&C->dmem, bytes));
     if (hipMemcpy(C->dmem, C->plan.discs.data(), sizeof(DiscDev) * n, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy((char *)C->dmem + bd, C->plan.wjobs.data(), sizeof(WJob) * C->plan.wjobs.size(),
-                  hipMemcpyHostToDevice) != hipSuccess) {
-        destroy(C);
+                  hipMemcpyHostToDevice) != hipSuccess)
         return SG_ERR_HIP;
-    }
     if (use_graph(C->plan)) {
         hipStream_t cs;
-        if (hipStreamCreateWithFlags(&cs, hipStreamNonBlocking) != hipSuccess) {
-            destroy(C);
-            return SG_ERR_HIP;
-        }
+        SG_HIP(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
         ForkRes R;
         bool ok = fork_resources(*C, R) == SG_OK;
         ok = ok && hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal) == hipSuccess;
@@ -1122,13 +1113,10 @@ static sg_status get_cached(const sg_disc *discs, int n, void *ws, Cached *&out)
         if (ok) ok = hipGraphInstantiate(&C->exec, gph, nullptr, nullptr, 0) == hipSuccess;
         (void)hipStreamDestroy(cs);
         C->graph = gph;
-        if (!ok) {
-            destroy(C);
-            return SG_ERR_HIP;
-        }
+        if (!ok) return SG_ERR_HIP;
     }
     g_cache[key] = C;
-    out = C;
+    out = own.release();
     return SG_OK;
 }
 
