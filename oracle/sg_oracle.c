@@ -524,7 +524,7 @@ double sg_oracle_potential_self_range(double r, double Ha, double Hb, double xlo
     for (int sgn = -1; sgn <= 1; sgn += 2) {  /* X < 0 and X > 0; phi: even, doubled */
         const double a = sgn > 0 ? xhi : -xlo;
         if (!(a > 0.0)) continue;
-            for (int tri = 0; tri < 2; ++tri) {
+        for (int tri = 0; tri < 2; ++tri) {
             const double V = asinh(tri == 0 ? b / a : a / b);
             double acc = 0.0;
             for (int i = 0; i < ORC_GL_N; ++i) {

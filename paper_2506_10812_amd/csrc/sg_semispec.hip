@@ -980,8 +980,7 @@ sg_status sg_ss_table_build(const sg_grid *grid, int nf, const double *d_H, uint
     const bool excl = (flags & SG_SELF_CELL_EXCLUDE) != 0;
     const bool second = (flags & SG_SECOND_ORDER) != 0;  // log grid, force operators
 
-    hipLaunchKernelGGL(k_twiddles, dim3((nphi + 255) / 256), dim3(256), 0, s, (float2 *)nullptr, 0,
-                       (float2 *)(tb + L.off_tw_phi), nphi);
+    hipLaunchKernelGGL(k_twiddles, dim3((nphi + 255) / 256), dim3(256), 0, s, (float2 *)(tb + L.off_tw_phi), nphi);
     SG_HIP(hipGetLastError());
     SsMode *modes = (SsMode *)(tb + L.off_modes);
     hipLaunchKernelGGL(k_ss_modes, dim3(1), dim3(256), 0, s, modes, L.ncol, nr, L.nrt, nf, du, full ? 1 : 0);

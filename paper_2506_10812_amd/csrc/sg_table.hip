@@ -33,14 +33,9 @@
 #include "sg_hat.h"
 
 // ------------------------------------------------------------------ twiddles
-__global__ void k_twiddles(float2 *tw_u, int nu, float2 *tw_phi, int nphi)
+__global__ void k_twiddles(float2 *tw_phi, int nphi)
 {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < nu) {
-        double s, c;
-        sincospi(-2.0 * i / nu, &s, &c);
-        tw_u[i] = make_float2((float)c, (float)s);
-    }
     if (i < nphi) {
         double s, c;
         sincospi(-2.0 * i / nphi, &s, &c);
@@ -422,7 +417,7 @@ __global__ void k_fill_f64(double *p, int64_t n, double v)
 
 // ------------------------------------------- second-order (hat) weights
 // (the rules themselves are in sg_hat.h)
-// One thread per entry of the wrapped offset grid (as k_sample): entries with
+// One thread per entry of the wrapped offset grid: entries with
 // |P| >= 2 or |Q| >= 2 (no singular square); row n_r (offset +-n_r) is zero.
 // which: 0 the weights, 1 and 2 their derivatives in h_a and h_b (the
 // kernel's derivatives integrated with the same rules).
