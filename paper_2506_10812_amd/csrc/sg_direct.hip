@@ -66,12 +66,15 @@ template <typename T> __device__ inline void sg_two_sum_acc(T &s, T &c, T v)
     s = t;
 }
 
-// The sums take lengths in units of the power of two below r_min: a pair's
-// factor (s^2/8)^{-3/2} and the masses r^3 Sigma would otherwise leave float's
-// range where lengths are far from 1 (discs in metres or centimetres: subnormal
-// from s = 1e13 on).  The field does not depend on the unit of length, the
-// potential is proportional to it; a power of two costs no rounding.
-static double length_unit(const sg_grid &g) { return ldexp(1.0, ilogb(g.r_min)); }
+// The float sums take lengths in units of the power of two below r_min: a
+// pair's factor (s^2/8)^{-3/2} and the masses r^3 Sigma would otherwise leave
+// float's range where lengths are far from 1 (discs in metres or centimetres:
+// subnormal from s = 1e13 on).  The field does not depend on the unit of length,
+// the potential is proportional to it; a power of two costs no rounding.
+template <typename T> static double length_unit(const sg_grid &g)
+{
+    return sizeof(T) == 4 ? ldexp(1.0, ilogb(g.r_min)) : 1.0;
+}
 
 // Ring radius: log grid (lin = 0) or uniform grid (a = r_min, b = dr).
 __device__ inline double dir_radius(int lin, double lnrmin, double du, double rmin, double dr, int i)
@@ -121,9 +124,9 @@ __global__ void k_direct_prep(int nr, int nphi, int nf, double lnrmin, double du
 // General sum (a scale height per cell): VALU bound.  Per source one
 // reciprocal square root (of s^2/8) serves every pair of fluids, per pair one
 // V(u) (17 float instructions with its table reads, 10 where the whole wave is
-// beyond x = 64).  Two fluids, 101 x 250 cells in float: 1.45 ms, 1.8e12 pairs/s
+// beyond x = 64).  Two fluids, 101 x 250 cells in float: 1.4 ms, 1.8e12 pairs/s
 // (2.9 ms with a reciprocal square root and the 9-node trapezoid per pair); the
-// double potential of 96 x 200 cells 0.82 ms (2.35 ms at first, 0.96 ms with F(x)
+// double potential of 96 x 200 cells 0.78 ms (2.35 ms at first, 0.96 ms with F(x)
 // per pair), bound by the 96 bytes of table per lane and pair.
 template <typename T, int NF>
 __global__ void __launch_bounds__(256) k_direct(DirectArgs<T> A)
@@ -223,8 +226,9 @@ __global__ void __launch_bounds__(256) k_direct(DirectArgs<T> A)
 //
 // FP32 / FP64 VALU bound, two FMAs per pair of cells and fluid pair (one for
 // the potential) in place of a kernel evaluation.  The whole call: 256 x 512 in
-// float 1.08 ms (32e12 FMA/s of 39e12), against 21.4 ms with a kernel
-// evaluation per pair; 64 x 128 in double 55 us against 580 us.  8 x 8 per step keeps LDS below the VALU
+// float 0.99 ms (35e12 FMA/s of 39e12), against 21.4 ms with a kernel
+// evaluation per pair; 64 x 128 in double 41 us (this kernel 21) against 690 us.
+// 8 x 8 per step keeps LDS below the VALU
 // (per wave 6 16-byte reads for 128 FMAs in float, 12 in double); rows are
 // padded by 16 bytes per 8 elements, which puts the 8 lanes of a 16-byte
 // access phase (one element group apart) on different banks.
@@ -545,7 +549,7 @@ __global__ void k_direct_reduce(const T *partial, int S, int64_t N, const double
 //   Phi_b(i) = sum_a sum_{k != i} Sigma_a[k] A_k P_ab(s_ik),
 //   P_ab(s) = -e^y K0(y) / (2 sqrt(pi) H_ab),  y = s^2/(8 H_ab^2),
 // H_ab from the source cell's H_a and the target cell's H_b; the own cell
-// adds Sigma_a[i] times the cell integral of P_ab (k_pot_self).  Same
+// adds Sigma_a[i] times the cell integral of P_ab (k_pot_cells).  Same
 // layout and splitting as the field sum; one accumulator per target fluid.
 template <typename T, int NF>
 __global__ void __launch_bounds__(256) k_potential(DirectArgs<T> A)
@@ -718,7 +722,7 @@ static sg_status direct_run(const sg_grid *g, int nf, const double *h, const T *
     const int64_t N = (int64_t)nr * nphi;
     const double du = log(g->r_max / g->r_min) / nr;
     const double dphi = 2.0 * SG_PI / nphi;
-    const double lnrmin = log(g->r_min), unit = length_unit(*g);
+    const double lnrmin = log(g->r_min), unit = length_unit<T>(*g);
     const int lin = (flags & SG_LINEAR_R) ? 1 : 0;
     const double dr = (g->r_max - g->r_min) / nr;
     int S = direct_splits(nr, N);
@@ -860,7 +864,7 @@ static sg_status potential_run(const sg_grid *g, int nf, const double *h, const 
     const int64_t N = (int64_t)nr * nphi;
     const double du = log(g->r_max / g->r_min) / nr;
     const double dphi = 2.0 * SG_PI / nphi;
-    const double lnrmin = log(g->r_min), unit = length_unit(*g);
+    const double lnrmin = log(g->r_min), unit = length_unit<T>(*g);
     int S = direct_splits(nr, N);
     const int rps = (nr + S - 1) / S;
     char *o = (char *)ws;
