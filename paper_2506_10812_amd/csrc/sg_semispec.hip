@@ -67,7 +67,7 @@ struct SsRowArgs {
 // (for H = h r this is the FFT path's table; otherwise the variation of h
 // across the hat is odd in s and enters at second order only).  Within
 // SG_SS_HAT_NEAR of the larger cell side from the singular point the weight
-// is integrated (sg_hat_weight1); beyond, it is the point value plus the
+// is integrated (sg_hat_weight_part); beyond, it is the point value plus the
 // second moments of the hats, W = K + (D_X^2 K + D_phi^2 K)/12, with central
 // second differences over one cell (D_phi from the neighbouring samples of
 // the row, D_X from two extra samples at X +- du): the remainder is
@@ -94,7 +94,10 @@ struct SsRowArgs {
 // rows of a unit are consecutive entries of a diagonal in the banded modes'
 // layout, and the units of one tile lie together for the full modes' (the
 // scatter goes through them in that order).
-#define SG_SS_ALIAS_GRAD 96.0  // h derivatives have double poles at phi = +-i X
+// The gradient's rows, whose result is a double, take 96: aliases below e^{-48}.
+// (A margin: the h derivatives' singularities at phi = +-i X are simple poles
+// like the kernel's, and e^{-40} would do; the table's derivative rows take 80.)
+#define SG_SS_ALIAS_GRAD 96.0
 #define SG_SS_TI 16
 
 struct SsClass {
@@ -426,7 +429,10 @@ k_ss_rows(const double *H, const double *self, SsRowArgs A, SsClass C, size_t r0
 // transform, where its rows took two and one; the table's entries are formed
 // from S~, held in double, by k_ss_scatter_pairs.  The differences cost
 // 1e-16/|X| of a row's largest coefficient (1e-16/dphi^2 for i' = i, whose
-// own-cell sample enters as a constant of all modes); the table holds floats.
+// own-cell sample enters as a constant of all modes), as an absolute error of
+// all its entries: the smallest that are kept, 2^-30 of the largest, hold
+// 1e-7/|X| of themselves where the transform alone would leave 1e-7.  The table
+// holds floats, and a ring's sum is led by its near pairs' entries.
 // C: offsets k >= 0 only.  out: [nrows][ld] double S~, m < ld <= N/2 + 1.
 // 1200 x 2048 one fluid, all rows 2.74 -> 1.14 ms, whole build and solve 3.84
 // -> 2.40 ms.
@@ -1359,7 +1365,8 @@ __device__ inline void ssg_mode(const float4 *lt, const float2 *st, size_t ro, s
 // the circle where the rows took two; a group transforms two ring pairs at
 // once as z_A + i z_B (S~ is real).  The differences cost digits of the double
 // rounding: 1e-16/|X| of a row's largest coefficient, for i' = i 1e-16/dphi^2
-// (dL/dH itself moved by 5e-13 of its largest at 600 x 1024).
+// (dL/dH itself moved by 5e-13 of its largest at 600 x 1024; the float spectra
+// of lam and Sigma leave 1e-7 of it).
 // The own-cell sample of i = i' enters as a constant of all modes.
 // On a uniform grid the classes of a row and of its mirror differ: rows then
 // stand alone (both signs of k).  Index: as ss_row's with offsets k >= 0.

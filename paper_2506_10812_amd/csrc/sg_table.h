@@ -23,14 +23,16 @@ struct GLNodes {
 // OwnEta) and the weight, the Jacobian's xi included.
 //
 // Both xi rules integrate over [0, 1] with a logarithm at 0.  xi = t^4 takes
-// the logarithm down to t^7 log t and 24 nodes then reach 1e-13, the level
-// of the panel rule's 112 (measured against 9 panels x 24 nodes on cells of
-// aspect 1/2 to 2 and H_a/H_b of 1/10 to 10: field <= 3e-13, its h
-// derivatives <= 2e-13, potential <= 1e-15).  It holds while the cell is not
-// much larger than H: at half side / H = 16 the derivatives are at 1e-11, so
-// beyond SG_OWN_RMAX the panels resolve the transition of F at distances
-// ~ H, the innermost one graded likewise (its logarithm left 1e-12 to 1e-10
-// in the potential of cells 10 to 1000 H across; 4e-16 with the grading).
+// the logarithm down to t^7 log t, and 24 nodes then leave less than 7e-17 of
+// the field, its h derivatives and the potential (in 32-digit arithmetic, half
+// sides of 0.03 to 7.9 H, heights equal and 10 apart).  In double a field's
+// two halves cancel to about a half side, which leaves 2e-15 on cells of 0.05,
+// 5e-14 on cells of 0.003 with equal heights, 1e-12 with heights 10 to 300
+// apart.  The rule holds while the cell is not much larger than H: at half side
+// / H = 16 the derivatives are at 1e-11, so beyond SG_OWN_RMAX the panels
+// resolve the transition of F at distances ~ H, the innermost one graded
+// likewise (its logarithm left 1e-12 to 1e-10 in the potential of cells 10 to
+// 1000 H across; 4e-16 with the grading).
 __device__ inline void sg_own_node(const GLNodes &gl, int nx, int idx, double &xi, double &s, double &wgt)
 {
     const int ix = idx / gl.ne, j = idx % gl.ne;
@@ -49,9 +51,9 @@ __device__ inline void sg_own_node(const GLNodes &gl, int nx, int idx, double &x
 
 // The triangle X = a xi, phi = b xi eta has its nearest singularities at eta
 // = +-i a/b (the other triangle at +-i b/a).  eta = q sinh(s asinh(1/q)), q
-// that ratio, moves them to a distance that shrinks only with log(1/q): 16
-// nodes reach 4e-14 up to an aspect of 8 and 24 nodes 2e-13 up to 500 (plain
-// Gauss-Legendre: 48 nodes 1e-13 at 20, 4e-7 at 100).
+// that ratio, moves them to a distance that shrinks only with log(1/q): in
+// 32-digit arithmetic 16 nodes leave less than 7e-17 at an aspect of 2, 24 nodes
+// 2.4e-16 at 390 (plain Gauss-Legendre: 48 nodes 1e-13 at 20, 4e-7 at 100).
 struct OwnEta {
     double q, L;
     __device__ inline OwnEta(double num, double den) : q(num / den), L(asinh(den / num)) {}

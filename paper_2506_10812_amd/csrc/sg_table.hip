@@ -20,9 +20,9 @@
 //      Hermitian and K_phi anti-Hermitian in k_u because K_r is even and K_phi
 //      odd in phi), scale by -du dphi/(2 n_r n_phi), round to float.
 // Four launches for up to SG_TAB_ITEMS pairs: own-cell integrals and twiddles
-// (9 us), rows (17 us), columns (36 us), header (4 us) on the two-fluid 1024 x
-// 2048 disc, bound by the columns' FP64 transforms; one sampling, one phi and
-// two u launches per pair on the full grid took 700 us.
+// (9 to 11 us), rows (16 us), columns (35 us), header (5 us) on the two-fluid
+// 1024 x 2048 disc, bound by the columns' FP64 transforms; one sampling, one phi
+// and two u launches per pair on the full grid took 700 us.
 #include <algorithm>
 #include <vector>
 
@@ -187,9 +187,9 @@ template <int n, typename Out> __device__ inline void own_block_sums(double (&v)
 // block.  FP64 VALU bound: a node's geometry (a sinh, a sine, two square
 // roots) depends on the grid only and is formed once for the CPB cells, whose
 // heights are wave-uniform; the two-fluid case takes 4 F per node and
-// triangle for its four pairs.  Two fluids, 101 x 250 cells: 1.43 ms, against
-// 30.9 ms with 112 x 48 nodes, one (cell, pair) per block and the kernel
-// evaluated whole at +-X.
+// triangle for its four pairs.  Two fluids, 101 x 250 cells: 0.80 ms (1.43 with
+// a Chebyshev series for F), against 30.9 ms with 112 x 48 nodes, one (cell,
+// pair) per block and the kernel evaluated whole at +-X.
 template <typename T, int NF, int CPB>
 __global__ void __launch_bounds__(256)
 k_self_cells(const T *H, int64_t N, int nphi, double lnrmin, double du, double dphi, double *out, GLNodes gl)
@@ -309,7 +309,7 @@ k_self_cell_ring(const double *H, int nf, int nr, double lnrmin, double du, doub
 //
 // One block per CPB cells and unordered pair (P_ab = P_ba), or rows when
 // per_row (H_f = h_f r: depends on the row only); a node's geometry is shared
-// by the CPB cells (96 x 200 cells in double: 0.30 ms, against 5.0 ms with
+// by the CPB cells (96 x 200 cells in double: 0.26 ms, against 5.0 ms with
 // 112 x 48 nodes and one cell per block).  which = 1, 2 of the item: the integral's derivative with
 // respect to h_a = H_a / r, h_b = H_b / r (dH_ab/dh_a = H_a r / (2 H_ab),
 // likewise for b) instead.

@@ -238,8 +238,8 @@ class SGField(torch.autograd.Function):
     aspect ratios; indirect: add the indirect term; second_order: the
     hat-weighted kernel table (SG_SECOND_ORDER).  Forward: sg_field_fft.
     Backward: sg_field_adjoint (dL/dSigma and dL/dh).  Repeated calls with the
-    same grid, aspect ratios and flags reuse one persistent slot (table,
-    buffers, workspaces) and therefore one cached plan."""
+    same grid, aspect ratios and flags reuse one persistent slot (table
+    and workspaces) and one cached plan."""
 
     @staticmethod
     def forward(ctx, sigma, h, n_r, n_phi, r_min, r_max, indirect=False, second_order=False):
