@@ -18,7 +18,9 @@
 // into one with K_r symmetrised in X (the 1/rho part of K_r is odd in X and
 // cancels only between the halves; K_phi, odd in phi, gives 0).  Elsewhere
 // tensor Gauss-Legendre rules of 6 x 6 points on sub-squares small against
-// their distance to the singular point (at most a third of it).
+// their distance to the singular point (at most a third of it; where a long
+// side starts beside the singular point, pieces that grow with the distance:
+// sg_hat_long_node).
 static __device__ __constant__ double sg_gl6_x[6] = {0.0337652428984239860, 0.1693953067668677431,
                                                      0.3806904069584015457, 0.6193095930415984543,
                                                      0.8306046932331322569, 0.9662347571015760140};
@@ -28,18 +30,54 @@ static __device__ __constant__ double sg_gl6_w[6] = {0.0856622461895851725, 0.18
 
 __device__ inline double sg_hat(double x) { return fmax(0.0, 1.0 - fabs(x)); }
 
+// A side of length len that starts beside the singular point, at the distance d
+// across: pieces uniform in v, the distance along it being d sinh v.  The
+// kernel's singularities lie at v = +-i pi/2, so pieces of 1/2 in v take 6 points
+// to 1e-13, where uniform ones of a third of the distance would number 3 len / d.
+// (Held at 32 of those, fields on cells 276 and 1103 times longer than wide were
+// 2e-5 and 4e-4 off.)  From the place u in [0, 1] in v: the place along the side
+// from its start, in units of len, the weight's factor in w.
+#define SG_HAT_PIECES 32
+__device__ inline double sg_hat_long_node(double len, double d, double u, double &w)
+{
+    const double q = d / len, V = asinh(len / d), e = sinh(u * V);
+    w *= q * V * sqrt(1.0 + e * e);
+    return q * e;
+}
+
 // Tensor Gauss-Legendre over pieces k in [k0, k1) (step dk) of the unit square
-// [ds, ds + 1] x [dt, dt + 1] of entry (P, Q), cut into ms x mt sub-squares.
+// [ds, ds + 1] x [dt, dt + 1] of entry (P, Q), cut into |ms| x |mt| sub-squares;
+// a negative count is that of a long side's pieces (sg_hat_split).  LONG: such
+// sides come up (sg_hat_long).  The semi-spectral rows, which hold the rule next
+// to a transform, have a kernel for either: the node of a long side, inlined for
+// all, took them from 3.0 to 3.7 ms (200 x 256).
+template <bool LONG>
 __device__ inline void sg_hat_square(int P, int Q, int ds, int dt, int ms, int mt, int k0, int k1, int dk,
                                      double du, double dphi, double ha, double hb, int which, const double *wq,
                                      double &wr, double &wp)
 {
+    const bool ls = LONG && ms < 0, lt = LONG && mt < 0;  // not both: each has the other's distance
+    if constexpr (LONG) {
+        ms = abs(ms);
+        mt = abs(mt);
+    }
     for (int k = k0; k < k1; k += dk) {
         const int piece = k / 36, node = k % 36;
         const int is = piece % ms, it = piece / ms;
         const int a = node % 6, b = node / 6;
-        const double s = ds + (is + sg_gl6_x[a]) / ms, t = dt + (it + sg_gl6_x[b]) / mt;
-        const double w = sg_gl6_w[a] * sg_gl6_w[b] / (ms * mt) * sg_hat(s) * sg_hat(t);
+        double s = ds + (is + sg_gl6_x[a]) / ms, t = dt + (it + sg_gl6_x[b]) / mt;
+        double w = sg_gl6_w[a] * sg_gl6_w[b] / (ms * mt);
+        if (LONG && (ls || lt)) {
+            // the distance across, and the end (-P or -Q) the side starts from
+            if (ls) {
+                const double u = sg_hat_long_node(du, (Q + dt >= 0 ? Q + dt : -(Q + dt + 1)) * dphi, s - ds, w);
+                s = ds == -P ? ds + u : ds + 1 - u;
+            } else {
+                const double u = sg_hat_long_node(dphi, (P + ds >= 0 ? P + ds : -(P + ds + 1)) * du, t - dt, w);
+                t = dt == -Q ? dt + u : dt + 1 - u;
+            }
+        }
+        w = w * sg_hat(s) * sg_hat(t);
         const double X = (P + s) * du, ph = (Q + t) * dphi;
         double kr, kp;
         sg_conv_kernel64(X, sin(0.5 * ph), sin(ph), ha, hb, which, wq, kr, kp);
@@ -48,16 +86,27 @@ __device__ inline void sg_hat_square(int P, int Q, int ds, int dt, int ms, int m
     }
 }
 
-// Sub-square count per side: pieces at most a third of their distance to
-// the singular point (physical units), at most 32.
+// Whether cells of these sides have squares with long sides.
+__host__ __device__ inline bool sg_hat_long(double du, double dphi)
+{
+    return 3.0 * fmax(du, dphi) > SG_HAT_PIECES * fmin(du, dphi);
+}
+
+// Sub-square count per side: pieces at most a third of their distance to the
+// singular point (physical units); more than 32 only where the side starts
+// beside it, which then counts its pieces in v, negative.
+template <bool LONG>
 __device__ inline void sg_hat_split(int P, int Q, int ds, int dt, double du, double dphi, int &ms, int &mt)
 {
     const double x0 = (P + ds) * du, x1 = x0 + du, y0 = (Q + dt) * dphi, y1 = y0 + dphi;
     const double dx = x0 > 0.0 ? x0 : (x1 < 0.0 ? -x1 : 0.0);
     const double dy = y0 > 0.0 ? y0 : (y1 < 0.0 ? -y1 : 0.0);
     const double d = sqrt(dx * dx + dy * dy);
-    ms = min(32, max(1, (int)ceil(3.0 * du / d)));
-    mt = min(32, max(1, (int)ceil(3.0 * dphi / d)));
+    const double ws = ceil(3.0 * du / d), wt = ceil(3.0 * dphi / d);
+    ms = max(1, (int)ws);
+    mt = max(1, (int)wt);
+    if (LONG && ws > SG_HAT_PIECES) ms = -(int)ceil(2.0 * asinh(du / d));
+    if (LONG && wt > SG_HAT_PIECES) mt = -(int)ceil(2.0 * asinh(dphi / d));
 }
 
 __device__ inline bool sg_hat_singular(int P, int Q, int ds, int dt)
@@ -104,6 +153,7 @@ __device__ inline void sg_hat_corner(int P, int Q, int sx, int sy, bool sym, dou
 // k0, k0 + dk, ... of every piece (the polar rules at the singular corner for
 // |P|, |Q| <= 1, split tensor squares elsewhere, as the table build's kernels
 // apply them); the sum of the parts over k0 = 0 .. dk - 1 is the weight.
+template <bool LONG>
 __device__ inline void sg_hat_weight_part(int P, int Q, double du, double dphi, double ha, double hb, int which,
                                           const GLNodes &gl, const double *wq, int k0, int dk, double &wr,
                                           double &wp)
@@ -124,8 +174,8 @@ __device__ inline void sg_hat_weight_part(int P, int Q, double du, double dphi, 
                 sg_hat_corner(P, Q, sx, sy, false, du, dphi, ha, hb, which, gl, wq, k0, dk, wr, wp);
             } else {
                 int ms, mt;
-                sg_hat_split(P, Q, ds, dt, du, dphi, ms, mt);
-                sg_hat_square(P, Q, ds, dt, ms, mt, k0, 36 * ms * mt, dk, du, dphi, ha, hb, which, wq, wr, wp);
+                sg_hat_split<LONG>(P, Q, ds, dt, du, dphi, ms, mt);
+                sg_hat_square<LONG>(P, Q, ds, dt, ms, mt, k0, 36 * abs(ms * mt), dk, du, dphi, ha, hb, which, wq, wr, wp);
             }
         }
 }

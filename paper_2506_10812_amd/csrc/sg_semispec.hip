@@ -200,9 +200,9 @@ __device__ inline void ss_far_weight(const ConvRow64 &c0, const ConvRow64 &c1, c
 // and Z_B from the imaginary part.  The row count is even (n_rt is) and so
 // is every chunk, so the two rows are always i and i + 1 of one (b, a, i').
 // N: the samples of the rows, n_phi or a class's M.  SO: 0 point samples; 1
-// second-order rows with samples to integrate (one row per group); 2
-// second-order rows beyond SG_SS_HAT_NEAR, whose samples are the weights of
-// ss_far_weight.  out: [nrows][mc] float2 (T_r, t_phi), m < mc <= N/2 + 1.
+// second-order rows with samples to integrate (one row per group), 3 the same
+// on long cells (sg_hat_long); 2 second-order rows beyond SG_SS_HAT_NEAR, whose
+// samples are the weights of ss_far_weight.  out: [nrows][mc] float2 (T_r, t_phi), m < mc <= N/2 + 1.
 template <int N, int SO>
 __global__ void __launch_bounds__(SsRowShape<N>::WGS)
 k_ss_rows(const double *H, const double *self, SsRowArgs A, SsClass C, size_t r0, int nrows, int mc, float2 *out)
@@ -210,10 +210,10 @@ k_ss_rows(const double *H, const double *self, SsRowArgs A, SsClass C, size_t r0
     using S = SsRowShape<N>;
     constexpr int P = S::P, T = S::T, G = S::G, W = LdsPlane<double>::elems(N);
     constexpr int NC = N / 2 + 1;
-    constexpr int RPG = SO == 1 ? 1 : 2;
+    constexpr int RPG = (SO & 1) ? 1 : 2;
     __shared__ __attribute__((aligned(16))) double2 lds[W * G];
     __shared__ __attribute__((aligned(16))) double wq[FQuad<double>::TABLE];
-    __shared__ double2 qres[SO == 1 ? NC * G : 1];  // SO: the group's integrated samples
+    __shared__ double2 qres[(SO & 1) ? NC * G : 1];  // SO: the group's integrated samples
     __shared__ int qmax_wg;                         // SO: last integrated sample of any group
     const int g = threadIdx.x / T, t = threadIdx.x % T;
     const LdsPlane<double> pl{lds + W * g};
@@ -252,7 +252,7 @@ k_ss_rows(const double *H, const double *self, SsRowArgs A, SsClass C, size_t r0
     const int ic = ic_[0], ip = ip_[0];
     const double ha = ha_[0], hb = hb_[0], X = X_[0];
     __syncthreads();
-    if constexpr (SO == 1) {
+    if constexpr ((SO & 1) != 0) {
         // 1'. hat-weighted samples (see SG_SS_HAT_NEAR): point values of K go
         // to the plane for the neighbours' second differences, the weights
         // stay in registers until every neighbour has been read
@@ -273,7 +273,7 @@ k_ss_rows(const double *H, const double *self, SsRowArgs A, SsClass C, size_t r0
         const int qm = qmax_wg;  // uniform over the workgroup: every group meets the same barriers
         for (int q = 0; q <= qm; ++q) {
             double wr = 0.0, wp = 0.0;
-            if (q <= qn) sg_hat_weight_part(Pr, q, A.du, A.dphi, ha, hb, 0, A.gl, wq, t, T, wr, wp);
+            if (q <= qn) sg_hat_weight_part<SO == 3>(Pr, q, A.du, A.dphi, ha, hb, 0, A.gl, wq, t, T, wr, wp);
             pl.st(t, make_double2(wr, wp));
             __syncthreads();
             if (q <= qn && t == 0) {
@@ -911,7 +911,9 @@ static void launch_ss_rows(const double *H, const double *self, const SsRowArgs 
     // the quadrature's registers stay out of the other rows; two rows per
     // group unless integrated (nrows is even: see k_ss_rows)
     const dim3 one((nrows + S::G - 1) / S::G), two((nrows + 2 * S::G - 1) / (2 * S::G));
-    if (P.kind == 1)
+    if (P.kind == 1 && sg_hat_long(A.du, A.dphi))
+        hipLaunchKernelGGL((k_ss_rows<N, 3>), one, dim3(S::WGS), 0, s, H, self, A, P.C, r0, nrows, mc, out);
+    else if (P.kind == 1)
         hipLaunchKernelGGL((k_ss_rows<N, 1>), one, dim3(S::WGS), 0, s, H, self, A, P.C, r0, nrows, mc, out);
     else if (P.kind == 2)
         hipLaunchKernelGGL((k_ss_rows<N, 2>), two, dim3(S::WGS), 0, s, H, self, A, P.C, r0, nrows, mc, out);
@@ -1562,7 +1564,7 @@ k_ssg_rows(const double *H, const double *dself, SsRowArgs A, SsClass C, int nph
     __shared__ __attribute__((aligned(16))) double2 lds[W * G];
     __shared__ __attribute__((aligned(16))) double wq[FQuad<double>::TABLE];
     __shared__ double red[S::WGS];
-    __shared__ double2 qres[SO == 1 ? 2 * NC * G : 1];  // SO: the group's integrated samples, both derivatives
+    __shared__ double2 qres[(SO & 1) ? 2 * NC * G : 1];  // SO: the group's integrated samples, both derivatives
     __shared__ int qmax_wg;
     const int g = threadIdx.x / T, t = threadIdx.x % T;
     const LdsPlane<double> pl{lds + W * g};
@@ -1590,7 +1592,7 @@ k_ssg_rows(const double *H, const double *dself, SsRowArgs A, SsClass C, int nph
     // the row and its D_X neighbours
     const ConvRowDh64 d0 = sg_conv_row64_dh(X, ha, hb), dp = sg_conv_row64_dh(X + A.du, ha, hb),
                       dm = sg_conv_row64_dh(X - A.du, ha, hb);
-    if constexpr (SO == 1) {
+    if constexpr ((SO & 1) != 0) {
         // integrated samples, cooperatively (as in k_ss_rows<N, true>)
         const int Pr = ic - ip;
         const double rn = SG_SS_HAT_NEAR * fmax(A.du, A.dphi), xq = Pr * A.du;
@@ -1605,7 +1607,7 @@ k_ssg_rows(const double *H, const double *dself, SsRowArgs A, SsClass C, int nph
         for (int q = 0; q <= qm; ++q) {
             for (int d = 1; d <= 2; ++d) {
                 double wr = 0.0, wp = 0.0;
-                if (q <= qn) sg_hat_weight_part(Pr, q, A.du, A.dphi, ha, hb, d, A.gl, wq, t, T, wr, wp);
+                if (q <= qn) sg_hat_weight_part<SO == 3>(Pr, q, A.du, A.dphi, ha, hb, d, A.gl, wq, t, T, wr, wp);
                 pl.st(t, make_double2(wr, wp));
                 __syncthreads();
                 if (q <= qn && t == 0) {
@@ -1829,7 +1831,10 @@ static void launch_ssg_rows(const double *H, const double *dself, const SsRowArg
     for (size_t r0 = 0; r0 < rows; r0 += chunk) {
         const int n = (int)std::min(chunk, rows - r0);
         const dim3 one((n + S::G - 1) / S::G), two((n / 2 + S::G - 1) / S::G);
-        if (P.kind == 1)
+        if (P.kind == 1 && sg_hat_long(A.du, A.dphi))
+            hipLaunchKernelGGL((k_ssg_rows<N, 3>), one, dim3(S::WGS), 0, s, H, dself, A, C, nphi, lt, st, r0, n,
+                               rowpart);
+        else if (P.kind == 1)
             hipLaunchKernelGGL((k_ssg_rows<N, 1>), one, dim3(S::WGS), 0, s, H, dself, A, C, nphi, lt, st, r0, n,
                                rowpart);
         else if (P.kind == 2)

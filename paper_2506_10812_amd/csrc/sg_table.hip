@@ -440,8 +440,8 @@ __global__ void __launch_bounds__(256) k_sample_hat_far(double2 *A, int nr, int 
     for (int ds = -1; ds <= 0; ++ds)
         for (int dt = -1; dt <= 0; ++dt) {
             int ms, mt;
-            sg_hat_split(P, Q, ds, dt, du, dphi, ms, mt);
-            sg_hat_square(P, Q, ds, dt, ms, mt, 0, 36 * ms * mt, 1, du, dphi, ha, hb, which, wq, wr, wp);
+            sg_hat_split<true>(P, Q, ds, dt, du, dphi, ms, mt);
+            sg_hat_square<true>(P, Q, ds, dt, ms, mt, 0, 36 * abs(ms * mt), 1, du, dphi, ha, hb, which, wq, wr, wp);
         }
     A[(size_t)p * nphi + q] = make_double2(wr, wp);
 }
@@ -473,8 +473,8 @@ __global__ void __launch_bounds__(256) k_sample_hat_near(double2 *A, int nr, int
                                   wr, wp);
                 } else {
                     int ms, mt;
-                    sg_hat_split(P, Q, ds, dt, du, dphi, ms, mt);
-                    sg_hat_square(P, Q, ds, dt, ms, mt, threadIdx.x, 36 * ms * mt, blockDim.x, du, dphi, ha, hb,
+                    sg_hat_split<true>(P, Q, ds, dt, du, dphi, ms, mt);
+                    sg_hat_square<true>(P, Q, ds, dt, ms, mt, threadIdx.x, 36 * abs(ms * mt), blockDim.x, du, dphi, ha, hb,
                                   which, wq, wr, wp);
                 }
             }
