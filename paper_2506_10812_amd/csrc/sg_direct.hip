@@ -15,7 +15,9 @@
 // once per call in double (rounded for the float path).  On a uniform radial
 // grid (SG_LINEAR_R: centres r_min + (i + 1/2) dr, sector areas r dr dphi)
 // the radial factors 4 sinh^2(X/2) = (r_i - r_k)^2 / (r_i r_k) and
-// expm1(X) = (r_i - r_k) / r_k are formed per source row instead.
+// expm1(X) = (r_i - r_k) / r_k are formed per source row instead, with r_i - r_k
+// = (i - k) dr (the difference of float radii left 1e-4 of the field of an
+// annulus of r_max / r_min = 1.01).
 //
 // H = h r (d_H == NULL) makes the kernel between two rings a function of the
 // azimuth offset alone: k_ring_sum evaluates it once per offset and sums it
@@ -49,6 +51,7 @@
 template <typename T> struct DirectArgs {
     int nr, nphi, rps;   // rows per split
     int lin;             // uniform radial grid
+    T dr;                // its spacing
     int64_t N;
     const T *rrow, *sx, *ex, *sph, *snp, *mass, *H2;
     T *partial;          // [split][fluid][component][hi, lo][N]
@@ -154,7 +157,7 @@ __global__ void __launch_bounds__(256) k_direct(DirectArgs<T> A)
         const T rk = A.rrow[kr];
         T SX, EX;
         if (A.lin) {
-            const T d = ri - rk;
+            const T d = T(ir - kr) * A.dr;
             SX = d * d / (ri * rk);
             EX = d / rk;
         } else {
@@ -274,7 +277,7 @@ __device__ inline void ring_kernel(const DirectArgs<T> &A, int ir, int kr, int a
     const T ri = A.rrow[ir], rk = A.rrow[kr];
     T SX, EX;
     if (A.lin) {
-        const T d = ri - rk;
+        const T d = T(ir - kr) * A.dr;
         SX = d * d / (ri * rk);
         EX = d / rk;
     } else {
@@ -802,6 +805,7 @@ static sg_status direct_run(const sg_grid *g, int nf, const double *h, const T *
     A.nphi = nphi;
     A.rps = rps;
     A.lin = lin;
+    A.dr = (T)(dr / unit);
     A.N = N;
     A.rrow = rrow;
     A.sx = sx;
@@ -905,6 +909,7 @@ static sg_status potential_run(const sg_grid *g, int nf, const double *h, const 
     }
     DirectArgs<T> A;
     A.lin = 0;
+    A.dr = T(0);
     A.nr = nr;
     A.nphi = nphi;
     A.rps = rps;
